@@ -303,10 +303,9 @@ int fa_pack_boxes(fa_ctx* ctx, const float* sizes, int32_t n, int32_t atlas_size
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc). The same frame as fa_build_atlas with a fixed configuration
  * (J = 64, gutter 1, min_box 2, no flags, default knobs) and no context:
- * every scratch buffer, including the triangle adjacency (rebuilt on every
- * call, nothing stays resident), lives in one static device array of
+ * every scratch buffer lives in one static device array of
  * FA_STATIC_SCRATCH_MIB MiB that each device holds for the life of the
- * process. The call allocates nothing and never synchronizes; it runs on the
+ * process (nothing of a scene stays resident). The call allocates nothing and never synchronizes; it runs on the
  * current device and enqueues on `stream`. Limits: T <= FA_STATIC_MAX_TRIANGLES,
  * V <= FA_STATIC_MAX_VERTICES (FA_ERR_CAPACITY above them), at most
  * FA_STATIC_MAX_CHARTS charts (FA_ERR_CAPACITY in meta->status),

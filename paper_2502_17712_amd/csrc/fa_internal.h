@@ -322,18 +322,14 @@ struct Marker {
   }
 };
 
-// Device-side index check of the allocation-free entry point: clear the flag,
-// then set it if any of the n indices is outside [0, V). The guard, launched
-// after the visible list is built, turns a set flag into FA_ERR_INVALID_ARG
-// in the frame state and an empty visible list, so no later kernel reads
-// an index.
-hipError_t launch_index_check(const int32_t* idx, int64_t n, int64_t V, int32_t* flag,
-                              hipStream_t st);
-hipError_t launch_index_guard(const int32_t* flag, const Work& w, hipStream_t st);
-
+// check_idx (the allocation-free entry point): the mesh's indices, checked
+// against [0, V) on the way; a bad one ends the frame with
+// FA_ERR_INVALID_ARG in the frame state and an empty visible list, so no later
+// kernel reads an index. NULL: checked already.
 hipError_t launch_prologue(int64_t V, const uint8_t* vis, const int32_t* nbr,
                            int64_t T, const FrameParams& p, const Work& w, int32_t* cov,
-                           int32_t* cot, int uf_init, Marker& mk, hipStream_t st);
+                           int32_t* cot, int uf_init, const int32_t* check_idx, Marker& mk,
+                           hipStream_t st);
 // occ_fill: when not NULL, this [omega][omega] occupancy map is filled with -1
 // by workgroups past the union-find tiles (hook mode 5) or past the box
 // gather (the other modes); both kernels are bound by dependent loads and
@@ -400,13 +396,13 @@ struct Knobs {
   int uf_link_init;  // union-find start linked to the smallest edge neighbour
 };
 // Every stage of one frame (clip transform to frame record) on stream st with
-// the scratch buffers of w and the scene adjacency nbr. index_flag: NULL, or
-// the device flag of launch_index_check (the frame then stops with
-// FA_ERR_INVALID_ARG in meta->status when it is set). Returns FA_OK or
+// the scratch buffers of w and the scene adjacency nbr (NULL where the hook mode
+// reads none: 5, without the edge-connected charts' flag). check_indices: the
+// indices have not been checked (see launch_prologue). Returns FA_OK or
 // FA_ERR_DEVICE (a launch failed).
 int run_frame_core(const Knobs& kn, const Work& w, const fa_mesh* mesh, const int32_t* nbr,
                    const uint8_t* visible, const FrameParams& p, const fa_atlas_out* out,
-                   const int32_t* index_flag, Marker& mk, hipStream_t st);
+                   bool check_indices, Marker& mk, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // batched frames: every stage of n views of one mesh in one launch per stage

@@ -525,7 +525,7 @@ namespace fa {
 // Every stage of one frame on stream st with scratch w (see fa_internal.h).
 int run_frame_core(const Knobs& kn, const Work& slot, const fa_mesh* mesh, const int32_t* nbr,
                    const uint8_t* visible, const FrameParams& p, const fa_atlas_out* out,
-                   const int32_t* index_flag, Marker& mk, hipStream_t st) {
+                   bool check_indices, Marker& mk, hipStream_t st) {
   const int64_t T = mesh->num_triangles, V = mesh->num_vertices;
   Work w = slot;
   w.pos = mesh->positions;
@@ -538,8 +538,8 @@ int run_frame_core(const Knobs& kn, const Work& slot, const fa_mesh* mesh, const
   const bool tiles_start = (p.flags & FA_FLAG_EDGE_ONLY_CHARTS) ? p.edge_hooks != 1
                                                                 : p.edge_hooks >= 2;
   ok(launch_prologue(V, visible, nbr, T, p, w, cov, out->chart_of_tri,
-                     tiles_start ? 0 : (kn.uf_link_init ? 2 : 1), mk, st));
-  if (index_flag) ok(launch_index_guard(index_flag, w, st));
+                     tiles_start ? 0 : (kn.uf_link_init ? 2 : 1),
+                     check_indices ? mesh->indices : nullptr, mk, st));
   // the occupancy map is filled with -1 by spare workgroups of the box gather
   int32_t* occ_fill = T > 0 ? out->occupancy : nullptr;
   ok(launch_charts(visible, mesh->indices, nbr, T, p, w, out->chart_of_tri, cov, out->charts,
@@ -603,7 +603,7 @@ static int run_frame(fa_ctx* ctx, const Work& w, const fa_mesh* mesh, Scene* sc,
   if (ctx->timing) { mk.ev = ctx->ev; mk.cap = kStages + 1; }
   FrameParams p = p_in;
   const Knobs kn = frame_knobs(ctx, mesh->num_triangles, &p);
-  const int rc = run_frame_core(kn, w, mesh, sc->nbr, visible, p, out, nullptr, mk, st);
+  const int rc = run_frame_core(kn, w, mesh, sc->nbr, visible, p, out, false, mk, st);
   ctx->ev_marks = mk.n;
   ctx->ev_recorded = ctx->timing && mk.n == kStages + 1;
   return rc;

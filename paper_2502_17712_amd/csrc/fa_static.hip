@@ -1,7 +1,10 @@
 // Allocation-free entry point: fa_build_atlas_static atlases one frame with
-// every scratch buffer (the frame's working set and the triangle adjacency,
-// rebuilt per call) carved from one file-scope device array, so the call
-// makes no device allocation. For callers that cannot allocate: code under
+// every scratch buffer carved from one file-scope device array, so the call
+// makes no device allocation. Its union-find joins through shared vertices
+// (hook mode 5), which cover every shared edge, so it needs no triangle
+// adjacency: the call is the 13 launches of fa_build_atlas, with the indices
+// checked by the first of them (an 8k-triangle frame: 172 us with the
+// adjacency rebuilt and a separate check, 80 us without). For callers that cannot allocate: code under
 // HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
 #include <algorithm>
 #include <cmath>
@@ -38,7 +41,7 @@ std::mutex g_mu;
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Carve the scratch at `base` (nullptr: only measure). Returns the bytes used.
-size_t carve(char* base, Work* w, AdjTmp* adj, int32_t** nbr, int32_t** flag) {
+size_t carve(char* base, Work* w) {
   size_t off = 0;
   auto take = [&](size_t bytes) {
     char* p = base ? base + off : nullptr;
@@ -81,16 +84,6 @@ size_t carve(char* base, Work* w, AdjTmp* adj, int32_t** nbr, int32_t** flag) {
   x.fp_group = (unsigned long long*)take(8);
   x.fp_pool = (uint32_t*)take(4);
   x.state = (FrameState*)take(sizeof(FrameState));
-  *nbr = (int32_t*)take(12 * T);
-  const size_t n = 3 * T;
-  adj->keys_a = (unsigned long long*)take(8 * n);
-  adj->keys_b = (unsigned long long*)take(8 * n);
-  adj->vals_a = (int32_t*)take(4 * n);
-  adj->vals_b = (int32_t*)take(4 * n);
-  adj->hist = (uint32_t*)take(4 * adjacency_hist_words(kStaticT));
-  adj->part = (uint32_t*)take(4 * adjacency_part_words(kStaticT));
-  adj->n_dev = nullptr;
-  *flag = (int32_t*)take(4);
   return off;
 }
 
@@ -105,9 +98,7 @@ int setup_device(int dev) {
   if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return d.rc;
   if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0) return d.rc;
   Work w;
-  AdjTmp a;
-  int32_t *nbr = nullptr, *flag = nullptr;
-  if (carve(nullptr, &w, &a, &nbr, &flag) > kScratchBytes) return d.rc;
+  if (carve(nullptr, &w) > kScratchBytes) return d.rc;
   void* p = nullptr;
   if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return d.rc;
   if (pack_kernel_attributes(2 * kMaxAtlas * (int)sizeof(int32_t)) != hipSuccess) return d.rc;
@@ -141,9 +132,7 @@ extern "C" int fa_build_atlas_static(const fa_mesh* mesh, const uint8_t* visible
   const int rc = setup_device(dev);
   if (rc != FA_OK) return rc;
   Work w;
-  AdjTmp adj;
-  int32_t *nbr = nullptr, *flag = nullptr;
-  carve(g_dev[dev].ptr, &w, &adj, &nbr, &flag);
+  carve(g_dev[dev].ptr, &w);
   p.W = cam->width;
   p.H = cam->height;
   p.omega = atlas_size;
@@ -160,12 +149,7 @@ extern "C" int fa_build_atlas_static(const fa_mesh* mesh, const uint8_t* visible
   p.uf_tile = 4096;
   p.fp_cap = 0;
   p.pool_stride = 0;
-  hipStream_t st = (hipStream_t)stream;
-  const int64_t T = mesh->num_triangles, V = mesh->num_vertices;
-  if (launch_index_check(mesh->indices, 3 * T, V, flag, st) != hipSuccess ||
-      launch_adjacency(mesh->indices, T, V, adj, nbr, st) != hipSuccess)
-    return FA_ERR_DEVICE;
   const Knobs kn{1024, 64, 64, 1};
   Marker none;
-  return run_frame_core(kn, w, mesh, nbr, visible, p, out, flag, none, st);
+  return run_frame_core(kn, w, mesh, nullptr, visible, p, out, true, none, (hipStream_t)stream);
 }

@@ -93,13 +93,21 @@ __device__ __forceinline__ void uf_join(int32_t* parent, int u, int v) {
 }
 
 constexpr int kProVerts = 4;  // vertices per prologue thread
+// Added to the visible count of a tile that holds a bad index: sums of counts
+// stay below it, and a sum of every tile's stays below 2^32.
+constexpr uint32_t kBadTile = 1u << 17;
+static_assert(FA_STATIC_MAX_TRIANGLES < (int64_t)kBadTile &&
+                  (FA_STATIC_MAX_TRIANGLES / kTriTile + 2) * (int64_t)kBadTile < (int64_t(1) << 32),
+              "kBadTile separates counts from bad tiles");
 static_assert(kTriTile % kBlock == 0, "prologue threads take whole strides of a tile");
 
 // Prologue of a frame: frame state, per-vertex scratch (vertex minima and
 // chart_of_vert = -1; clip positions are computed where they are read),
 // chart_of_tri = -1, the union-find start of every visible triangle and the
-// visible count of every tile of kTriTile triangles. Blocks [0, vblocks)
-// handle vertices, the rest triangle tiles. uf_init 2: a visible triangle
+// visible count of every tile of kTriTile triangles. With check_idx (the
+// allocation-free entry point, whose indices no resident scene has checked) a
+// tile with an index outside [0, V) adds kBadTile to its count. Blocks
+// [0, vblocks) handle vertices, the rest triangle tiles. uf_init 2: a visible triangle
 // starts linked to the smallest of itself and its visible edge neighbours
 // (Alg. 1, first loop); 1: as its own root (same labels); 0: not written (a
 // later pass writes it).
@@ -109,7 +117,8 @@ __device__ __forceinline__ void k_prologue_body(int64_t V, int32_t* __restrict__
                            int32_t* __restrict__ parent, int32_t* __restrict__ cot,
                            uint32_t* __restrict__ tile_vis, int uf_init,
                            unsigned vblocks, FrameState* st,
-                           unsigned long long* __restrict__ big_counter) {
+                           unsigned long long* __restrict__ big_counter,
+                           const int32_t* __restrict__ check_idx = nullptr) {
   __shared__ uint32_t sh[kBlock / kWave];
   if (blockIdx.x < vblocks) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -139,6 +148,15 @@ __device__ __forceinline__ void k_prologue_body(int64_t V, int32_t* __restrict__
     const int64_t t = base + (int64_t)k * kBlock;
     if (t >= T) break;
     cot[t] = -1;
+    if (check_idx) {
+      bool bad = false;
+#pragma unroll
+      for (int e = 0; e < 3; ++e) {
+        const int32_t v = check_idx[3 * t + e];
+        bad = bad || v < 0 || (int64_t)v >= V;
+      }
+      if (bad) nv += 2 * kTriTile;  // (a tile counts at most kTriTile visible)
+    }
     if (!vis[t]) continue;
     ++nv;
     int q = (int)t;
@@ -152,6 +170,7 @@ __device__ __forceinline__ void k_prologue_body(int64_t V, int32_t* __restrict__
     if (uf_init) astore(&parent[t], q);
   }
   nv = block_sum<uint32_t>(nv, sh);
+  if (check_idx) nv = nv % (2 * kTriTile) + (nv >= 2 * kTriTile ? kBadTile : 0u);
   if (threadIdx.x == 0) tile_vis[tile] = nv;
 }
 __global__ void k_prologue(int64_t V, int32_t* __restrict__ vmin,
@@ -160,8 +179,10 @@ __global__ void k_prologue(int64_t V, int32_t* __restrict__ vmin,
                            int32_t* __restrict__ parent, int32_t* __restrict__ cot,
                            uint32_t* __restrict__ tile_vis, int uf_init,
                            unsigned vblocks, FrameState* st,
-                           unsigned long long* __restrict__ big_counter) {
-  k_prologue_body(V, vmin, cov, vis, nbr, T, parent, cot, tile_vis, uf_init, vblocks, st, big_counter);
+                           unsigned long long* __restrict__ big_counter,
+                           const int32_t* __restrict__ check_idx) {
+  k_prologue_body(V, vmin, cov, vis, nbr, T, parent, cot, tile_vis, uf_init, vblocks, st,
+                  big_counter, check_idx);
 }
 
 // Sum of cnt[0 .. n) by one workgroup (the exclusive prefix of tile n);
@@ -214,13 +235,17 @@ __device__ __forceinline__ void k_tile_scan_body(uint32_t* tile_vis, unsigned ti
 // For one frame each workgroup sums the visible counts of the tiles before
 // its own (a few thousand words at most) instead of waiting for a separate
 // scan; batched launches scan first (scanned). The last workgroup records
-// the total.
+// the total; of a checked frame with a bad index (kBadTile) it ends the frame
+// with FA_ERR_INVALID_ARG.
 __device__ __forceinline__ void k_vis_compact_body(const uint8_t* __restrict__ vis, int64_t T,
                               const uint32_t* __restrict__ tile_vis, int32_t* __restrict__ vlist,
-                              FrameState* __restrict__ st, bool scanned = false) {
+                              FrameState* __restrict__ st, bool scanned = false,
+                              bool checked = false) {
   __shared__ uint32_t sh[kBlock / kWave];
   // scanned: tile_vis holds each tile's exclusive prefix (k_tile_scan_body)
-  const uint32_t off = scanned ? tile_vis[blockIdx.x] : tiles_before(tile_vis, blockIdx.x, sh);
+  uint32_t off = scanned ? tile_vis[blockIdx.x] : tiles_before(tile_vis, blockIdx.x, sh);
+  const uint32_t bad = checked ? off / kBadTile : 0u;  // earlier tiles with a bad index
+  if (checked) off %= kBadTile;
   const int64_t base = (int64_t)blockIdx.x * kTriTile + (int64_t)threadIdx.x * 4;
   bool f[4];
   uint32_t mine = 0;
@@ -234,12 +259,19 @@ __device__ __forceinline__ void k_vis_compact_body(const uint8_t* __restrict__ v
 #pragma unroll
   for (int k = 0; k < 4; ++k)
     if (f[k]) vlist[at++] = (int32_t)(base + k);
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) st->visible = (int32_t)(off + tot);
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    if (checked && (bad || tile_vis[blockIdx.x] >= kBadTile)) {
+      st->status = FA_ERR_INVALID_ARG;  // and an empty list: no later kernel reads an index
+      st->visible = 0;
+    } else {
+      st->visible = (int32_t)(off + tot);
+    }
+  }
 }
 __global__ void k_vis_compact(const uint8_t* __restrict__ vis, int64_t T,
                               const uint32_t* __restrict__ tile_vis, int32_t* __restrict__ vlist,
-                              FrameState* __restrict__ st) {
-  k_vis_compact_body(vis, T, tile_vis, vlist, st);
+                              FrameState* __restrict__ st, bool checked) {
+  k_vis_compact_body(vis, T, tile_vis, vlist, st, false, checked);
 }
 
 // Hook across every shared edge once (u < v) (Alg. 1, second loop).
@@ -1009,26 +1041,6 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_boxes(
 
 inline unsigned grid_for(int64_t n, int block) { return (unsigned)((n + block - 1) / block); }
 
-__global__ void k_flag_clear(int32_t* flag) { *flag = 0; }
-
-__global__ void k_index_check(const int32_t* __restrict__ idx, int64_t n, int64_t V,
-                              int32_t* flag) {
-  bool bad = false;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t v = idx[i];
-    bad = bad || v < 0 || (int64_t)v >= V;
-  }
-  if (__ballot(bad) && lane_id() == 0) atomicExch(flag, 1);
-}
-
-__global__ void k_index_guard(const int32_t* __restrict__ flag, FrameState* st) {
-  if (*flag) {
-    st->status = FA_ERR_INVALID_ARG;
-    st->visible = 0;
-  }
-}
-
 // ---- batched wrappers (view = blockIdx.y) --------------------------------
 __global__ void k_prologue_b(const BatchView* __restrict__ bv, int64_t V, const int32_t* __restrict__ nbr, int64_t T,
                              unsigned vblocks) {
@@ -1074,35 +1086,24 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_boxes_b(const BatchView
 
 }  // namespace
 
-hipError_t launch_index_check(const int32_t* idx, int64_t n, int64_t V, int32_t* flag,
-                              hipStream_t st) {
-  k_flag_clear<<<1, 1, 0, st>>>(flag);
-  if (n > 0)
-    k_index_check<<<(unsigned)std::min<int64_t>(1024, (n + kBlock - 1) / kBlock), kBlock, 0, st>>>(
-        idx, n, V, flag);
-  return hipGetLastError();
-}
-
-hipError_t launch_index_guard(const int32_t* flag, const Work& w, hipStream_t st) {
-  k_index_guard<<<1, 1, 0, st>>>(flag, w.state);
-  return hipGetLastError();
-}
-
 unsigned visible_grid(int64_t T) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>((T + kBlock - 1) / kBlock, 2048));
 }
 
 hipError_t launch_prologue(int64_t V, const uint8_t* vis, const int32_t* nbr,
                            int64_t T, const FrameParams& p, const Work& w, int32_t* cov,
-                           int32_t* cot, int uf_init, Marker& mk, hipStream_t st) {
+                           int32_t* cot, int uf_init, const int32_t* check_idx, Marker& mk,
+                           hipStream_t st) {
   const unsigned vb = std::max(1u, grid_for(V, kBlock * kProVerts));
   const unsigned tt = grid_for(T, kTriTile);
   k_prologue<<<vb + tt, kBlock, 0, st>>>(V, w.vmin, cov, vis, nbr, T, w.parent,
                                          cot, w.tile_vis, uf_init, vb, w.state,
-                                         w.big_counter);
+                                         w.big_counter, check_idx);
   mk(st);
   mk(st);  // (the visible-count scan is part of the compaction)
-  if (T > 0) k_vis_compact<<<tt, kBlock, 0, st>>>(vis, T, w.tile_vis, w.vlist, w.state);
+  if (T > 0)
+    k_vis_compact<<<tt, kBlock, 0, st>>>(vis, T, w.tile_vis, w.vlist, w.state,
+                                         check_idx != nullptr);
   mk(st);
   return hipGetLastError();
 }

@@ -122,3 +122,25 @@ def test_static_errors_and_recovery():
     with pytest.raises(fa.FastAtlasError) as e:
         fa.build_atlas_static(big, vis, f.view_proj, f.width, f.height, 1024, 1.0, out=out)
     assert e.value.code == fa.FA_ERR_CAPACITY
+
+
+@pytest.mark.parametrize("tri,corner,value", [(0, 0, -1), (1023, 2, "V"), (1024, 1, "V"),
+                                              (8191, 2, -5), ("all", 0, "V")])
+def test_static_index_check_covers_every_tile(tri, corner, value):
+    # bad indices in the first, an inner or the last tile of 1024 triangles,
+    # of triangles that are not visible too, and in every triangle at once
+    fa = _fa()
+    f = scenes.grid_frame(7)
+    assert f.num_triangles == 8192
+    idx = f.indices.copy()
+    idx[slice(None) if tri == "all" else tri, corner] = f.num_vertices if value == "V" else value
+    vis = f.visible.copy()
+    vis[tri if tri != "all" else 0] = 0
+    out = fa.AtlasOutputs(f.num_triangles, f.num_vertices, fa.STATIC_MAX_CHARTS, f.atlas_size, 64)
+    print(f"[gpu] static: bad index at triangle {tri}", flush=True)
+    mesh = fa.Mesh(f.positions, idx, 88300)
+    fa.build_atlas_static(mesh, torch.as_tensor(vis).cuda(), f.view_proj, f.width, f.height,
+                          f.atlas_size, f.rate, out=out)
+    torch.cuda.synchronize()
+    m = out.to_numpy()["meta"]
+    assert m["status"] == fa.FA_ERR_INVALID_ARG and m["visible_triangles"] == 0
