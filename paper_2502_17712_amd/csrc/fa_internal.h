@@ -20,7 +20,7 @@ constexpr int kRadix = 1 << kRadixBits;
 constexpr int kSortTile = 2048;      // keys per workgroup in one radix pass
 constexpr int kCandStride = 8;       // int32 per candidate in the table
 constexpr int kMaxAtlas = 8192;
-constexpr int kCountGrid = 256;      // workgroups of the occupancy count
+constexpr int kCountGrid = 256;      // most workgroups that publish sums in Work::partial
 constexpr int kOrderGroups = 32;     // workgroups of the chart order above 1024 charts
 static_assert(kOrderGroups <= kCountGrid, "the order's chunk sums use Work::partial");
 constexpr int kOccBigGrid = 2048;    // blocks of the large-footprint raster
@@ -119,7 +119,8 @@ struct Work {
   unsigned long long* partial;  // [kCountGrid] per-block occupied texel counts
   ulonglong2* big;       // [kBigCap] queued large occupancy footprints: code, tiles
   int4* big_fp;          // [kBigCap][3] their footprints (edge data, texel range, chart)
-  unsigned long long* big_counter; // [1] queued footprints << 40 | queued tiles
+  unsigned long long* big_counter; // [2] queued footprints << 40 | queued tiles; finished
+                         // workgroups of the reuse count (0 between calls)
   fa_chart* pack_charts; // [max_charts] chart records of the packer-only entry
   int32_t* cand_rs;      // [J][max_charts + 1] row starts of each candidate (frames above
                          // the LDS capacity of the packer)
@@ -380,7 +381,7 @@ hipError_t launch_occupancy_scaled(const int32_t* idx, int64_t T, const FramePar
 unsigned visible_grid(int64_t T);  // blocks of the kernels that walk the visible list
 hipError_t launch_reuse_flags(const float* pos, const int32_t* idx, int64_t T, const KeyClip& kc,
                               const uint8_t* key_vis, const uint8_t* vis, uint8_t* flags,
-                              unsigned long long* reused, hipStream_t st);
+                              unsigned long long* reused, const Work& w, hipStream_t st);
 hipError_t launch_visibility(const float* pos, const int32_t* idx, int64_t T, const VisParams& q,
                              int32_t* occl, uint32_t* count, unsigned long long* depth,
                              uint8_t* vis, hipStream_t st);

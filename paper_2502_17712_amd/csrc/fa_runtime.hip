@@ -185,7 +185,7 @@ int fa_create(const fa_config* cfg_in, fa_ctx** out_ctx) {
         {(void**)&w.vlist, 4 * T},
         {(void**)&w.big, 16 * std::min<size_t>(2 * T, (size_t)kBigCap)},
         {(void**)&w.big_fp, 48 * std::min<size_t>(2 * T, (size_t)kBigCap)},
-        {(void**)&w.big_counter, 8},             {(void**)&w.partial, 8 * kCountGrid},
+        {(void**)&w.big_counter, 16},            {(void**)&w.partial, 8 * kCountGrid},
         {(void**)&w.pack_charts, sizeof(fa_chart) * C}, {(void**)&w.chart_tex, 16 * C},
         {(void**)&w.cand_rs, 4 * J * (C + 1)},
         {(void**)&w.fp_off, footprint ? 4 * (C + 1) : 4},
@@ -239,6 +239,13 @@ int fa_create(const fa_config* cfg_in, fa_ctx** out_ctx) {
     return FA_ERR_DEVICE;
   }
   for (int i = 0; i <= kStages; ++i) (void)hipEventCreate(&ctx->ev[i]);
+  // (the reuse count's ticket starts at 0; every count sets it back)
+  const unsigned long long zero[2] = {0ull, 0ull};
+  if (hipMemcpy(ctx->slots[0].big_counter, zero, sizeof(zero), hipMemcpyHostToDevice) !=
+      hipSuccess) {
+    fa_destroy(ctx);
+    return FA_ERR_DEVICE;
+  }
   *out_ctx = ctx;
   return FA_OK;
 }
@@ -473,7 +480,7 @@ int fa_reuse_flags(fa_ctx* ctx, const fa_mesh* mesh, const fa_camera* key_cam,
   if (rc) return rc;
   if (launch_reuse_flags(mesh->positions, mesh->indices, mesh->num_triangles, kc, key_visible,
                          visible, flags, reinterpret_cast<unsigned long long*>(reused),
-                         st) != hipSuccess)
+                         ctx->slots[0], st) != hipSuccess)
     return FA_ERR_DEVICE;
   return FA_OK;
 }

@@ -14,6 +14,7 @@
 //              proven hidden) or some covered sample has z <= D + 1e-6;
 //              candidates crossing the near plane stay visible.
 // Small footprints are walked by their own lane, larger ones by their wave.
+#include <algorithm>
 #include <cmath>
 
 #include "fa_internal.h"
@@ -252,46 +253,92 @@ __global__ __launch_bounds__(kBlock) void k_vis_depth(const float* __restrict__ 
 // Temporal reuse classification (Sec. "Temporal Reuse"): 0 not visible now,
 // 1 reuse the key frame's shading, 2 shade (newly visible, or some vertex had
 // max(|x|, |y|) >= w in the key frame's clip space, float32 as the atlas path
-// computes it). One atomic per wave counts the reused triangles.
-__global__ void k_zero64(unsigned long long* p) { *p = 0ull; }
+// computes it).
+//
+// Bound by the dependent loads of the visible triangles (visible byte,
+// indices, positions), so every thread issues kReusePer triangles level by
+// level. The reused triangles are counted per workgroup; the last one to
+// finish adds the sums (stored at device scope and completed before the
+// ticket is drawn) and sets the ticket back to 0. One atomic per wave on a
+// single counter, which serializes at about 3 ns each, took 102 us on a
+// 2.2M-triangle scene and its clearing launch 5 (visibility and reuse together
+// 220 -> 133 us).
+constexpr int kReuseBlock = 1024;
+constexpr int kReusePer = 4;
+constexpr int kReuseGrid = 256;  // workgroups
+static_assert(kReuseGrid <= kCountGrid, "the reuse count's sums use Work::partial");
 
-__global__ __launch_bounds__(kBlock) void k_reuse_flags(
+__global__ __launch_bounds__(kReuseBlock) void k_reuse_flags(
     const float* __restrict__ pos, const int32_t* __restrict__ idx, int64_t T, KeyClip kc,
     const uint8_t* __restrict__ key_vis, const uint8_t* __restrict__ vis,
-    uint8_t* __restrict__ flags, unsigned long long* __restrict__ reused) {
-  for (int64_t b0 = (int64_t)blockIdx.x * blockDim.x; b0 < T;
-       b0 += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t t = b0 + threadIdx.x;
-    bool reuse = false;
-    if (t < T) {
-      uint8_t f = 0;
-      if (vis[t]) {
-        bool partial = false;
+    uint8_t* __restrict__ flags, unsigned long long* __restrict__ reused,
+    unsigned long long* __restrict__ partial, unsigned long long* __restrict__ ticket) {
+  __shared__ uint32_t sh[kReuseBlock / kWave];
+  __shared__ uint32_t last;
+  uint32_t count = 0;
+  const int64_t step = (int64_t)gridDim.x * kReuseBlock;
+  for (int64_t t0 = (int64_t)blockIdx.x * kReuseBlock + threadIdx.x; t0 < T;
+       t0 += kReusePer * step) {
+    bool on[kReusePer], key[kReusePer];
+    int32_t vi[kReusePer][3];
+    float q[kReusePer][3][3];
 #pragma unroll
-        for (int e = 0; e < 3; ++e) {
-          const int64_t v = idx[3 * t + e];
-          const float x = pos[3 * v], y = pos[3 * v + 1], z = pos[3 * v + 2];
-          float r[4];
+    for (int k = 0; k < kReusePer; ++k) {
+      const int64_t t = t0 + k * step;
+      on[k] = t < T && vis[t];
+      key[k] = t < T && key_vis[t] != 0;
+    }
 #pragma unroll
-          for (int i = 0; i < 4; i += 1) {
-            if (i == 2) { r[i] = 0.0f; continue; }  // z is not needed
-            float acc = kc.M[4 * i] * x;
-            acc = acc + kc.M[4 * i + 1] * y;
-            acc = acc + kc.M[4 * i + 2] * z;
-            r[i] = acc + kc.M[4 * i + 3];
-          }
-          if (fmaxf(fabsf(r[0]), fabsf(r[1])) >= r[3]) partial = true;
+    for (int k = 0; k < kReusePer; ++k)
+#pragma unroll
+      for (int e = 0; e < 3; ++e) vi[k][e] = on[k] ? idx[3 * (t0 + k * step) + e] : 0;
+#pragma unroll
+    for (int k = 0; k < kReusePer; ++k)
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) q[k][e][i] = on[k] ? pos[3 * (int64_t)vi[k][e] + i] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < kReusePer; ++k) {
+      const int64_t t = t0 + k * step;
+      bool partly = false;
+#pragma unroll
+      for (int e = 0; e < 3; ++e) {
+        float r[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (i == 2) continue;  // z is not needed
+          float acc = kc.M[4 * i] * q[k][e][0];
+          acc = acc + kc.M[4 * i + 1] * q[k][e][1];
+          acc = acc + kc.M[4 * i + 2] * q[k][e][2];
+          r[i] = acc + kc.M[4 * i + 3];
         }
-        reuse = key_vis[t] != 0 && !partial;
-        f = reuse ? 1 : 2;
+        if (fmaxf(fabsf(r[0]), fabsf(r[1])) >= r[3]) partly = true;
       }
-      flags[t] = f;
+      const bool reuse = on[k] && key[k] && !partly;
+      count += reuse;
+      if (t < T) flags[t] = on[k] ? (reuse ? 1 : 2) : 0;
     }
-    if (reused) {
-      const unsigned long long m = __ballot(reuse);
-      if (m && lane_id() == __ffsll((long long)m) - 1)
-        atomicAdd(reused, (unsigned long long)__popcll(m));
-    }
+  }
+  if (!reused) return;
+  count = block_sum<uint32_t>(count, sh);
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(&partial[blockIdx.x], (unsigned long long)count, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0);
+    last = __hip_atomic_fetch_add(ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+           gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  // at most 2^30 triangles: the total fits 32 bits
+  uint32_t all = 0;
+  for (int i = threadIdx.x; i < (int)gridDim.x; i += kReuseBlock)
+    all += (uint32_t)__hip_atomic_load(&partial[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  all = block_sum<uint32_t>(all, sh);
+  if (threadIdx.x == 0) {
+    *reused = all;
+    __hip_atomic_store(ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -299,12 +346,12 @@ __global__ __launch_bounds__(kBlock) void k_reuse_flags(
 
 hipError_t launch_reuse_flags(const float* pos, const int32_t* idx, int64_t T, const KeyClip& kc,
                               const uint8_t* key_vis, const uint8_t* vis, uint8_t* flags,
-                              unsigned long long* reused, hipStream_t st) {
-  if (reused) k_zero64<<<1, 1, 0, st>>>(reused);
-  if (T > 0) {
-    const unsigned g = (unsigned)std::min<int64_t>((T + kBlock - 1) / kBlock, 8192);
-    k_reuse_flags<<<g, kBlock, 0, st>>>(pos, idx, T, kc, key_vis, vis, flags, reused);
-  }
+                              unsigned long long* reused, const Work& w, hipStream_t st) {
+  // (one workgroup even without triangles: it writes the count)
+  const unsigned g = (unsigned)std::max<int64_t>(
+      1, std::min<int64_t>((T + kReuseBlock - 1) / kReuseBlock, kReuseGrid));
+  k_reuse_flags<<<g, kReuseBlock, 0, st>>>(pos, idx, T, kc, key_vis, vis, flags, reused, w.partial,
+                                           w.big_counter + 1);
   return hipGetLastError();
 }
 

@@ -195,3 +195,27 @@ def test_reuse_flags(key, frames):
         ref, n = oracle.reuse_flags(f.positions, f.indices, kf.view_proj, kf.visible, f.visible)
         assert np.array_equal(flags.cpu().numpy(), ref)
         assert int(reused.item()) == n
+
+
+@pytest.mark.parametrize("T", [0, 1, 1023, 1025, 262143, 262145, 1048577])
+def test_reuse_flags_sizes(T):
+    # around a workgroup (1024), one triangle per thread (262144) and a full
+    # round of the launch (1048576); a second count follows the first
+    fa = _fa()
+    rng = np.random.default_rng(T)
+    pos = rng.uniform(-1.5, 1.5, (60, 3)).astype(np.float32)
+    idx = rng.integers(0, 60, (max(T, 1), 3)).astype(np.int32)
+    cam = scenes.orbit_frame(0).view_proj
+    ctx = fa.Context(max(T, 1), 60, max_charts=16, max_atlas=16)
+    mesh = fa.Mesh(pos, idx, 1)
+    mesh.c.num_triangles = T  # (an empty mesh still has its arrays)
+    for _ in range(2):
+        kvis, vis = (rng.integers(0, 2, max(T, 1)).astype(np.uint8) for _ in range(2))
+        print(f"[gpu] reuse flags T={T}", flush=True)
+        flags, reused = ctx.reuse_flags(mesh, cam, torch.as_tensor(kvis).cuda(),
+                                        torch.as_tensor(vis).cuda())
+        torch.cuda.synchronize()
+        ref, n = oracle.reuse_flags(pos, idx[:T], cam, kvis[:T], vis[:T])
+        assert np.array_equal(flags.cpu().numpy()[:T], ref)
+        assert int(reused.item()) == n
+    ctx.close()
