@@ -268,6 +268,19 @@ __device__ __forceinline__ int wave_max_dpp(int v) {
   return max(max(a, b), max(c, d));
 }
 
+// Unsigned minimum over the wave (uniform result).
+__device__ __forceinline__ uint32_t wave_min_dpp(uint32_t v) {
+  v = min(v, (uint32_t)dpp_keep<0xB1>((int)v));
+  v = min(v, (uint32_t)dpp_keep<0x4E>((int)v));
+  v = min(v, (uint32_t)dpp_keep<0x141>((int)v));
+  v = min(v, (uint32_t)dpp_keep<0x140>((int)v));
+  const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 0),
+                 b = (uint32_t)__builtin_amdgcn_readlane((int)v, 16),
+                 c = (uint32_t)__builtin_amdgcn_readlane((int)v, 32),
+                 d = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+  return min(min(a, b), min(c, d));
+}
+
 // Inclusive prefix sum over the wave: shifts by 1, 2, 4 and 8 lanes inside
 // each row of 16, then the totals of rows 0 and 2 into rows 1 and 3, then
 // the total of rows 0-1 into rows 2 and 3.

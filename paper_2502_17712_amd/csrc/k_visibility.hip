@@ -261,8 +261,8 @@ __global__ __launch_bounds__(kBlock) void k_vis_depth(const float* __restrict__ 
 // finish adds the sums (stored at device scope and completed before the
 // ticket is drawn) and sets the ticket back to 0. One atomic per wave on a
 // single counter, which serializes at about 3 ns each, took 102 us on a
-// 2.2M-triangle scene and its clearing launch 5 (visibility and reuse together
-// 220 -> 133 us).
+// 2.2M-triangle scene and its clearing launch 5; the count per workgroup takes
+// 18 us in all.
 constexpr int kReuseBlock = 1024;
 constexpr int kReusePer = 4;
 constexpr int kReuseGrid = 256;  // workgroups
