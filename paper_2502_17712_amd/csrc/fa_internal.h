@@ -23,6 +23,8 @@ constexpr int kMaxAtlas = 8192;
 constexpr int kCountGrid = 256;      // most workgroups that publish sums in Work::partial
 constexpr int kOrderGroups = 32;     // workgroups of the chart order above 1024 charts
 static_assert(kOrderGroups <= kCountGrid, "the order's chunk sums use Work::partial");
+constexpr int kStripTexels = 64;     // atlas columns per strip of the occupancy count
+constexpr int kMaxStrips = kMaxAtlas / kStripTexels;
 constexpr int kOccBigGrid = 2048;    // blocks of the large-footprint raster
 constexpr int64_t kBigCap = 1 << 20; // queue capacity (more: rasterized where found)
 
@@ -44,6 +46,8 @@ struct FrameState {
   uint32_t ticket;    // workgroups of the occupancy count that have finished
   uint32_t order_claim[5];  // many-chart order: chunks claimed per phase
   uint32_t order_done[4];   // ... and chunks finished per phase
+  uint32_t strip_rows[kMaxStrips];  // atlas rows below the top of the highest placed box that
+                            // reaches a strip of kStripTexels atlas columns
 };
 
 // Constants of one visibility pass, passed by value (float64).
@@ -122,8 +126,7 @@ struct Work {
   unsigned long long* big_counter; // [2] queued footprints << 40 | queued tiles; finished
                          // workgroups of the reuse count (0 between calls)
   fa_chart* pack_charts; // [max_charts] chart records of the packer-only entry
-  int32_t* cand_rs;      // [J][max_charts + 1] row starts of each candidate (frames above
-                         // the LDS capacity of the packer)
+  int32_t* cand_rs;      // [J][max_charts + 1] row starts of each candidate (footprint push)
   int4* chart_tex;       // [max_charts] texel range of each placed box (lo_x, hi_x, lo_y, hi_y)
   int32_t* fp_off;       // [max_charts + 1] first profile column of each chart (footprint push)
   int2* fp_prof;         // [max_profile_columns] full-scale (top, bottom) row of each column

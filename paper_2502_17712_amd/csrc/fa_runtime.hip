@@ -187,7 +187,7 @@ int fa_create(const fa_config* cfg_in, fa_ctx** out_ctx) {
         {(void**)&w.big_fp, 48 * std::min<size_t>(2 * T, (size_t)kBigCap)},
         {(void**)&w.big_counter, 16},            {(void**)&w.partial, 8 * kCountGrid},
         {(void**)&w.pack_charts, sizeof(fa_chart) * C}, {(void**)&w.chart_tex, 16 * C},
-        {(void**)&w.cand_rs, 4 * J * (C + 1)},
+        {(void**)&w.cand_rs, footprint ? 4 * J * (C + 1) : 4},
         {(void**)&w.fp_off, footprint ? 4 * (C + 1) : 4},
         {(void**)&w.fp_prof, footprint ? 8 * (size_t)cfg.max_profile_columns : 8},
         {(void**)&w.fp_group, footprint ? 8 * (T / kWave + 2) : 8},

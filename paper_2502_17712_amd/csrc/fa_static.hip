@@ -77,9 +77,9 @@ size_t carve(char* base, Work* w) {
   x.big_fp = (int4*)take(48 * big);
   x.big_counter = (unsigned long long*)take(8);
   x.pack_charts = nullptr;  // packer-only entry: not used here
-  x.cand_rs = (int32_t*)take(4 * J * (C + 1));
+  x.cand_rs = (int32_t*)take(4);       // no footprint push on this path
   x.chart_tex = (int4*)take(16 * C);
-  x.fp_off = (int32_t*)take(4);        // no footprint push on this path
+  x.fp_off = (int32_t*)take(4);
   x.fp_prof = (int2*)take(8);
   x.fp_group = (unsigned long long*)take(8);
   x.fp_pool = (uint32_t*)take(4);

@@ -121,11 +121,12 @@ __device__ __forceinline__ void k_prologue_body(int64_t V, int32_t* __restrict__
                            const int32_t* __restrict__ check_idx = nullptr) {
   __shared__ uint32_t sh[kBlock / kWave];
   if (blockIdx.x < vblocks) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      FrameState s = {};
-      s.status = FA_OK;
-      *st = s;
-      *big_counter = 0ull;
+    if (blockIdx.x == 0) {
+      // (FA_OK is 0)
+      static_assert(sizeof(FrameState) % 4 == 0 && FA_OK == 0, "the state clears word by word");
+      for (unsigned i = threadIdx.x; i < sizeof(FrameState) / 4; i += blockDim.x)
+        reinterpret_cast<uint32_t*>(st)[i] = 0u;
+      if (threadIdx.x == 0) *big_counter = 0ull;
     }
     // kProVerts vertices per thread, a workgroup apart (contiguous stores)
     const int64_t v0 = (int64_t)blockIdx.x * (blockDim.x * kProVerts) + threadIdx.x;

@@ -29,6 +29,7 @@
 // frontline value only grows, F[x+d] = max over the k covering d of
 // min(y + b, y + 2g + B_k + 1), applied with LDS atomic max.
 #include <climits>
+#include <cstddef>
 
 #include "fa_internal.h"
 
@@ -671,6 +672,41 @@ __device__ __forceinline__ bool sel_better(int j1, int L1, int j2, int L2) {
   return a > b || (a == b && j1 > j2);
 }
 
+// Box i of the packing order at its place in candidate jm + 1; its texel range
+// and the rows it reaches in the strips of the occupancy count.
+__device__ __forceinline__ void place_box(const FrameParams& p, int jm, int L, int i,
+                                          const int32_t* __restrict__ order,
+                                          const long long* __restrict__ cand_x,
+                                          const uint32_t* __restrict__ cand_ab,
+                                          const int32_t* __restrict__ cand_y, int64_t stride,
+                                          fa_chart* __restrict__ charts,
+                                          int4* __restrict__ chart_tex, uint32_t* strips) {
+  const long long Xi = cand_x[(int64_t)jm * stride + i];
+  const uint32_t ab = cand_ab[(int64_t)jm * stride + i];
+  const int a = (int)(ab & 0xFFFFu), b = (int)(ab >> 16);
+  const long long r = Xi >> p.log2omega;
+  const int o = (int)(Xi - (r << p.log2omega));
+  fa_chart& ch = charts[order[i]];
+  const int x = (r % 3 == 0) ? o : L - o - a, y = cand_y[(int64_t)jm * stride + i];
+  ch.x = x;
+  ch.y = y;
+  ch.w = a;
+  ch.h = b;
+  if (chart_tex) {
+    // texels t whose centre lies in the box: 2 x omega <= (2t+1) L < 2 (x+w) omega
+    const int64_t om = p.omega, L2 = 2 * (int64_t)L;
+    const int4 r = make_int4((int)ceil_div64(2 * (int64_t)x * om - L, L2),
+                             (int)ceil_div64(2 * ((int64_t)x + a) * om - L, L2) - 1,
+                             (int)ceil_div64(2 * (int64_t)y * om - L, L2),
+                             (int)ceil_div64(2 * ((int64_t)y + b) * om - L, L2) - 1);
+    chart_tex[order[i]] = r;
+    const int c0 = max(r.x, 0) / kStripTexels, c1 = min(r.y, p.omega - 1) / kStripTexels;
+    const int top = min(r.w + 1, p.omega);  // (box sides may lie past the map's edge)
+    if (top > 0 && r.y >= 0)
+      for (int c = c0; c <= c1; ++c) atomicMax(&strips[c], (uint32_t)top);
+  }
+}
+
 __device__ __forceinline__ void k_select_place_body(
     FrameParams p, const int32_t* __restrict__ cand_tab, FrameState* st,
     int32_t* __restrict__ cand_out, const int32_t* __restrict__ order,
@@ -678,6 +714,7 @@ __device__ __forceinline__ void k_select_place_body(
     const int32_t* __restrict__ cand_y, int64_t stride, fa_chart* __restrict__ charts,
     int4* __restrict__ chart_tex) {
   __shared__ int sj, sL;
+  __shared__ uint32_t strips[kMaxStrips];
   const bool ok = st->status == FA_OK;
   const int C = st->num_charts;
   const int tid = threadIdx.x;
@@ -688,6 +725,7 @@ __device__ __forceinline__ void k_select_place_body(
   }
   if (!ok) return;
   if (blockIdx.x > 0 && (int64_t)blockIdx.x * kBlock >= C) return;
+  if (tid < kMaxStrips) strips[tid] = 0u;
   if (tid < kWave) {
     int j = 0, L = 1, H = 0, rows = 0;
     if (tid < p.J) {
@@ -719,28 +757,11 @@ __device__ __forceinline__ void k_select_place_body(
   }
   __syncthreads();
   const int jm = sj - 1, L = sL;
+  if (jm < 0) return;
   const int i = blockIdx.x * kBlock + tid;
-  if (jm < 0 || i >= C) return;
-  const long long Xi = cand_x[(int64_t)jm * stride + i];
-  const uint32_t ab = cand_ab[(int64_t)jm * stride + i];
-  const int a = (int)(ab & 0xFFFFu), b = (int)(ab >> 16);
-  const long long r = Xi >> p.log2omega;
-  const int o = (int)(Xi - (r << p.log2omega));
-  fa_chart& ch = charts[order[i]];
-  const int x = (r % 3 == 0) ? o : L - o - a, y = cand_y[(int64_t)jm * stride + i];
-  ch.x = x;
-  ch.y = y;
-  ch.w = a;
-  ch.h = b;
-  if (chart_tex) {
-    // texels t whose centre lies in the box: 2 x omega <= (2t+1) L < 2 (x+w) omega
-    const int64_t om = p.omega, L2 = 2 * (int64_t)L;
-    chart_tex[order[i]] = make_int4(
-        (int)ceil_div64(2 * (int64_t)x * om - L, L2),
-        (int)ceil_div64(2 * ((int64_t)x + a) * om - L, L2) - 1,
-        (int)ceil_div64(2 * (int64_t)y * om - L, L2),
-        (int)ceil_div64(2 * ((int64_t)y + b) * om - L, L2) - 1);
-  }
+  if (i < C) place_box(p, jm, L, i, order, cand_x, cand_ab, cand_y, stride, charts, chart_tex, strips);
+  __syncthreads();
+  if (chart_tex && tid < kMaxStrips && strips[tid]) atomicMax(&st->strip_rows[tid], strips[tid]);
 }
 __global__ __launch_bounds__(kBlock) void k_select_place(
     FrameParams p, const int32_t* __restrict__ cand_tab, FrameState* st,
@@ -768,12 +789,9 @@ __global__ __launch_bounds__(kBlock) void k_select_place_b(const BatchView* __re
 
 // ---- packer-only entry: box sizes in, placements out ---------------------
 __global__ void k_pack_state(FrameState* st, int32_t n) {
-  if (threadIdx.x == 0) {
-    FrameState s = {};
-    s.status = FA_OK;
-    s.num_charts = n;
-    *st = s;
-  }
+  constexpr unsigned kCharts = offsetof(FrameState, num_charts) / 4;
+  for (unsigned i = threadIdx.x; i < sizeof(FrameState) / 4; i += blockDim.x)
+    reinterpret_cast<uint32_t*>(st)[i] = i == kCharts ? (uint32_t)n : 0u;  // (FA_OK is 0)
 }
 
 __global__ void k_pack_prepare(const float* __restrict__ sizes, int32_t n,

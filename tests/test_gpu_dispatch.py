@@ -73,3 +73,15 @@ def test_gather_table_overflow():
     # second ones run out of probes and go to the global words
     f = fans(np.concatenate([np.arange(1536), np.arange(512)]), atlas_size=2048)
     compare(check(f), oracle.build_frame(f))
+
+
+# the occupied texels are counted per strip of 64 atlas columns, up to the
+# strip's highest box: maps narrower than a strip, of one row of words per
+# workgroup (4096) and of two (8192)
+@pytest.mark.parametrize("omega,n", [(16, 3), (32, 7), (64, 20), (128, 5), (4096, 30), (8192, 300)])
+def test_occupied_texels(omega, n):
+    f = fans(np.repeat(np.arange(n), 3), seed=omega, atlas_size=omega)
+    g = check(f)
+    assert g["meta"]["status"] == 0
+    assert g["meta"]["occupied_texels"] == int((g["occupancy"] >= 0).sum()) > 0
+    compare(g, oracle.build_frame(f))
