@@ -446,8 +446,9 @@ hipError_t launch_charts_batched(const BatchView* dev, int n, const float* pos,
 hipError_t launch_order_batched(const BatchView* dev, int n, hipStream_t st);
 hipError_t launch_pack_batched(const BatchView* dev, int n, int J, int64_t max_charts, int block,
                                hipStream_t st);
+// max_omega: the largest atlas side of the views
 hipError_t launch_occupancy_batched(const BatchView* dev, int n, const int32_t* idx, int64_t T,
-                                    int64_t V, int small_texels, int lane_texels,
+                                    int64_t V, int max_omega, int small_texels, int lane_texels,
                                     hipStream_t st);
 
 // packer-only path: sizes [n][2] -> charts' oriented sizes and keys

@@ -696,7 +696,7 @@ static int enqueue_views(fa_ctx* ctx, const fa_mesh* mesh, Scene* sc, int32_t n,
 // [r0, r0 + S) run as one round on slots 0..S-1, one launch per stage, with
 // the packing and raster-split knobs kn.
 static int enqueue_batched(fa_ctx* ctx, const fa_mesh* mesh, Scene* sc, int32_t n,
-                           const Knobs& kn, hipStream_t st) {
+                           const fa_view* views, const Knobs& kn, hipStream_t st) {
   const int S = (int)ctx->slots.size();
   const int64_t T = mesh->num_triangles, V = mesh->num_vertices;
   hipError_t e = hipSuccess;
@@ -707,7 +707,10 @@ static int enqueue_batched(fa_ctx* ctx, const fa_mesh* mesh, Scene* sc, int32_t 
     ok(launch_charts_batched(d, m, mesh->positions, mesh->indices, sc->nbr, T, V, st));
     ok(launch_order_batched(d, m, st));
     ok(launch_pack_batched(d, m, ctx->cfg.num_scales, ctx->cfg.max_charts, kn.pack_block, st));
-    ok(launch_occupancy_batched(d, m, mesh->indices, T, V, kn.small_texels, kn.lane_texels, st));
+    int omega = 0;
+    for (int i = r0; i < r0 + m; ++i) omega = std::max(omega, views[i].atlas_size);
+    ok(launch_occupancy_batched(d, m, mesh->indices, T, V, omega, kn.small_texels, kn.lane_texels,
+                                st));
   }
   return e == hipSuccess ? FA_OK : FA_ERR_DEVICE;
 }
@@ -786,7 +789,7 @@ int fa_build_atlas_batch(fa_ctx* ctx, const fa_mesh* mesh, int32_t n, const fa_v
                        st) != hipSuccess ||
         hipEventRecord(ctx->ev_upload, st) != hipSuccess)
       return FA_ERR_DEVICE;
-    if (!ctx->batch_graph) return enqueue_batched(ctx, mesh, sc, n, bkn, st);
+    if (!ctx->batch_graph) return enqueue_batched(ctx, mesh, sc, n, views, bkn, st);
   }
   const bool timing = ctx->timing;
   ctx->timing = false;  // no stage events inside a batch
@@ -809,7 +812,7 @@ int fa_build_atlas_batch(fa_ctx* ctx, const fa_mesh* mesh, int32_t n, const fa_v
       ctx->timing = timing;
       return FA_ERR_DEVICE;
     }
-    rc = batched ? enqueue_batched(ctx, mesh, sc, n, bkn, ctx->cap_stream)
+    rc = batched ? enqueue_batched(ctx, mesh, sc, n, views, bkn, ctx->cap_stream)
                  : enqueue_views(ctx, mesh, sc, n, views, ps, ctx->cap_stream);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(ctx->cap_stream, &g);

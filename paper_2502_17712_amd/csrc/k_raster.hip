@@ -682,13 +682,13 @@ __device__ __forceinline__ void k_occ_count_meta_body(
     fa_atlas_meta* __restrict__ meta) {
   __shared__ unsigned long long sh[kCountBlock / kWave];
   __shared__ uint32_t last;
-  const int row4 = p.omega / 4;                 // 16-byte words per row (a power of two)
-  const int cols = min(row4, kCountBlock);      // columns the workgroup covers at once
-  const int per = kCountBlock / cols;           // ... and rows
-  const int step = (int)gridDim.x * per;
-  const int r_first = (int)blockIdx.x * per + (int)threadIdx.x / cols;
+  const int row4 = p.omega / 4;  // 16-byte words per row (a power of two)
+  static_assert(kCountBlock == 1 << 10, "columns and rows of a workgroup by shifts");
+  const int lc = min(p.log2omega - 2, 10);  // log2 of the columns a workgroup covers at once
+  const int step = (int)gridDim.x << (10 - lc);
+  const int r_first = ((int)blockIdx.x << (10 - lc)) + ((int)threadIdx.x >> lc);
   uint32_t c32 = 0;
-  for (int c = (int)threadIdx.x % cols; c < row4; c += cols) {
+  for (int c = (int)threadIdx.x & ((1 << lc) - 1); c < row4; c += 1 << lc) {
     const int rows = (int)stp->strip_rows[4 * c / kStripTexels];
     const int4* __restrict__ col = occ + c;
     for (int r0 = r_first; r0 < rows; r0 += kCountRows * step) {
@@ -755,6 +755,17 @@ __global__ __launch_bounds__(kCountBlock) void k_occ_count_meta_b(
 
 }  // namespace
 
+namespace {
+// Workgroups of the count: every thread has its kCountRows loads (more
+// workgroups than words keep a small map's count waiting for their launch: 10
+// views of 512^2 took 26.5 us with kCountGrid each, 7.2 so).
+unsigned count_grid(int omega) {
+  const int64_t words = (int64_t)omega * omega / 4;
+  return (unsigned)std::max<int64_t>(
+      1, std::min<int64_t>(words / (kCountBlock * kCountRows), kCountGrid));
+}
+}  // namespace
+
 hipError_t launch_uv(const int64_t V, const FrameParams& p, const Work& w, const int32_t* cov,
                      const fa_chart* charts, float* uv, hipStream_t st) {
   if (V > 0)
@@ -798,7 +809,7 @@ hipError_t launch_occupancy(const int32_t* idx, int64_t T, const FrameParams& p,
                                               w.big, w.big_fp, cap, w.big_counter, w.state);
   mk(st);
   if (x.meta)  // a scaled copy (no frame record) needs no count
-    k_occ_count_meta<<<kCountGrid, kCountBlock, 0, st>>>(p, reinterpret_cast<const int4*>(occ),
+    k_occ_count_meta<<<count_grid(p.omega), kCountBlock, 0, st>>>(p, reinterpret_cast<const int4*>(occ),
                                                          w.partial, w.state, w.big_counter, x.meta);
   mk(st);
   return hipGetLastError();
@@ -1156,7 +1167,7 @@ hipError_t launch_meta(const FrameParams& p, const Work& w, fa_atlas_meta* meta,
 }
 
 hipError_t launch_occupancy_batched(const BatchView* dev, int n, const int32_t* idx, int64_t T,
-                                    int64_t V, int small_texels, int lane_texels,
+                                    int64_t V, int max_omega, int small_texels, int lane_texels,
                                     hipStream_t st) {
   if (n <= 0) return hipSuccess;
   const uint32_t cap = (uint32_t)std::min<int64_t>(2 * std::max<int64_t>(T, 1), kBigCap);
@@ -1167,7 +1178,7 @@ hipError_t launch_occupancy_batched(const BatchView* dev, int n, const int32_t* 
     k_occ_small_b<<<dim3(occ_blocks + uv_blocks, n), kOccSmallBlock, 0, st>>>(
         dev, idx, cap, small_texels, lane_texels, occ_blocks, V);
   if (T > 0) k_occ_big_b<<<dim3(kOccBigGrid, n), kBlock, 0, st>>>(dev, idx, cap);
-  k_occ_count_meta_b<<<dim3(kCountGrid, n), kCountBlock, 0, st>>>(dev);
+  k_occ_count_meta_b<<<dim3(count_grid(max_omega), n), kCountBlock, 0, st>>>(dev);
   return hipGetLastError();
 }
 
