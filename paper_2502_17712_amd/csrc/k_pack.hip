@@ -28,6 +28,7 @@
 // y = max over k of (max F over the window) - T_k, and, since the new
 // frontline value only grows, F[x+d] = max over the k covering d of
 // min(y + b, y + 2g + B_k + 1), applied with LDS atomic max.
+#include <algorithm>
 #include <climits>
 #include <cstddef>
 
@@ -263,25 +264,677 @@ __global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
 
 // Box push of one candidate per workgroup (the default packing). Everything
 // the row loop reads is in LDS, so its only global accesses are the stores of
-// the box positions, which no later instruction of the workgroup waits for:
-//   [2 omega]  frontline F (int32)
+// the box positions, which no later instruction of the workgroup waits for.
+// Dynamic LDS, in 32-bit words (box_lds):
 //   [kcap]     fold position of each box of the current chunk, relative to
-//              the chunk's first box (uint32: a chunk spans less than 2^32)
+//              the chunk's first box (kcap boxes of at most 2 omega + 1 columns
+//              span less than 2^31)
 //   [kcap]     a | b << 16 of each box of the chunk
-//   [kcap + 1] chunk-local starts of the chunk's row segments
-// Frames with more than kcap charts are pushed in chunks of kcap boxes in
-// order, reloaded from the fold written to global memory; a row that
-// straddles two chunks is pushed as two segments (its boxes have disjoint
-// spans, so the split changes nothing). Two barriers per segment (its narrow
-// boxes, then its wider ones); cross-lane maxima and scans use DPP lane
+//   [kcap + 4] by rows: the boxes under each box, then its top; by columns:
+//              chunk-local starts of the chunk's row segments
+//   by rows: the frontline's edge columns, the tables of shared boxes, the
+//   cells (16 bits: box at every 2^g-th fold position) and the row starts (16
+//   bits); by columns: the whole frontline, then the lists of mid and wide
+//   boxes.
+// Frames with more than kcap charts are pushed in chunks, reloaded from the
+// fold written to global memory. Cross-lane maxima and scans use DPP lane
 // moves.
-constexpr int kFoldItems = 4;  // consecutive boxes per thread in the fold
-constexpr int kNarrow = 8;     // boxes up to this wide are pushed by one lane
+//
+// By rows (push_rows). A row's boxes follow each other without holes, so all
+// columns but the at most m on either side of it are covered by the row
+// before, and what a box rises to is the highest top among the few boxes of
+// that row under it. Those are found for all boxes of a chunk at once, before
+// the push; a row then costs two dependent LDS accesses and one barrier,
+// however wide its boxes are. Only the m edge columns on each side, which a
+// row may leave to an older one, keep a frontline value each. Reading and
+// raising every column of every box (push_columns) took about 2.4 us a row of
+// 4096 columns: 273 us for 23.7k charts and 64 us for 3000 boxes of 33
+// columns; by rows, at about 1 us a row, they take 179 and 34 us.
+// By columns: candidates with a wide overflow m (a few boxes nearly as wide as
+// the atlas), where the edges are most of the frontline, rows so long that two
+// of them do not fit a chunk, and frames of up to kFewBoxes charts, whose few
+// columns walks take less than finding what lies under each box (one chart:
+// 7.6 us by columns, 8.5 by rows).
+constexpr int kFoldItems = 4;   // consecutive boxes per thread in the fold
+constexpr int kNarrow = 8;      // by columns: boxes up to this wide are pushed by one lane
+constexpr int kMidList = 2048, kWideList = 256;  // by columns: entries of the box lists
+constexpr int kFewBoxes = 8;
+constexpr int kEdgeMax = 1024;  // by rows: most edge columns on either side
+constexpr int kUnderLane = 8;   // by rows: boxes under a box that one lane looks at
+// By rows: the mark of a box that 16 lanes push together, in its a | b << 16
+// (a and b are below 2^15), which the push leaves as it is.
+constexpr uint32_t kShared16 = 1u << 31;
 
-// Dynamic LDS of the box push: frontline plus kcap boxes of 12 bytes.
-constexpr int kBoxPushLds = 131072;
+constexpr int kCellBits = 12;   // by rows: 2^12 cells index a chunk's fold positions
+constexpr int kCells = 1 << kCellBits;
+constexpr int kTabRows = 128;   // by rows: rows of a chunk with a table of their shared boxes
+constexpr int kTabBoxes = 8;    // ... of this many
+
+// Boxes per chunk by columns (by rows: the multiples of it end a segment too,
+// so that both stop at the same box) and by rows, and the dynamic LDS of a
+// push.
 __host__ __device__ inline int box_kcap(int omega) {
-  return ((kBoxPushLds - 8 * omega - 4) / 12) & ~63;
+  return ((131072 - 8 * omega - 4) / 12) & ~63;
+}
+__host__ __device__ inline int row_kcap(int omega) {
+  return box_kcap(omega) < 8128 ? box_kcap(omega) : 8128;
+}
+__host__ inline size_t box_lds(int omega) {
+  const size_t kc = (size_t)box_kcap(omega), kr = (size_t)row_kcap(omega);
+  const size_t rows = 4 * kc + 8 * kr + 16 + 8 * (size_t)std::min(omega, kEdgeMax) +
+                      (16 * kTabBoxes + 4) * kTabRows + 2 * (kCells + 8) + 2 * (kr + 2);
+  const size_t columns = 12 * kc + 16 + 8 * (size_t)omega + 4 * (kMidList + kWideList);
+  return (std::max(rows, columns) + 15) & ~size_t(15);
+}
+// ... at any atlas side
+__host__ inline size_t box_lds_max() {
+  size_t most = 0;
+  for (int om = 16; om <= kMaxAtlas; om *= 2) most = std::max(most, box_lds(om));
+  return most;
+}
+
+// What both pushes work on.
+struct PushArgs {
+  const long long* Xg;     // the candidate's fold in global memory
+  const uint32_t* ABg;
+  int32_t* Y;              // positions out
+  int C, omega, lg, m, kcap;
+};
+
+// The next chunk [c0, c0 + cn) from the fold in global memory.
+template <int NT>
+__device__ __forceinline__ long long load_chunk(const PushArgs& q, int c0, int cn, uint32_t* Xr,
+                                                uint32_t* AB) {
+  const long long xbase = q.Xg[c0];
+  constexpr int U = 4;  // loads in flight per thread
+  for (int i0 = threadIdx.x; i0 < cn; i0 += U * NT) {
+    long long xv[U];
+    uint32_t abv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * NT;
+      xv[u] = i < cn ? q.Xg[c0 + i] : 0;
+      abv[u] = i < cn ? q.ABg[c0 + i] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * NT;
+      if (i < cn) {
+        Xr[i] = (uint32_t)(xv[u] - xbase);
+        AB[i] = abv[u];
+      }
+    }
+  }
+  __syncthreads();
+  return xbase;
+}
+
+// First box of every row among the cn boxes of a chunk, in order, into RS
+// (ROW_OF: also each box's number of rows started up to it, less one, into
+// row_of). Returns the number of rows; ends before a barrier.
+template <int NT, bool ROW_OF, typename R>
+__device__ __forceinline__ int row_starts(const PushArgs& q, long long xbase, int cn,
+                                          const uint32_t* Xr, R* RS, uint32_t* row_of,
+                                          uint32_t (*shs)[NT / kWave], int& pass) {
+  int nr = 0;
+  for (int base = 0; base < cn; base += kFoldItems * NT, ++pass) {
+    const int i0 = base + kFoldItems * threadIdx.x;
+    uint32_t fl = 0, own = 0;
+    if (i0 < cn) {
+      const uint4 v = *reinterpret_cast<const uint4*>(Xr + i0);
+      const uint32_t xv[kFoldItems + 1] = {i0 > 0 ? Xr[i0 - 1] : 0u, v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int u = 0; u < kFoldItems; ++u) {
+        const int i = i0 + u;
+        const bool f = i < cn && (i == 0 || ((xbase + xv[u + 1]) >> q.lg) !=
+                                                ((xbase + xv[u]) >> q.lg));
+        fl |= (uint32_t)f << u;
+        own += f;
+      }
+    }
+    uint32_t tot;
+    int at = nr + (int)(block_incl_scan_dpp<NT>(own, shs[pass & 1], &tot) - own);
+#pragma unroll
+    for (int u = 0; u < kFoldItems; ++u) {
+      if (fl >> u & 1u) RS[at++] = (R)(i0 + u);
+      if (ROW_OF && i0 + u < cn) row_of[i0 + u] = (uint32_t)(at - 1);
+    }
+    nr += (int)tot;
+  }
+  return nr;
+}
+
+// A row in a chunk: its base (fold position of column 0, relative to the
+// chunk) and whether it runs right to left.
+struct Row {
+  int base;
+  bool right;
+};
+__device__ __forceinline__ Row row_at(const PushArgs& q, long long xbase, uint32_t x) {
+  const long long r = (xbase + x) >> q.lg;
+  return Row{(int)((r << q.lg) - xbase), (uint32_t)r % 3u != 0u};
+}
+
+// A zero that the compiler takes to differ between lanes: a uniform LDS word
+// loaded at an index with it added stays in a vector register until its own
+// readfirstlane, instead of being waited for at once.
+__device__ __forceinline__ int lane_zero() {
+  int z;
+  asm volatile("v_mov_b32 %0, 0" : "=v"(z));
+  return z;
+}
+
+// The edge value of column u counted from a row's start is E[base + step u],
+// with the base of the row's own low (u < m) or high (u >= omega) side.
+__device__ __forceinline__ int edge_step(bool right) { return right ? -1 : 1; }
+__device__ __forceinline__ int edge_low(const PushArgs& q, bool right) {
+  return right ? 2 * q.m - 1 : 0;
+}
+__device__ __forceinline__ int edge_high(const PushArgs& q, bool right) {
+  return right ? q.omega + q.m - 1 : q.m - q.omega;
+}
+
+// What the push of a shared box needs: the box and its height, the boxes under
+// it, and the edge words under it on either side (first and count each, the
+// height or count in the upper half).
+__device__ __forceinline__ uint4 shared_box(const PushArgs& q, int k, uint32_t ab, int first, int n,
+                                            int u, bool right, int pf, int pe) {
+  const int a = (int)(ab & 0xFFFFu), step = edge_step(right);
+  const int l1 = min(u + a, pf), h0 = max(u, pe);  // columns [u, l1) and [h0, u + a)
+  const int nl = max(l1 - u, 0), nh = max(u + a - h0, 0);
+  const int l = edge_low(q, right) + step * (right ? l1 - 1 : u);
+  const int h = edge_high(q, right) + step * (right ? u + a - 1 : h0);
+  return make_uint4((uint32_t)k | (ab & 0xFFFF0000u), (uint32_t)first | ((uint32_t)n << 16),
+                    nl ? (uint32_t)l | ((uint32_t)nl << 16) : 0u,
+                    nh ? (uint32_t)h | ((uint32_t)nh << 16) : 0u);
+}
+
+// Push a shared box by the 16 lanes of a row of the wave (sl: the lane's place
+// among them); v: its words, wanted or not. Returns the box's top in every
+// lane; every lane of the wave calls it.
+__device__ __forceinline__ int push_shared(const uint4 v, bool wanted, int sl, const uint32_t* PT,
+                                           const int32_t* E) {
+  const uint32_t vy = wanted ? v.y : 0u, vz = wanted ? v.z : 0u, vw = wanted ? v.w : 0u;
+  const int first = (int)(vy & 0xFFFFu), n = (int)(vy >> 16);
+  const int l = (int)(vz & 0xFFFFu), nl = (int)(vz >> 16);
+  const int h = (int)(vw & 0xFFFFu), nh = (int)(vw >> 16);
+  // the first 16 boxes and 32 columns of either edge load together (a word
+  // that is not wanted reads another)
+  const int v0 = (int)PT[first + min(sl, max(n - 1, 0))];
+  const int v1 = E[l + min(sl, max(nl - 1, 0))], v2 = E[l + min(sl + 16, max(nl - 1, 0))];
+  const int v3 = E[h + min(sl, max(nh - 1, 0))], v4 = E[h + min(sl + 16, max(nh - 1, 0))];
+  int y = n ? v0 : 0;
+  y = max(y, nl ? max(v1, v2) : 0);
+  y = max(y, nh ? max(v3, v4) : 0);
+  if (__ballot(n > 16 || nl > 32 || nh > 32)) {
+    for (int i = sl + 16; i < n; i += 16) y = max(y, (int)PT[first + i]);
+    for (int i = sl + 32; i < nl; i += 16) y = max(y, E[l + i]);
+    for (int i = sl + 32; i < nh; i += 16) y = max(y, E[h + i]);
+  }
+  return row16_max(y);
+}
+
+// cell[c]: the box of the chunk that holds fold position c << g (boxes follow
+// each other without holes from position 0); returns g, the least with the
+// whole chunk in kCells cells and in one to four cells a box. The entry past
+// the last position's holds the last box. Ends before a barrier.
+template <int NT>
+__device__ __forceinline__ int fill_cells(int cn, const uint32_t* Xr, const uint32_t* AB,
+                                          uint16_t* cell) {
+  const int span = (int)Xr[cn - 1] + (int)(AB[cn - 1] & 0xFFFFu);
+  // (cells a power of two: the span's bit length less the cells')
+  const int bits = min(kCellBits, 33 - __clz(cn));
+  const int g = max(0, 32 - __clz(span - 1) - bits);
+  const int last = (span - 1) >> g;
+  const int lane = lane_id();
+  for (int ib = (int)(threadIdx.x & ~(kWave - 1)); ib < cn; ib += NT) {
+    const int i = ib + lane;
+    int c = 0, e = 0;  // cells [c, e) start inside box i
+    if (i < cn) {
+      const int x = (int)Xr[i];
+      c = (x + (1 << g) - 1) >> g;
+      e = i == cn - 1 ? last + 2 : (x + (int)(AB[i] & 0xFFFFu) + (1 << g) - 1) >> g;
+    }
+    const bool wide = e - c > 8;
+    if (!wide)
+      for (; c < e; ++c) cell[c] = (uint16_t)i;
+    for (unsigned long long todo = __ballot(wide); todo; todo &= todo - 1) {
+      const int l = __ffsll((long long)todo) - 1;
+      const int c0 = __builtin_amdgcn_readlane(c, l), c1 = __builtin_amdgcn_readlane(e, l);
+      for (int k = c0 + lane; k < c1; k += kWave) cell[k] = (uint16_t)(ib + l);
+    }
+  }
+  return g;
+}
+
+// The boxes of the row before under each box of a chunk, into PT: first |
+// count << 14; kShared16 in AB where they are more than kUnderLane or some
+// columns are the edge's. On entry PT holds each box's row. A box under an end of the
+// span is looked up through its cell: a search over the boxes of that cell
+// (one or two steps; over the whole row, eight). The shared boxes of the first
+// kTabRows rows also go to their row's table, with all that their push needs
+// (tab_n counts them, past kTabBoxes too).
+template <int NT>
+__device__ __forceinline__ void boxes_under(const PushArgs& q, long long xbase, int c0, int cn,
+                                            const uint32_t* Xr, uint32_t* AB, const uint16_t* RS,
+                                            const uint16_t* cell, int g, uint32_t* PT, uint4* tab, uint32_t* tab_n) {
+  const int L = q.omega + q.m;
+  for (int i = threadIdx.x; i < cn; i += NT) {
+    const int ri = (int)PT[i];
+    const uint32_t ab = AB[i];
+    if (ri == 0) {
+      // the first row of the frame rests on nothing; that of a later chunk is
+      // pushed already: its top
+      PT[i] = c0 > 0 ? (uint32_t)q.Y[c0 + i] + (ab >> 16) : 0u;
+      continue;
+    }
+    const int rs = RS[ri], ps = RS[ri - 1];
+    const int a = (int)(ab & 0xFFFFu), x = (int)Xr[i], xr = (int)Xr[rs], xp = (int)Xr[ps];
+    const Row cur = row_at(q, xbase, xr), prv = row_at(q, xbase, xp);
+    const int o = x - cur.base;
+    const int u = cur.right != prv.right ? L - o - a : o;  // from the start of the row before
+    const int b0 = prv.base + u, b1 = b0 + a;              // ... as fold positions
+    // the boxes that hold the first and the last position in that row
+    const int p0 = min(max(b0, xp), xr - 1), p1 = min(max(b1 - 1, xp), xr - 1);
+    int lo = cell[p0 >> g], hi = cell[(p0 >> g) + 1];
+    int lo2 = cell[p1 >> g], hi2 = cell[(p1 >> g) + 1];
+    while (lo < hi || lo2 < hi2) {
+      const int mid = (lo + hi + 1) >> 1, mid2 = (lo2 + hi2 + 1) >> 1;
+      const int v = (int)Xr[mid], v2 = (int)Xr[mid2];
+      if (lo < hi) {
+        if (v <= p0) lo = mid;
+        else hi = mid - 1;
+      }
+      if (lo2 < hi2) {
+        if (v2 <= p1) lo2 = mid2;
+        else hi2 = mid2 - 1;
+      }
+    }
+    const bool none = b0 >= xr || b1 <= xp;  // all of it over edge columns
+    const int n = none ? 0 : lo2 - lo + 1;
+    const bool shared = n > kUnderLane || b0 < xp || b1 > xr;
+    PT[i] = (uint32_t)lo | ((uint32_t)n << 14);
+    if (shared) AB[i] = ab | kShared16;
+    if (shared && ri < kTabRows) {
+      const uint32_t slot = atomicAdd(&tab_n[ri], 1u);
+      if (slot < kTabBoxes)
+        tab[ri * kTabBoxes + slot] = shared_box(q, i, ab, lo, n, u, prv.right, xp - prv.base,
+                                                xr - prv.base);
+    }
+  }
+}
+
+// Push by rows; over[0] receives the height. The push stops one segment after
+// the first one whose top lies above L, a segment being a row or, where a
+// multiple of kcap boxes falls inside it, its part on either side.
+//
+// A segment is one step between two barriers, bound by the latency of its
+// instructions, so its parts run in different waves: half of them push the
+// plain boxes, one a lane; a quarter the shared ones, 16 lanes each; the last
+// quarter stores the tops of the row before in its edge columns. Everything of
+// a step that the step before cannot change (the boxes' words, row bounds) is
+// loaded before the barrier.
+template <int NT>
+__device__ __forceinline__ void push_rows(const PushArgs& q, int32_t* S, int& pass,
+                                          uint32_t (*shs)[NT / kWave], int32_t* over) {
+  int Hw = 0;  // the thread's highest top
+  constexpr int NW = NT / kWave;
+  constexpr int NP = NW / 2, NS = NW / 4, NE = NW - NP - NS;  // plain, shared, edge waves
+  static_assert(NW % 4 == 0, "every part has a wave");
+  const int kr = row_kcap(q.omega);
+  uint32_t* Xr = reinterpret_cast<uint32_t*>(S);
+  uint32_t* AB = Xr + q.kcap;  // (where the fold put the first chunk)
+  uint32_t* PT = AB + kr;
+  int32_t* E = reinterpret_cast<int32_t*>(PT + kr + 4);  // [m] left, [m] right edge columns
+  uint4* tab = reinterpret_cast<uint4*>(E + 2 * min(q.omega, kEdgeMax));
+  uint32_t* tab_n = reinterpret_cast<uint32_t*>(tab + kTabRows * kTabBoxes);
+  uint16_t* cell = reinterpret_cast<uint16_t*>(tab_n + kTabRows);
+  uint16_t* RS = cell + kCells + 8;
+  const int tid = threadIdx.x, lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int sub = lane >> 4, sl = lane & 15;
+  const int m = q.m, L = q.omega + m, C = q.C;
+  const int zero = lane_zero();
+  for (int c = tid; c < 2 * m; c += NT) E[c] = 0;
+  if (tid < 3) over[tid] = 0;
+
+  int o_prev = 2, o_cur = 0;  // slots of `over`: the segment before, this one
+  int rbegin = 0;             // rows at the chunk's start that are pushed already
+  long long xbase = 0;
+  for (int c0 = 0;;) {
+    const int cn = min(kr, C - c0);
+    if (c0 > 0) xbase = load_chunk<NT>(q, c0, cn, Xr, AB);
+    const int g = fill_cells<NT>(cn, Xr, AB, cell);
+    if (tid < kTabRows) tab_n[tid] = 0u;
+    const int nr = row_starts<NT, true>(q, xbase, cn, Xr, RS, PT, shs, pass);
+    if (tid < 2) RS[nr + tid] = (uint16_t)cn;
+    __syncthreads();
+    boxes_under<NT>(q, xbase, c0, cn, Xr, AB, RS, cell, g, PT, tab, tab_n);
+    __syncthreads();
+
+    // ---- push (a row that the chunk cuts waits for the next chunk)
+    const int full = c0 + cn == C ? nr : nr - 1;
+    int ri = rbegin;
+    int s0 = RS[ri], s1 = RS[ri + 1];
+    int ps = ri > 0 ? (int)RS[ri - 1] : 0;
+    uint32_t x0 = Xr[s0];
+    Row cur = row_at(q, xbase, x0), prv = row_at(q, xbase, Xr[ps]);
+    int pf = (int)Xr[ps] - prv.base, pe = (int)x0 - prv.base;
+    int cut = ((c0 + s0) / q.kcap + 1) * q.kcap - c0;  // the next multiple of kcap
+    int e0 = s0;
+    bool stop = false;
+    // this lane's first box of the segment (plain waves), the 16 lanes' first
+    // table entry of the row (shared waves)
+    const int at = w * kWave + lane, slot0 = 4 * (w - NP) + sub;
+    const bool tabled = w >= NP && w < NP + NS && slot0 < kTabBoxes;
+    uint32_t pt_nxt = 0u, ab_nxt = 0u, n_nxt = 0u;
+    uint4 t_nxt = make_uint4(0u, 0u, 0u, 0u);
+    if (w < NP) {
+      pt_nxt = PT[min(e0 + at, cn - 1)];
+      ab_nxt = AB[min(e0 + at, cn - 1)];
+    } else if (w < NP + NS) {
+      n_nxt = tab_n[min(ri, kTabRows - 1) + zero];
+      if (tabled) t_nxt = tab[min(ri, kTabRows - 1) * kTabBoxes + slot0];
+    }
+    while (ri < full) {
+      const int e1 = min(s1, cut);
+      const int32_t was_over = over[o_prev + zero];
+      const int rs2_v = RS[ri + 2 + zero];
+      const uint32_t x1_v = Xr[min(s1, cn - 1) + zero];
+      bool above = false;
+
+      if (w < NP) {
+        // plain boxes (the next segment starts at e1)
+        const uint32_t pt_seg = PT[min(e1 + at, cn - 1)], ab_seg = AB[min(e1 + at, cn - 1)];
+        for (int k0 = e0 + w * kWave; k0 < e1; k0 += NP * kWave) {
+          const int k = k0 + lane;
+          const bool mine = k < e1 && !(ab_nxt & kShared16);
+          const uint32_t pt = mine ? pt_nxt : 0u;
+          const int b = (int)(ab_nxt >> 16);
+          if (k0 + NP * kWave < e1) {
+            pt_nxt = PT[min(k + NP * kWave, cn - 1)];
+            ab_nxt = AB[min(k + NP * kWave, cn - 1)];
+          }
+          const int first = (int)(pt & 0x3FFFu), n = (int)(pt >> 14);
+          int v[kUnderLane / 2];
+#pragma unroll
+          for (int u = 0; u < kUnderLane / 2; ++u) v[u] = (int)PT[first + max(0, min(u, n - 1))];
+          int y = max(max(v[0], v[1]), max(v[2], v[3]));
+          if (__ballot(n > kUnderLane / 2)) {
+#pragma unroll
+            for (int u = 0; u < kUnderLane / 2; ++u)
+              v[u] = (int)PT[first + max(0, min(u + kUnderLane / 2, n - 1))];
+            y = max(y, max(max(v[0], v[1]), max(v[2], v[3])));
+          }
+          if (n == 0) y = 0;
+          if (mine) {
+            PT[k] = (uint32_t)(y + b);
+            q.Y[c0 + k] = y;
+            Hw = max(Hw, y + b);
+            above = above || y + b > L;
+          }
+        }
+        pt_nxt = pt_seg;
+        ab_nxt = ab_seg;
+      } else if (w < NP + NS) {
+        // shared boxes: 16 lanes each, four at a time
+        const int rn = min(e1 == s1 ? ri + 1 : ri, kTabRows - 1);
+        const uint32_t n_seg = tab_n[rn + zero];
+        uint4 t_seg = make_uint4(0u, 0u, 0u, 0u);
+        if (tabled) t_seg = tab[rn * kTabBoxes + slot0];
+        auto put = [&](int k, int b, int y, bool wanted) {
+          if (wanted && sl == 0) {
+            PT[k] = (uint32_t)(y + b);
+            q.Y[c0 + k] = y;
+            Hw = max(Hw, y + b);
+            above = above || y + b > L;
+          }
+        };
+        const int ns = __builtin_amdgcn_readfirstlane((int)n_nxt);
+        if (ri < kTabRows && ns <= kTabBoxes) {
+          // from the row's table, 4 NS entries at a time
+          for (int t0 = 4 * (w - NP); t0 < ns; t0 += 4 * NS) {
+            if (t0 != 4 * (w - NP)) t_nxt = tab[ri * kTabBoxes + min(t0 + sub, kTabBoxes - 1)];
+            const int k = (int)(t_nxt.x & 0xFFFFu);
+            const bool wanted = t0 + sub < ns && k >= e0 && k < e1;
+            put(k, (int)(t_nxt.x >> 16), push_shared(t_nxt, wanted, sl, PT, E), wanted);
+          }
+        } else {
+          // found among the row's boxes
+          for (int k0 = e0 + (w - NP) * kWave; k0 < e1; k0 += NS * kWave) {
+            const int ko = k0 + lane;
+            unsigned long long todo = __ballot(ko < e1 && (AB[min(ko, cn - 1)] & kShared16));
+            while (todo) {
+              int src = -1;
+#pragma unroll
+              for (int g4 = 0; g4 < 4; ++g4) {
+                if (todo) {
+                  const int l = __ffsll((long long)todo) - 1;
+                  todo &= todo - 1;
+                  if (sub == g4) src = l;
+                }
+              }
+              const int k = k0 + max(src, 0);
+              const uint32_t pt = PT[k], ab = AB[k] & ~kShared16;
+              const int a = (int)(ab & 0xFFFFu), o = (int)Xr[k] - cur.base;
+              const int u = cur.right != prv.right ? L - o - a : o;
+              const uint4 v = shared_box(q, k, ab, (int)(pt & 0x3FFFu), (int)(pt >> 14), u,
+                                         prv.right, pf, pe);
+              put(k, (int)(ab >> 16), push_shared(v, src >= 0, sl, PT, E), src >= 0);
+            }
+          }
+        }
+        n_nxt = n_seg;
+        t_nxt = t_seg;
+      } else if (e0 == s0 && ri > 0) {
+        // the tops of the row before into its edge columns (boxes read only
+        // the columns it left): the even waves on the low side, the odd ones
+        // (or the same one) on the high side, four boxes at a time
+        const int we = w - NP - NS;
+        constexpr int NH = NE > 1 ? NE / 2 : 1;  // waves per side
+        const int p_step = edge_step(prv.right);
+        const int p_low = edge_low(q, prv.right), p_high = edge_high(q, prv.right);
+        if (NE == 1 || we % 2 == 0) {
+          for (int kb = ps + 4 * (we / 2); kb < s0; kb += 4 * NH) {
+            const int k = min(kb + sub, s0 - 1);
+            const uint32_t ab = AB[k], x = Xr[k];
+            const int top = (int)PT[k];
+            const int o = (int)x - prv.base;
+            if (!__ballot(o < m)) break;
+            const int e = min(o + (int)(ab & 0xFFFFu), m);
+            for (int c = o + sl; c < e; c += 16) E[p_low + p_step * c] = top;
+            if (__ballot(e == m)) break;  // the boxes after it start past the edge
+          }
+        }
+        if (NE == 1 || we % 2 == 1) {
+          for (int kb = s0 - 1 - 4 * (we / 2); kb >= ps; kb -= 4 * NH) {
+            const int k = max(kb - sub, ps);
+            const uint32_t ab = AB[k], x = Xr[k];
+            const int top = (int)PT[k];
+            const int o = (int)x - prv.base, e = o + (int)(ab & 0xFFFFu);
+            if (!__ballot(e > q.omega)) break;
+            for (int c = max(o, q.omega) + sl; c < e; c += 16) E[p_high + p_step * c] = top;
+            if (__ballot(o <= q.omega)) break;  // the boxes before it end before the edge
+          }
+        }
+      }
+      if (above) over[o_cur] = 1;
+      const uint32_t x1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)x1_v);
+      const int s2 = __builtin_amdgcn_readfirstlane(rs2_v);
+      const Row nxt = row_at(q, xbase, x1);
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(was_over)) {
+        stop = true;
+        break;
+      }
+      o_prev = o_cur;
+      o_cur = o_cur == 2 ? 0 : o_cur + 1;
+      if (e1 == cut) cut += q.kcap;
+      e0 = e1;
+      if (e1 == s1) {
+        ++ri;
+        ps = s0;
+        prv = cur;
+        pf = (int)x0 - prv.base;
+        pe = (int)x1 - prv.base;
+        s0 = s1;
+        s1 = s2;
+        x0 = x1;
+        cur = nxt;
+      }
+    }
+    if (stop || c0 + cn == C) break;
+    // the next chunk starts with the last row pushed
+    c0 += ps;
+    rbegin = 1;
+    __syncthreads();  // (every thread has read its words of this chunk)
+  }
+  // the height in over[0] (which every thread has read)
+  if (tid < 3) over[tid] = 0;
+  __syncthreads();
+  const int hw = wave_max_dpp(Hw);
+  if (lane == 0) atomicMax(&over[0], hw);
+  __syncthreads();
+}
+
+// The start of a push by columns (the frontline at its widest).
+template <int NT>
+__device__ __forceinline__ void columns_clear(int omega, int32_t* F, int32_t* Hsh,
+                                              int32_t (*LC)[2]) {
+  const int tid = threadIdx.x;
+  for (int c = tid; c < 2 * omega; c += NT) F[c] = 0;
+  if (tid < 3) Hsh[tid] = 0;
+  if (tid < 4) LC[tid >> 1][tid & 1] = 0;
+}
+
+// Push by columns: the boxes of a chunk segment by segment in two phases. A:
+// the threads take the segment's boxes in order; a box at most kNarrow columns
+// wide is pushed by its own lane, the others go to a list of mid boxes (up to
+// 64 columns) or of wide ones. B (after a barrier): the mid boxes four per
+// wave step, 16 lanes each; the wide boxes one per wave. Boxes of a row have
+// disjoint spans, so the order inside a segment changes nothing. A row that
+// straddles two chunks is pushed as two segments. Bounds of the lists: a row's
+// boxes lie in L <= 2 omega <= 16384 columns, so at most 1820 are wider than 8
+// and 252 wider than 64.
+template <int NT>
+__device__ __forceinline__ void push_columns(const PushArgs& q, int32_t* S, int& pass,
+                                             uint32_t (*shs)[NT / kWave], int32_t* Hsh,
+                                             int32_t (*LC)[2]) {
+  constexpr int NW = NT / kWave;
+  uint32_t* Xr = reinterpret_cast<uint32_t*>(S);
+  uint32_t* AB = Xr + q.kcap;
+  int32_t* RS = reinterpret_cast<int32_t*>(AB + q.kcap);
+  int32_t* F = RS + q.kcap + 4;
+  int32_t* WM = F + 2 * q.omega;
+  int32_t* WW = WM + kMidList;
+  const int tid = threadIdx.x, w = tid / kWave, lane = lane_id();
+  const int sub = lane >> 4, sl = lane & 15;
+  const int L = q.omega + q.m, C = q.C;
+  if (C > kFewBoxes) {  // (cleared beside the fold otherwise)
+    columns_clear<NT>(q.omega, F, Hsh, LC);
+    __syncthreads();
+  }
+
+  int seg = 0, Hw = 0;
+  bool over = false;
+  for (int c0 = 0; c0 < C && !over; c0 += q.kcap) {
+    const int cn = min(q.kcap, C - c0);
+    long long xbase = 0;
+    if (c0 > 0) xbase = load_chunk<NT>(q, c0, cn, Xr, AB);
+    const int nr = row_starts<NT, false>(q, xbase, cn, Xr, RS, nullptr, shs, pass);
+    if (tid == 0) RS[nr] = cn;
+    __syncthreads();
+
+    int s0 = 0, s1 = nr > 0 ? RS[1] : 0;
+    Row row = row_at(q, xbase, Xr[0]);
+    for (int rr = 0; rr < nr; ++rr, ++seg) {
+      // next segment: its end and its row
+      const int s1n = rr + 2 <= nr ? RS[rr + 2] : cn;
+      const uint32_t xfirst = rr + 1 < nr ? Xr[s1] : 0u;
+      const int hprev = Hsh[(seg + 2) % 3];  // the height after segment seg - 1
+      int* cnt = LC[seg & 1];
+      for (int k = s0 + tid; k < s1; k += NT) {
+        const uint32_t ab = AB[k];
+        const int a = (int)(ab & 0xFFFFu), b = (int)(ab >> 16);
+        const int o = (int)Xr[k] - row.base;
+        const int x = row.right ? L - o - a : o;
+        const bool narrow = a <= kNarrow;
+        if (narrow) {
+          int v[kNarrow];
+#pragma unroll
+          for (int c = 0; c < kNarrow; ++c) v[c] = c < a ? F[x + c] : 0;
+          int mx = 0;
+#pragma unroll
+          for (int c = 0; c < kNarrow; ++c) mx = max(mx, v[c]);
+#pragma unroll
+          for (int c = 0; c < kNarrow; ++c)
+            if (c < a) F[x + c] = mx + b;
+          q.Y[c0 + k] = mx;
+          Hw = max(Hw, mx + b);
+        }
+        const bool wide = a > kWave;
+        const unsigned long long mm = __ballot(!narrow && !wide), mw = __ballot(wide);
+        const unsigned long long below = lanes_below();
+        int bm = 0, bw = 0;
+        if (lane == __ffsll((long long)__ballot(true)) - 1) {
+          if (mm) bm = atomicAdd(&cnt[0], __popcll(mm));
+          if (mw) bw = atomicAdd(&cnt[1], __popcll(mw));
+        }
+        bm = __builtin_amdgcn_readfirstlane(bm);
+        bw = __builtin_amdgcn_readfirstlane(bw);
+        if (!narrow && !wide) WM[bm + __popcll(mm & below)] = k;
+        if (wide) WW[bw + __popcll(mw & below)] = k;
+      }
+      __syncthreads();
+      const int nm = cnt[0], nwd = cnt[1];
+      if (tid == 0) {
+        LC[(seg + 1) & 1][0] = 0;
+        LC[(seg + 1) & 1][1] = 0;
+      }
+      for (int e0 = 4 * w; e0 < nm; e0 += 4 * NW) {
+        const int e = e0 + sub;
+        int a = 0, b = 0, x = 0, k = 0;
+        if (e < nm) {
+          k = WM[e];
+          const uint32_t ab = AB[k];
+          a = (int)(ab & 0xFFFFu);
+          b = (int)(ab >> 16);
+          const int o = (int)Xr[k] - row.base;
+          x = row.right ? L - o - a : o;
+        }
+        int mx = 0;
+        for (int c = x + sl; c < x + a; c += 16) mx = max(mx, F[c]);
+        mx = row16_max(mx);
+        for (int c = x + sl; c < x + a; c += 16) F[c] = mx + b;
+        if (e < nm && sl == 0) q.Y[c0 + k] = mx;
+        if (e < nm) Hw = max(Hw, mx + b);
+      }
+      for (int e = w; e < nwd; e += NW) {
+        const int k = WW[e];
+        const uint32_t ab = AB[k];
+        const int a = (int)(ab & 0xFFFFu), b = (int)(ab >> 16);
+        const int o = (int)Xr[k] - row.base;
+        const int x = row.right ? L - o - a : o;
+        int mx = 0;
+        for (int c = x + lane; c < x + a; c += kWave) mx = max(mx, F[c]);
+        const int y = wave_max_dpp(mx);
+        for (int c = x + lane; c < x + a; c += kWave) F[c] = y + b;
+        if (lane == 0) q.Y[c0 + k] = y;
+        Hw = max(Hw, y + b);
+      }
+      const int hw = wave_max_dpp(Hw);
+      if (lane == 0) atomicMax(&Hsh[seg % 3], hw);
+      __syncthreads();
+      // every wave read the same settled value: all leave at the same segment
+      if (hprev > L) {
+        over = true;
+        break;
+      }
+      s0 = s1;
+      s1 = s1n;
+      row = row_at(q, xbase, xfirst);
+    }
+  }
 }
 
 template <int NT>
@@ -292,14 +945,14 @@ __device__ __forceinline__ void k_pack_box_body(const float2* __restrict__ wh,
                                                  int32_t* __restrict__ cand_y,
                                                  int32_t* __restrict__ cand_tab, int64_t stride,
                                                  int kcap) {
-  extern __shared__ int32_t F[];
+  extern __shared__ __align__(16) int32_t S[];
   constexpr int NW = NT / kWave;
   __shared__ uint32_t shs[2][NW];
   __shared__ int32_t shm[NW], shb[NW];
   __shared__ int32_t Hsh[3];
   __shared__ long long last_x;
   __shared__ long long sh64[NW];
-  __shared__ int32_t WM[2048], WW[256], LC[2][2];  // mid and wide box lists, their counts
+  __shared__ int32_t LC[2][2];  // by columns: boxes in the mid and the wide list
 
   if (st->status != FA_OK) return;
   const int j = blockIdx.x + 1;
@@ -310,9 +963,8 @@ __device__ __forceinline__ void k_pack_box_body(const float2* __restrict__ wh,
   uint32_t* ABg = cand_ab + (int64_t)(j - 1) * stride;
   int32_t* Y = cand_y + (int64_t)(j - 1) * stride;
   int32_t* tab = cand_tab + (j - 1) * kCandStride;
-  uint32_t* Xr = reinterpret_cast<uint32_t*>(F + 2 * omega);
+  uint32_t* Xr = reinterpret_cast<uint32_t*>(S);
   uint32_t* AB = Xr + kcap;
-  int32_t* RS = reinterpret_cast<int32_t*>(AB + kcap);
 
   // ---- sizes, fold and overflow: kFoldItems consecutive boxes per thread, a
   // thread-local prefix, then one block scan of the thread sums; the first
@@ -322,11 +974,7 @@ __device__ __forceinline__ void k_pack_box_body(const float2* __restrict__ wh,
   long long run = 0;
   int mloc = INT_MIN, bad = 0;
   if (tid == 0) last_x = 0;
-  // the frontline is cleared up front (its widest extent, 2 omega): the
-  // fold's barriers order it before the push
-  for (int c = tid; c < 2 * omega; c += NT) F[c] = 0;
-  if (tid < 3) Hsh[tid] = 0;
-  if (tid < 4) LC[tid >> 1][tid & 1] = 0;
+  if (C <= kFewBoxes) columns_clear<NT>(omega, S + 3 * kcap + 4, Hsh, LC);
   int pass = 0;
   for (int base = 0; base < C; base += kFoldItems * NT, ++pass) {
     const int i0 = base + kFoldItems * tid;
@@ -426,163 +1074,14 @@ __device__ __forceinline__ void k_pack_box_body(const float2* __restrict__ wh,
   }
   const int L = omega + m;
 
-  int Hw = 0, seg = 0;
-  bool over = false;
-  const int sub = lane >> 4, sl = lane & 15;
-  for (int c0 = 0; c0 < C && !over; c0 += kcap) {
-    const int cn = min(kcap, C - c0);
-    long long xbase = 0;
-    if (c0 > 0) {
-      // the previous chunk's segments are done (the barrier ending the last
-      // one); reload the next chunk from the fold in global memory
-      xbase = Xg[c0];
-      constexpr int U = 4;  // loads in flight per thread
-      for (int i0 = tid; i0 < cn; i0 += U * NT) {
-        long long xv[U];
-        uint32_t abv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int i = i0 + u * NT;
-          xv[u] = i < cn ? Xg[c0 + i] : 0;
-          abv[u] = i < cn ? ABg[c0 + i] : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int i = i0 + u * NT;
-          if (i < cn) {
-            Xr[i] = (uint32_t)(xv[u] - xbase);
-            AB[i] = abv[u];
-          }
-        }
-      }
-      __syncthreads();
-    }
-    // ---- chunk-local segment starts (first box of each row in the chunk)
-    int nr = 0;
-    for (int base = 0; base < cn; base += kFoldItems * NT, ++pass) {
-      const int i0 = base + kFoldItems * tid;
-      uint32_t fl = 0, own = 0;
-      if (i0 < cn) {
-        const uint4 q = *reinterpret_cast<const uint4*>(Xr + i0);
-        const uint32_t xv[kFoldItems + 1] = {i0 > 0 ? Xr[i0 - 1] : 0u, q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int u = 0; u < kFoldItems; ++u) {
-          const int i = i0 + u;
-          const bool f =
-              i < cn && (i == 0 || ((xbase + xv[u + 1]) >> lg) != ((xbase + xv[u]) >> lg));
-          fl |= (uint32_t)f << u;
-          own += f;
-        }
-      }
-      uint32_t tot;
-      int at = nr + (int)(block_incl_scan_dpp<NT>(own, shs[pass & 1], &tot) - own);
-#pragma unroll
-      for (int u = 0; u < kFoldItems; ++u)
-        if (fl >> u & 1u) RS[at++] = i0 + u;
-      nr += (int)tot;
-    }
-    if (tid == 0) RS[nr] = cn;
-    __syncthreads();
-
-    // ---- push, segment by segment, in two phases. A: the threads take the
-    // segment's boxes in order; a box at most kNarrow columns wide is pushed
-    // by its own lane, the others go to a list of mid boxes (up to 64
-    // columns) or of wide ones. B (after a barrier): the mid boxes four per
-    // wave step, 16 lanes each; the wide boxes one per wave. Boxes of a row
-    // have disjoint spans, so the order inside a segment changes nothing.
-    // Bounds of the lists: a row's boxes lie in L <= 2 omega <= 16384
-    // columns, so at most 1820 are wider than 8 and 252 wider than 64.
-    int s0 = 0, s1 = nr > 0 ? RS[1] : 0;
-    long long r = nr > 0 ? (xbase + Xr[0]) >> lg : 0;
-    for (int rr = 0; rr < nr; ++rr, ++seg) {
-      // next segment: its end and its row
-      const int s1n = rr + 2 <= nr ? RS[rr + 2] : cn;
-      const uint32_t xfirst = rr + 1 < nr ? Xr[s1] : 0u;
-      const int hprev = Hsh[(seg + 2) % 3];  // the height after segment seg - 1
-      const long long rbase = (r << lg) - xbase;
-      const bool right = (r % 3) != 0;
-      int* cnt = LC[seg & 1];
-      for (int k = s0 + tid; k < s1; k += NT) {
-        const uint32_t ab = AB[k];
-        const int a = (int)(ab & 0xFFFFu), b = (int)(ab >> 16);
-        const int o = (int)((long long)Xr[k] - rbase);
-        const int x = right ? L - o - a : o;
-        const bool narrow = a <= kNarrow;
-        if (narrow) {
-          int v[kNarrow];
-#pragma unroll
-          for (int c = 0; c < kNarrow; ++c) v[c] = c < a ? F[x + c] : 0;
-          int mx = 0;
-#pragma unroll
-          for (int c = 0; c < kNarrow; ++c) mx = max(mx, v[c]);
-#pragma unroll
-          for (int c = 0; c < kNarrow; ++c)
-            if (c < a) F[x + c] = mx + b;
-          Y[c0 + k] = mx;
-          Hw = max(Hw, mx + b);
-        }
-        const bool wide = a > kWave;
-        const unsigned long long mm = __ballot(!narrow && !wide), mw = __ballot(wide);
-        const unsigned long long below = lanes_below();
-        int bm = 0, bw = 0;
-        if (lane == __ffsll((long long)__ballot(true)) - 1) {
-          if (mm) bm = atomicAdd(&cnt[0], __popcll(mm));
-          if (mw) bw = atomicAdd(&cnt[1], __popcll(mw));
-        }
-        bm = __builtin_amdgcn_readfirstlane(bm);
-        bw = __builtin_amdgcn_readfirstlane(bw);
-        if (!narrow && !wide) WM[bm + __popcll(mm & below)] = k;
-        if (wide) WW[bw + __popcll(mw & below)] = k;
-      }
-      __syncthreads();
-      const int nm = cnt[0], nwd = cnt[1];
-      if (tid == 0) {
-        LC[(seg + 1) & 1][0] = 0;
-        LC[(seg + 1) & 1][1] = 0;
-      }
-      for (int e0 = 4 * w; e0 < nm; e0 += 4 * NW) {
-        const int e = e0 + sub;
-        int a = 0, b = 0, x = 0, k = 0;
-        if (e < nm) {
-          k = WM[e];
-          const uint32_t ab = AB[k];
-          a = (int)(ab & 0xFFFFu);
-          b = (int)(ab >> 16);
-          const int o = (int)((long long)Xr[k] - rbase);
-          x = right ? L - o - a : o;
-        }
-        int mx = 0;
-        for (int c = x + sl; c < x + a; c += 16) mx = max(mx, F[c]);
-        mx = row16_max(mx);
-        for (int c = x + sl; c < x + a; c += 16) F[c] = mx + b;
-        if (e < nm && sl == 0) Y[c0 + k] = mx;
-        if (e < nm) Hw = max(Hw, mx + b);
-      }
-      for (int e = w; e < nwd; e += NW) {
-        const int k = WW[e];
-        const uint32_t ab = AB[k];
-        const int a = (int)(ab & 0xFFFFu), b = (int)(ab >> 16);
-        const int o = (int)((long long)Xr[k] - rbase);
-        const int x = right ? L - o - a : o;
-        int mx = 0;
-        for (int c = x + lane; c < x + a; c += kWave) mx = max(mx, F[c]);
-        const int y = wave_max_dpp(mx);
-        for (int c = x + lane; c < x + a; c += kWave) F[c] = y + b;
-        if (lane == 0) Y[c0 + k] = y;
-        Hw = max(Hw, y + b);
-      }
-      const int hw = wave_max_dpp(Hw);
-      if (lane == 0) atomicMax(&Hsh[seg % 3], hw);
-      __syncthreads();
-      // every wave read the same settled value: all leave at the same segment
-      if (hprev > L) {
-        over = true;
-        break;
-      }
-      s0 = s1;
-      s1 = s1n;
-      r = (xbase + xfirst) >> lg;
-    }
+  const PushArgs q{Xg, ABg, Y, C, omega, lg, m, kcap};
+  // two rows have to fit a chunk (a row holds boxes at least min_box + 2
+  // gutter wide that start in omega columns)
+  if (C > kFewBoxes && m <= kEdgeMax &&
+      2 * (omega / (p.min_box + pad) + 2) <= row_kcap(omega)) {
+    push_rows<NT>(q, S, pass, shs, Hsh);
+  } else {
+    push_columns<NT>(q, S, pass, shs, Hsh, LC);
   }
   if (tid == 0) {
     const int H = C > 0 ? max(Hsh[0], max(Hsh[1], Hsh[2])) : 0;
@@ -843,7 +1342,7 @@ hipError_t box_attributes() {
                        (const void*)k_pack_box_b<512>, (const void*)k_pack_box_b<1024>};
   for (const void* k : ks) {
     const hipError_t e =
-        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kBoxPushLds);
+        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)box_lds_max());
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -852,7 +1351,7 @@ hipError_t box_attributes() {
 void box_launch(const FrameParams& p, const Work& w, int block, hipStream_t st) {
   const int64_t stride = p.max_charts;
   const int kcap = box_kcap(p.omega);
-  const size_t dyn = (size_t)8 * p.omega + (size_t)12 * kcap + 4;
+  const size_t dyn = box_lds(p.omega);
   if (block == 1024)
     k_pack_box<1024><<<p.J, 1024, dyn, st>>>(w.sorted_wh, w.state, p, w.cand_x, w.cand_ab,
                                              w.cand_y, w.cand_tab, stride, kcap);
@@ -946,7 +1445,7 @@ hipError_t launch_pack_emit(int32_t n, const fa_chart* charts, int32_t* placemen
 hipError_t launch_pack_batched(const BatchView* dev, int n, int J, int64_t max_charts, int block,
                                hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  const size_t dyn = (size_t)kBoxPushLds;  // each view sizes its chunks from its own omega
+  const size_t dyn = box_lds_max();  // each view sizes its chunks from its own omega
   if (block == 1024)
     k_pack_box_b<1024><<<dim3(J, n), 1024, dyn, st>>>(dev, max_charts);
   else if (block == 512)

@@ -85,3 +85,73 @@ def test_occupied_texels(omega, n):
     assert g["meta"]["status"] == 0
     assert g["meta"]["occupied_texels"] == int((g["occupancy"] >= 0).sum()) > 0
     compare(g, oracle.build_frame(f))
+
+
+# The box push goes by rows (each box rests on the few boxes of the row before)
+# or by columns (a whole frontline): by columns up to 8 boxes, with overflows
+# above 1024 columns and where two rows may not fit a chunk. Other edges: chunks
+# of 8128 boxes (and stop checks at multiples of another number), boxes over
+# more than 8 and 16 others, more than 8 boxes of a row over edge columns.
+def _uniform(n, lo, hi, seed=0):
+    return np.random.default_rng(seed).uniform(lo, hi, (n, 2))
+
+
+def _thin_and_square(seed=1):
+    rng = np.random.default_rng(seed)
+    thin = np.stack([rng.uniform(1, 3, 900), rng.uniform(99, 101, 900)], 1)
+    return rng.permutation(np.concatenate([thin, rng.uniform(60, 98, (200, 2))]))
+
+
+def _narrow_and_wide(n, side, seed=2):
+    # small boxes with a few as wide as `side` among the lowest rows: wide edges
+    rng = np.random.default_rng(seed)
+    wide = np.stack([rng.uniform(0.5 * side, side, 12), rng.uniform(side, 1.01 * side, 12)], 1)
+    return np.concatenate([rng.uniform(1, 9, (n, 2)), wide])
+
+
+PUSH_CASES = {
+    "7 boxes": (_uniform(7, 5, 60), 128, {}),
+    "8 boxes": (_uniform(8, 5, 60), 128, {}),
+    "9 boxes": (_uniform(9, 5, 60), 128, {}),
+    "65 boxes": (_uniform(65, 5, 60), 512, {}),
+    "wide overflow": (_uniform(40, 100, 3900), 4096, {}),
+    "overflow on both sides of 1024": (_uniform(60, 100, 1400), 4096, {}),
+    "rows longer than a chunk": (_uniform(30000, 0.2, 6), 8192, dict(g=0, mmin=1)),
+    "rows of a third of a chunk": (_uniform(20000, 0.2, 6), 4096, dict(g=0, mmin=2)),
+    "8127 boxes": (_uniform(8127, 1, 30), 4096, {}),
+    "8128 boxes": (_uniform(8128, 1, 30), 4096, {}),
+    "8129 boxes": (_uniform(8129, 1, 30), 4096, {}),
+    "three chunks": (_uniform(24000, 1, 40), 4096, {}),
+    "chunks short of the stop checks": (_uniform(22000, 1, 12), 1024, {}),
+    "thin under square": (_thin_and_square(), 1024, {}),
+    "narrow over wide edges": (_narrow_and_wide(3000, 400), 1024, {}),
+    "narrow over very wide edges": (_narrow_and_wide(3000, 900), 2048, {}),
+    "tiny atlas": (_uniform(300, 0.5, 4), 16, dict(J=7)),
+}
+
+
+@pytest.mark.parametrize("name", list(PUSH_CASES))
+@pytest.mark.parametrize("block", [256, 512, 1024])
+def test_push_paths(name, block):
+    from test_gpu_parity import _oracle_pack
+    fa = _fa()
+    sizes, omega, opt = PUSH_CASES[name]
+    sizes = sizes.astype(np.float32)
+    J, g, mmin = opt.get("J", 64), opt.get("g", 1), opt.get("mmin", 2)
+    print(f"[gpu] push {name} n={len(sizes)} omega={omega} block={block}", flush=True)
+    ctx = fa.Context(1, 1, max_charts=65536, max_atlas=8192, num_scales=J, gutter=g, min_box=mmin,
+                     tuning_table=None)
+    ctx.set_tuning(fa.FA_TUNE_PACK_BLOCK, block)
+    pl, meta, cand = ctx.pack_boxes(torch.as_tensor(sizes).cuda(), omega)
+    torch.cuda.synchronize()
+    m, c = fa.parse_meta(meta), cand.cpu().numpy()
+    pl = pl.cpu().numpy()
+    ctx.close()
+    js, table, want = _oracle_pack(sizes, omega, J, g, mmin)
+    assert m["chosen_j"] == js
+    assert np.array_equal(c[:, :3], table[:, :3])
+    fit = table[:, 0] == 1
+    assert np.array_equal(c[fit, 3], table[fit, 3])
+    assert ((c[~fit, 3] == -1) | (c[~fit, 3] > c[~fit, 2])).all()
+    if js:
+        assert np.array_equal(pl, want)
