@@ -458,7 +458,21 @@ hipError_t launch_pack_emit(int32_t n, const fa_chart* charts, int32_t* placemen
                             const Work& w, hipStream_t st);
 hipError_t pack_kernel_attributes(int max_dyn_bytes);
 
-// adjacency (per scene): sorts 3T half-edge keys; tmp buffers from the caller
+// adjacency (per scene) by vertex ranges: count, then (no bad index and the
+// largest bucket fits) match. tmp holds pl.bytes; info [2] on the device
+// receives a flag for an index outside [0, V) and the largest bucket.
+constexpr int64_t kAdjMaxBuckets = 8192;
+struct AdjPlan {
+  int shift = 0, buckets = 0;  // ranges of 2^shift vertices; 0 buckets: not this way
+  size_t bytes = 0;
+};
+AdjPlan adjacency_plan(int64_t T, int64_t V);
+hipError_t launch_adjacency_count(const int32_t* idx, int64_t T, int64_t V, const AdjPlan& pl,
+                                  void* tmp, uint32_t* info, hipStream_t st);
+bool adjacency_fits(uint32_t largest_bucket);
+hipError_t launch_adjacency_match(const int32_t* idx, int64_t T, int64_t V, const AdjPlan& pl,
+                                  void* tmp, int32_t* nbr, hipStream_t st);
+// ... by sorting 3T half-edge keys; tmp buffers from the caller
 struct AdjTmp {
   unsigned long long* keys_a;
   unsigned long long* keys_b;

@@ -89,7 +89,9 @@ struct fa_ctx {
   int uf_edge_hooks = 5;
   int uf_tile = 4096;
   std::vector<TuneEntry> table;    // knobs by frame shape (fa_load_tuning_table)
-  int32_t* check_flag = nullptr;  // device int for index validation
+  uint32_t* check_flag = nullptr;  // [2] device words of index validation and the adjacency
+  void* spare = nullptr;           // slot 0's large-footprint queue, free between frames: the
+  size_t spare_bytes = 0;          // adjacency of a new scene is built in it
   // visibility pass scratch: occluder list [max_triangles] + its counter, and
   // a depth buffer that grows to the largest grid asked for
   int32_t* vis_list = nullptr;
@@ -99,11 +101,11 @@ struct fa_ctx {
 };
 
 namespace {
-__global__ void k_check_indices(const int32_t* idx, int64_t n, int64_t V, int32_t* bad) {
+__global__ void k_check_indices(const int32_t* idx, int64_t n, int64_t V, uint32_t* bad) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int32_t v = idx[i];
-    if (v < 0 || (int64_t)v >= V) atomicExch(bad, 1);
+    if (v < 0 || (int64_t)v >= V) atomicExch(bad, 1u);
   }
 }
 }  // namespace
@@ -207,7 +209,10 @@ int fa_create(const fa_config* cfg_in, fa_ctx** out_ctx) {
     for (auto& p : parts) {
       *p.p = base;
       base += align_up(p.bytes);
+      if (v == 0 && (p.p == (void**)&w.big || p.p == (void**)&w.big_fp))
+        ctx->spare_bytes += align_up(p.bytes);  // (the two follow each other)
     }
+    if (v == 0) ctx->spare = w.big;
     hipStream_t s = nullptr;
     hipEvent_t e = nullptr;
     if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess ||
@@ -223,7 +228,7 @@ int fa_create(const fa_config* cfg_in, fa_ctx** out_ctx) {
     fa_destroy(ctx);
     return FA_ERR_OUT_OF_MEMORY;
   }
-  if (hipMalloc(&ctx->check_flag, 4) != hipSuccess ||
+  if (hipMalloc(&ctx->check_flag, 8) != hipSuccess ||
       hipMalloc(&ctx->bv_dev, sizeof(BatchView) * kMaxBatchViews) != hipSuccess ||
       hipHostMalloc((void**)&ctx->bv_host, sizeof(BatchView) * kMaxBatchViews,
                     hipHostMallocDefault) != hipSuccess ||
@@ -330,16 +335,28 @@ static int get_scene(fa_ctx* ctx, const fa_mesh* mesh, hipStream_t st, Scene** o
     free_scene(ctx, it);
   }
   const int64_t T = mesh->num_triangles, V = mesh->num_vertices;
-  // the indices are read by every later kernel: reject out-of-range ones once
-  int32_t zero = 0, bad = 0;
-  if (hipMemcpyAsync(ctx->check_flag, &zero, 4, hipMemcpyHostToDevice, st) != hipSuccess)
-    return FA_ERR_DEVICE;
-  if (T > 0)
-    k_check_indices<<<1024, kBlock, 0, st>>>(mesh->indices, 3 * T, V, ctx->check_flag);
-  if (hipMemcpyAsync(&bad, ctx->check_flag, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipStreamSynchronize(st) != hipSuccess)
-    return FA_ERR_DEVICE;
-  if (bad) return FA_ERR_INVALID_ARG;
+  // the indices are read by every later kernel: reject out-of-range ones once,
+  // with the bucket counts of the adjacency where it is built by vertex ranges
+  // in the spare scratch (calls on a context do not overlap, so no frame is
+  // using it)
+  AdjPlan plan = adjacency_plan(T, V);
+  if (plan.bytes > ctx->spare_bytes) plan.buckets = 0;
+  uint32_t info[2] = {0u, 0u};  // bad index, largest bucket
+  if (T > 0) {
+    if (plan.buckets) {
+      if (launch_adjacency_count(mesh->indices, T, V, plan, ctx->spare, ctx->check_flag, st) !=
+          hipSuccess)
+        return FA_ERR_DEVICE;
+    } else {
+      if (hipMemcpyAsync(ctx->check_flag, info, 8, hipMemcpyHostToDevice, st) != hipSuccess)
+        return FA_ERR_DEVICE;
+      k_check_indices<<<1024, kBlock, 0, st>>>(mesh->indices, 3 * T, V, ctx->check_flag);
+    }
+    if (hipMemcpyAsync(info, ctx->check_flag, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+      return FA_ERR_DEVICE;
+    if (info[0]) return FA_ERR_INVALID_ARG;
+  }
   Scene sc;
   sc.T = T;
   sc.V = V;
@@ -353,7 +370,13 @@ static int get_scene(fa_ctx* ctx, const fa_mesh* mesh, hipStream_t st, Scene** o
   if (!make_room(ctx, scene_bytes(T) + tmp_bytes, mesh->scene_key, st))
     return FA_ERR_OUT_OF_MEMORY;
   if (hipMalloc(&sc.nbr, scene_bytes(T)) != hipSuccess) return FA_ERR_OUT_OF_MEMORY;
-  if (T > 0) {
+  if (T > 0 && plan.buckets && adjacency_fits(info[1])) {
+    if (launch_adjacency_match(mesh->indices, T, V, plan, ctx->spare, sc.nbr, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess) {
+      (void)hipFree(sc.nbr);
+      return FA_ERR_DEVICE;
+    }
+  } else if (T > 0) {
     AdjTmp tmp{};
     size_t hist_words = adjacency_hist_words(T);
     void* blk = nullptr;

@@ -11,6 +11,8 @@
 // One pass = tile histograms -> one exclusive scan over (digit, tile) ->
 // stable scatter. Within a tile, items are ranked round by round; inside a
 // wave, lanes with equal digits are found with eight ballots.
+#include <algorithm>
+
 #include "fa_internal.h"
 
 namespace fa {
@@ -213,6 +215,187 @@ __global__ void k_edge_runs(const unsigned long long* __restrict__ keys,
     }
   }
   nbr[vals[i]] = out;
+}
+
+// ---- adjacency by vertex ranges -------------------------------------------
+// Half-edges of one undirected edge share their smaller vertex, so they meet in
+// the bucket of its range of 2^shift vertices. Two passes over the indices
+// count and fill the buckets (a workgroup takes kAdjTile triangles and reserves
+// its share of each bucket it touches with one atomic; meshes keep vertices
+// and triangles near each other in order, so a share is a long run), then a
+// workgroup per bucket matches its half-edges in LDS: a hash table of edges
+// with a chain each, in which every half-edge finds the next one of its edge
+// by index. The order inside a bucket changes nothing.
+//
+// Bound by memory: the indices read twice, 4 bytes a half-edge written and
+// read, the indices of a bucket gathered (from the L2, mostly) and 4 bytes a
+// half-edge written. Six radix passes of 12-byte keys and values took 715 us
+// for 2.2M triangles, their 160 MB of buffers another 400 us to allocate and
+// free (1188 us in all for a scene that comes in); this way 110 and none (198 us).
+// A bucket above kAdjCap half-edges (a vertex with thousands of triangles, or
+// few of many vertices in use) sends the mesh to the sort.
+constexpr int kAdjTile = 2048;
+constexpr int kAdjThreads = 512;
+constexpr int kAdjCap = 4096;
+constexpr int kAdjSlots = 4096;
+
+__device__ __forceinline__ uint32_t adj_hash(uint32_t lo, uint32_t hi) {
+  uint32_t x = lo * 0x9E3779B1u ^ (hi * 0x85EBCA77u);
+  x ^= x >> 15;
+  return (x * 0x2C1B3C6Du) >> (32 - 12);
+}
+static_assert(kAdjSlots == 1 << 12, "adj_hash gives a slot");
+
+__global__ void k_adj_begin(uint32_t* __restrict__ count, int n, uint32_t* __restrict__ info) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) count[i] = 0u;
+  if (i < 2) info[i] = 0u;
+}
+
+// One lane per distinct bucket of a wave's first lane adds for all of them
+// (neighbouring half-edges mostly share a bucket). Returns the lane's place in
+// its bucket's count; every lane of the wave calls it, b < 0: none.
+__device__ __forceinline__ uint32_t bucket_add(uint32_t* cnt, int b) {
+  const unsigned long long any = __ballot(b >= 0);
+  if (!any) return 0u;
+  const int lead = __ffsll((long long)any) - 1;
+  const int b0 = __builtin_amdgcn_readlane(b, lead);
+  const unsigned long long same = __ballot(b == b0);
+  uint32_t at = 0;
+  if (lane_id() == lead) at = atomicAdd(&cnt[b0], (uint32_t)__popcll(same));
+  at = (uint32_t)__builtin_amdgcn_readlane((int)at, lead);
+  if (b == b0) return at + (uint32_t)__popcll(same & lanes_below());
+  return b >= 0 ? atomicAdd(&cnt[b], 1u) : 0u;
+}
+
+// Pass 1 (FILL false): the half-edges of every bucket into count; info[0] is
+// set where an index is outside [0, V). Pass 2: the half-edges into their
+// buckets (count holds the buckets' next free places); degenerate edges get
+// their result.
+template <bool FILL>
+__global__ __launch_bounds__(kAdjThreads) void k_adj_buckets(
+    const int32_t* __restrict__ idx, int64_t T, int64_t V, int shift, int nb,
+    uint32_t* __restrict__ count, uint32_t* __restrict__ info, uint32_t* __restrict__ half,
+    int32_t* __restrict__ nbr) {
+  extern __shared__ uint32_t cnt[];  // [nb] half-edges of the tile, then (FILL) first places
+  constexpr int kPer = kAdjTile / kAdjThreads;
+  const int64_t t0 = (int64_t)blockIdx.x * kAdjTile;
+  for (int b = threadIdx.x; b < nb; b += kAdjThreads) cnt[b] = 0u;
+  __syncthreads();
+  int bk[kPer][3];
+  uint32_t at[kPer][3];
+  bool bad = false;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int64_t t = t0 + threadIdx.x + k * kAdjThreads;
+    int v[3] = {0, 0, 0};
+    if (t < T) {
+#pragma unroll
+      for (int e = 0; e < 3; ++e) v[e] = idx[3 * t + e];
+    }
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      const int a = v[e], c = v[e == 2 ? 0 : e + 1];
+      bk[k][e] = -1;
+      if (t < T) {
+        bad = bad || a < 0 || (int64_t)a >= V;
+        if (a != c) bk[k][e] = min(a, c) >> shift;
+        else if (FILL) nbr[3 * t + e] = -1;
+      }
+    }
+    // (a bad index has no bucket; pass 2 only follows where there is none)
+    if (!FILL && bad) bk[k][0] = bk[k][1] = bk[k][2] = -1;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) at[k][e] = bucket_add(cnt, bk[k][e]);
+  }
+  if (!FILL && __ballot(bad) && lane_id() == 0) atomicOr(&info[0], 1u);
+  __syncthreads();
+  for (int b = threadIdx.x; b < nb; b += kAdjThreads) {
+    const uint32_t c = cnt[b];
+    if (c) {
+      const uint32_t first = atomicAdd(&count[b], c);
+      if (FILL) cnt[b] = first;
+    }
+  }
+  if (!FILL) return;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int64_t t = t0 + threadIdx.x + k * kAdjThreads;
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (bk[k][e] >= 0) half[cnt[bk[k][e]] + at[k][e]] = (uint32_t)(3 * t + e);
+  }
+}
+
+// Exclusive prefix of the buckets' counts into first [nb + 1] and next [nb]
+// (one workgroup); info[1] gets the largest count.
+__global__ __launch_bounds__(1024) void k_adj_scan(uint32_t* __restrict__ next, int nb,
+                                                   uint32_t* __restrict__ first,
+                                                   uint32_t* __restrict__ info) {
+  __shared__ uint32_t sh[1024 / kWave];
+  uint32_t run = 0, most = 0;
+  for (int b0 = 0; b0 < nb; b0 += 1024) {
+    const int b = b0 + threadIdx.x;
+    const uint32_t c = b < nb ? next[b] : 0u;
+    most = max(most, c);
+    uint32_t tot;
+    const uint32_t ex = run + block_incl_scan<uint32_t>(c, sh, &tot) - c;
+    if (b < nb) {
+      first[b] = ex;
+      next[b] = ex;
+    }
+    run += tot;
+  }
+  most = block_max<uint32_t>(most, sh);
+  if (threadIdx.x == 0) {
+    first[nb] = run;
+    info[1] = most;
+  }
+}
+
+// The half-edges of one bucket matched by edge.
+__global__ __launch_bounds__(kAdjThreads) void k_adj_match(const int32_t* __restrict__ idx,
+                                                           const uint32_t* __restrict__ first,
+                                                           const uint32_t* __restrict__ half,
+                                                           int32_t* __restrict__ nbr) {
+  __shared__ uint32_t head[kAdjSlots];
+  __shared__ uint2 key[kAdjCap];
+  __shared__ uint32_t hs[kAdjCap];
+  __shared__ uint16_t nxt[kAdjCap];
+  constexpr uint32_t kEnd = 0xFFFFu;
+  static_assert(kAdjCap <= (int)kEnd, "chain links fit 16 bits");
+  const uint32_t b0 = first[blockIdx.x];
+  const int n = min((int)(first[blockIdx.x + 1] - b0), kAdjCap);
+  for (int s = threadIdx.x; s < kAdjSlots; s += kAdjThreads) head[s] = kEnd;
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += kAdjThreads) {
+    const uint32_t h = half[b0 + i];
+    const uint32_t t = h / 3u, e = h - 3u * t;
+    const uint32_t a = (uint32_t)idx[3 * (int64_t)t + e];
+    const uint32_t c = (uint32_t)idx[3 * (int64_t)t + (e == 2u ? 0u : e + 1u)];
+    const uint2 k = make_uint2(min(a, c), max(a, c));
+    key[i] = k;
+    hs[i] = h;
+    nxt[i] = (uint16_t)atomicExch(&head[adj_hash(k.x, k.y)], (uint32_t)i);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += kAdjThreads) {
+    const uint2 k = key[i];
+    const uint32_t h = hs[i];
+    // the smallest half-edge of this edge above h, and the smallest of all
+    // others
+    uint32_t above = 0xFFFFFFFFu, least = 0xFFFFFFFFu;
+    for (uint32_t j = head[adj_hash(k.x, k.y)]; j != kEnd; j = nxt[j]) {
+      const uint2 kj = key[j];
+      const uint32_t hj = hs[j];
+      if (kj.x != k.x || kj.y != k.y || hj == h) continue;
+      least = min(least, hj);
+      if (hj > h) above = min(above, hj);
+    }
+    const uint32_t to = above != 0xFFFFFFFFu ? above : least;
+    nbr[h] = to == 0xFFFFFFFFu ? -1 : (int32_t)(to / 3u);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -694,6 +877,43 @@ size_t adjacency_hist_words(int64_t T) {
 
 size_t adjacency_part_words(int64_t T) {
   return adjacency_hist_words(T) / kScanChunk + 2;
+}
+
+AdjPlan adjacency_plan(int64_t T, int64_t V) {
+  // ranges of 2^shift vertices with about 1536 of the 3 T half-edges each, if
+  // every vertex is the smaller one of as many
+  AdjPlan pl;
+  while (pl.shift < 30 && ((int64_t)3 * T << (pl.shift + 1)) <= (int64_t)2048 * V) ++pl.shift;
+  const int64_t nb = std::max<int64_t>(1, ((V - 1) >> pl.shift) + 1);
+  pl.buckets = nb <= kAdjMaxBuckets && T <= (int64_t(1) << 29) ? (int)nb : 0;
+  pl.bytes = 4 * (size_t)(3 * T) + 4 * (2 * (size_t)nb + 1);
+  return pl;
+}
+
+hipError_t launch_adjacency_count(const int32_t* idx, int64_t T, int64_t V, const AdjPlan& pl,
+                                  void* tmp, uint32_t* info, hipStream_t st) {
+  uint32_t* next = static_cast<uint32_t*>(tmp) + 3 * T;
+  uint32_t* first = next + pl.buckets;
+  k_adj_begin<<<(unsigned)(pl.buckets + kBlock - 1) / kBlock, kBlock, 0, st>>>(next, pl.buckets,
+                                                                               info);
+  k_adj_buckets<false><<<(unsigned)((T + kAdjTile - 1) / kAdjTile), kAdjThreads,
+                         4 * (size_t)pl.buckets, st>>>(idx, T, V, pl.shift, pl.buckets, next, info,
+                                                       nullptr, nullptr);
+  k_adj_scan<<<1, 1024, 0, st>>>(next, pl.buckets, first, info);
+  return hipGetLastError();
+}
+
+bool adjacency_fits(uint32_t largest_bucket) { return largest_bucket <= (uint32_t)kAdjCap; }
+
+hipError_t launch_adjacency_match(const int32_t* idx, int64_t T, int64_t V, const AdjPlan& pl,
+                                  void* tmp, int32_t* nbr, hipStream_t st) {
+  uint32_t* half = static_cast<uint32_t*>(tmp);
+  uint32_t* next = half + 3 * T;
+  k_adj_buckets<true><<<(unsigned)((T + kAdjTile - 1) / kAdjTile), kAdjThreads,
+                        4 * (size_t)pl.buckets, st>>>(idx, T, V, pl.shift, pl.buckets, next,
+                                                      nullptr, half, nbr);
+  k_adj_match<<<(unsigned)pl.buckets, kAdjThreads, 0, st>>>(idx, next + pl.buckets, half, nbr);
+  return hipGetLastError();
 }
 
 hipError_t launch_adjacency(const int32_t* idx, int64_t T, int64_t V, const AdjTmp& tmp,

@@ -155,3 +155,61 @@ def test_push_paths(name, block):
     assert ((c[~fit, 3] == -1) | (c[~fit, 3] > c[~fit, 2])).all()
     if js:
         assert np.array_equal(pl, want)
+
+
+# The adjacency is built by ranges of vertices matched in LDS; meshes with a
+# range of more than 4096 half-edges (a vertex of many triangles) or without
+# room in the context's scratch are sorted instead. Tiles hold 2048 triangles.
+def _fan_mesh(n):
+    rim = np.arange(n)
+    return np.stack([np.zeros(n, np.int64), 1 + rim, 1 + (rim + 1) % n], 1)
+
+
+def _strip_mesh(n):
+    i = np.arange(n)
+    return np.stack([i, i + 1, i + 2], 1)
+
+
+def _soup(n, V, seed):
+    return np.random.default_rng(seed).integers(0, V, (n, 3))
+
+
+ADJACENCY = {
+    "one triangle": np.array([[0, 1, 2]]),
+    "one vertex": np.zeros((5, 3), np.int64),
+    "same triangle four times": np.tile([[4, 2, 7]], (4, 1)),
+    "both windings": np.array([[0, 1, 2], [2, 1, 0], [0, 1, 3], [1, 0, 0]]),
+    "2047 triangles": _strip_mesh(2047),
+    "2049 triangles": _strip_mesh(2049),
+    "fan of 1300": _fan_mesh(1300),             # 2600 half-edges meet at vertex 0
+    "fan of 2100": _fan_mesh(2100),             # 4200: above a bucket
+    "fan of 60000": _fan_mesh(60000),
+    "few of many vertices": 1_000_000 + _soup(7000, 300, 1),
+    "soup": _soup(20000, 9000, 2),
+    "edges of many triangles": _soup(6000, 12, 3),
+    "last vertices": 49_990 + _soup(3000, 10, 4),
+}
+
+
+@pytest.mark.parametrize("name", list(ADJACENCY))
+def test_adjacency_ways(name):
+    fa = _fa()
+    idx = ADJACENCY[name].astype(np.int32)
+    V = int(idx.max()) + 1
+    print(f"[gpu] adjacency {name} T={len(idx)} V={V}", flush=True)
+    ctx = fa.Context(len(idx), V, max_charts=16, max_atlas=16)
+    mesh = fa.Mesh(np.zeros((V, 3), np.float32), idx, 5)
+    want = oracle.adjacency(idx)
+    for _ in range(2):  # a scene that comes back is built anew
+        nbr = ctx.adjacency(mesh)
+        torch.cuda.synchronize()
+        assert np.array_equal(nbr.cpu().numpy(), want)
+        assert fa.fa_scene_evict(ctx.h, 5) == fa.FA_OK
+    bad = idx.copy()
+    bad[-1, 1] = V
+    for value in (V, -1):
+        bad[-1, 1] = value
+        with pytest.raises(fa.FastAtlasError) as e:
+            ctx.adjacency(fa.Mesh(np.zeros((V, 3), np.float32), bad, 6))
+        assert e.value.code == fa.FA_ERR_INVALID_ARG
+    ctx.close()
