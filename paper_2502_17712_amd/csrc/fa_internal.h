@@ -347,6 +347,13 @@ hipError_t launch_prologue(int64_t V, const uint8_t* vis, const int32_t* nbr,
                            int64_t T, const FrameParams& p, const Work& w, int32_t* cov,
                            int32_t* cot, int uf_init, const int32_t* check_idx, Marker& mk,
                            hipStream_t st);
+// Small meshes: launch_prologue and launch_charts in two launches (the charts do
+// not depend on the hook mode). false: not such a mesh, nothing launched.
+bool launch_front(const uint8_t* vis, const int32_t* idx, int64_t T, int64_t V,
+                  const FrameParams& p, const Work& w, int32_t* cot, int32_t* cov,
+                  fa_chart* charts, int32_t* occ_fill, bool check, Marker& mk, hipStream_t st,
+                  hipError_t* err);
+hipError_t front_kernel_attributes();
 // occ_fill: when not NULL, this [omega][omega] occupancy map is filled with -1
 // by workgroups past the union-find tiles (hook mode 5) or past the box
 // gather (the other modes); both kernels are bound by dependent loads and
@@ -442,7 +449,7 @@ struct BatchView {
 // launch shapes). Every view's results equal fa_build_atlas's for it.
 hipError_t launch_charts_batched(const BatchView* dev, int n, const float* pos,
                                  const int32_t* idx, const int32_t* nbr, int64_t T, int64_t V,
-                                 hipStream_t st);
+                                 int max_omega, hipStream_t st);
 hipError_t launch_order_batched(const BatchView* dev, int n, hipStream_t st);
 hipError_t launch_pack_batched(const BatchView* dev, int n, int J, int64_t max_charts, int block,
                                hipStream_t st);

@@ -239,7 +239,8 @@ int fa_create(const fa_config* cfg_in, fa_ctx** out_ctx) {
     fa_destroy(ctx);
     return FA_ERR_DEVICE;
   }
-  if (pack_kernel_attributes(2 * cfg.max_atlas * (int)sizeof(int32_t)) != hipSuccess) {
+  if (pack_kernel_attributes(2 * cfg.max_atlas * (int)sizeof(int32_t)) != hipSuccess ||
+      front_kernel_attributes() != hipSuccess) {
     fa_destroy(ctx);
     return FA_ERR_DEVICE;
   }
@@ -567,13 +568,20 @@ int run_frame_core(const Knobs& kn, const Work& slot, const fa_mesh* mesh, const
   // charts use them unless the global edge hook is chosen)
   const bool tiles_start = (p.flags & FA_FLAG_EDGE_ONLY_CHARTS) ? p.edge_hooks != 1
                                                                 : p.edge_hooks >= 2;
-  ok(launch_prologue(V, visible, nbr, T, p, w, cov, out->chart_of_tri,
-                     tiles_start ? 0 : (kn.uf_link_init ? 2 : 1),
-                     check_indices ? mesh->indices : nullptr, mk, st));
-  // the occupancy map is filled with -1 by spare workgroups of the box gather
+  // the occupancy map is filled with -1 by spare workgroups of the front, the
+  // union-find tiles or the box gather
   int32_t* occ_fill = T > 0 ? out->occupancy : nullptr;
-  ok(launch_charts(visible, mesh->indices, nbr, T, p, w, out->chart_of_tri, cov, out->charts,
-                   occ_fill, mk, st));
+  hipError_t front = hipSuccess;
+  if (launch_front(visible, mesh->indices, T, V, p, w, out->chart_of_tri, cov, out->charts,
+                   occ_fill, check_indices, mk, st, &front)) {
+    ok(front);
+  } else {
+    ok(launch_prologue(V, visible, nbr, T, p, w, cov, out->chart_of_tri,
+                       tiles_start ? 0 : (kn.uf_link_init ? 2 : 1),
+                       check_indices ? mesh->indices : nullptr, mk, st));
+    ok(launch_charts(visible, mesh->indices, nbr, T, p, w, out->chart_of_tri, cov, out->charts,
+                     occ_fill, mk, st));
+  }
   ok(launch_order(p, w, out->charts, 1, st));
   mk(st);
   ok(launch_footprint(mesh->indices, T, p, w, out->chart_of_tri, out->charts, mk, st));
@@ -727,11 +735,11 @@ static int enqueue_batched(fa_ctx* ctx, const fa_mesh* mesh, Scene* sc, int32_t 
   for (int r0 = 0; r0 < n; r0 += S) {
     const int m = std::min(S, n - r0);
     const BatchView* d = ctx->bv_dev + r0;
-    ok(launch_charts_batched(d, m, mesh->positions, mesh->indices, sc->nbr, T, V, st));
-    ok(launch_order_batched(d, m, st));
-    ok(launch_pack_batched(d, m, ctx->cfg.num_scales, ctx->cfg.max_charts, kn.pack_block, st));
     int omega = 0;
     for (int i = r0; i < r0 + m; ++i) omega = std::max(omega, views[i].atlas_size);
+    ok(launch_charts_batched(d, m, mesh->positions, mesh->indices, sc->nbr, T, V, omega, st));
+    ok(launch_order_batched(d, m, st));
+    ok(launch_pack_batched(d, m, ctx->cfg.num_scales, ctx->cfg.max_charts, kn.pack_block, st));
     ok(launch_occupancy_batched(d, m, mesh->indices, T, V, omega, kn.small_texels, kn.lane_texels,
                                 st));
   }

@@ -101,7 +101,9 @@ int setup_device(int dev) {
   if (carve(nullptr, &w) > kScratchBytes) return d.rc;
   void* p = nullptr;
   if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return d.rc;
-  if (pack_kernel_attributes(2 * kMaxAtlas * (int)sizeof(int32_t)) != hipSuccess) return d.rc;
+  if (pack_kernel_attributes(2 * kMaxAtlas * (int)sizeof(int32_t)) != hipSuccess ||
+      front_kernel_attributes() != hipSuccess)
+    return d.rc;
   d.ptr = static_cast<char*>(p);
   d.rc = FA_OK;
   return d.rc;

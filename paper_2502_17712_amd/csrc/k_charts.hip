@@ -9,6 +9,7 @@
 // list with full waves instead of masking out invisible lanes.
 #include <algorithm>
 #include <climits>
+#include <cstddef>
 
 #include "fa_internal.h"
 
@@ -758,6 +759,228 @@ __global__ void k_assign_roots(const int32_t* __restrict__ vlist,
 }
 
 // ---------------------------------------------------------------------------
+// small meshes: everything before the boxes in one workgroup
+// ---------------------------------------------------------------------------
+// For meshes of up to kFrontTris triangles and kFrontVerts vertices one
+// workgroup does what the prologue, the compaction, the union-find (through
+// shared vertices) and the root assignment do in six launches, with the
+// vertices' first triangles and the parents of the triangles in LDS, indexed
+// directly. Six launches of little work each cost about 4 us of launch and
+// drain. This one is bound by LDS latency, the walks of the joins above all.
+// A whole frame with the six launches and with this one: 70 and 54 us at 2048
+// triangles, 76 and 69 at 8192, 81 and 92 at 15842 (grids in row order), so the
+// line lies at 8192 (other meshes there: 82 and 70, 80 and 77).
+// Workgroups past the first fill the occupancy map.
+constexpr int kFrontTris = 8192;
+constexpr int kFrontVerts = 16384;
+constexpr int kFrontThreads = 1024;
+constexpr int kFrontMasks = kFrontTris / kWave;
+
+inline bool use_front(const FrameParams& p, int64_t T, int64_t V) {
+  return T > 0 && T <= kFrontTris && V <= kFrontVerts && !(p.flags & FA_FLAG_EDGE_ONLY_CHARTS);
+}
+inline size_t front_lds(int64_t T, int64_t V) { return 4 * (size_t)(T + V); }
+
+// Exclusive prefix of the set bits of mask[0 .. n) into pre, the total into
+// *total, by the first wave (n <= 4 waves).
+__device__ __forceinline__ void mask_prefix(const unsigned long long* mask, int n, uint32_t* pre,
+                                            uint32_t* total) {
+  const int lane = lane_id();
+  uint32_t c[4], sum = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int i = 4 * lane + k;
+    c[k] = i < n ? (uint32_t)__popcll(mask[i]) : 0u;
+    sum += c[k];
+  }
+  const uint32_t incl = wave_incl_scan_dpp(sum);
+  uint32_t at = incl - sum;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int i = 4 * lane + k;
+    if (i < n) pre[i] = at;
+    at += c[k];
+  }
+  if (lane == kWave - 1) *total = incl;
+}
+static_assert(kFrontMasks <= 4 * kWave, "four masks per lane of one wave");
+constexpr int kFrontFew = 2 * kFrontThreads;  // up to this many: two triangles a thread, else 8
+
+template <int PER>
+__device__ __forceinline__ void k_front_body(
+    const uint8_t* __restrict__ vis, const int32_t* __restrict__ idx, int T, int V,
+    int32_t* __restrict__ cov, int32_t* __restrict__ cot, int32_t* __restrict__ vlist,
+    fa_chart* __restrict__ charts, uint32_t* __restrict__ accum, int32_t max_charts,
+    FrameState* __restrict__ st, unsigned long long* __restrict__ big_counter, bool check,
+    int4* __restrict__ occ_fill, int64_t n4) {
+  extern __shared__ uint32_t dyn[];
+  __shared__ unsigned long long vm[kFrontMasks], rm[kFrontMasks];
+  __shared__ uint32_t vp[kFrontMasks], rp[kFrontMasks], total[2], bad_index;
+  const int tid = threadIdx.x, lane = lane_id();
+  if (blockIdx.x > 0) {
+    const int4 neg = make_int4(-1, -1, -1, -1);
+    const int64_t step = (int64_t)(gridDim.x - 1) * kFrontThreads;
+    if (occ_fill)
+      for (int64_t i = (int64_t)(blockIdx.x - 1) * kFrontThreads + tid; i < n4; i += step)
+        occ_fill[i] = neg;
+    return;
+  }
+  uint32_t* own = dyn;                           // [V] smallest visible triangle of a vertex
+  int* lp = reinterpret_cast<int*>(dyn + V);     // [T] parents of the visible triangles
+  constexpr uint32_t kNone = ~0u;
+  bool on[PER];
+  int vk[PER][3];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int t = k * kFrontThreads + tid;
+    on[k] = t < T && vis[t];
+  }
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int t = k * kFrontThreads + tid;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) vk[k][e] = t < T ? idx[3 * t + e] : 0;  // (beside vis)
+  }
+  if (tid == 0) {
+    bad_index = 0u;
+    *big_counter = 0ull;
+  }
+  for (int v = tid; v < V; v += kFrontThreads) own[v] = kNone;
+  __syncthreads();
+  if (check) {
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (k * kFrontThreads + tid < T) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) bad = bad || vk[k][e] < 0 || vk[k][e] >= V;
+      }
+    if (bad) bad_index = 1u;
+    __syncthreads();
+  }
+  // a bad index ends the frame with an empty visible list
+  const bool dead = check && bad_index != 0u;
+  const int w = tid / kWave;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    on[k] = on[k] && !dead;
+    const unsigned long long m = __ballot(on[k]);
+    if (lane == 0) vm[k * (kFrontThreads / kWave) + w] = m;
+    if (on[k]) {
+#pragma unroll
+      for (int e = 0; e < 3; ++e) atomicMin(&own[vk[k][e]], (uint32_t)(k * kFrontThreads + tid));
+    }
+  }
+  __syncthreads();
+  const int masks = PER * (kFrontThreads / kWave);
+  if (w == 0) mask_prefix(vm, masks, vp, &total[0]);
+  // each triangle starts linked to the smallest triangle at its vertices (vk
+  // becomes the vertices' first triangles); then the links are halved until
+  // none changes (a grid in row order starts with a link per row)
+  int up[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    up[k] = 0;
+    if (on[k]) {
+#pragma unroll
+      for (int e = 0; e < 3; ++e) vk[k][e] = (int)own[vk[k][e]];
+      up[k] = min(vk[k][0], min(vk[k][1], vk[k][2]));
+      lp[k * kFrontThreads + tid] = up[k];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int t = k * kFrontThreads + tid;
+    if (on[k]) vlist[vp[t / kWave] + __popcll(vm[t / kWave] & lanes_below())] = t;
+  }
+  for (int round = 0; round < 16; ++round) {
+    bool more = false;
+    int q[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) q[k] = on[k] ? lds_get(lp, up[k]) : 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (on[k] && q[k] != up[k]) {
+        up[k] = q[k];
+        lds_put(lp, k * kFrontThreads + tid, q[k]);
+        more = true;
+      }
+    if (!__syncthreads_or(more)) break;
+  }
+  // every triangle joins the first triangles of its vertices
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    if (!on[k]) continue;
+    const int t = k * kFrontThreads + tid;
+    int q[3];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) q[e] = lds_get(lp, vk[k][e]);
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (q[e] != up[k]) lds_join(lp, t, vk[k][e]);
+  }
+  __syncthreads();
+  int r[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int t = k * kFrontThreads + tid;
+    r[k] = on[k] ? lds_root(lp, t) : -1;
+    const unsigned long long m = __ballot(r[k] == t);
+    if (lane == 0) rm[k * (kFrontThreads / kWave) + w] = m;
+  }
+  __syncthreads();  // (every walk has ended: a walk's own stores may not follow these)
+  if (w == 0) mask_prefix(rm, masks, rp, &total[1]);
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (on[k]) lp[k * kFrontThreads + tid] = r[k];
+  __syncthreads();
+  // chart = rank of the root among the roots
+  const uint32_t charts_n = total[1];
+  const bool over = charts_n > (uint32_t)max_charts;
+  auto chart_of_root = [&](int root) {
+    return (int)(rp[root / kWave] +
+                 (uint32_t)__popcll(rm[root / kWave] & ((1ull << (root & (kWave - 1))) - 1ull)));
+  };
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int t = k * kFrontThreads + tid;
+    if (t >= T) continue;
+    int c = on[k] ? chart_of_root(r[k]) : -1;
+    const bool root = on[k] && r[k] == t;
+    if (root && c < max_charts) {
+      charts[c].root_tri = t;
+      reinterpret_cast<uint4*>(accum)[c] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0u, 0u);
+    }
+    if (over && !(root && c < max_charts)) c = -1;
+    cot[t] = c;
+  }
+  for (int v = tid; v < V; v += kFrontThreads) {
+    const uint32_t o = own[v];
+    cov[v] = o == kNone || over ? -1 : chart_of_root(lp[o]);
+  }
+  static_assert(sizeof(FrameState) % 4 == 0 && FA_OK == 0, "the state clears word by word");
+  constexpr unsigned kStatus = offsetof(FrameState, status) / 4,
+                     kCharts = offsetof(FrameState, num_charts) / 4,
+                     kVisible = offsetof(FrameState, visible) / 4;
+  for (unsigned i = tid; i < sizeof(FrameState) / 4; i += kFrontThreads)
+    reinterpret_cast<uint32_t*>(st)[i] =
+        i == kStatus ? (uint32_t)(dead ? FA_ERR_INVALID_ARG : over ? FA_ERR_CAPACITY : FA_OK)
+        : i == kCharts ? charts_n
+        : i == kVisible ? total[0] : 0u;
+}
+template <int PER>
+__global__ __launch_bounds__(kFrontThreads) void k_front(
+    const uint8_t* __restrict__ vis, const int32_t* __restrict__ idx, int T, int V,
+    int32_t* __restrict__ cov, int32_t* __restrict__ cot, int32_t* __restrict__ vlist,
+    fa_chart* __restrict__ charts, uint32_t* __restrict__ accum, int32_t max_charts,
+    FrameState* __restrict__ st, unsigned long long* __restrict__ big_counter, bool check,
+    int4* __restrict__ occ_fill, int64_t n4) {
+  k_front_body<PER>(vis, idx, T, V, cov, cot, vlist, charts, accum, max_charts, st, big_counter,
+                    check, occ_fill, n4);
+}
+
+// ---------------------------------------------------------------------------
 // per-triangle conservative box (NDC)
 // ---------------------------------------------------------------------------
 // plane distances: 0 left w+x, 1 right w-x, 2 bottom w+y, 3 top w-y,
@@ -891,8 +1114,9 @@ __device__ __forceinline__ bool triangle_ndc_box(const float4& a, const float4& 
   return true;
 }
 
-// Gather: chart of every visible triangle and its vertices, and the chart's
-// box as the union of its triangles' boxes. Each thread handles kGatherItems
+// Gather: chart of every visible triangle and its vertices (unless they are
+// labelled already, by k_front), and the chart's box as the union of its
+// triangles' boxes. Each thread handles kGatherItems
 // entries of the visible list, issuing the dependent loads of all its entries
 // level by level (list, root, chart and indices, clip vertices) so that their
 // latencies overlap; the boxes are merged into a per-workgroup table of charts
@@ -916,12 +1140,17 @@ constexpr int kGatherGroup = 8;
 static_assert((kSlots & (kSlots - 1)) == 0, "table slots: a power of two");
 constexpr unsigned kFillBlocks = 1024;  // least workgroups that fill the occupancy map
 constexpr unsigned kFillGroups = 256;   // the same for the 1024-thread union-find tiles
+// Workgroups of 1024 threads that fill a map of n4 16-byte words beside one
+// other: four stores a thread, at most kFillGroups.
+inline unsigned fill_groups(int64_t n4) {
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>(n4 / 4096, kFillGroups));
+}
 
 __device__ __forceinline__ void k_gather_boxes_body(
     const int32_t* __restrict__ vlist, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ parent, const float* __restrict__ pos, int32_t* cot,
     int32_t* __restrict__ cov, uint32_t* __restrict__ accum, const FrameParams& p,
-    const FrameState* __restrict__ st, int4* __restrict__ occ_fill, int64_t n4) {
+    const FrameState* __restrict__ st, int4* __restrict__ occ_fill, int64_t n4, bool labelled) {
   __shared__ int32_t skey[kSlots];
   __shared__ uint32_t sbox[4][kSlots];
   const int nv = st->visible;
@@ -954,7 +1183,8 @@ __device__ __forceinline__ void k_gather_boxes_body(
     tv[k] = i < nv ? vlist[i] : -1;
   }
 #pragma unroll
-  for (int k = 0; k < kGatherItems; ++k) cv[k] = tv[k] >= 0 ? aload(&parent[tv[k]]) : 0;
+  for (int k = 0; k < kGatherItems; ++k)
+    cv[k] = tv[k] < 0 ? 0 : labelled ? tv[k] : aload(&parent[tv[k]]);
 #pragma unroll
   for (int k = 0; k < kGatherItems; ++k) {
     const int t = max(tv[k], 0);
@@ -975,14 +1205,17 @@ __device__ __forceinline__ void k_gather_boxes_body(
     bool has = false;
     float4 box = make_float4(0.f, 0.f, 0.f, 0.f);
     if (valid) {
-      cot[tv[0]] = c;
-      if (p.flags & FA_FLAG_EDGE_ONLY_CHARTS) {
+      if (labelled) {
+        // (chart_of_tri and chart_of_vert are written)
+      } else if (p.flags & FA_FLAG_EDGE_ONLY_CHARTS) {
+        cot[tv[0]] = c;
         // a vertex may touch several edge-connected charts: keep the smallest
         // (chart_of_vert starts at -1, the largest unsigned value)
 #pragma unroll
         for (int e = 0; e < 3; ++e)
           atomicMin(reinterpret_cast<uint32_t*>(&cov[vi[0][e]]), (uint32_t)c);
       } else {
+        cot[tv[0]] = c;
         cov[vi[0][0]] = c;
         cov[vi[0][1]] = c;
         cov[vi[0][2]] = c;
@@ -1053,8 +1286,8 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_boxes(
     const int32_t* __restrict__ vlist, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ parent, const float* __restrict__ pos, int32_t* cot,
     int32_t* __restrict__ cov, uint32_t* __restrict__ accum, FrameParams p,
-    const FrameState* __restrict__ st, int4* __restrict__ occ_fill, int64_t n4) {
-  k_gather_boxes_body(vlist, idx, parent, pos, cot, cov, accum, p, st, occ_fill, n4);
+    const FrameState* __restrict__ st, int4* __restrict__ occ_fill, int64_t n4, bool labelled) {
+  k_gather_boxes_body(vlist, idx, parent, pos, cot, cov, accum, p, st, occ_fill, n4, labelled);
 }
 
 inline unsigned grid_for(int64_t n, int block) { return (unsigned)((n + block - 1) / block); }
@@ -1096,10 +1329,20 @@ __global__ void k_assign_roots_b(const BatchView* __restrict__ bv) {
                       v.p.max_charts, v.w.state);
 }
 __global__ __launch_bounds__(kGatherBlock) void k_gather_boxes_b(const BatchView* __restrict__ bv,
-                                                           const int32_t* __restrict__ idx) {
+                                                           const int32_t* __restrict__ idx,
+                                                           bool labelled) {
   const BatchView& v = bv[blockIdx.y];
   k_gather_boxes_body(v.w.vlist, idx, v.w.parent, v.w.pos, v.cot, v.cov, v.w.accum, v.p,
-                      v.w.state, nullptr, 0);
+                      v.w.state, nullptr, 0, labelled);
+}
+template <int PER>
+__global__ __launch_bounds__(kFrontThreads) void k_front_b(const BatchView* __restrict__ bv,
+                                                           const int32_t* __restrict__ idx, int T,
+                                                           int V) {
+  const BatchView& v = bv[blockIdx.y];
+  k_front_body<PER>(v.visible, idx, T, V, v.cov, v.cot, v.w.vlist, v.charts, v.w.accum,
+                    v.p.max_charts, v.w.state, v.w.big_counter, false,
+                    reinterpret_cast<int4*>(v.occ), (int64_t)v.p.omega * v.p.omega / 4);
 }
 
 }  // namespace
@@ -1124,6 +1367,39 @@ hipError_t launch_prologue(int64_t V, const uint8_t* vis, const int32_t* nbr,
                                          check_idx != nullptr);
   mk(st);
   return hipGetLastError();
+}
+
+hipError_t front_kernel_attributes() {
+  const void* ks[4] = {(const void*)k_front<2>, (const void*)k_front<8>,
+                       (const void*)k_front_b<2>, (const void*)k_front_b<8>};
+  for (const void* k : ks) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)front_lds(kFrontTris, kFrontVerts));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+bool launch_front(const uint8_t* vis, const int32_t* idx, int64_t T, int64_t V,
+                  const FrameParams& p, const Work& w, int32_t* cot, int32_t* cov,
+                  fa_chart* charts, int32_t* occ_fill, bool check, Marker& mk, hipStream_t st,
+                  hipError_t* err) {
+  if (!use_front(p, T, V)) return false;
+  const int64_t n4 = (int64_t)p.omega * p.omega / 4;
+  const unsigned grid = 1u + (occ_fill ? fill_groups(n4) : 0u);
+  auto launch = [&](auto kernel) {
+    kernel<<<grid, kFrontThreads, front_lds(T, V), st>>>(
+        vis, idx, (int)T, (int)V, cov, cot, w.vlist, charts, w.accum, p.max_charts, w.state,
+        w.big_counter, check, reinterpret_cast<int4*>(occ_fill), n4);
+  };
+  if (T <= kFrontFew) launch(k_front<2>);
+  else launch(k_front<8>);
+  for (int k = 0; k < 9; ++k) mk(st);  // (prologue to root assignment in one)
+  k_gather_boxes<<<grid_for(T, kGatherBlock * kGatherItems), kGatherBlock, 0, st>>>(
+      w.vlist, idx, w.parent, w.pos, cot, cov, w.accum, p, w.state, nullptr, 0, true);
+  mk(st);
+  *err = hipGetLastError();
+  return true;
 }
 
 hipError_t launch_charts(const uint8_t* vis, const int32_t* idx, const int32_t* nbr, int64_t T,
@@ -1206,7 +1482,7 @@ hipError_t launch_charts(const uint8_t* vis, const int32_t* idx, const int32_t* 
     k_gather_boxes<<<grid_for(T, kGatherBlock * kGatherItems) + fill_blocks, kGatherBlock, 0,
                      st>>>(
         w.vlist, idx, w.parent, w.pos, cot, cov, w.accum, p, w.state,
-        reinterpret_cast<int4*>(gfill), n4);
+        reinterpret_cast<int4*>(gfill), n4, false);
   } else {
     mk(st);
   }
@@ -1216,8 +1492,18 @@ hipError_t launch_charts(const uint8_t* vis, const int32_t* idx, const int32_t* 
 
 hipError_t launch_charts_batched(const BatchView* dev, int n, const float* pos,
                                  const int32_t* idx, const int32_t* nbr, int64_t T, int64_t V,
-                                 hipStream_t st) {
+                                 int max_omega, hipStream_t st) {
   if (n <= 0) return hipSuccess;
+  if (T > 0 && T <= kFrontTris && V <= kFrontVerts) {  // (batched views have vertex charts)
+    const dim3 grid(1u + fill_groups((int64_t)max_omega * max_omega / 4), n);
+    if (T <= kFrontFew)
+      k_front_b<2><<<grid, kFrontThreads, front_lds(T, V), st>>>(dev, idx, (int)T, (int)V);
+    else
+      k_front_b<8><<<grid, kFrontThreads, front_lds(T, V), st>>>(dev, idx, (int)T, (int)V);
+    k_gather_boxes_b<<<dim3(grid_for(T, kGatherBlock * kGatherItems), n), kGatherBlock, 0, st>>>(
+        dev, idx, true);
+    return hipGetLastError();
+  }
   const unsigned vb = std::max(1u, grid_for(V, kBlock * kProVerts));
   const unsigned tt = grid_for(T, kTriTile);
   const unsigned vt = std::max(1u, tt);
@@ -1232,7 +1518,7 @@ hipError_t launch_charts_batched(const BatchView* dev, int n, const float* pos,
     k_uf_flatten_count_b<<<dim3(vt, n), kBlock, 0, st>>>(dev);
     k_assign_roots_b<<<dim3(vt, n), kBlock, 0, st>>>(dev);
     k_gather_boxes_b<<<dim3(grid_for(T, kGatherBlock * kGatherItems), n), kGatherBlock, 0, st>>>(
-        dev, idx);
+        dev, idx, false);
   }
   return hipGetLastError();
 }

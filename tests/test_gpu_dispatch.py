@@ -213,3 +213,47 @@ def test_adjacency_ways(name):
             ctx.adjacency(fa.Mesh(np.zeros((V, 3), np.float32), bad, 6))
         assert e.value.code == fa.FA_ERR_INVALID_ARG
     ctx.close()
+
+
+# Meshes of up to 8192 triangles and 16384 vertices have their charts built by
+# one workgroup (2 triangles a thread up to 2048 of them); larger ones by the
+# tiled union-find.
+@pytest.mark.parametrize("n", [1, 63, 64, 1023, 1025, 2048, 2049, 4000, 8191, 8192, 8193])
+@pytest.mark.parametrize("per", [1, 5])
+def test_front_sizes(n, per):
+    rng = np.random.default_rng(n)
+    owners = np.sort(rng.integers(0, max(1, n // per), n)) if per > 1 else np.arange(n)
+    f = fans(np.unique(owners, return_inverse=True)[1], seed=n, atlas_size=2048)
+    f.visible = (rng.uniform(size=n) < 0.7).astype(np.uint8)
+    f.visible[rng.integers(n)] = 1
+    compare(check(f), oracle.build_frame(f))
+
+
+@pytest.mark.parametrize("V", [16384, 16385])
+def test_front_vertices(V):
+    # a strip over V vertices (the triangles wrap around it): long chains of
+    # triangles in shuffled order
+    rng = np.random.default_rng(V)
+    t = rng.permutation(8000) * V // 8000
+    f = fans(np.zeros(1, np.int64))
+    pos = np.zeros((V, 3), np.float32)
+    pos[:, 0] = np.linspace(-0.9, 0.9, V)
+    pos[:, 1] = 0.4 * (-1.0) ** np.arange(V)
+    idx = np.stack([t % V, (t + 1) % V, (t + 2) % V], 1).astype(np.int32)
+    f.positions, f.indices = pos, idx
+    f.visible = (rng.uniform(size=len(idx)) < 0.9).astype(np.uint8)
+    f.name = f"strip/{V}"
+    compare(check(f), oracle.build_frame(f))
+
+
+def test_front_over_capacity():
+    f = fans(np.repeat(np.arange(40), 2))
+    fa = _fa()
+    ctx = fa.Context(f.num_triangles, f.num_vertices, max_charts=32, max_atlas=1024)
+    print("[gpu] 40 charts, capacity 32", flush=True)
+    out = ctx.build_atlas(fa.Mesh(f.positions, f.indices, 3), torch.as_tensor(f.visible).cuda(),
+                          f.view_proj, f.width, f.height, 1024, 1.0)
+    torch.cuda.synchronize()
+    m = out.to_numpy()["meta"]
+    ctx.close()
+    assert m["status"] == fa.FA_ERR_CAPACITY and m["num_charts"] == 40
