@@ -384,8 +384,9 @@ class Context:
         """sizes: float32 cuda tensor [n,2]. Returns (placements [n,5], meta, candidates)."""
         n = int(sizes.shape[0])
         pl = torch.empty((max(n, 1), 5), dtype=torch.int32, device="cuda")
-        meta = torch.zeros(16, dtype=torch.int32, device="cuda")
-        cand = torch.zeros((self.cfg.num_scales, 4), dtype=torch.int32, device="cuda")
+        # (the call writes all of both)
+        meta = torch.empty(16, dtype=torch.int32, device="cuda")
+        cand = torch.empty((self.cfg.num_scales, 4), dtype=torch.int32, device="cuda")
         _check(fa_pack_boxes(self.h, _ptr(sizes), n, int(atlas_size), _ptr(pl), _ptr(meta),
                              _ptr(cand), _stream_handle(stream)), "fa_pack_boxes")
         return pl[:n], meta, cand

@@ -21,7 +21,7 @@ constexpr int kSortTile = 2048;      // keys per workgroup in one radix pass
 constexpr int kCandStride = 8;       // int32 per candidate in the table
 constexpr int kMaxAtlas = 8192;
 constexpr int kCountGrid = 256;      // most workgroups that publish sums in Work::partial
-constexpr int kOrderGroups = 32;     // workgroups of the chart order above 1024 charts
+constexpr int kOrderGroups = 32;     // workgroups of the chart order above 2048 charts
 static_assert(kOrderGroups <= kCountGrid, "the order's chunk sums use Work::partial");
 constexpr int kStripTexels = 64;     // atlas columns per strip of the occupancy count
 constexpr int kMaxStrips = kMaxAtlas / kStripTexels;
@@ -237,6 +237,33 @@ __device__ __forceinline__ T block_sum(T v, T* sh) {
   return m;
 }
 
+// Frame record for the caller (one thread); `occ` is the occupied texel count
+// when the occupancy map was built.
+__device__ __forceinline__ void write_meta(const FrameParams& p, FrameState* stp,
+                                           const unsigned long long* __restrict__ big_counter,
+                                           bool with_occ, unsigned long long occ,
+                                           fa_atlas_meta* __restrict__ meta) {
+  if (with_occ && stp->status == FA_OK) stp->occupied = occ;
+  const FrameState st = *stp;
+  fa_atlas_meta m;
+  m.status = st.status;
+  m.num_charts = st.num_charts;
+  m.chosen_j = st.jstar;
+  m.num_scales = p.J;
+  m.atlas_size = p.omega;
+  m.layout_width = st.layout_w;
+  m.layout_height = st.layout_h;
+  m.rows = st.rows;
+  m.s_eff = st.status == FA_OK ? st.s_star * st.q_star : 0.0f;
+  m.rate = p.rate;
+  m.occupied_texels = (int64_t)st.occupied;
+  m.visible_triangles = (int64_t)st.visible;
+  m.large_tiles = (int64_t)(__hip_atomic_load(big_counter, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT) &
+                            ((1ull << 40) - 1));
+  *meta = m;
+}
+
 // ---------------------------------------------------------------------------
 // cross-lane primitives on the DPP (data-parallel primitives) network: the
 // lane moves ride on VALU instructions instead of LDS permutes. Every lane of
@@ -361,7 +388,9 @@ hipError_t front_kernel_attributes();
 hipError_t launch_charts(const uint8_t* vis, const int32_t* idx, const int32_t* nbr, int64_t T,
                          const FrameParams& p, const Work& w, int32_t* cot, int32_t* cov,
                          fa_chart* charts, int32_t* occ_fill, Marker& mk, hipStream_t st);
-hipError_t launch_order(const FrameParams& p, const Work& w, fa_chart* charts, int from_accum,
+// sizes: NULL (the charts' boxes), or the [n][2] given sizes of the packer-only
+// entry
+hipError_t launch_order(const FrameParams& p, const Work& w, fa_chart* charts, const float* sizes,
                         hipStream_t st);
 // footprint push: the full-scale profile of every chart (clear, then raster)
 hipError_t launch_footprint(const int32_t* idx, int64_t T, const FrameParams& p, const Work& w,
@@ -458,11 +487,12 @@ hipError_t launch_occupancy_batched(const BatchView* dev, int n, const int32_t* 
                                     int64_t V, int max_omega, int small_texels, int lane_texels,
                                     hipStream_t st);
 
-// packer-only path: sizes [n][2] -> charts' oriented sizes and keys
-hipError_t launch_pack_prepare(const float* sizes, int32_t n, const FrameParams& p,
-                               const Work& w, fa_chart* charts, hipStream_t st);
-hipError_t launch_pack_emit(int32_t n, const fa_chart* charts, int32_t* placements,
-                            const Work& w, hipStream_t st);
+// packer-only path: the frame state of n boxes, then (after the order and the
+// push) selection, placements [n][5] and frame record in one launch
+hipError_t launch_pack_state(int32_t n, const Work& w, hipStream_t st);
+hipError_t launch_select_emit(const FrameParams& p, const Work& w, int32_t n, fa_chart* charts,
+                              int32_t* cand_out, int32_t* placements, fa_atlas_meta* meta,
+                              hipStream_t st);
 hipError_t pack_kernel_attributes(int max_dyn_bytes);
 
 // adjacency (per scene) by vertex ranges: count, then (no bad index and the

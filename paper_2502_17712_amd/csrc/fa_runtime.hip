@@ -582,7 +582,7 @@ int run_frame_core(const Knobs& kn, const Work& slot, const fa_mesh* mesh, const
     ok(launch_charts(visible, mesh->indices, nbr, T, p, w, out->chart_of_tri, cov, out->charts,
                      occ_fill, mk, st));
   }
-  ok(launch_order(p, w, out->charts, 1, st));
+  ok(launch_order(p, w, out->charts, nullptr, st));
   mk(st);
   ok(launch_footprint(mesh->indices, T, p, w, out->chart_of_tri, out->charts, mk, st));
   ok(launch_pack(p, w, kn.pack_block, p.fp_cap > 0, st));
@@ -883,12 +883,10 @@ int fa_pack_boxes(fa_ctx* ctx, const float* sizes, int32_t n, int32_t atlas_size
   fa_chart* charts = w.pack_charts;
   hipError_t e = hipSuccess;
   auto ok = [&](hipError_t x) { if (x != hipSuccess && e == hipSuccess) e = x; };
-  ok(launch_pack_prepare(sizes, n, p, w, charts, st));
-  ok(launch_order(p, w, charts, 0, st));
+  ok(launch_pack_state(n, w, st));
+  if (n > 0) ok(launch_order(p, w, charts, sizes, st));
   ok(launch_pack(p, w, ctx->pack_block, false, st));
-  ok(launch_select_place(p, w, charts, candidates, st));
-  ok(launch_pack_emit(n, charts, placements, w, st));
-  ok(launch_meta(p, w, meta, st));
+  ok(launch_select_emit(p, w, n, charts, candidates, placements, meta, st));
   return e == hipSuccess ? FA_OK : FA_ERR_DEVICE;
 }
 

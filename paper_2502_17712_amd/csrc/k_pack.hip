@@ -1179,7 +1179,8 @@ __device__ __forceinline__ void place_box(const FrameParams& p, int jm, int L, i
                                           const uint32_t* __restrict__ cand_ab,
                                           const int32_t* __restrict__ cand_y, int64_t stride,
                                           fa_chart* __restrict__ charts,
-                                          int4* __restrict__ chart_tex, uint32_t* strips) {
+                                          int4* __restrict__ chart_tex, uint32_t* strips,
+                                          int32_t* __restrict__ placements) {
   const long long Xi = cand_x[(int64_t)jm * stride + i];
   const uint32_t ab = cand_ab[(int64_t)jm * stride + i];
   const int a = (int)(ab & 0xFFFFu), b = (int)(ab >> 16);
@@ -1191,6 +1192,15 @@ __device__ __forceinline__ void place_box(const FrameParams& p, int jm, int L, i
   ch.y = y;
   ch.w = a;
   ch.h = b;
+  if (placements) {
+    int32_t* o = placements + 5 * (int64_t)order[i];
+    o[0] = x;
+    o[1] = y;
+    o[2] = a;
+    o[3] = b;
+    o[4] = ch.rotated;
+    return;  // (no occupancy map follows)
+  }
   if (chart_tex) {
     // texels t whose centre lies in the box: 2 x omega <= (2t+1) L < 2 (x+w) omega
     const int64_t om = p.omega, L2 = 2 * (int64_t)L;
@@ -1211,7 +1221,9 @@ __device__ __forceinline__ void k_select_place_body(
     int32_t* __restrict__ cand_out, const int32_t* __restrict__ order,
     const long long* __restrict__ cand_x, const uint32_t* __restrict__ cand_ab,
     const int32_t* __restrict__ cand_y, int64_t stride, fa_chart* __restrict__ charts,
-    int4* __restrict__ chart_tex) {
+    int4* __restrict__ chart_tex, int32_t* __restrict__ placements = nullptr,
+    fa_atlas_meta* __restrict__ meta = nullptr,
+    const unsigned long long* __restrict__ big_counter = nullptr) {
   __shared__ int sj, sL;
   __shared__ uint32_t strips[kMaxStrips];
   const bool ok = st->status == FA_OK;
@@ -1222,7 +1234,10 @@ __device__ __forceinline__ void k_select_place_body(
     int32_t* o = cand_out + 4 * tid;
     o[0] = ok ? t[0] : 0; o[1] = ok ? t[1] : 0; o[2] = ok ? t[2] : 0; o[3] = ok ? t[3] : 0;
   }
-  if (!ok) return;
+  if (!ok) {
+    if (meta && blockIdx.x == 0 && tid == 0) write_meta(p, st, big_counter, false, 0ull, meta);
+    return;
+  }
   if (blockIdx.x > 0 && (int64_t)blockIdx.x * kBlock >= C) return;
   if (tid < kMaxStrips) strips[tid] = 0u;
   if (tid < kWave) {
@@ -1251,6 +1266,7 @@ __device__ __forceinline__ void k_select_place_body(
           st->s_star = (float)j / (float)p.J;
           st->q_star = (float)p.omega / (float)L;
         }
+        if (meta) write_meta(p, st, big_counter, false, 0ull, meta);
       }
     }
   }
@@ -1258,7 +1274,8 @@ __device__ __forceinline__ void k_select_place_body(
   const int jm = sj - 1, L = sL;
   if (jm < 0) return;
   const int i = blockIdx.x * kBlock + tid;
-  if (i < C) place_box(p, jm, L, i, order, cand_x, cand_ab, cand_y, stride, charts, chart_tex, strips);
+  if (i < C) place_box(p, jm, L, i, order, cand_x, cand_ab, cand_y, stride, charts, chart_tex, strips,
+                       placements);
   __syncthreads();
   if (chart_tex && tid < kMaxStrips && strips[tid]) atomicMax(&st->strip_rows[tid], strips[tid]);
 }
@@ -1269,6 +1286,18 @@ __global__ __launch_bounds__(kBlock) void k_select_place(
     const int32_t* __restrict__ cand_y, int64_t stride, fa_chart* __restrict__ charts,
     int4* __restrict__ chart_tex) {
   k_select_place_body(p, cand_tab, st, cand_out, order, cand_x, cand_ab, cand_y, stride, charts, chart_tex);
+}
+
+// ... of the packer-only entry: placements and the frame record with it
+__global__ __launch_bounds__(kBlock) void k_select_emit(
+    FrameParams p, const int32_t* __restrict__ cand_tab, FrameState* st,
+    int32_t* __restrict__ cand_out, const int32_t* __restrict__ order,
+    const long long* __restrict__ cand_x, const uint32_t* __restrict__ cand_ab,
+    const int32_t* __restrict__ cand_y, int64_t stride, fa_chart* __restrict__ charts,
+    int32_t* __restrict__ placements, fa_atlas_meta* __restrict__ meta,
+    const unsigned long long* __restrict__ big_counter) {
+  k_select_place_body(p, cand_tab, st, cand_out, order, cand_x, cand_ab, cand_y, stride, charts,
+                      nullptr, placements, meta, big_counter);
 }
 
 // ---- batched wrappers (view = blockIdx.y) --------------------------------
@@ -1291,45 +1320,6 @@ __global__ void k_pack_state(FrameState* st, int32_t n) {
   constexpr unsigned kCharts = offsetof(FrameState, num_charts) / 4;
   for (unsigned i = threadIdx.x; i < sizeof(FrameState) / 4; i += blockDim.x)
     reinterpret_cast<uint32_t*>(st)[i] = i == kCharts ? (uint32_t)n : 0u;  // (FA_OK is 0)
-}
-
-__global__ void k_pack_prepare(const float* __restrict__ sizes, int32_t n,
-                               fa_chart* __restrict__ charts, uint32_t* __restrict__ keys,
-                               int32_t* __restrict__ vals, FrameState* st) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n) return;
-  const float tw = sizes[2 * c], th = sizes[2 * c + 1];
-  const float lim = 16777216.0f;  // 2^24 texels
-  if (!(tw >= 0.0f && tw <= lim && th >= 0.0f && th <= lim)) {
-    st->status = FA_ERR_INVALID_ARG;  // every writer stores the same value
-    return;
-  }
-  const int rot = tw > th ? 1 : 0;
-  const float bw = rot ? th : tw, bh = rot ? tw : th;
-  const int key = min((int)ceilf(bh), kKeyCap);
-  fa_chart& ch = charts[c];
-  ch.root_tri = c;
-  ch.ndc_box[0] = ch.ndc_box[1] = ch.ndc_box[2] = ch.ndc_box[3] = 0.0f;
-  ch.target_w = tw;
-  ch.target_h = th;
-  ch.oriented_w = bw;
-  ch.oriented_h = bh;
-  ch.rotated = rot;
-  ch.key = key;
-  keys[c] = (uint32_t)(kKeyCap - key);
-  vals[c] = c;
-}
-
-__global__ void k_pack_emit(int32_t n, const fa_chart* __restrict__ charts,
-                            int32_t* __restrict__ out, const FrameState* __restrict__ st) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n || st->status != FA_OK) return;
-  const fa_chart& ch = charts[c];
-  out[5 * c + 0] = ch.x;
-  out[5 * c + 1] = ch.y;
-  out[5 * c + 2] = ch.w;
-  out[5 * c + 3] = ch.h;
-  out[5 * c + 4] = ch.rotated;
 }
 
 }  // namespace
@@ -1424,21 +1414,17 @@ hipError_t launch_select_place(const FrameParams& p, const Work& w, fa_chart* ch
   return hipGetLastError();
 }
 
-hipError_t launch_pack_prepare(const float* sizes, int32_t n, const FrameParams& p, const Work& w,
-                               fa_chart* charts, hipStream_t st) {
-  (void)p;
-  k_pack_state<<<1, 64, 0, st>>>(w.state, n);
-  if (n > 0)
-    k_pack_prepare<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(
-        sizes, n, charts, w.keys_a, w.vals_a, w.state);
+hipError_t launch_pack_state(int32_t n, const Work& w, hipStream_t st) {
+  k_pack_state<<<1, 256, 0, st>>>(w.state, n);
   return hipGetLastError();
 }
 
-hipError_t launch_pack_emit(int32_t n, const fa_chart* charts, int32_t* placements,
-                            const Work& w, hipStream_t st) {
-  if (n > 0)
-    k_pack_emit<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(n, charts, placements,
-                                                                         w.state);
+hipError_t launch_select_emit(const FrameParams& p, const Work& w, int32_t n, fa_chart* charts,
+                              int32_t* cand_out, int32_t* placements, fa_atlas_meta* meta,
+                              hipStream_t st) {
+  k_select_emit<<<(unsigned)std::max(1, (n + kBlock - 1) / kBlock), kBlock, 0, st>>>(
+      p, w.cand_tab, w.state, cand_out, w.vals_a, w.cand_x, w.cand_ab, w.cand_y, p.max_charts,
+      charts, placements, meta, w.big_counter);
   return hipGetLastError();
 }
 

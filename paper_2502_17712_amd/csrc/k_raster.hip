@@ -629,33 +629,6 @@ __global__ __launch_bounds__(kBlock) void k_occ_big(
   k_occ_big_body(idx, p, pos, cot, charts, chart_tex, occ, big, big_fp, big_cap, big_counter, stp);
 }
 
-// Frame record for the caller (one thread); `occ` is the occupied texel count
-// when the occupancy map was built.
-__device__ __forceinline__ void write_meta(const FrameParams& p, FrameState* stp,
-                                           const unsigned long long* __restrict__ big_counter,
-                                           bool with_occ, unsigned long long occ,
-                                           fa_atlas_meta* __restrict__ meta) {
-  if (with_occ && stp->status == FA_OK) stp->occupied = occ;
-  const FrameState st = *stp;
-  fa_atlas_meta m;
-  m.status = st.status;
-  m.num_charts = st.num_charts;
-  m.chosen_j = st.jstar;
-  m.num_scales = p.J;
-  m.atlas_size = p.omega;
-  m.layout_width = st.layout_w;
-  m.layout_height = st.layout_h;
-  m.rows = st.rows;
-  m.s_eff = st.status == FA_OK ? st.s_star * st.q_star : 0.0f;
-  m.rate = p.rate;
-  m.occupied_texels = (int64_t)st.occupied;
-  m.visible_triangles = (int64_t)st.visible;
-  m.large_tiles = (int64_t)(__hip_atomic_load(big_counter, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT) &
-                            ((1ull << 40) - 1));
-  *meta = m;
-}
-
 __global__ void k_meta(FrameParams p, FrameState* stp,
                        const unsigned long long* __restrict__ big_counter,
                        fa_atlas_meta* __restrict__ meta) {

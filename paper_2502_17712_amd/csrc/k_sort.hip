@@ -430,33 +430,67 @@ __device__ __forceinline__ void chart_size(const FrameParams& p, const uint4 e, 
   oriented = make_float2(bw, bh);
 }
 
-// Sizes (when from_accum) and the stable order by (height desc, chart asc):
-// two 8-bit LSD radix passes over the 13-bit keys in one workgroup, items
-// ranked 1024 at a time (ballot matching inside a wave, per-wave digit counts
-// across the 16 waves), then the sorted oriented sizes for the packer. Frames
-// of up to kOrderLds charts keep keys, values and sizes in LDS throughout
-// (only the final order goes to global memory). With
+// The packer-only entry: chart record, key and oriented size of a box given by
+// its sizes. false: a size outside [0, 2^24].
+__device__ __forceinline__ bool box_size(const float* __restrict__ sizes, int c, fa_chart& ch,
+                                         uint32_t& key_out, float2& oriented) {
+  const float tw = sizes[2 * c], th = sizes[2 * c + 1];
+  const float lim = 16777216.0f;  // 2^24 texels
+  const bool ok = tw >= 0.0f && tw <= lim && th >= 0.0f && th <= lim;
+  const int rot = tw > th ? 1 : 0;
+  const float bw = rot ? th : tw, bh = rot ? tw : th;
+  const int key = ok ? min((int)ceilf(bh), kKeyCap) : 0;
+  ch.root_tri = c;
+  ch.ndc_box[0] = ch.ndc_box[1] = ch.ndc_box[2] = ch.ndc_box[3] = 0.0f;
+  ch.target_w = tw; ch.target_h = th;
+  ch.oriented_w = bw; ch.oriented_h = bh;
+  ch.rotated = rot;
+  ch.key = key;
+  key_out = (uint32_t)(kKeyCap - key);
+  oriented = make_float2(bw, bh);
+  return ok;
+}
+
+// Sizes (from the charts' boxes, or given) and the stable order by (height
+// desc, chart asc): two 8-bit LSD radix passes over the 13-bit keys in one
+// workgroup, items ranked 1024 at a time (ballot matching inside a wave,
+// per-wave digit counts across the 16 waves), then the sorted oriented sizes
+// for the packer. Frames of up to kOrderLds charts keep keys, values and sizes
+// in LDS throughout (only the final order goes to global memory). With
 // fp_off (footprint push): each chart's full-scale profile columns,
 // floor(oriented width) + 1, are laid out in chart order (exclusive scan);
 // a total above the capacity ends the frame with FA_ERR_CAPACITY.
 constexpr int kOrderThreads = 1024;
-constexpr int kOrderLds = 2048;     // most charts whose keys, values and sizes fit in LDS
-constexpr int kOrderSingle = 1024;  // most charts one workgroup orders in global memory
+constexpr int kOrderLds = 2048;  // most charts one workgroup orders, in LDS
 
-// The body for one placement of the keys and values (LDS or global memory),
-// so that every access of the sort has a known address space.
-template <bool LDS>
+// One workgroup, with keys, values and sizes in LDS. The packer-only entry's
+// sizes are read here too (a kernel of their own and the frame's two for
+// placements and record cost 3 x 3 us more: 3000 boxes 69 -> 60 us, 100 boxes
+// 44 -> 27 us).
 __device__ __forceinline__ void order_body(const FrameParams& p, const uint32_t* __restrict__ accum,
                                            fa_chart* __restrict__ charts, uint32_t* KA,
                                            int32_t* VA, uint32_t* KB, int32_t* VB, float2* lwh,
                                            int32_t* __restrict__ vals_out,
-                                           float2* __restrict__ sorted_wh, int from_accum,
+                                           float2* __restrict__ sorted_wh,
+                                           const float* __restrict__ sizes,
                                            int32_t* __restrict__ fp_off, FrameState* st, int C,
                                            uint32_t* base, uint32_t (*wcnt)[kRadix],
                                            uint32_t* sh, long long* sh64) {
   constexpr int NW = kOrderThreads / kWave;
   const int tid = threadIdx.x, w = tid / kWave;
-  if (from_accum) {
+  if (sizes) {
+    bool bad = false;
+    for (int c = tid; c < C; c += kOrderThreads) {
+      uint32_t key;
+      float2 wh;
+      bad = !box_size(sizes, c, charts[c], key, wh) || bad;
+      KA[c] = key;
+      VA[c] = c;
+      lwh[c] = wh;
+    }
+    if (bad) st->status = FA_ERR_INVALID_ARG;  // (every writer stores the same value)
+    __syncthreads();
+  } else {
     for (int c = tid; c < C; c += kOrderThreads) {
       uint32_t key;
       // the box words were reduced with atomics (possibly on other XCDs):
@@ -470,7 +504,7 @@ __device__ __forceinline__ void order_body(const FrameParams& p, const uint32_t*
       chart_size(p, box, charts[c], key, wh);
       KA[c] = key;
       VA[c] = c;
-      if (LDS) lwh[c] = wh;
+      lwh[c] = wh;
     }
     __syncthreads();
   }
@@ -534,12 +568,8 @@ __device__ __forceinline__ void order_body(const FrameParams& p, const uint32_t*
   for (int i = tid; i < C; i += kOrderThreads) {
     const int c = VA[i];
     fa_chart& ch = charts[c];
-    if (LDS) {
-      sorted_wh[i] = lwh[c];
-      vals_out[i] = c;
-    } else {
-      sorted_wh[i] = make_float2(ch.oriented_w, ch.oriented_h);
-    }
+    sorted_wh[i] = lwh[c];
+    vals_out[i] = c;
     ch.order_rank = i;
   }
   if (fp_off) {
@@ -547,7 +577,7 @@ __device__ __forceinline__ void order_body(const FrameParams& p, const uint32_t*
     for (int base0 = 0; base0 < C; base0 += kOrderThreads) {
       const int c = base0 + tid;
       const long long n =
-          c < C ? (long long)floorf(LDS ? lwh[c].x : charts[c].oriented_w) + 1 : 0;
+          c < C ? (long long)floorf(lwh[c].x) + 1 : 0;
       long long tot;
       const long long incl = block_incl_scan<long long>(n, sh64, &tot);
       if (c < C) fp_off[c] = (int32_t)min(run + incl - n, (long long)p.fp_cap);
@@ -713,7 +743,8 @@ __device__ __forceinline__ void chunk_scatter(const uint32_t* kin, const int32_t
 __device__ __forceinline__ void order_multi(const FrameParams& p, const uint32_t* __restrict__ accum,
                                             fa_chart* __restrict__ charts, uint32_t* KA,
                                             int32_t* VA, uint32_t* KB, int32_t* VB,
-                                            float2* __restrict__ sorted_wh, int from_accum,
+                                            float2* __restrict__ sorted_wh,
+                                            const float* __restrict__ sizes,
                                             int32_t* __restrict__ fp_off, FrameState* st, int C,
                                             uint32_t* hist, unsigned long long* part,
                                             uint32_t* base, uint32_t (*wcnt)[kRadix],
@@ -730,21 +761,21 @@ __device__ __forceinline__ void order_multi(const FrameParams& p, const uint32_t
     long long cols = 0;
     for (int c = lo + tid; c < hi; c += kOrderThreads) {
       float2 wh;
-      if (from_accum) {
+      uint32_t key;
+      if (sizes) {
+        if (!box_size(sizes, c, charts[c], key, wh)) st->status = FA_ERR_INVALID_ARG;
+      } else {
         uint4 box;
         box.x = aload_u(&accum[4 * c + 0]);
         box.y = aload_u(&accum[4 * c + 1]);
         box.z = aload_u(&accum[4 * c + 2]);
         box.w = aload_u(&accum[4 * c + 3]);
-        uint32_t key;
         chart_size(p, box, charts[c], key, wh);
-        astore_u(&KA[c], key);
-        astore_i(&VA[c], c);
-        astore_i(reinterpret_cast<int32_t*>(&charts[c].oriented_w), __float_as_int(wh.x));
-        astore_i(reinterpret_cast<int32_t*>(&charts[c].oriented_h), __float_as_int(wh.y));
-      } else {
-        wh = make_float2(charts[c].oriented_w, charts[c].oriented_h);
       }
+      astore_u(&KA[c], key);
+      astore_i(&VA[c], c);
+      astore_i(reinterpret_cast<int32_t*>(&charts[c].oriented_w), __float_as_int(wh.x));
+      astore_i(reinterpret_cast<int32_t*>(&charts[c].oriented_h), __float_as_int(wh.y));
       if (fp_off) cols += (long long)floorf(wh.x) + 1;
     }
     if (fp_off) {
@@ -825,7 +856,7 @@ __device__ __forceinline__ void order_multi(const FrameParams& p, const uint32_t
 __device__ __forceinline__ void k_sizes_order_body(
     FrameParams p, const uint32_t* __restrict__ accum, fa_chart* __restrict__ charts,
     uint32_t* __restrict__ keys_a, int32_t* __restrict__ vals_a, uint32_t* __restrict__ keys_b,
-    int32_t* __restrict__ vals_b, float2* __restrict__ sorted_wh, int from_accum,
+    int32_t* __restrict__ vals_b, float2* __restrict__ sorted_wh, const float* __restrict__ sizes,
     int32_t* __restrict__ fp_off, FrameState* __restrict__ st, uint32_t* __restrict__ hist,
     unsigned long long* __restrict__ part) {
   constexpr int NW = kOrderThreads / kWave;
@@ -837,36 +868,35 @@ __device__ __forceinline__ void k_sizes_order_body(
   __shared__ int32_t lv[2][kOrderLds];
   __shared__ float2 lwh[kOrderLds];
   __shared__ int flag, slot;
-  if (st->status != FA_OK) return;
+  // (read once for the workgroup: a chunk or a wave may set the status below
+  // while others start)
+  if (threadIdx.x == 0) flag = st->status == FA_OK;
+  __syncthreads();
+  if (!flag) return;
   const int C = min(st->num_charts, p.max_charts);
-  const bool in_lds = from_accum && C <= kOrderLds;
-  if (gridDim.x > 1 && !in_lds && C > kOrderSingle) {
-    order_multi(p, accum, charts, keys_a, vals_a, keys_b, vals_b, sorted_wh, from_accum, fp_off,
+  if (C > kOrderLds) {
+    order_multi(p, accum, charts, keys_a, vals_a, keys_b, vals_b, sorted_wh, sizes, fp_off,
                 st, C, hist, part, base, wcnt, sh, sh64, &flag, &slot);
     return;
   }
   if (blockIdx.x != 0) return;
-  if (in_lds)
-    order_body<true>(p, accum, charts, lk[0], lv[0], lk[1], lv[1], lwh, vals_a, sorted_wh,
-                     from_accum, fp_off, st, C, base, wcnt, sh, sh64);
-  else
-    order_body<false>(p, accum, charts, keys_a, vals_a, keys_b, vals_b, nullptr, vals_a,
-                      sorted_wh, from_accum, fp_off, st, C, base, wcnt, sh, sh64);
+  order_body(p, accum, charts, lk[0], lv[0], lk[1], lv[1], lwh, vals_a, sorted_wh, sizes, fp_off,
+             st, C, base, wcnt, sh, sh64);
 }
 __global__ __launch_bounds__(kOrderThreads) void k_sizes_order(
     FrameParams p, const uint32_t* __restrict__ accum, fa_chart* __restrict__ charts,
     uint32_t* __restrict__ keys_a, int32_t* __restrict__ vals_a, uint32_t* __restrict__ keys_b,
-    int32_t* __restrict__ vals_b, float2* __restrict__ sorted_wh, int from_accum,
+    int32_t* __restrict__ vals_b, float2* __restrict__ sorted_wh, const float* __restrict__ sizes,
     int32_t* __restrict__ fp_off, FrameState* __restrict__ st, uint32_t* __restrict__ hist,
     unsigned long long* __restrict__ part) {
-  k_sizes_order_body(p, accum, charts, keys_a, vals_a, keys_b, vals_b, sorted_wh, from_accum,
-                     fp_off, st, hist, part);
+  k_sizes_order_body(p, accum, charts, keys_a, vals_a, keys_b, vals_b, sorted_wh, sizes, fp_off,
+                     st, hist, part);
 }
 
 __global__ __launch_bounds__(kOrderThreads) void k_sizes_order_b(const BatchView* __restrict__ bv) {
   const BatchView& v = bv[blockIdx.y];
   k_sizes_order_body(v.p, v.w.accum, v.charts, v.w.keys_a, v.w.vals_a, v.w.keys_b, v.w.vals_b,
-                     v.w.sorted_wh, 1, nullptr, v.w.state, v.w.hist, v.w.partial);
+                     v.w.sorted_wh, nullptr, nullptr, v.w.state, v.w.hist, v.w.partial);
 }
 
 }  // namespace
@@ -934,12 +964,12 @@ hipError_t launch_adjacency(const int32_t* idx, int64_t T, int64_t V, const AdjT
   return hipGetLastError();
 }
 
-hipError_t launch_order(const FrameParams& p, const Work& w, fa_chart* charts, int from_accum,
+hipError_t launch_order(const FrameParams& p, const Work& w, fa_chart* charts, const float* sizes,
                         hipStream_t st) {
-  int32_t* fp_off = (from_accum && p.fp_cap > 0) ? w.fp_off : nullptr;
+  int32_t* fp_off = (!sizes && p.fp_cap > 0) ? w.fp_off : nullptr;
   k_sizes_order<<<kOrderGroups, kOrderThreads, 0, st>>>(p, w.accum, charts, w.keys_a, w.vals_a,
                                                         w.keys_b, w.vals_b, w.sorted_wh,
-                                                        from_accum, fp_off, w.state, w.hist,
+                                                        sizes, fp_off, w.state, w.hist,
                                                         w.partial);
   return hipGetLastError();
 }

@@ -118,6 +118,9 @@ PUSH_CASES = {
     "overflow on both sides of 1024": (_uniform(60, 100, 1400), 4096, {}),
     "rows longer than a chunk": (_uniform(30000, 0.2, 6), 8192, dict(g=0, mmin=1)),
     "rows of a third of a chunk": (_uniform(20000, 0.2, 6), 4096, dict(g=0, mmin=2)),
+    "2047 boxes": (_uniform(2047, 1, 30), 2048, {}),
+    "2048 boxes": (_uniform(2048, 1, 30), 2048, {}),
+    "2049 boxes": (_uniform(2049, 1, 30), 2048, {}),
     "8127 boxes": (_uniform(8127, 1, 30), 4096, {}),
     "8128 boxes": (_uniform(8128, 1, 30), 4096, {}),
     "8129 boxes": (_uniform(8129, 1, 30), 4096, {}),
@@ -155,6 +158,29 @@ def test_push_paths(name, block):
     assert ((c[~fit, 3] == -1) | (c[~fit, 3] > c[~fit, 2])).all()
     if js:
         assert np.array_equal(pl, want)
+
+
+# A size outside [0, 2^24] ends the call before the push, in the order of one
+# workgroup (up to 2048 boxes) and of several; the context goes on to pack.
+@pytest.mark.parametrize("n", [1, 2048, 2049, 20000])
+@pytest.mark.parametrize("bad", [-1.0, float("nan"), float("inf"), 16777218.0])
+def test_refused_sizes(n, bad):
+    fa = _fa()
+    sizes = _uniform(n, 1, 8).astype(np.float32)
+    ctx = fa.Context(1, 1, max_charts=65536, max_atlas=8192)
+    for at in (0, n - 1):
+        wrong = sizes.copy()
+        wrong[at, at % 2] = bad
+        print(f"[gpu] refused n={n} {bad} at {at}", flush=True)
+        _, meta, cand = ctx.pack_boxes(torch.as_tensor(wrong).cuda(), 2048)
+        m = fa.parse_meta(meta)
+        assert m["status"] == fa.FA_ERR_INVALID_ARG and m["num_charts"] == n
+        assert m["chosen_j"] == 0 and m["layout_width"] == 0
+        assert not cand.cpu().numpy().any()
+    sizes[0] = 16777216.0, 0.0
+    _, meta, _ = ctx.pack_boxes(torch.as_tensor(sizes).cuda(), 2048)
+    assert fa.parse_meta(meta)["status"] in (fa.FA_OK, fa.FA_ERR_NOFIT)
+    ctx.close()
 
 
 # The adjacency is built by ranges of vertices matched in LDS; meshes with a
