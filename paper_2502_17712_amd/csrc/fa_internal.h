@@ -435,8 +435,8 @@ hipError_t launch_reuse_flags(const float* pos, const int32_t* idx, int64_t T, c
                               const uint8_t* key_vis, const uint8_t* vis, uint8_t* flags,
                               unsigned long long* reused, const Work& w, hipStream_t st);
 hipError_t launch_visibility(const float* pos, const int32_t* idx, int64_t T, const VisParams& q,
-                             int32_t* occl, uint32_t* count, unsigned long long* depth,
-                             uint8_t* vis, hipStream_t st);
+                             int32_t* occl, unsigned long long* depth, uint8_t* vis,
+                             const Work& w, hipStream_t st);
 // Frame record without an occupancy map.
 hipError_t launch_meta(const FrameParams& p, const Work& w, fa_atlas_meta* meta,
                        hipStream_t st);

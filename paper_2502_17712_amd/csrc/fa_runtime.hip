@@ -92,10 +92,9 @@ struct fa_ctx {
   uint32_t* check_flag = nullptr;  // [2] device words of index validation and the adjacency
   void* spare = nullptr;           // slot 0's large-footprint queue, free between frames: the
   size_t spare_bytes = 0;          // adjacency of a new scene is built in it
-  // visibility pass scratch: occluder list [max_triangles] + its counter, and
-  // a depth buffer that grows to the largest grid asked for
+  // visibility pass scratch: occluder list [max_triangles], and a depth buffer
+  // that grows to the largest grid asked for
   int32_t* vis_list = nullptr;
-  uint32_t* vis_count = nullptr;
   unsigned long long* vis_depth = nullptr;
   int64_t vis_depth_cap = 0;
 };
@@ -277,7 +276,6 @@ void fa_destroy(fa_ctx* ctx) {
   if (ctx->bv_host) (void)hipHostFree(ctx->bv_host);
   if (ctx->ev_upload) (void)hipEventDestroy(ctx->ev_upload);
   if (ctx->vis_list) (void)hipFree(ctx->vis_list);
-  if (ctx->vis_count) (void)hipFree(ctx->vis_count);
   if (ctx->vis_depth) (void)hipFree(ctx->vis_depth);
   delete ctx;
 }
@@ -461,11 +459,9 @@ int fa_visibility(fa_ctx* ctx, const fa_mesh* mesh, const fa_camera* cam, const 
   if (rc) return rc;
   if (!ctx->vis_list) {
     const size_t T = (size_t)std::max<int64_t>(ctx->cfg.max_triangles, 1);
-    if (!make_room(ctx, 4 * T + 4, mesh->scene_key, st)) return FA_ERR_OUT_OF_MEMORY;
-    if (hipMalloc(&ctx->vis_list, 4 * T) != hipSuccess ||
-        hipMalloc(&ctx->vis_count, 4) != hipSuccess)
-      return FA_ERR_OUT_OF_MEMORY;
-    ctx->held_bytes += 4 * T + 4;
+    if (!make_room(ctx, 4 * T, mesh->scene_key, st)) return FA_ERR_OUT_OF_MEMORY;
+    if (hipMalloc(&ctx->vis_list, 4 * T) != hipSuccess) return FA_ERR_OUT_OF_MEMORY;
+    ctx->held_bytes += 4 * T;
   }
   const int64_t nd = (int64_t)q.Wc * q.Hc;
   if (nd > ctx->vis_depth_cap) {
@@ -480,7 +476,7 @@ int fa_visibility(fa_ctx* ctx, const fa_mesh* mesh, const fa_camera* cam, const 
     ctx->held_bytes += 8 * (size_t)nd;
   }
   if (launch_visibility(mesh->positions, mesh->indices, mesh->num_triangles, q, ctx->vis_list,
-                        ctx->vis_count, ctx->vis_depth, visible, st) != hipSuccess)
+                        ctx->vis_depth, visible, ctx->slots[0], st) != hipSuccess)
     return FA_ERR_DEVICE;
   return FA_OK;
 }

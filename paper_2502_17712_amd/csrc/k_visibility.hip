@@ -13,7 +13,6 @@
 //   marking    an occluder stays visible iff it covers no sample (it cannot be
 //              proven hidden) or some covered sample has z <= D + 1e-6;
 //              candidates crossing the near plane stay visible.
-// Small footprints are walked by their own lane, larger ones by their wave.
 #include <algorithm>
 #include <cmath>
 
@@ -22,9 +21,8 @@
 namespace fa {
 namespace {
 
-__device__ __forceinline__ double4 clip64(const VisParams& q, const float* __restrict__ pos,
-                                          int64_t v) {
-  const double x = pos[3 * v], y = pos[3 * v + 1], z = pos[3 * v + 2];
+__device__ __forceinline__ double4 clip64(const VisParams& q, const double (&p)[3]) {
+  const double x = p[0], y = p[1], z = p[2];
   double r[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -42,86 +40,10 @@ __device__ __forceinline__ double dval(unsigned long long k) {
   return __longlong_as_double((long long)b);
 }
 
-// the depth buffer and the occluder count are produced by atomics (possibly
-// on other XCDs): read them with agent-scope loads
+// the depth buffer is produced by atomics (possibly on other XCDs): read it
+// with agent-scope loads
 __device__ __forceinline__ unsigned long long dload(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__global__ void k_vis_clear(unsigned long long* __restrict__ depth, int64_t n,
-                            uint32_t* __restrict__ count) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *count = 0u;
-  const unsigned long long inf = 0xFFF0000000000000ull;  // dkey(+infinity)
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    depth[i] = inf;
-}
-
-// Candidates and occluders. Occluders are gathered per workgroup in LDS and
-// appended to the global list with one atomic per full buffer (a single
-// counter serializes at about 12 ns per atomic).
-constexpr int kCullBlock = 1024;
-constexpr int kCullBuf = 8192;
-
-__global__ __launch_bounds__(kCullBlock) void k_vis_cull(const float* __restrict__ pos,
-                                                         const int32_t* __restrict__ idx,
-                                                         int64_t T, VisParams q,
-                                                         uint8_t* __restrict__ vis,
-                                                         int32_t* __restrict__ occl,
-                                                         uint32_t* __restrict__ count) {
-  __shared__ int32_t buf[kCullBuf];
-  __shared__ uint32_t sh[kCullBlock / kWave];
-  __shared__ uint32_t gbase;
-  uint32_t fill = 0;  // entries in buf (block-uniform)
-  for (int64_t b0 = (int64_t)blockIdx.x * blockDim.x; b0 < T;
-       b0 += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t t = b0 + threadIdx.x;
-    bool occluder = false;
-    if (t < T) {
-      const int64_t i0 = idx[3 * t], i1 = idx[3 * t + 1], i2 = idx[3 * t + 2];
-      double a[3], b[3], d[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const double q0 = pos[3 * i0 + k], q1 = pos[3 * i1 + k], q2 = pos[3 * i2 + k];
-        a[k] = q1 - q0;
-        b[k] = q2 - q0;
-        d[k] = q.eye[k] - q0;
-      }
-      const double n0 = a[1] * b[2] - a[2] * b[1];
-      const double n1 = a[2] * b[0] - a[0] * b[2];
-      const double n2 = a[0] * b[1] - a[1] * b[0];
-      const bool front = ((n0 * d[0] + n1 * d[1]) + n2 * d[2]) > 0.0;
-      const double4 c0 = clip64(q, pos, i0), c1 = clip64(q, pos, i1), c2 = clip64(q, pos, i2);
-      const bool outside =
-          (c0.w + c0.x < 0.0 && c1.w + c1.x < 0.0 && c2.w + c2.x < 0.0) ||
-          (c0.w - c0.x < 0.0 && c1.w - c1.x < 0.0 && c2.w - c2.x < 0.0) ||
-          (c0.w + c0.y < 0.0 && c1.w + c1.y < 0.0 && c2.w + c2.y < 0.0) ||
-          (c0.w - c0.y < 0.0 && c1.w - c1.y < 0.0 && c2.w - c2.y < 0.0) ||
-          (c0.w + c0.z < 0.0 && c1.w + c1.z < 0.0 && c2.w + c2.z < 0.0) ||
-          (c0.w - c0.z < 0.0 && c1.w - c1.z < 0.0 && c2.w - c2.z < 0.0);
-      const bool cand = front && !outside;
-      vis[t] = cand ? 1 : 0;
-      occluder = q.coarse > 0 && cand && c0.w > q.near_w && c1.w > q.near_w && c2.w > q.near_w;
-    }
-    uint32_t tot;
-    const uint32_t one = occluder ? 1u : 0u;
-    const uint32_t at = block_incl_scan<uint32_t>(one, sh, &tot) - one;
-    if (fill + tot > (uint32_t)kCullBuf) {  // flush the full buffer first
-      if (threadIdx.x == 0) gbase = atomicAdd(count, fill);
-      __syncthreads();
-      for (uint32_t k = threadIdx.x; k < fill; k += blockDim.x) occl[gbase + k] = buf[k];
-      __syncthreads();
-      fill = 0;
-    }
-    if (occluder) buf[fill + at] = (int32_t)t;
-    fill += tot;
-  }
-  __syncthreads();
-  if (fill) {
-    if (threadIdx.x == 0) gbase = atomicAdd(count, fill);
-    __syncthreads();
-    for (uint32_t k = threadIdx.x; k < fill; k += blockDim.x) occl[gbase + k] = buf[k];
-  }
 }
 
 // Screen footprint of an occluder: vertices in coarse pixels (x right, y down)
@@ -131,14 +53,14 @@ struct Shot {
   int ix0, ix1, iy0, iy1;
 };
 
-__device__ __forceinline__ void shot_of(const VisParams& q, const float* __restrict__ pos,
-                                        const int32_t* __restrict__ idx, int64_t t, Shot& s) {
+// (from the clip-space vertices: the cull asks for the range alone)
+
+__device__ __forceinline__ void shot_of(const VisParams& q, const double4 (&c)[3], Shot& s) {
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
-    const double4 c = clip64(q, pos, idx[3 * t + e]);
-    s.X[e] = ((c.x / c.w) * 0.5 + 0.5) * (double)q.Wc;
-    s.Y[e] = (0.5 - (c.y / c.w) * 0.5) * (double)q.Hc;
-    s.Z[e] = c.z / c.w;
+    s.X[e] = ((c[e].x / c[e].w) * 0.5 + 0.5) * (double)q.Wc;
+    s.Y[e] = (0.5 - (c[e].y / c[e].w) * 0.5) * (double)q.Hc;
+    s.Z[e] = c[e].z / c[e].w;
   }
   const double xmin = fmin(fmin(s.X[0], s.X[1]), s.X[2]), xmax = fmax(fmax(s.X[0], s.X[1]), s.X[2]);
   const double ymin = fmin(fmin(s.Y[0], s.Y[1]), s.Y[2]), ymax = fmax(fmax(s.Y[0], s.Y[1]), s.Y[2]);
@@ -148,105 +70,220 @@ __device__ __forceinline__ void shot_of(const VisParams& q, const float* __restr
   s.iy1 = (int)fmin(fmax(floor(ymax - 0.5), -1.0), (double)(q.Hc - 1));
 }
 
-// depth of sample (px, py) if the footprint covers it
-__device__ __forceinline__ bool sample(const Shot& s, int px, int py, double& z) {
+// Candidates, the list of occluders that have a sample in their bounding box
+// (the others stay visible whatever the depth buffer holds), and the clearing
+// of the depth buffer.
+//
+// Bound by the chain of index and position loads with about 200 float64
+// instructions a triangle behind it: the next triangle's positions and the
+// indices after those are in flight while one is computed. Each workgroup owns
+// the chunks w, w + nseg, ... of kCullBlock triangles and a segment of the
+// list as long as they are, so there is no counter to share or clear.
+constexpr int kCullBlock = 512;
+constexpr int kCullSegs = 512;  // most segments (workgroups with triangles)
+static_assert(4 * kCullSegs <= 8 * kCountGrid, "the segments' counts use Work::partial");
+
+__host__ __device__ inline int cull_segments(int64_t T) {
+  const int64_t nc = (T + kCullBlock - 1) / kCullBlock;
+  return (int)(nc < kCullSegs ? nc : kCullSegs);
+}
+// First entry of segment `w`: the triangles of the segments before it.
+__device__ __forceinline__ int64_t segment_base(int64_t T, int nseg, int w) {
+  const int64_t nc = (T + kCullBlock - 1) / kCullBlock;
+  const int64_t each = nc / nseg, more = nc - each * nseg;
+  const int64_t chunks = each * w + (w < more ? w : more);
+  const int last = (int)((nc - 1) % nseg);  // owner of the last, perhaps partial, chunk
+  return chunks * kCullBlock - (w > last ? nc * kCullBlock - T : 0);
+}
+
+__global__ __launch_bounds__(kCullBlock) void k_vis_cull(
+    const float* __restrict__ pos, const int32_t* __restrict__ idx, int64_t T, int nseg,
+    VisParams q, uint8_t* __restrict__ vis, int32_t* __restrict__ occl,
+    uint32_t* __restrict__ counts, unsigned long long* __restrict__ depth, int64_t nd) {
+  __shared__ uint32_t fill;
+  const unsigned long long inf = 0xFFF0000000000000ull;  // dkey(+infinity)
+  for (int64_t i = (int64_t)blockIdx.x * kCullBlock + threadIdx.x; i < nd;
+       i += (int64_t)gridDim.x * kCullBlock)
+    depth[i] = inf;
+  if ((int)blockIdx.x >= nseg) return;
+  if (threadIdx.x == 0) fill = 0u;
+  __syncthreads();
+  int32_t* seg = occl + segment_base(T, nseg, blockIdx.x);
+  const int64_t step = (int64_t)nseg * kCullBlock;
+  const int64_t first = (int64_t)blockIdx.x * kCullBlock + threadIdx.x;
+  int32_t vn[3];      // indices of the triangle after next
+  float pn[3][3];     // positions of the next triangle
+#pragma unroll
+  for (int e = 0; e < 3; ++e) vn[e] = first < T ? idx[3 * first + e] : 0;
+#pragma unroll
+  for (int e = 0; e < 3; ++e)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) pn[e][k] = first < T ? pos[3 * (int64_t)vn[e] + k] : 0.0f;
+#pragma unroll
+  for (int e = 0; e < 3; ++e) vn[e] = first + step < T ? idx[3 * (first + step) + e] : 0;
+  // (whole waves: the appending below counts over the wave)
+  for (int64_t t = first; t - lane_id() < T; t += step) {
+    double p[3][3];
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) p[e][k] = pn[e][k];
+    const int64_t t1 = t + step, t2 = t1 + step;
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) pn[e][k] = t1 < T ? pos[3 * (int64_t)vn[e] + k] : 0.0f;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) vn[e] = t2 < T ? idx[3 * t2 + e] : 0;
+    double a[3], b[3], d[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      a[k] = p[1][k] - p[0][k];
+      b[k] = p[2][k] - p[0][k];
+      d[k] = q.eye[k] - p[0][k];
+    }
+    const double n0 = a[1] * b[2] - a[2] * b[1];
+    const double n1 = a[2] * b[0] - a[0] * b[2];
+    const double n2 = a[0] * b[1] - a[1] * b[0];
+    bool cand = t < T && ((n0 * d[0] + n1 * d[1]) + n2 * d[2]) > 0.0;
+    bool listed = false;
+    if (cand) {
+      const double4 c[3] = {clip64(q, p[0]), clip64(q, p[1]), clip64(q, p[2])};
+      const bool outside =
+          (c[0].w + c[0].x < 0.0 && c[1].w + c[1].x < 0.0 && c[2].w + c[2].x < 0.0) ||
+          (c[0].w - c[0].x < 0.0 && c[1].w - c[1].x < 0.0 && c[2].w - c[2].x < 0.0) ||
+          (c[0].w + c[0].y < 0.0 && c[1].w + c[1].y < 0.0 && c[2].w + c[2].y < 0.0) ||
+          (c[0].w - c[0].y < 0.0 && c[1].w - c[1].y < 0.0 && c[2].w - c[2].y < 0.0) ||
+          (c[0].w + c[0].z < 0.0 && c[1].w + c[1].z < 0.0 && c[2].w + c[2].z < 0.0) ||
+          (c[0].w - c[0].z < 0.0 && c[1].w - c[1].z < 0.0 && c[2].w - c[2].z < 0.0);
+      cand = !outside;
+      if (q.coarse > 0 && cand && c[0].w > q.near_w && c[1].w > q.near_w && c[2].w > q.near_w) {
+        Shot s;
+        shot_of(q, c, s);
+        listed = s.ix0 <= s.ix1 && s.iy0 <= s.iy1;
+      }
+    }
+    if (t < T) vis[t] = cand ? 1 : 0;
+    const unsigned long long m = __ballot(listed);
+    if (m) {
+      uint32_t at = 0;
+      if (lane_id() == 0) at = atomicAdd(&fill, (uint32_t)__popcll(m));
+      at = __builtin_amdgcn_readfirstlane(at);
+      if (listed) seg[at + (uint32_t)__popcll(m & lanes_below())] = (int32_t)t;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) counts[blockIdx.x] = fill;
+}
+
+// Depth pre-pass and (MARK) the test against it. A workgroup sets up
+// kVisBatch listed occluders at a time and its threads share the samples of
+// their bounding boxes, whichever triangle they belong to: neighbours in the
+// list are neighbours on the screen, and with a lane or a wave per triangle a
+// few waves under the camera had most of the samples (2.2M triangles: 569k
+// occluders, 113k of them with samples, 325k samples).
+constexpr int kVisBatch = kWave;
+constexpr int kVisGrid = 2048;  // most workgroups: what the chip holds at once
+
+// depth of sample (px, py) if footprint `o` covers it
+__device__ __forceinline__ bool sample(const double (*X)[kVisBatch], const double (*Y)[kVisBatch],
+                                       const double (*Z)[kVisBatch], int o, int px, int py,
+                                       double& z) {
   const double cx = (double)px + 0.5, cy = (double)py + 0.5;
-  const double e0 = (s.X[2] - s.X[1]) * (cy - s.Y[1]) - (s.Y[2] - s.Y[1]) * (cx - s.X[1]);
-  const double e1 = (s.X[0] - s.X[2]) * (cy - s.Y[2]) - (s.Y[0] - s.Y[2]) * (cx - s.X[2]);
-  const double e2 = (s.X[1] - s.X[0]) * (cy - s.Y[0]) - (s.Y[1] - s.Y[0]) * (cx - s.X[0]);
+  const double e0 = (X[2][o] - X[1][o]) * (cy - Y[1][o]) - (Y[2][o] - Y[1][o]) * (cx - X[1][o]);
+  const double e1 = (X[0][o] - X[2][o]) * (cy - Y[2][o]) - (Y[0][o] - Y[2][o]) * (cx - X[2][o]);
+  const double e2 = (X[1][o] - X[0][o]) * (cy - Y[0][o]) - (Y[1][o] - Y[0][o]) * (cx - X[0][o]);
   const double area = (e0 + e1) + e2;
   const bool in = area != 0.0 &&
                   ((e0 >= 0.0 && e1 >= 0.0 && e2 >= 0.0) || (e0 <= 0.0 && e1 <= 0.0 && e2 <= 0.0));
   if (!in) return false;
-  z = ((e0 * s.Z[0] + e1 * s.Z[1]) + e2 * s.Z[2]) / area;
+  z = ((e0 * Z[0][o] + e1 * Z[1][o]) + e2 * Z[2][o]) / area;
   return true;
 }
 
-__device__ __forceinline__ double rl_d(double v, int lane) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, lane);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-__device__ __forceinline__ Shot rl_shot(const Shot& s, int lane) {
-  Shot r;
-#pragma unroll
-  for (int e = 0; e < 3; ++e) {
-    r.X[e] = rl_d(s.X[e], lane);
-    r.Y[e] = rl_d(s.Y[e], lane);
-    r.Z[e] = rl_d(s.Z[e], lane);
-  }
-  r.ix0 = __builtin_amdgcn_readlane(s.ix0, lane);
-  r.ix1 = __builtin_amdgcn_readlane(s.ix1, lane);
-  r.iy0 = __builtin_amdgcn_readlane(s.iy0, lane);
-  r.iy1 = __builtin_amdgcn_readlane(s.iy1, lane);
-  return r;
-}
-
-constexpr int kVisLaneSamples = 32;  // larger footprints are walked by the wave
-
 template <bool MARK>
 __global__ __launch_bounds__(kBlock) void k_vis_depth(const float* __restrict__ pos,
-                                                      const int32_t* __restrict__ idx,
-                                                      VisParams q,
+                                                      const int32_t* __restrict__ idx, int64_t T,
+                                                      int nseg, VisParams q,
                                                       const int32_t* __restrict__ occl,
-                                                      const uint32_t* __restrict__ count,
+                                                      const uint32_t* __restrict__ counts,
                                                       unsigned long long* __restrict__ depth,
                                                       uint8_t* __restrict__ vis) {
-  const int n_occ = (int)__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int lane = lane_id();
-  for (int b0 = blockIdx.x * blockDim.x; b0 < n_occ; b0 += gridDim.x * blockDim.x) {
-    const int i = b0 + threadIdx.x;
-    Shot s;
-    int n = 0, nx = 1;
-    int t = -1;
-    if (i < n_occ) {
-      t = occl[i];
-      shot_of(q, pos, idx, t, s);
-      nx = max(s.ix1 - s.ix0 + 1, 0);
-      n = nx * max(s.iy1 - s.iy0 + 1, 0);
-    }
-    const bool big = n > kVisLaneSamples;
-    bool any = false, pass = false;
-    if (!big) {
-      for (int k = 0; k < n && !pass; ++k) {
-        const int px = s.ix0 + k % nx, py = s.iy0 + k / nx;
-        double z;
-        if (!sample(s, px, py, z)) continue;
-        const int64_t pix = (int64_t)py * q.Wc + px;
-        if (MARK) {
-          any = true;
-          if (z <= dval(dload(&depth[pix])) + 1e-6) pass = true;
-        } else {
-          atomicMin(&depth[pix], dkey(z));
+  static_assert(kCullSegs == 2 * kBlock, "two segments a thread");
+  __shared__ uint32_t seg0[kCullSegs];  // listed occluders before each segment
+  __shared__ uint32_t sh[kBlock / kWave];
+  __shared__ double X[3][kVisBatch], Y[3][kVisBatch], Z[3][kVisBatch];
+  __shared__ int ix0[kVisBatch], iy0[kVisBatch], nx[kVisBatch];
+  __shared__ unsigned long long end[kVisBatch];  // samples of the batch up to and with each
+  __shared__ uint32_t seen[kVisBatch];           // 1: covers a sample, 3: ... and passes at one
+  const int tid = threadIdx.x, lane = lane_id();
+  uint32_t n_occ;
+  {
+    const int g = 2 * tid;
+    const uint32_t a = g < nseg ? counts[g] : 0u, b = g + 1 < nseg ? counts[g + 1] : 0u;
+    const uint32_t incl = block_incl_scan<uint32_t>(a + b, sh, &n_occ);
+    seg0[g] = incl - b - a;
+    seg0[g + 1] = incl - b;
+    __syncthreads();
+  }
+  for (uint32_t b0 = blockIdx.x * kVisBatch; b0 < n_occ; b0 += gridDim.x * kVisBatch) {
+    int32_t t = -1;
+    if (tid < kVisBatch) {  // (the first wave)
+      unsigned long long n = 0;
+      const uint32_t i = b0 + lane;
+      if (i < n_occ) {
+        int lo = 0, hi = nseg;  // last segment that starts at or before i
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (seg0[mid] <= i) lo = mid; else hi = mid;
         }
-      }
-    }
-    for (unsigned long long bm = __ballot(big); bm; bm &= bm - 1) {
-      const int src = __ffsll((long long)bm) - 1;
-      const Shot w = rl_shot(s, src);
-      const int wnx = w.ix1 - w.ix0 + 1, wn = wnx * (w.iy1 - w.iy0 + 1);
-      bool wany = false, wpass = false;
-      for (int k0 = 0; k0 < wn; k0 += kWave) {
-        const int k = k0 + lane;
-        double z;
-        if (k < wn && sample(w, w.ix0 + k % wnx, w.iy0 + k / wnx, z)) {
-          const int64_t pix = (int64_t)(w.iy0 + k / wnx) * q.Wc + (w.ix0 + k % wnx);
-          if (MARK) {
-            wany = true;
-            if (z <= dval(dload(&depth[pix])) + 1e-6) wpass = true;
-          } else {
-            atomicMin(&depth[pix], dkey(z));
-          }
+        t = occl[segment_base(T, nseg, lo) + (i - seg0[lo])];
+        double p[3][3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          const int64_t v = idx[3 * (int64_t)t + e];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) p[e][k] = pos[3 * v + k];
         }
-        if (MARK && __ballot(wpass)) break;
+        const double4 c[3] = {clip64(q, p[0]), clip64(q, p[1]), clip64(q, p[2])};
+        Shot s;
+        shot_of(q, c, s);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          X[e][lane] = s.X[e];
+          Y[e][lane] = s.Y[e];
+          Z[e][lane] = s.Z[e];
+        }
+        const int w = max(s.ix1 - s.ix0 + 1, 0);
+        ix0[lane] = s.ix0;
+        iy0[lane] = s.iy0;
+        nx[lane] = w;
+        n = (unsigned long long)w * max(s.iy1 - s.iy0 + 1, 0);
       }
-      if (MARK) {
-        const bool ga = __ballot(wany) != 0, gp = __ballot(wpass) != 0;
-        if (lane == src) { any = ga; pass = gp; }
-      }
+      end[lane] = wave_incl_scan<unsigned long long>(n);
+      if (MARK) seen[lane] = 0u;
     }
-    if (MARK && t >= 0) vis[t] = (!any || pass) ? 1 : 0;
+    __syncthreads();
+    const unsigned long long all = end[kVisBatch - 1];
+    for (unsigned long long s = tid; s < all; s += kBlock) {
+      int o = 0;  // first occluder whose samples end after s
+#pragma unroll
+      for (int h = kVisBatch / 2; h > 0; h >>= 1)
+        if (end[o + h - 1] <= s) o += h;
+      if (MARK && seen[o] == 3u) continue;
+      const uint32_t k = (uint32_t)(s - (o ? end[o - 1] : 0ull));
+      const uint32_t row = k / (uint32_t)nx[o];
+      const int px = ix0[o] + (int)(k - row * (uint32_t)nx[o]), py = iy0[o] + (int)row;
+      double z;
+      if (!sample(X, Y, Z, o, px, py, z)) continue;
+      const int64_t pix = (int64_t)py * q.Wc + px;
+      if (MARK)
+        atomicOr(&seen[o], z <= dval(dload(&depth[pix])) + 1e-6 ? 3u : 1u);
+      else
+        atomicMin(&depth[pix], dkey(z));
+    }
+    __syncthreads();
+    if (MARK && t >= 0) vis[t] = seen[lane] != 1u ? 1 : 0;
   }
 }
 
@@ -356,18 +393,21 @@ hipError_t launch_reuse_flags(const float* pos, const int32_t* idx, int64_t T, c
 }
 
 hipError_t launch_visibility(const float* pos, const int32_t* idx, int64_t T, const VisParams& q,
-                             int32_t* occl, uint32_t* count, unsigned long long* depth,
-                             uint8_t* vis, hipStream_t st) {
+                             int32_t* occl, unsigned long long* depth, uint8_t* vis,
+                             const Work& w, hipStream_t st) {
+  if (T == 0) return hipSuccess;
   const int64_t nd = q.coarse > 0 ? (int64_t)q.Wc * q.Hc : 0;
-  const unsigned cg = (unsigned)std::max<int64_t>(1, std::min<int64_t>((nd + kBlock - 1) / kBlock, 1024));
-  k_vis_clear<<<cg, kBlock, 0, st>>>(depth, nd, count);
-  if (T == 0) return hipGetLastError();
-  const unsigned g = (unsigned)std::min<int64_t>((T + kCullBlock - 1) / kCullBlock, 256);
-  k_vis_cull<<<g, kCullBlock, 0, st>>>(pos, idx, T, q, vis, occl, count);
+  uint32_t* counts = reinterpret_cast<uint32_t*>(w.partial);
+  const int nseg = cull_segments(T);
+  // (a depth buffer of many samples is cleared by more workgroups than few triangles need)
+  const int64_t clear = std::min<int64_t>(nd / (8 * kCullBlock), 1024);
+  const unsigned g = (unsigned)std::max<int64_t>(nseg, clear);
+  k_vis_cull<<<g, kCullBlock, 0, st>>>(pos, idx, T, nseg, q, vis, occl, counts, depth, nd);
   if (q.coarse > 0) {
-    const unsigned og = visible_grid(T);
-    k_vis_depth<false><<<og, kBlock, 0, st>>>(pos, idx, q, occl, count, depth, vis);
-    k_vis_depth<true><<<og, kBlock, 0, st>>>(pos, idx, q, occl, count, depth, vis);
+    const unsigned og =
+        (unsigned)std::min<int64_t>((T + kVisBatch - 1) / kVisBatch, kVisGrid);
+    k_vis_depth<false><<<og, kBlock, 0, st>>>(pos, idx, T, nseg, q, occl, counts, depth, vis);
+    k_vis_depth<true><<<og, kBlock, 0, st>>>(pos, idx, T, nseg, q, occl, counts, depth, vis);
   }
   return hipGetLastError();
 }

@@ -181,6 +181,31 @@ def test_serve_device_visibility_equals_precomputed():
         assert a["meta"] == b["meta"]
 
 
+# Occluders are listed in up to 512 segments of 512 triangles each turn and set
+# up 64 at a time: soups around those sizes, with triangles that cover no
+# sample, a few, or the whole depth buffer, either way round.
+@pytest.mark.parametrize("T", [1, 63, 64, 65, 511, 513, 40000, 262143, 262145, 263169])
+@pytest.mark.parametrize("coarse", [0, 4])
+def test_soup_sizes(T, coarse):
+    fa = _fa()
+    rng = np.random.default_rng(T)
+    z = -rng.uniform(1.0, 20.0, T)
+    size = np.where(rng.uniform(size=T) < 0.02, 0.3, 0.004) * -z
+    size[rng.integers(0, T, 3)] = 60.0
+    centre = np.stack([rng.uniform(-1, 1, T) * -z, rng.uniform(-0.6, 0.6, T) * -z, z], 1)
+    p = centre[:, None, :] + rng.uniform(-1, 1, (T, 3, 3)) * size[:, None, None] * [1, 1, 0.02]
+    pos = p.reshape(-1, 3).astype(np.float32)
+    tri = np.arange(3 * T, dtype=np.int32).reshape(T, 3)
+    cam = _camera(1280, 720)
+    print(f"[gpu] visibility soup T={T} coarse={coarse}", flush=True)
+    ctx = fa.Context(T, 3 * T, max_charts=16, max_atlas=16)
+    g = ctx.visibility(fa.Mesh(pos, tri, 1), cam.view_proj, 1280, 720, cam.eye, cam.near,
+                       coarse).cpu().numpy()
+    ctx.close()
+    o = oracle.visibility(pos, tri, cam.view_proj, cam.eye, cam.near, 1280, 720, coarse)
+    assert np.array_equal(g, o)
+
+
 @pytest.mark.parametrize("key,frames", [(10, (11, 14, 19)), (0, (0, 3))])
 def test_reuse_flags(key, frames):
     kf = scenes.orbit_frame(key)
