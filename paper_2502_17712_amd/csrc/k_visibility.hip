@@ -76,7 +76,9 @@ __device__ __forceinline__ void shot_of(const VisParams& q, const double4 (&c)[3
 //
 // Bound by the chain of index and position loads with about 200 float64
 // instructions a triangle behind it: the next triangle's positions and the
-// indices after those are in flight while one is computed. Each workgroup owns
+// indices after those are in flight while one is computed, as whole 12-byte
+// loads (nine single words a triangle kept the address units busy: 28 us on
+// 2.2M triangles, 20 so). Each workgroup owns
 // the chunks w, w + nseg, ... of kCullBlock triangles and a segment of the
 // list as long as they are, so there is no counter to share or clear.
 constexpr int kCullBlock = 512;
@@ -111,30 +113,21 @@ __global__ __launch_bounds__(kCullBlock) void k_vis_cull(
   int32_t* seg = occl + segment_base(T, nseg, blockIdx.x);
   const int64_t step = (int64_t)nseg * kCullBlock;
   const int64_t first = (int64_t)blockIdx.x * kCullBlock + threadIdx.x;
-  int32_t vn[3];      // indices of the triangle after next
-  float pn[3][3];     // positions of the next triangle
-#pragma unroll
-  for (int e = 0; e < 3; ++e) vn[e] = first < T ? idx[3 * first + e] : 0;
-#pragma unroll
-  for (int e = 0; e < 3; ++e)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) pn[e][k] = first < T ? pos[3 * (int64_t)vn[e] + k] : 0.0f;
-#pragma unroll
-  for (int e = 0; e < 3; ++e) vn[e] = first + step < T ? idx[3 * (first + step) + e] : 0;
+  const float3* pos3 = reinterpret_cast<const float3*>(pos);
+  const int3* idx3 = reinterpret_cast<const int3*>(idx);
+  // (beyond the end: the last triangle, so that no load depends on a branch)
+  int3 vn = idx3[min(first, T - 1)];  // indices of the triangle after next
+  float3 pn[3] = {pos3[vn.x], pos3[vn.y], pos3[vn.z]};  // positions of the next triangle
+  vn = idx3[min(first + step, T - 1)];
   // (whole waves: the appending below counts over the wave)
   for (int64_t t = first; t - lane_id() < T; t += step) {
-    double p[3][3];
-#pragma unroll
-    for (int e = 0; e < 3; ++e)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) p[e][k] = pn[e][k];
-    const int64_t t1 = t + step, t2 = t1 + step;
-#pragma unroll
-    for (int e = 0; e < 3; ++e)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) pn[e][k] = t1 < T ? pos[3 * (int64_t)vn[e] + k] : 0.0f;
-#pragma unroll
-    for (int e = 0; e < 3; ++e) vn[e] = t2 < T ? idx[3 * t2 + e] : 0;
+    const double p[3][3] = {{pn[0].x, pn[0].y, pn[0].z},
+                            {pn[1].x, pn[1].y, pn[1].z},
+                            {pn[2].x, pn[2].y, pn[2].z}};
+    pn[0] = pos3[vn.x];
+    pn[1] = pos3[vn.y];
+    pn[2] = pos3[vn.z];
+    vn = idx3[min(t + 2 * step, T - 1)];
     double a[3], b[3], d[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -176,14 +169,19 @@ __global__ __launch_bounds__(kCullBlock) void k_vis_cull(
   if (threadIdx.x == 0) counts[blockIdx.x] = fill;
 }
 
-// Depth pre-pass and (MARK) the test against it. A workgroup sets up
-// kVisBatch listed occluders at a time and its threads share the samples of
-// their bounding boxes, whichever triangle they belong to: neighbours in the
-// list are neighbours on the screen, and with a lane or a wave per triangle a
-// few waves under the camera had most of the samples (2.2M triangles: 569k
-// occluders, 113k of them with samples, 325k samples).
+// Depth pre-pass and (MARK) the test against it. A workgroup sets up a batch
+// of up to kVisBatch listed occluders and its threads share the samples of
+// their bounding boxes, whichever triangle they belong to. Neighbours in the
+// list are neighbours on the screen, and those under the camera have most of
+// the samples (2.2M triangles: 569k occluders, 113k of them with samples, 325k
+// samples), so a batch takes runs of kVisRun from all over the list; the work
+// is then even and the passes wait for loads. The two passes on that scene,
+// with the cull and the reuse flags: 133 us with a lane or a wave per occluder,
+// 71 with consecutive batches of 64, 61 of 16, 45.2 in runs of 4 (runs of 8
+// 47.2, single ones 46.5; 8 or 4 workgroups per CU 47, 3 52).
 constexpr int kVisBatch = kWave;
-constexpr int kVisGrid = 2048;  // most workgroups: what the chip holds at once
+constexpr int kVisRun = 4;
+constexpr int kVisGrid = 6 * 256;  // most workgroups: what the chip holds at once
 
 // depth of sample (px, py) if footprint `o` covers it
 __device__ __forceinline__ bool sample(const double (*X)[kVisBatch], const double (*Y)[kVisBatch],
@@ -202,7 +200,7 @@ __device__ __forceinline__ bool sample(const double (*X)[kVisBatch], const doubl
 }
 
 template <bool MARK>
-__global__ __launch_bounds__(kBlock) void k_vis_depth(const float* __restrict__ pos,
+__global__ __launch_bounds__(kBlock, 6) void k_vis_depth(const float* __restrict__ pos,
                                                       const int32_t* __restrict__ idx, int64_t T,
                                                       int nseg, VisParams q,
                                                       const int32_t* __restrict__ occl,
@@ -226,11 +224,14 @@ __global__ __launch_bounds__(kBlock) void k_vis_depth(const float* __restrict__ 
     seg0[g + 1] = incl - b;
     __syncthreads();
   }
-  for (uint32_t b0 = blockIdx.x * kVisBatch; b0 < n_occ; b0 += gridDim.x * kVisBatch) {
+  // one batch a workgroup, smaller ones if that makes more workgroups
+  const uint32_t batches = max((n_occ + kVisBatch - 1) / kVisBatch,
+                               min(gridDim.x, (n_occ + kVisRun - 1) / kVisRun));
+  for (uint32_t b = blockIdx.x; b < batches; b += gridDim.x) {
     int32_t t = -1;
     if (tid < kVisBatch) {  // (the first wave)
       unsigned long long n = 0;
-      const uint32_t i = b0 + lane;
+      const uint32_t i = ((lane / kVisRun) * batches + b) * kVisRun + lane % kVisRun;
       if (i < n_occ) {
         int lo = 0, hi = nseg;  // last segment that starts at or before i
         while (hi - lo > 1) {
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(kBlock) void k_vis_depth(const float* __restrict__ 
 // ticket is drawn) and sets the ticket back to 0. One atomic per wave on a
 // single counter, which serializes at about 3 ns each, took 102 us on a
 // 2.2M-triangle scene and its clearing launch 5; the count per workgroup takes
-// 18 us in all.
+// 18 us in all, and 12 with indices and positions in 12-byte loads.
 constexpr int kReuseBlock = 1024;
 constexpr int kReusePer = 4;
 constexpr int kReuseGrid = 256;  // workgroups
@@ -313,12 +314,14 @@ __global__ __launch_bounds__(kReuseBlock) void k_reuse_flags(
   __shared__ uint32_t sh[kReuseBlock / kWave];
   __shared__ uint32_t last;
   uint32_t count = 0;
+  const float3* pos3 = reinterpret_cast<const float3*>(pos);
+  const int3* idx3 = reinterpret_cast<const int3*>(idx);
   const int64_t step = (int64_t)gridDim.x * kReuseBlock;
   for (int64_t t0 = (int64_t)blockIdx.x * kReuseBlock + threadIdx.x; t0 < T;
        t0 += kReusePer * step) {
     bool on[kReusePer], key[kReusePer];
-    int32_t vi[kReusePer][3];
-    float q[kReusePer][3][3];
+    int3 vi[kReusePer];
+    float3 q[kReusePer][3];
 #pragma unroll
     for (int k = 0; k < kReusePer; ++k) {
       const int64_t t = t0 + k * step;
@@ -326,15 +329,19 @@ __global__ __launch_bounds__(kReuseBlock) void k_reuse_flags(
       key[k] = t < T && key_vis[t] != 0;
     }
 #pragma unroll
-    for (int k = 0; k < kReusePer; ++k)
+    for (int k = 0; k < kReusePer; ++k) {
+      vi[k] = make_int3(0, 0, 0);
+      if (on[k]) vi[k] = idx3[t0 + k * step];
+    }
 #pragma unroll
-      for (int e = 0; e < 3; ++e) vi[k][e] = on[k] ? idx[3 * (t0 + k * step) + e] : 0;
-#pragma unroll
-    for (int k = 0; k < kReusePer; ++k)
-#pragma unroll
-      for (int e = 0; e < 3; ++e)
-#pragma unroll
-        for (int i = 0; i < 3; ++i) q[k][e][i] = on[k] ? pos[3 * (int64_t)vi[k][e] + i] : 0.0f;
+    for (int k = 0; k < kReusePer; ++k) {
+      q[k][0] = q[k][1] = q[k][2] = make_float3(0.0f, 0.0f, 0.0f);
+      if (on[k]) {
+        q[k][0] = pos3[vi[k].x];
+        q[k][1] = pos3[vi[k].y];
+        q[k][2] = pos3[vi[k].z];
+      }
+    }
 #pragma unroll
     for (int k = 0; k < kReusePer; ++k) {
       const int64_t t = t0 + k * step;
@@ -345,9 +352,9 @@ __global__ __launch_bounds__(kReuseBlock) void k_reuse_flags(
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           if (i == 2) continue;  // z is not needed
-          float acc = kc.M[4 * i] * q[k][e][0];
-          acc = acc + kc.M[4 * i + 1] * q[k][e][1];
-          acc = acc + kc.M[4 * i + 2] * q[k][e][2];
+          float acc = kc.M[4 * i] * q[k][e].x;
+          acc = acc + kc.M[4 * i + 1] * q[k][e].y;
+          acc = acc + kc.M[4 * i + 2] * q[k][e].z;
           r[i] = acc + kc.M[4 * i + 3];
         }
         if (fmaxf(fabsf(r[0]), fabsf(r[1])) >= r[3]) partly = true;
@@ -405,7 +412,7 @@ hipError_t launch_visibility(const float* pos, const int32_t* idx, int64_t T, co
   k_vis_cull<<<g, kCullBlock, 0, st>>>(pos, idx, T, nseg, q, vis, occl, counts, depth, nd);
   if (q.coarse > 0) {
     const unsigned og =
-        (unsigned)std::min<int64_t>((T + kVisBatch - 1) / kVisBatch, kVisGrid);
+        (unsigned)std::min<int64_t>((T + kVisRun - 1) / kVisRun, kVisGrid);
     k_vis_depth<false><<<og, kBlock, 0, st>>>(pos, idx, T, nseg, q, occl, counts, depth, vis);
     k_vis_depth<true><<<og, kBlock, 0, st>>>(pos, idx, T, nseg, q, occl, counts, depth, vis);
   }
