@@ -139,6 +139,13 @@ struct Work {
 // ---------------------------------------------------------------------------
 // small device helpers
 // ---------------------------------------------------------------------------
+// A pointer read from memory is generic to the compiler: its loads are flat
+// ones, which count as LDS accesses too and are waited for with them. The
+// batched kernels read their buffers from BatchView, all in global memory.
+template <typename T>
+__device__ __forceinline__ T* in_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+}
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ __forceinline__ unsigned long long lanes_below() {
   return (1ull << lane_id()) - 1ull;

@@ -1296,53 +1296,53 @@ inline unsigned grid_for(int64_t n, int block) { return (unsigned)((n + block - 
 __global__ void k_prologue_b(const BatchView* __restrict__ bv, int64_t V, const int32_t* __restrict__ nbr, int64_t T,
                              unsigned vblocks) {
   const BatchView& v = bv[blockIdx.y];
-  k_prologue_body(V, v.w.vmin, v.cov, v.visible, nbr, T, v.w.parent, v.cot,
-                  v.w.tile_vis, 0, vblocks, v.w.state, v.w.big_counter);
+  k_prologue_body(V, in_global(v.w.vmin), in_global(v.cov), in_global(v.visible), nbr, T, in_global(v.w.parent), in_global(v.cot),
+                  in_global(v.w.tile_vis), 0, vblocks, in_global(v.w.state), in_global(v.w.big_counter));
 }
 __global__ __launch_bounds__(1024) void k_tile_scan_b(const BatchView* __restrict__ bv,
                                                       unsigned tiles) {
-  k_tile_scan_body(bv[blockIdx.y].w.tile_vis, tiles);
+  k_tile_scan_body(in_global(bv[blockIdx.y].w.tile_vis), tiles);
 }
 __global__ void k_vis_compact_b(const BatchView* __restrict__ bv, int64_t T) {
   const BatchView& v = bv[blockIdx.y];
-  k_vis_compact_body(v.visible, T, v.w.tile_vis, v.w.vlist, v.w.state, true);
+  k_vis_compact_body(in_global(v.visible), T, in_global(v.w.tile_vis), in_global(v.w.vlist), in_global(v.w.state), true);
 }
 __global__ __launch_bounds__(1024) void k_uf_local_vertex_b(const BatchView* __restrict__ bv,
                                                             const int32_t* __restrict__ idx) {
   const BatchView& v = bv[blockIdx.y];
-  k_uf_local_vertex_body<2048, 1024, 4096>(idx, v.w.vlist, v.w.parent, v.w.vmin, v.w.state,
-                                           reinterpret_cast<int4*>(v.occ),
+  k_uf_local_vertex_body<2048, 1024, 4096>(idx, in_global(v.w.vlist), in_global(v.w.parent), in_global(v.w.vmin), in_global(v.w.state),
+                                           reinterpret_cast<int4*>(in_global(v.occ)),
                                            (int64_t)v.p.omega * v.p.omega / 4);
 }
 __global__ __launch_bounds__(kHookThreads) void k_uf_vertex_hook_b(const BatchView* __restrict__ bv,
                                    const int32_t* __restrict__ idx) {
   const BatchView& v = bv[blockIdx.y];
-  k_uf_vertex_hook_body(idx, v.w.vlist, v.w.parent, v.w.vmin, v.w.state);
+  k_uf_vertex_hook_body(idx, in_global(v.w.vlist), in_global(v.w.parent), in_global(v.w.vmin), in_global(v.w.state));
 }
 __global__ void k_uf_flatten_count_b(const BatchView* __restrict__ bv) {
   const BatchView& v = bv[blockIdx.y];
-  k_uf_flatten_count_body(v.w.vlist, v.w.parent, v.w.tile_count, v.w.state);
+  k_uf_flatten_count_body(in_global(v.w.vlist), in_global(v.w.parent), in_global(v.w.tile_count), in_global(v.w.state));
 }
 __global__ void k_assign_roots_b(const BatchView* __restrict__ bv) {
   const BatchView& v = bv[blockIdx.y];
-  k_assign_roots_body(v.w.vlist, v.w.parent, v.w.tile_count, v.cot, v.charts, v.w.accum,
-                      v.p.max_charts, v.w.state);
+  k_assign_roots_body(in_global(v.w.vlist), in_global(v.w.parent), in_global(v.w.tile_count), in_global(v.cot), in_global(v.charts), in_global(v.w.accum),
+                      v.p.max_charts, in_global(v.w.state));
 }
 __global__ __launch_bounds__(kGatherBlock) void k_gather_boxes_b(const BatchView* __restrict__ bv,
                                                            const int32_t* __restrict__ idx,
                                                            bool labelled) {
   const BatchView& v = bv[blockIdx.y];
-  k_gather_boxes_body(v.w.vlist, idx, v.w.parent, v.w.pos, v.cot, v.cov, v.w.accum, v.p,
-                      v.w.state, nullptr, 0, labelled);
+  k_gather_boxes_body(in_global(v.w.vlist), idx, in_global(v.w.parent), in_global(v.w.pos), in_global(v.cot), in_global(v.cov), in_global(v.w.accum), v.p,
+                      in_global(v.w.state), nullptr, 0, labelled);
 }
 template <int PER>
 __global__ __launch_bounds__(kFrontThreads) void k_front_b(const BatchView* __restrict__ bv,
                                                            const int32_t* __restrict__ idx, int T,
                                                            int V) {
   const BatchView& v = bv[blockIdx.y];
-  k_front_body<PER>(v.visible, idx, T, V, v.cov, v.cot, v.w.vlist, v.charts, v.w.accum,
-                    v.p.max_charts, v.w.state, v.w.big_counter, false,
-                    reinterpret_cast<int4*>(v.occ), (int64_t)v.p.omega * v.p.omega / 4);
+  k_front_body<PER>(in_global(v.visible), idx, T, V, in_global(v.cov), in_global(v.cot), in_global(v.w.vlist), in_global(v.charts), in_global(v.w.accum),
+                    v.p.max_charts, in_global(v.w.state), in_global(v.w.big_counter), false,
+                    reinterpret_cast<int4*>(in_global(v.occ)), (int64_t)v.p.omega * v.p.omega / 4);
 }
 
 }  // namespace

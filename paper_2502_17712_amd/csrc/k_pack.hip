@@ -1305,14 +1305,14 @@ template <int NT>
 __global__ __launch_bounds__(NT) void k_pack_box_b(const BatchView* __restrict__ bv,
                                                    int64_t stride) {
   const BatchView& v = bv[blockIdx.y];
-  k_pack_box_body<NT>(v.w.sorted_wh, v.w.state, v.p, v.w.cand_x, v.w.cand_ab, v.w.cand_y,
-                      v.w.cand_tab, stride, box_kcap(v.p.omega));
+  k_pack_box_body<NT>(in_global(v.w.sorted_wh), in_global(v.w.state), v.p, in_global(v.w.cand_x), in_global(v.w.cand_ab), in_global(v.w.cand_y),
+                      in_global(v.w.cand_tab), stride, box_kcap(v.p.omega));
 }
 __global__ __launch_bounds__(kBlock) void k_select_place_b(const BatchView* __restrict__ bv,
                                                            int64_t stride) {
   const BatchView& v = bv[blockIdx.y];
-  k_select_place_body(v.p, v.w.cand_tab, v.w.state, v.cand_out, v.w.vals_a, v.w.cand_x,
-                      v.w.cand_ab, v.w.cand_y, stride, v.charts, v.w.chart_tex);
+  k_select_place_body(v.p, in_global(v.w.cand_tab), in_global(v.w.state), in_global(v.cand_out), in_global(v.w.vals_a), in_global(v.w.cand_x),
+                      in_global(v.w.cand_ab), in_global(v.w.cand_y), stride, in_global(v.charts), in_global(v.w.chart_tex));
 }
 
 // ---- packer-only entry: box sizes in, placements out ---------------------

@@ -708,22 +708,22 @@ __global__ __launch_bounds__(kOccSmallBlock) void k_occ_small_b(
     const BatchView* __restrict__ bv, const int32_t* __restrict__ idx, uint32_t big_cap,
     int small_texels, int lane_texels, unsigned occ_blocks, int64_t V) {
   const BatchView& v = bv[blockIdx.y];
-  k_occ_small_body<kUvPerBatch>(idx, v.w.vlist, v.p, v.w.pos, v.cot, v.charts, v.w.chart_tex, v.occ, v.w.big,
-                   v.w.big_fp, big_cap, small_texels, lane_texels, v.w.big_counter, v.w.state,
-                   occ_blocks, V, v.cov, reinterpret_cast<float2*>(v.uv));
+  k_occ_small_body<kUvPerBatch>(idx, in_global(v.w.vlist), v.p, in_global(v.w.pos), in_global(v.cot), in_global(v.charts), in_global(v.w.chart_tex), in_global(v.occ), in_global(v.w.big),
+                   in_global(v.w.big_fp), big_cap, small_texels, lane_texels, in_global(v.w.big_counter), in_global(v.w.state),
+                   occ_blocks, V, in_global(v.cov), reinterpret_cast<float2*>(in_global(v.uv)));
 }
 __global__ __launch_bounds__(kBlock) void k_occ_big_b(const BatchView* __restrict__ bv,
                                                       const int32_t* __restrict__ idx,
                                                       uint32_t big_cap) {
   const BatchView& v = bv[blockIdx.y];
-  k_occ_big_body(idx, v.p, v.w.pos, v.cot, v.charts, v.w.chart_tex, v.occ, v.w.big, v.w.big_fp,
-                 big_cap, v.w.big_counter, v.w.state);
+  k_occ_big_body(idx, v.p, in_global(v.w.pos), in_global(v.cot), in_global(v.charts), in_global(v.w.chart_tex), in_global(v.occ), in_global(v.w.big), in_global(v.w.big_fp),
+                 big_cap, in_global(v.w.big_counter), in_global(v.w.state));
 }
 __global__ __launch_bounds__(kCountBlock) void k_occ_count_meta_b(
     const BatchView* __restrict__ bv) {
   const BatchView& v = bv[blockIdx.y];
-  k_occ_count_meta_body(v.p, reinterpret_cast<const int4*>(v.occ), v.w.partial, v.w.state,
-                        v.w.big_counter, v.meta);
+  k_occ_count_meta_body(v.p, reinterpret_cast<const int4*>(in_global(v.occ)), in_global(v.w.partial), in_global(v.w.state),
+                        in_global(v.w.big_counter), in_global(v.meta));
 }
 
 }  // namespace

@@ -895,8 +895,8 @@ __global__ __launch_bounds__(kOrderThreads) void k_sizes_order(
 
 __global__ __launch_bounds__(kOrderThreads) void k_sizes_order_b(const BatchView* __restrict__ bv) {
   const BatchView& v = bv[blockIdx.y];
-  k_sizes_order_body(v.p, v.w.accum, v.charts, v.w.keys_a, v.w.vals_a, v.w.keys_b, v.w.vals_b,
-                     v.w.sorted_wh, nullptr, nullptr, v.w.state, v.w.hist, v.w.partial);
+  k_sizes_order_body(v.p, in_global(v.w.accum), in_global(v.charts), in_global(v.w.keys_a), in_global(v.w.vals_a), in_global(v.w.keys_b), in_global(v.w.vals_b),
+                     in_global(v.w.sorted_wh), nullptr, nullptr, in_global(v.w.state), in_global(v.w.hist), in_global(v.w.partial));
 }
 
 }  // namespace
