@@ -93,14 +93,45 @@ __device__ __forceinline__ void uf_join(int32_t* parent, int u, int v) {
   }
 }
 
-constexpr int kProVerts = 4;  // vertices per prologue thread
+constexpr int kProVerts = 16;  // vertices per prologue thread
+constexpr int kTilesPer = kBlock / kWave;  // triangle tiles per workgroup: one a wave
+constexpr int kTileSteps = kTriTile / (4 * kWave);  // four triangles a lane each
 // Added to the visible count of a tile that holds a bad index: sums of counts
 // stay below it, and a sum of every tile's stays below 2^32.
 constexpr uint32_t kBadTile = 1u << 17;
 static_assert(FA_STATIC_MAX_TRIANGLES < (int64_t)kBadTile &&
                   (FA_STATIC_MAX_TRIANGLES / kTriTile + 2) * (int64_t)kBadTile < (int64_t(1) << 32),
               "kBadTile separates counts from bad tiles");
-static_assert(kTriTile % kBlock == 0, "prologue threads take whole strides of a tile");
+
+inline __host__ __device__ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
+
+// Fill x[i .. i + 4) below n (i a multiple of four; wide: x is 16-byte aligned).
+__device__ __forceinline__ void fill4(int32_t* __restrict__ x, int64_t i, int64_t n, int32_t v,
+                                      bool wide) {
+  if (wide && i + 4 <= n) {
+    *reinterpret_cast<int4*>(x + i) = make_int4(v, v, v, v);
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (i + e < n) x[i + e] = v;
+}
+
+// Which of the triangles [t, t + 4) below T are visible, as four bits (t a
+// multiple of four; wide: vis is 4-byte aligned).
+__device__ __forceinline__ uint32_t visible4(const uint8_t* __restrict__ vis, int64_t t, int64_t T,
+                                             bool wide) {
+  uint32_t m = 0;
+  if (wide && t + 4 <= T) {
+    const uint32_t x = *reinterpret_cast<const uint32_t*>(vis + t);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m |= ((x >> (8 * e)) & 0xFFu) ? 1u << e : 0u;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m |= t + e < T && vis[t + e] ? 1u << e : 0u;
+  }
+  return m;
+}
 
 // Prologue of a frame: frame state, per-vertex scratch (vertex minima and
 // chart_of_vert = -1; clip positions are computed where they are read),
@@ -108,7 +139,11 @@ static_assert(kTriTile % kBlock == 0, "prologue threads take whole strides of a 
 // visible count of every tile of kTriTile triangles. With check_idx (the
 // allocation-free entry point, whose indices no resident scene has checked) a
 // tile with an index outside [0, V) adds kBadTile to its count. Blocks
-// [0, vblocks) handle vertices, the rest triangle tiles. uf_init 2: a visible triangle
+// [0, vblocks) handle vertices, the rest triangle tiles, one a wave. Bound by
+// the stores: 16 bytes a lane each, and few enough workgroups that starting
+// them does not count (with one tile or 1024 vertices a workgroup in single
+// words 2.2M triangles took 8.1 us, now 6.5, and the compaction 7.4, now 5.3;
+// 16 views 102 and 45, now 84 and 20). uf_init 2: a visible triangle
 // starts linked to the smallest of itself and its visible edge neighbours
 // (Alg. 1, first loop); 1: as its own root (same labels); 0: not written (a
 // later pass writes it).
@@ -120,7 +155,6 @@ __device__ __forceinline__ void k_prologue_body(int64_t V, int32_t* __restrict__
                            unsigned vblocks, FrameState* st,
                            unsigned long long* __restrict__ big_counter,
                            const int32_t* __restrict__ check_idx = nullptr) {
-  __shared__ uint32_t sh[kBlock / kWave];
   if (blockIdx.x < vblocks) {
     if (blockIdx.x == 0) {
       // (FA_OK is 0)
@@ -129,51 +163,57 @@ __device__ __forceinline__ void k_prologue_body(int64_t V, int32_t* __restrict__
         reinterpret_cast<uint32_t*>(st)[i] = 0u;
       if (threadIdx.x == 0) *big_counter = 0ull;
     }
-    // kProVerts vertices per thread, a workgroup apart (contiguous stores)
-    const int64_t v0 = (int64_t)blockIdx.x * (blockDim.x * kProVerts) + threadIdx.x;
+    const int64_t v0 = (int64_t)blockIdx.x * (kBlock * kProVerts) + 4 * threadIdx.x;
+    const bool wide_min = aligned16(vmin), wide_cov = aligned16(cov);
 #pragma unroll
-    for (int k = 0; k < kProVerts; ++k) {
-      const int64_t v = v0 + (int64_t)k * blockDim.x;
-      if (v < V) {
-        astore(&vmin[v], INT_MAX);
-        cov[v] = -1;
-      }
+    for (int k = 0; k < kProVerts / 4; ++k) {
+      const int64_t v = v0 + (int64_t)k * 4 * kBlock;
+      fill4(vmin, v, V, INT_MAX, wide_min);
+      fill4(cov, v, V, -1, wide_cov);
     }
     return;
   }
-  // four triangles of the tile per thread, a workgroup apart
-  const unsigned tile = blockIdx.x - vblocks;
-  const int64_t base = (int64_t)tile * kTriTile + (int64_t)threadIdx.x;
+  const int64_t tile =
+      (int64_t)(blockIdx.x - vblocks) * kTilesPer + threadIdx.x / kWave;
+  if (tile * kTriTile >= T) return;
+  const int64_t t0 = tile * kTriTile + 4 * lane_id();
+  const bool wide_vis = ((uintptr_t)vis & 3u) == 0, wide_cot = aligned16(cot);
+  uint32_t m[kTileSteps];
+#pragma unroll
+  for (int k = 0; k < kTileSteps; ++k) m[k] = visible4(vis, t0 + k * 4 * kWave, T, wide_vis);
   uint32_t nv = 0;
 #pragma unroll
-  for (int k = 0; k < kTriTile / kBlock; ++k) {
-    const int64_t t = base + (int64_t)k * kBlock;
-    if (t >= T) break;
-    cot[t] = -1;
+  for (int k = 0; k < kTileSteps; ++k) {
+    const int64_t t = t0 + k * 4 * kWave;
+    fill4(cot, t, T, -1, wide_cot);
+    nv += (uint32_t)__popc(m[k]);
     if (check_idx) {
-      bool bad = false;
 #pragma unroll
-      for (int e = 0; e < 3; ++e) {
-        const int32_t v = check_idx[3 * t + e];
-        bad = bad || v < 0 || (int64_t)v >= V;
-      }
-      if (bad) nv += 2 * kTriTile;  // (a tile counts at most kTriTile visible)
-    }
-    if (!vis[t]) continue;
-    ++nv;
-    int q = (int)t;
-    if (uf_init == 2) {
-#pragma unroll
-      for (int e = 0; e < 3; ++e) {
-        const int n = nbr[3 * t + e];
-        if (n >= 0 && vis[n]) q = min(q, n);
+      for (int j = 0; j < 4; ++j) {
+        if (t + j >= T) break;
+        const int3 v = reinterpret_cast<const int3*>(check_idx)[t + j];
+        if (v.x < 0 || v.x >= V || v.y < 0 || v.y >= V || v.z < 0 || v.z >= V)
+          nv += 2 * kTriTile;  // (a tile counts at most kTriTile visible)
       }
     }
-    if (uf_init) astore(&parent[t], q);
+    if (!uf_init) continue;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (!(m[k] >> j & 1u)) continue;
+      int q = (int)(t + j);
+      if (uf_init == 2) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          const int n = nbr[3 * (t + j) + e];
+          if (n >= 0 && vis[n]) q = min(q, n);
+        }
+      }
+      astore(&parent[t + j], q);
+    }
   }
-  nv = block_sum<uint32_t>(nv, sh);
+  nv = wave_sum<uint32_t>(nv);
   if (check_idx) nv = nv % (2 * kTriTile) + (nv >= 2 * kTriTile ? kBadTile : 0u);
-  if (threadIdx.x == 0) tile_vis[tile] = nv;
+  if (lane_id() == 0) tile_vis[tile] = nv;
 }
 __global__ void k_prologue(int64_t V, int32_t* __restrict__ vmin,
                            int32_t* __restrict__ cov, const uint8_t* __restrict__ vis,
@@ -233,43 +273,62 @@ __device__ __forceinline__ void k_tile_scan_body(uint32_t* tile_vis, unsigned ti
   }
 }
 
-// Stable compaction of the visible triangles into vlist (ascending index).
-// For one frame each workgroup sums the visible counts of the tiles before
-// its own (a few thousand words at most) instead of waiting for a separate
-// scan; batched launches scan first (scanned). The last workgroup records
-// the total; of a checked frame with a bad index (kBadTile) it ends the frame
+// Stable compaction of the visible triangles into vlist (ascending index), a
+// tile by each wave. For one frame each workgroup sums the visible counts of
+// the tiles before its own (a few thousand words at most) instead of waiting
+// for a separate scan; batched launches scan first (scanned). The last tile's
+// wave records the total; of a checked frame with a bad index (kBadTile) it ends the frame
 // with FA_ERR_INVALID_ARG.
 __device__ __forceinline__ void k_vis_compact_body(const uint8_t* __restrict__ vis, int64_t T,
                               const uint32_t* __restrict__ tile_vis, int32_t* __restrict__ vlist,
                               FrameState* __restrict__ st, bool scanned = false,
                               bool checked = false) {
   __shared__ uint32_t sh[kBlock / kWave];
-  // scanned: tile_vis holds each tile's exclusive prefix (k_tile_scan_body)
-  uint32_t off = scanned ? tile_vis[blockIdx.x] : tiles_before(tile_vis, blockIdx.x, sh);
+  const int w = threadIdx.x / kWave, lane = lane_id();
+  const int64_t tiles = (T + kTriTile - 1) / kTriTile;
+  const int64_t first = (int64_t)blockIdx.x * kTilesPer, tile = first + w;
+  const int64_t t0 = tile * kTriTile + 4 * lane;
+  const bool wide = ((uintptr_t)vis & 3u) == 0;
+  uint32_t m[kTileSteps];
+#pragma unroll
+  for (int k = 0; k < kTileSteps; ++k) m[k] = visible4(vis, t0 + k * 4 * kWave, T, wide);
+  uint32_t off;
+  if (scanned) {  // tile_vis holds each tile's exclusive prefix (k_tile_scan_body)
+    if (tile >= tiles) return;
+    off = tile_vis[tile];
+  } else {
+    off = tiles_before(tile_vis, first, sh);
+    if (tile >= tiles) return;
+    for (int j = 0; j < w; ++j) off += tile_vis[first + j];
+  }
   const uint32_t bad = checked ? off / kBadTile : 0u;  // earlier tiles with a bad index
   if (checked) off %= kBadTile;
-  const int64_t base = (int64_t)blockIdx.x * kTriTile + (int64_t)threadIdx.x * 4;
-  bool f[4];
-  uint32_t mine = 0;
+  // two steps' counts a scan (a step has at most 256)
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    f[k] = base + k < T && vis[base + k];
-    mine += f[k];
+  for (int k = 0; k < kTileSteps; k += 2) {
+    const uint32_t c = (uint32_t)__popc(m[k]) | (uint32_t)__popc(m[k + 1]) << 16;
+    const uint32_t incl = wave_incl_scan_dpp(c);
+    const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+    const uint32_t before = incl - c;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      uint32_t at = off + (h ? before >> 16 : before & 0xFFFFu);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (m[k + h] >> j & 1u) vlist[at++] = (int32_t)(t0 + (k + h) * 4 * kWave + j);
+      off += h ? tot >> 16 : tot & 0xFFFFu;
+    }
   }
-  uint32_t tot;
-  uint32_t at = off + block_incl_scan<uint32_t>(mine, sh, &tot) - mine;
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    if (f[k]) vlist[at++] = (int32_t)(base + k);
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    if (checked && (bad || tile_vis[blockIdx.x] >= kBadTile)) {
+  if (tile == tiles - 1 && lane == 0) {
+    if (checked && (bad || tile_vis[tile] >= kBadTile)) {
       st->status = FA_ERR_INVALID_ARG;  // and an empty list: no later kernel reads an index
       st->visible = 0;
     } else {
-      st->visible = (int32_t)(off + tot);
+      st->visible = (int32_t)off;
     }
   }
 }
+static_assert(kTileSteps % 2 == 0, "the compaction scans two steps at a time");
 __global__ void k_vis_compact(const uint8_t* __restrict__ vis, int64_t T,
                               const uint32_t* __restrict__ tile_vis, int32_t* __restrict__ vlist,
                               FrameState* __restrict__ st, bool checked) {
@@ -1356,7 +1415,7 @@ hipError_t launch_prologue(int64_t V, const uint8_t* vis, const int32_t* nbr,
                            int32_t* cot, int uf_init, const int32_t* check_idx, Marker& mk,
                            hipStream_t st) {
   const unsigned vb = std::max(1u, grid_for(V, kBlock * kProVerts));
-  const unsigned tt = grid_for(T, kTriTile);
+  const unsigned tt = grid_for(T, kTriTile * kTilesPer);
   k_prologue<<<vb + tt, kBlock, 0, st>>>(V, w.vmin, cov, vis, nbr, T, w.parent,
                                          cot, w.tile_vis, uf_init, vb, w.state,
                                          w.big_counter, check_idx);
@@ -1505,11 +1564,11 @@ hipError_t launch_charts_batched(const BatchView* dev, int n, const float* pos,
     return hipGetLastError();
   }
   const unsigned vb = std::max(1u, grid_for(V, kBlock * kProVerts));
-  const unsigned tt = grid_for(T, kTriTile);
-  const unsigned vt = std::max(1u, tt);
+  const unsigned tt = grid_for(T, kTriTile * kTilesPer);
+  const unsigned vt = std::max(1u, grid_for(T, kTriTile));
   k_prologue_b<<<dim3(vb + tt, n), kBlock, 0, st>>>(dev, V, nbr, T, vb);
   if (T > 0) {
-    k_tile_scan_b<<<dim3(1, n), 1024, 0, st>>>(dev, tt);
+    k_tile_scan_b<<<dim3(1, n), 1024, 0, st>>>(dev, vt);
     k_vis_compact_b<<<dim3(tt, n), kBlock, 0, st>>>(dev, T);
     k_uf_local_vertex_b<<<dim3(std::max(1u, grid_for(T, 2048)) + kFillGroups, n), 1024, 0, st>>>(
         dev, idx);

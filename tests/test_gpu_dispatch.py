@@ -160,6 +160,33 @@ def test_push_paths(name, block):
         assert np.array_equal(pl, want)
 
 
+# Prologue and compaction take four triangles or vertices a lane, a tile of 1024
+# triangles a wave and four a workgroup, in wide words where a buffer's address
+# allows: sizes around those, hidden triangles in between, and buffers that are
+# not aligned to more than their elements.
+@pytest.mark.parametrize("T", [8193, 9217, 12287, 12289, 16384, 20002])
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_prologue_tiles(T, shift):
+    fa = _fa()
+    frame = fans(np.arange(T) // 4, seed=T, atlas_size=2048)
+    frame.visible = (np.random.default_rng(T).uniform(size=T) < 0.6).astype(np.uint8)
+    frame.visible[-1] = T % 2
+    V = frame.num_vertices
+    print(f"[gpu] prologue T={T} shift={shift}", flush=True)
+    ctx = fa.Context(T, V, max_charts=16384, max_atlas=2048, tuning_table=None)
+    out = ctx.outputs(fa.Mesh(frame.positions, frame.indices, 5), 2048)
+    vis = torch.zeros(T + 4, dtype=torch.uint8, device="cuda")[shift:shift + T]
+    vis.copy_(torch.as_tensor(frame.visible))
+    out.chart_of_tri = torch.zeros(T + 4, dtype=torch.int32, device="cuda")[shift:shift + T]
+    out.chart_of_vert = torch.zeros(V + 4, dtype=torch.int32, device="cuda")[shift:shift + V]
+    ctx.build_atlas(fa.Mesh(frame.positions, frame.indices, 5), vis, frame.view_proj, frame.width,
+                    frame.height, 2048, frame.rate, out=out)
+    torch.cuda.synchronize()
+    g = out.to_numpy()
+    ctx.close()
+    compare(g, oracle.build_frame(frame))
+
+
 # A size outside [0, 2^24] ends the call before the push, in the order of one
 # workgroup (up to 2048 boxes) and of several; the context goes on to pack.
 @pytest.mark.parametrize("n", [1, 2048, 2049, 20000])
