@@ -318,6 +318,36 @@ __device__ __forceinline__ Edges madd(const Edges& a, int64_t k, const Edges& b)
   return Edges{a.e0 + k * b.e0, a.e1 + k * b.e1, a.e2 + k * b.e2};
 }
 
+// The same in 32 bits. At texel (tx0 + i, ty0 + j) an edge function is its
+// value at (tx0, ty0) plus 256 (i dx + j dy) with dx, dy differences of the
+// vertices, so its sign is that of (value >> 8) + i dx + j dy (the shift rounds
+// down). With every vertex within 2^17 (512 texels) of the first one the
+// texel range is at most 1024 a side, |dx|, |dy| < 2^18 and |value| < 2^37, so
+// that these stay below 2^30 over the range and a 16-texel tile past its end.
+struct Edges32 {
+  int32_t e0, e1, e2;
+};
+constexpr int32_t kNear32 = 1 << 17;
+__device__ __forceinline__ bool fits32(const Footprint& f) {
+  return max(max(abs(f.bx), abs(f.by)), max(abs(f.cx), abs(f.cy))) < kNear32;
+}
+__device__ __forceinline__ Edges32 start32(const Footprint& f) {
+  const Edges e = edges_at(f, f.tx0, f.ty0);
+  return Edges32{(int32_t)(e.e0 >> 8), (int32_t)(e.e1 >> 8), (int32_t)(e.e2 >> 8)};
+}
+__device__ __forceinline__ Edges32 dx32(const Footprint& f) {
+  const int32_t s = f.neg ? -1 : 1;
+  return Edges32{-s * f.by, -s * (f.cy - f.by), s * f.cy};
+}
+__device__ __forceinline__ Edges32 dy32(const Footprint& f) {
+  const int32_t s = f.neg ? -1 : 1;
+  return Edges32{s * f.bx, s * (f.cx - f.bx), -s * f.cx};
+}
+__device__ __forceinline__ bool inside(const Edges32& e) { return (e.e0 | e.e1 | e.e2) >= 0; }
+__device__ __forceinline__ void add(Edges32& e, const Edges32& d) {
+  e.e0 += d.e0; e.e1 += d.e1; e.e2 += d.e2;
+}
+
 __global__ void k_occ_fill(int4* __restrict__ occ, int64_t n4, const FrameState* __restrict__ st) {
   const int4 neg = make_int4(-1, -1, -1, -1);
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4;
@@ -326,19 +356,25 @@ __global__ void k_occ_fill(int4* __restrict__ occ, int64_t n4, const FrameState*
 }
 
 // All texels of a footprint by one lane, row by row, edge functions stepped.
-__device__ __forceinline__ void raster_lane(const Footprint& fp, int32_t* __restrict__ occ,
-                                            int omega) {
-  Edges r = edges_at(fp, fp.tx0, fp.ty0);
-  const Edges dx = step_x(fp), dy = step_y(fp);
+template <typename E>
+__device__ __forceinline__ void raster_rows(const Footprint& fp, E r, const E dx, const E dy,
+                                            int32_t* __restrict__ occ, int omega) {
   for (int ty = fp.ty0; ty <= fp.ty1; ++ty) {
     int32_t* row = occ + (int64_t)ty * omega;
-    Edges e = r;
+    E e = r;
     for (int tx = fp.tx0; tx <= fp.tx1; ++tx) {
       if (inside(e)) row[tx] = fp.chart;
       add(e, dx);
     }
     add(r, dy);
   }
+}
+__device__ __forceinline__ void raster_lane(const Footprint& fp, int32_t* __restrict__ occ,
+                                            int omega) {
+  if (fits32(fp))
+    raster_rows(fp, start32(fp), dx32(fp), dy32(fp), occ, omega);
+  else
+    raster_rows(fp, edges_at(fp, fp.tx0, fp.ty0), step_x(fp), step_y(fp), occ, omega);
 }
 
 __device__ __forceinline__ int rl(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
@@ -514,6 +550,13 @@ __global__ __launch_bounds__(kOccSmallBlock) void k_occ_small(
 // are split evenly over all waves of the grid; a wave finds its first
 // footprint by a 64-way search over the (increasing) first-tile indices and
 // walks forward, 4 texels per lane.
+// Bound by the vector unit: a tile is 256 texels whose edge functions took
+// about 150 instructions in 64 bits. In 32 bits, with one sign test for edges
+// and range, the last rows left out where the range ends before them, and tiles
+// outside an edge dropped by the scalar unit, it is about 36 (91k tiles of a
+// 2.2M-triangle frame 31 -> 22 us, 158k tiles 42 -> 28; of the rest the search
+// and the set-up take 7 and the footprints' broadcasts 4). Wider searches (256
+// probes a round) read more lines and are 1 us slower.
 __device__ __forceinline__ void k_occ_big_body(
     const int32_t* __restrict__ idx, FrameParams p, const float* __restrict__ pos,
     const int32_t* __restrict__ cot, const fa_chart* __restrict__ charts,
@@ -527,8 +570,12 @@ __device__ __forceinline__ void k_occ_big_body(
   const uint32_t nent = (uint32_t)min<unsigned long long>(ctr >> kSlotShift, big_cap);
   if (nent == 0) return;
   constexpr unsigned long long kLow = (1ull << kSlotShift) - 1;
-  const ulonglong2 lastv = big[nent - 1];
-  const uint64_t total = (lastv.y & kLow) + (lastv.y >> kSlotShift);
+  // (all tiles counted are queued unless the queue was full)
+  uint64_t total = ctr & kLow;
+  if (ctr >> kSlotShift > big_cap) {
+    const ulonglong2 lastv = big[nent - 1];
+    total = (lastv.y & kLow) + (lastv.y >> kSlotShift);
+  }
   const uint64_t nwaves = (uint64_t)gridDim.x * (kBlock / kWave);
   // the wave index through readfirstlane: the compiler then knows it (and all
   // loop bounds below) to be uniform and keeps the tile loop's control scalar
@@ -553,11 +600,13 @@ __device__ __forceinline__ void k_occ_big_body(
   // footprint broadcast from its lane.
   const int lx = lane % kOccTile, ly = lane / kOccTile;
   constexpr int kRows = kWave / kOccTile;
+  static_assert(kOccTile == 4 * kRows, "a tile is four rows of texels a lane");
+  const uint32_t row_bytes = 4u * (uint32_t)p.omega;
   for (uint32_t e0 = lo; e0 < nent;) {
     const uint32_t my = e0 + (uint32_t)lane;
     uint64_t base = 0, nt = 0;
     uint32_t tiles_x = 1;
-    bool mine = false, ok = false;
+    bool mine = false;
     Footprint f;
     f.ax = f.ay = f.bx = f.by = f.cx = f.cy = 0;
     f.tx0 = f.tx1 = f.ty0 = f.ty1 = f.chart = f.neg = 0;
@@ -567,28 +616,94 @@ __device__ __forceinline__ void k_occ_big_body(
       nt = ent.y >> kSlotShift;
       tiles_x = (uint32_t)(ent.x >> 32);
       mine = base < k1;
-      if (mine) {
-        f = get_footprint(big_fp + 3 * (int64_t)my);
-        ok = true;
-      }
+      if (mine) f = get_footprint(big_fp + 3 * (int64_t)my);
     }
     const int cnt = __popcll(__ballot(mine));  // entries start in order: a prefix of lanes
+    // this wave's tiles of the footprint (it has fewer than 2^32, at most
+    // (omega / 16)^2)
+    const uint32_t first = (uint32_t)((k0 > base ? k0 : base) - base);
+    const uint32_t last = (uint32_t)((k1 < base + nt ? k1 : base + nt) - base);
+    const unsigned long long small = __ballot(fits32(f));
+    const Edges32 start = start32(f), fdx = dx32(f), fdy = dy32(f);
     for (int j = 0; j < cnt; ++j) {
-      if (!rl((int)ok, j)) continue;
+      const uint32_t t0 = (uint32_t)rl((int)first, j), t1 = (uint32_t)rl((int)last, j);
+      const uint32_t txj = (uint32_t)rl((int)tiles_x, j);
+      const int fx0 = rl(f.tx0, j), fx1 = rl(f.tx1, j), fy0 = rl(f.ty0, j), fy1 = rl(f.ty1, j);
+      const int chart = rl(f.chart, j);
+      // tile column and row of the first tile, stepped below
+      uint32_t ti = 0, tj = 0;
+      if (t0) {
+        ti = t0 % txj;
+        tj = t0 / txj;
+      }
+      if (small >> j & 1ull) {
+        const Edges32 dx{rl(fdx.e0, j), rl(fdx.e1, j), rl(fdx.e2, j)};
+        const Edges32 dy{rl(fdy.e0, j), rl(fdy.e1, j), rl(fdy.e2, j)};
+        // at the tile's first texel (uniform) and at that of its row of tiles;
+        // the lane's offset; the most that a tile's texels have over its first
+        constexpr int32_t kIn = kOccTile - 1;
+        const int32_t ci = kOccTile * (int)ti, ri = kOccTile * (int)tj;
+        Edges32 row{rl(start.e0, j) + ri * dy.e0, rl(start.e1, j) + ri * dy.e1,
+                    rl(start.e2, j) + ri * dy.e2};
+        Edges32 eo{row.e0 + ci * dx.e0, row.e1 + ci * dx.e1, row.e2 + ci * dx.e2};
+        const Edges32 off{__mul24(lx, dx.e0) + __mul24(ly, dy.e0),
+                          __mul24(lx, dx.e1) + __mul24(ly, dy.e1),
+                          __mul24(lx, dx.e2) + __mul24(ly, dy.e2)};
+        const Edges32 most{kIn * (max(dx.e0, 0) + max(dy.e0, 0)),
+                           kIn * (max(dx.e1, 0) + max(dy.e1, 0)),
+                           kIn * (max(dx.e2, 0) + max(dy.e2, 0))};
+        const Edges32 dq{kRows * dy.e0, kRows * dy.e1, kRows * dy.e2};
+        // texels to the range's last column and row from the lane's texel of
+        // the first tile, and that texel's byte in the map (below 2^28)
+        const int wide = fx1 - fx0 - lx, high = fy1 - fy0 - ly;
+        const uint32_t lane_at = 4u * ((uint32_t)(fy0 + ly) * (uint32_t)p.omega +
+                                       (uint32_t)(fx0 + lx));
+        int i = ci, r = ri;
+        for (uint32_t tt = t0; tt < t1; ++tt) {
+          if (inside(Edges32{eo.e0 + most.e0, eo.e1 + most.e1, eo.e2 + most.e2})) {
+            Edges32 ev{eo.e0 + off.e0, eo.e1 + off.e1, eo.e2 + off.e2};
+            // negative where the lane's texel is past the last column or row,
+            // or outside an edge
+            const int left = wide - i, below = high - r;
+            const uint32_t at =
+                lane_at + 4u * ((uint32_t)r * (uint32_t)p.omega + (uint32_t)i);
+            char* map = reinterpret_cast<char*>(occ);
+            auto rows = [&](int q0) {
+              int32_t out[2];
+#pragma unroll
+              for (int q = 0; q < 2; ++q) {
+                out[q] = ev.e0 | ev.e1 | ev.e2 | left | (below - (q0 + q) * kRows);
+                add(ev, dq);
+              }
+#pragma unroll
+              for (int q = 0; q < 2; ++q)
+                if (out[q] >= 0)
+                  *reinterpret_cast<int32_t*>(map + at + (q0 + q) * kRows * row_bytes) = chart;
+            };
+            rows(0);
+            if (fy0 + r + 2 * kRows <= fy1) rows(2);
+          }
+          i += kOccTile;
+          eo.e0 += kOccTile * dx.e0;
+          eo.e1 += kOccTile * dx.e1;
+          eo.e2 += kOccTile * dx.e2;
+          if (++ti == txj) {
+            ti = 0;
+            i = 0;
+            r += kOccTile;
+            row.e0 += kOccTile * dy.e0;
+            row.e1 += kOccTile * dy.e1;
+            row.e2 += kOccTile * dy.e2;
+            eo = row;
+          }
+        }
+        continue;
+      }
       Footprint fp;
       fp.ax = rl(f.ax, j); fp.ay = rl(f.ay, j);
       fp.bx = rl(f.bx, j); fp.by = rl(f.by, j);
       fp.cx = rl(f.cx, j); fp.cy = rl(f.cy, j);
-      fp.tx0 = rl(f.tx0, j); fp.tx1 = rl(f.tx1, j);
-      fp.ty0 = rl(f.ty0, j); fp.ty1 = rl(f.ty1, j);
-      fp.chart = rl(f.chart, j); fp.neg = rl(f.neg, j);
-      const uint64_t bj = ((uint64_t)(uint32_t)rl((int)(uint32_t)(base >> 32), j) << 32) |
-                          (uint32_t)rl((int)(uint32_t)base, j);
-      const uint64_t nj = (uint64_t)(uint32_t)rl((int)(uint32_t)nt, j);
-      const uint32_t txj = (uint32_t)rl((int)tiles_x, j);
-      // a footprint has fewer than 2^32 tiles (at most (omega / 16)^2)
-      const uint32_t t0 = (uint32_t)((k0 > bj ? k0 : bj) - bj);
-      const uint32_t t1 = (uint32_t)((k1 < bj + nj ? k1 : bj + nj) - bj);
+      fp.neg = rl(f.neg, j);
       // The edge functions are linear in the texel: at the lane's texel they
       // are their value at the tile's first texel (uniform, scalar unit) plus
       // the lane's offset, fixed per footprint.
@@ -596,17 +711,16 @@ __device__ __forceinline__ void k_occ_big_body(
       const Edges off = madd(madd(Edges{0, 0, 0}, lx, dx), ly, dy);
       const Edges dq = madd(Edges{0, 0, 0}, kRows, dy);
       const int64_t row_step = (int64_t)kRows * p.omega;
-      uint32_t ti = t0 % txj, tj = t0 / txj;  // tile column and row, stepped below
       for (uint32_t tt = t0; tt < t1; ++tt) {
-        const int ox = fp.tx0 + kOccTile * (int)ti, oy = fp.ty0 + kOccTile * (int)tj;
+        const int ox = fx0 + kOccTile * (int)ti, oy = fy0 + kOccTile * (int)tj;
         const Edges eo = edges_at(fp, ox, oy);
         Edges ev{eo.e0 + off.e0, eo.e1 + off.e1, eo.e2 + off.e2};
         const int tx = ox + lx, ty0 = oy + ly;
-        const bool col = tx <= fp.tx1;
+        const bool col = tx <= fx1;
         int32_t* dst = occ + (int64_t)ty0 * p.omega + tx;
 #pragma unroll
         for (int q = 0; q < kOccTile / kRows; ++q) {
-          if (col && ty0 + q * kRows <= fp.ty1 && inside(ev)) *dst = fp.chart;
+          if (col && ty0 + q * kRows <= fy1 && inside(ev)) *dst = chart;
           add(ev, dq);
           dst += row_step;
         }

@@ -92,6 +92,17 @@ def test_occupied_texels(omega, n):
 # above 1024 columns and where two rows may not fit a chunk. Other edges: chunks
 # of 8128 boxes (and stop checks at multiples of another number), boxes over
 # more than 8 and 16 others, more than 8 boxes of a row over edge columns.
+# Triangles whose vertices are within 512 texels of the first one are tested in
+# 32 bits, larger ones in 64: fans of a few triangles whose sides go from
+# beyond 2000 texels to below 60, some of them on both sides of 512.
+@pytest.mark.parametrize("n,per", [(1, 1), (1, 2), (1, 5), (2, 3), (4, 5), (5, 1), (9, 4), (12, 5),
+                                   (16, 3), (25, 5), (36, 2), (400, 5)])
+@pytest.mark.parametrize("omega", [2048, 8192])
+def test_occupancy_sides(n, per, omega):
+    f = fans(np.arange(n * per) // per, seed=n + per, atlas_size=omega, width=3840, height=2160)
+    compare(check(f), oracle.build_frame(f))
+
+
 def _uniform(n, lo, hi, seed=0):
     return np.random.default_rng(seed).uniform(lo, hi, (n, 2))
 
