@@ -330,6 +330,16 @@ __device__ __forceinline__ uint32_t wave_incl_scan_dpp(uint32_t v) {
   v += dpp_u32<0x143, 0xC>(v);  // row_bcast:31
   return v;
 }
+// Inclusive prefix maximum, likewise (lanes without a source read 0).
+__device__ __forceinline__ uint32_t wave_incl_max_dpp(uint32_t v) {
+  v = max(v, dpp_u32<0x111>(v));       // row_shr:1
+  v = max(v, dpp_u32<0x112>(v));       // row_shr:2
+  v = max(v, dpp_u32<0x114>(v));       // row_shr:4
+  v = max(v, dpp_u32<0x118>(v));       // row_shr:8
+  v = max(v, dpp_u32<0x142, 0xA>(v));  // row_bcast:15
+  v = max(v, dpp_u32<0x143, 0xC>(v));  // row_bcast:31
+  return v;
+}
 
 // Block-wide inclusive sum of 32-bit values with one barrier: `sh` holds
 // NW words and must not be the `sh` of the previous call (callers alternate

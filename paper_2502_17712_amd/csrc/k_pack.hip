@@ -41,28 +41,61 @@ namespace {
 // their prefix sums and sizes in LDS next to the frontline.
 constexpr int kPackLds = 4096;
 
+constexpr uint32_t kEmpty = 0xFFFFFFFFu;  // no texel in the box's column
+constexpr int kAllCols = 768;  // wider boxes are pushed by the whole workgroup
+constexpr int kAllList = 256;  // ... as many of them
+
+// Content column kk (pooled value q) of a box of a columns whose first column
+// is F[0]: the height that it needs, and the frontline raised over it by a box
+// of b rows at y (its new top).
+// (The gutter's columns are read four at a time, and without a branch, so that
+// the reads of several columns are in flight together; past the box they read
+// its last column.)
+__device__ __forceinline__ int rise_of(const int32_t* F, int kk, uint32_t q, int g, int a) {
+  const int dend = min(kk + 2 * g, a - 1);
+  int fm = 0;
+  for (int h = 0; h <= 2 * g; h += 4) {
+    const int f0 = F[min(kk + h, dend)], f1 = F[min(kk + h + 1, dend)];
+    const int f2 = F[min(kk + h + 2, dend)], f3 = F[min(kk + h + 3, dend)];
+    fm = max(fm, max(max(f0, f1), max(f2, f3)));
+  }
+  return q == kEmpty ? 0 : fm - (int)(q & 0xFFFFu);
+}
+__device__ __forceinline__ int raise_by(int32_t* F, int kk, uint32_t q, int g, int a, int b,
+                                        int y) {
+  if (q == kEmpty) return 0;
+  const int Bk = (int)(q >> 16);
+  const int v = Bk == 0x7FFF ? y + b : min(y + b, y + 2 * g + Bk + 1);
+  const int dend = min(kk + 2 * g, a - 1);
+  atomicMax(&F[kk], v);
+  for (int h = 1; h <= 2 * g; ++h) atomicMax(&F[min(kk + h, dend)], v);
+  return v;
+}
+
 // Footprint push in three launches: MODE 1 sizes, fold, overflow and row
 // starts (to global memory; tab[3] = -1 marks a rejected candidate, tab[5]
 // the number of rows with boxes), then k_fp_pool, then MODE 2 the push. (The
 // box push is k_pack_box.)
-template <int NT, int MODE>
-__global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
-                                             const FrameState* __restrict__ st, FrameParams p,
-                                             long long* __restrict__ cand_x,
-                                             uint32_t* __restrict__ cand_ab,
-                                             int32_t* __restrict__ cand_y,
-                                             int32_t* __restrict__ cand_rs,
-                                             int32_t* __restrict__ cand_tab, int64_t stride,
-                                             const uint32_t* __restrict__ fp_pool,
-                                             int64_t pool_stride) {
-  // [2 * omega] frontline, then the LDS copies of X, AB and the row starts
-  extern __shared__ int32_t F[];
-  __shared__ long long sh64[NT / kWave];
-  __shared__ int32_t sh32[NT / kWave];
-  __shared__ int32_t Hsh[2];
+// LDS: at most kPackLds charts (a body of its own, so that the compiler knows
+// these accesses for LDS ones: flat loads are waited for together with the
+// prefetched pool values).
+// The push is bound by the chain of LDS accesses from box to box. Boxes over
+// kAllCols columns by the whole workgroup, maxima by DPP, the columns of a
+// gutter read together and two (not four) columns a lane prefetched took it
+// from 44 to 28 us on a 2.2M-triangle frame (144 charts) and from 58 to 37 on
+// one of 86k (234 charts).
+template <int NT, int MODE, bool LDS>
+__device__ __forceinline__ void pack_body(const float2* __restrict__ wh,
+                                          const FrameState* __restrict__ st, const FrameParams& p,
+                                          long long* __restrict__ cand_x,
+                                          uint32_t* __restrict__ cand_ab,
+                                          int32_t* __restrict__ cand_y,
+                                          int32_t* __restrict__ cand_rs,
+                                          int32_t* __restrict__ cand_tab, int64_t stride,
+                                          const uint32_t* __restrict__ fp_pool,
+                                          int64_t pool_stride, int32_t* F, long long* sh64,
+                                          int32_t* sh32, int32_t* Hsh, int32_t* all_box) {
   constexpr int NW = NT / kWave;
-
-  if (st->status != FA_OK) return;
   const int j = blockIdx.x + 1;
   const int tid = threadIdx.x, w = tid / kWave, lane = lane_id();
   const int C = st->num_charts;
@@ -70,10 +103,9 @@ __global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
   long long* Xg = cand_x + (int64_t)(j - 1) * stride;
   uint32_t* ABg = cand_ab + (int64_t)(j - 1) * stride;
   int32_t* RSg = cand_rs + (int64_t)(j - 1) * (stride + 1);
-  const bool in_lds = C <= kPackLds;
-  long long* X = in_lds ? reinterpret_cast<long long*>(F + 2 * omega) : Xg;
-  uint32_t* AB = in_lds ? reinterpret_cast<uint32_t*>(F + 2 * omega + 2 * kPackLds) : ABg;
-  int32_t* RS = (in_lds && MODE != 1) ? F + 2 * omega + 3 * kPackLds : RSg;
+  long long* X = LDS ? reinterpret_cast<long long*>(F + 2 * omega) : Xg;
+  uint32_t* AB = LDS ? reinterpret_cast<uint32_t*>(F + 2 * omega + 2 * kPackLds) : ABg;
+  int32_t* RS = (LDS && MODE != 1) ? F + 2 * omega + 3 * kPackLds : RSg;
   int32_t* Y = cand_y + (int64_t)(j - 1) * stride;
   int32_t* tab = cand_tab + (j - 1) * kCandStride;
   long long m, rows;
@@ -104,7 +136,7 @@ __global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
         if (a > 2 * omega || b > 2 * omega) bad = 1;  // cannot fit: m > omega or H > L
         const uint32_t ca = (uint32_t)min(a, 2 * omega + 1), cb = (uint32_t)min(b, 2 * omega + 1);
         ABg[i] = ca | (cb << 16);
-        if (in_lds) {
+        if (LDS) {
           X[i] = Xi;
           AB[i] = ca | (cb << 16);
         }
@@ -151,7 +183,7 @@ __global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
     m = tab[1];
     rows = tab[4];
     nr = tab[5];
-    if (in_lds) {
+    if (LDS) {
       for (int i = tid; i < C; i += NT) {
         X[i] = Xg[i];
         AB[i] = ABg[i];
@@ -170,10 +202,24 @@ __global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
   // one barrier per row orders the rows. The height test reads a slot that
   // no wave can touch again before every wave has read it.
   int Hw = 0;
+  // boxes of more than kAllCols columns are pushed by the whole workgroup
+  // (list of the first kAllList of them, in order)
+  int n_all = 0;
+  for (int base = 0; base < C && n_all < kAllList; base += NT) {
+    const int i = base + tid;
+    const int one = i < C && (int)(AB[i] & 0xFFFFu) - p.gutter > kAllCols ? 1 : 0;
+    int tot;
+    const int at = n_all + block_incl_scan<int>(one, sh32, &tot) - one;
+    if (one && at < kAllList) all_box[at] = i;
+    n_all += tot;
+  }
+  n_all = min(n_all, kAllList);
+  __syncthreads();
+  const int last_all = n_all > 0 ? all_box[n_all - 1] : -1;
+  int next_all = 0;
   // footprint push: the pooled values do not depend on the frontline, so each
   // wave loads its next box's first R x 64 columns while it pushes the current
-  constexpr int R = 4;
-  constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+  constexpr int R = 2;
   uint32_t nxt[R];
   int prr = 0, pk = 0;
   auto advance = [&](bool first) {
@@ -203,6 +249,35 @@ __global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
     const long long r = X[s0] >> lg;
     const bool right = (r % 3) != 0;
     {
+      // the row's widest boxes, column by column over the workgroup (the
+      // boxes of a row do not touch each other's columns)
+      for (; next_all < n_all && all_box[next_all] < s1; ++next_all) {
+        const int k = all_box[next_all];
+        const uint32_t ab = AB[k];
+        const int a = (int)(ab & 0xFFFFu), b = (int)(ab >> 16);
+        const int o = (int)(X[k] - (r << lg));
+        const int x = right ? L - o - a : o;
+        const int g = p.gutter, ncol = a - g;
+        const uint32_t* src = pool + X[k];
+        int mx = 0;
+        for (int k0 = tid; k0 < ncol; k0 += R * NT) {
+          uint32_t q[R];
+#pragma unroll
+          for (int h = 0; h < R; ++h) q[h] = k0 + h * NT < ncol ? src[k0 + h * NT] : kEmpty;
+#pragma unroll
+          for (int h = 0; h < R; ++h) mx = max(mx, rise_of(F + x, k0 + h * NT, q[h], g, a));
+        }
+        const int y = block_max<int>(mx, sh32);
+        for (int k0 = tid; k0 < ncol; k0 += R * NT) {
+          uint32_t q[R];
+#pragma unroll
+          for (int h = 0; h < R; ++h) q[h] = k0 + h * NT < ncol ? src[k0 + h * NT] : kEmpty;
+#pragma unroll
+          for (int h = 0; h < R; ++h)
+            Hw = max(Hw, raise_by(F + x, k0 + h * NT, q[h], g, a, b, y));
+        }
+        if (tid == 0) Y[k] = y;
+      }
       for (int k = s0 + w; k < s1; k += NW) {
         const long long Xk = X[k];
         const uint32_t ab = AB[k];
@@ -218,36 +293,38 @@ __global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
           for (int rk = 0; rk < R; ++rk) keep[rk] = nxt[rk];
           advance(false);
           prefetch();
+          if (ncol > kAllCols && k <= last_all) continue;  // (done above)
           int mx = 0;
-          auto rise = [&](int kk, uint32_t q) {
-            if (q == kEmpty) return;
-            const int dend = min(kk + 2 * g, a - 1);
-            int fm = 0;
-            for (int d = kk; d <= dend; ++d) fm = max(fm, F[x + d]);
-            mx = max(mx, fm - (int)(q & 0xFFFFu));
-          };
-  #pragma unroll
-          for (int rk = 0; rk < R; ++rk) rise(lane + rk * kWave, keep[rk]);
-          for (int kk = lane + R * kWave; kk < ncol; kk += kWave) rise(kk, src[kk]);
-          const int y = wave_max<int>(mx);
-          int hv = 0;
-          auto raise = [&](int kk, uint32_t q) {
-            if (q == kEmpty) return;
-            const int Bk = (int)(q >> 16);
-            const int v = Bk == 0x7FFF ? y + b : min(y + b, y + 2 * g + Bk + 1);
-            const int dend = min(kk + 2 * g, a - 1);
-            for (int d = kk; d <= dend; ++d) atomicMax(&F[x + d], v);
-            hv = max(hv, v);
-          };
-  #pragma unroll
-          for (int rk = 0; rk < R; ++rk) raise(lane + rk * kWave, keep[rk]);
-          for (int kk = lane + R * kWave; kk < ncol; kk += kWave) raise(kk, src[kk]);
-          Hw = max(Hw, wave_max<int>(hv));
+#pragma unroll
+          for (int rk = 0; rk < R; ++rk)
+            mx = max(mx, rise_of(F + x, lane + rk * kWave, keep[rk], g, a));
+          for (int k0 = lane + R * kWave; k0 < ncol; k0 += R * kWave) {
+            uint32_t q[R];
+#pragma unroll
+            for (int h = 0; h < R; ++h)
+              q[h] = k0 + h * kWave < ncol ? src[k0 + h * kWave] : kEmpty;
+#pragma unroll
+            for (int h = 0; h < R; ++h)
+              mx = max(mx, rise_of(F + x, k0 + h * kWave, q[h], g, a));
+          }
+          const int y = wave_max_dpp(mx);
+#pragma unroll
+          for (int rk = 0; rk < R; ++rk)
+            Hw = max(Hw, raise_by(F + x, lane + rk * kWave, keep[rk], g, a, b, y));
+          for (int k0 = lane + R * kWave; k0 < ncol; k0 += R * kWave) {
+            uint32_t q[R];
+#pragma unroll
+            for (int h = 0; h < R; ++h)
+              q[h] = k0 + h * kWave < ncol ? src[k0 + h * kWave] : kEmpty;
+#pragma unroll
+            for (int h = 0; h < R; ++h)
+              Hw = max(Hw, raise_by(F + x, k0 + h * kWave, q[h], g, a, b, y));
+          }
           if (lane == 0) Y[k] = y;
         }
       }
     }
-    Hw = wave_max<int>(Hw);  // lane 0 publishes the wave's height
+    Hw = wave_max_dpp(Hw);  // lane 0 publishes the wave's height
     if (lane == 0) atomicMax(&Hsh[rr & 1], Hw);
     __syncthreads();
     if (Hsh[rr & 1] > L) break;
@@ -260,6 +337,31 @@ __global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
     tab[3] = H;
     tab[4] = (int32_t)min(rows, (long long)INT_MAX);
   }
+}
+
+template <int NT, int MODE>
+__global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
+                                             const FrameState* __restrict__ st, FrameParams p,
+                                             long long* __restrict__ cand_x,
+                                             uint32_t* __restrict__ cand_ab,
+                                             int32_t* __restrict__ cand_y,
+                                             int32_t* __restrict__ cand_rs,
+                                             int32_t* __restrict__ cand_tab, int64_t stride,
+                                             const uint32_t* __restrict__ fp_pool,
+                                             int64_t pool_stride) {
+  // [2 * omega] frontline, then the LDS copies of X, AB and the row starts
+  extern __shared__ int32_t F[];
+  __shared__ long long sh64[NT / kWave];
+  __shared__ int32_t sh32[NT / kWave];
+  __shared__ int32_t Hsh[2];
+  __shared__ int32_t all_box[kAllList];
+  if (st->status != FA_OK) return;
+  if (st->num_charts <= kPackLds)
+    pack_body<NT, MODE, true>(wh, st, p, cand_x, cand_ab, cand_y, cand_rs, cand_tab, stride,
+                              fp_pool, pool_stride, F, sh64, sh32, Hsh, all_box);
+  else
+    pack_body<NT, MODE, false>(wh, st, p, cand_x, cand_ab, cand_y, cand_rs, cand_tab, stride,
+                               fp_pool, pool_stride, F, sh64, sh32, Hsh, all_box);
 }
 
 // Box push of one candidate per workgroup (the default packing). Everything
@@ -1107,8 +1209,27 @@ __global__ __launch_bounds__(NT) void k_pack_box(const float2* __restrict__ wh,
 // fold did not reject, content column k of box i at pool[X_i + k] as
 // T | B << 16 (B = 0x7FFF: the box bottom; 0xFFFFFFFF: empty). One lane per
 // fold position of candidate blockIdx.y + 1: the box is the last one starting
-// at or before it (binary search over the fold), positions in the box's
-// right gutter are skipped.
+// at or before it, positions in the box's right gutter are skipped.
+// Bound by dependent loads: a wave searches the fold 64 ways for its first
+// position, fetches the boxes from there on, one a lane (each has a column at
+// least), and a lane finds its own from marks where they start; the profile
+// columns under a position are loaded four or sixteen at a time (144 charts, 64
+// candidates: 21 -> 12 us).
+template <int N>
+__device__ __forceinline__ void rows_of(const int2* pr, int u0, int u1, int& tmin, int& bmax) {
+  for (int u = u0; u <= u1; u += N) {
+    int2 v[N];
+#pragma unroll
+    for (int h = 0; h < N; ++h) v[h] = pr[min(u + h, u1)];
+#pragma unroll
+    for (int h = 0; h < N; ++h) {
+      if (v[h].y < 0) continue;
+      tmin = min(tmin, v[h].x);
+      bmax = max(bmax, v[h].y);
+    }
+  }
+}
+
 __global__ __launch_bounds__(kBlock) void k_fp_pool(
     const float2* __restrict__ wh, const FrameState* __restrict__ st, FrameParams p,
     const long long* __restrict__ cand_x, const uint32_t* __restrict__ cand_ab,
@@ -1125,31 +1246,40 @@ __global__ __launch_bounds__(kBlock) void k_fp_pool(
   const uint32_t* AB = cand_ab + (int64_t)(j - 1) * stride;
   uint32_t* pool = fp_pool + (int64_t)(j - 1) * pool_stride;
   const long long end = X[C - 1] + (long long)(AB[C - 1] & 0xFFFFu);
-  for (long long pos = (long long)blockIdx.x * kBlock + threadIdx.x; pos < end;
-       pos += (long long)gridDim.x * kBlock) {
-    int lo = 0, hi = C - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (X[mid] <= pos) lo = mid;
-      else hi = mid - 1;
+  __shared__ uint32_t marks[kBlock / kWave][kWave];
+  const int lane = lane_id();
+  uint32_t* mark = marks[threadIdx.x / kWave];
+  for (long long pos0 = (long long)blockIdx.x * kBlock + (threadIdx.x & ~(kWave - 1)); pos0 < end;
+       pos0 += (long long)gridDim.x * kBlock) {
+    int lo = 0, hi = C;  // the last box starting at or before pos0
+    while (hi - lo > 1) {
+      const int step = (hi - lo + kWave - 1) / kWave;
+      const int probe = lo + lane * step;
+      const int n = __popcll(__ballot(probe < hi && X[probe] <= pos0));
+      lo += (n - 1) * step;
+      hi = min(hi, lo + step);
     }
-    const int i = lo;
-    const int kk = (int)(pos - X[i]);
-    if (kk >= (int)(AB[i] & 0xFFFFu) - p.gutter) continue;
+    // starts relative to pos0 (the first one's at most 2^15 before it)
+    const int rel = lo + lane < C ? (int)min(X[lo + lane] - pos0, (long long)kWave) : kWave;
+    mark[lane] = 0u;
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (rel < kWave) mark[max(rel, 0)] = (uint32_t)lane + 1u;
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int own = (int)wave_incl_max_dpp(mark[lane]) - 1;
+    const int i = lo + own;
+    const int kk = lane - __shfl(rel, own, kWave);
+    const long long pos = pos0 + lane;
+    if (pos >= end || kk >= (int)(AB[i] & 0xFFFFu) - p.gutter) continue;
     const float2 sz = wh[i];
     const int Uc = (int)floorf(sz.x) + 1, Rc = (int)floorf(sz.y) + 1;
     const int2* pr = fp_prof + fp_off[order[i]];
     const int u0 = min(Uc - 1, max(0, (kk * J + j - 1) / j - 1));
     const int u1 = min(Uc - 1, ((kk + 1) * J + j - 1) / j - 1);
     int tmin = INT_MAX, bmax = -1;
-#pragma unroll 4
-    for (int u = u0; u <= u1; ++u) {
-      const int2 v = pr[u];
-      if (v.y >= 0) {
-        tmin = min(tmin, v.x);
-        bmax = max(bmax, v.y);
-      }
-    }
+    if (J < 4 * j) rows_of<4>(pr, u0, u1, tmin, bmax);  // (uniform)
+    else rows_of<16>(pr, u0, u1, tmin, bmax);
     uint32_t q = 0xFFFFFFFFu;
     if (bmax >= 0) {
       const int T = tmin * j / J;

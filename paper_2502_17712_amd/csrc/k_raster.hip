@@ -968,6 +968,23 @@ __device__ __forceinline__ int32_t crossing_row(int64_t px, int64_t py, int64_t 
   return (int32_t)floor_div64(num, d);
 }
 
+// The same for coordinates within 2^24, in doubles: products, sums and the
+// remainder are whole numbers below 2^53 and so exact, the quotient is below
+// 2^17 and comes from an approximate reciprocal (2^-20 or better) within one
+// of the floor, and the remainder settles it.
+constexpr int32_t kNearRow = 1 << 24;
+__device__ __forceinline__ int32_t crossing_row_near(int32_t px, int32_t py, int32_t qx,
+                                                     int32_t qy, int32_t x0) {
+  const double run = (double)(qx - px), sg = run < 0.0 ? -1.0 : 1.0;
+  const double num = sg * fma((double)py, run, (double)(x0 - px) * (double)(qy - py));
+  const double d = 256.0 * sg * run;
+  double q = floor(num * __builtin_amdgcn_rcp(d));
+  const double r = fma(-q, d, num);
+  if (r < 0.0) q -= 1.0;
+  else if (r >= d) q += 1.0;
+  return (int32_t)q;
+}
+
 // Setup of one visible-list entry for the profile raster: its near-clipped
 // polygon snapped to the chart-local unit grid (1/256), the chart's column
 // and row counts and first profile entry, and the columns [u0, u0 + cnt) it
@@ -975,6 +992,7 @@ __device__ __forceinline__ int32_t crossing_row(int64_t px, int64_t py, int64_t 
 struct FpSetup {
   int32_t X[4], Y[4];
   int n, Uc, Rc, off, u0, cnt;
+  bool near;  // every coordinate within kNearRow
 };
 __device__ __forceinline__ void fp_setup(int i, int nv, const int32_t* __restrict__ vlist,
                                          const int32_t* __restrict__ idx,
@@ -985,7 +1003,7 @@ __device__ __forceinline__ void fp_setup(int i, int nv, const int32_t* __restric
                                          FpSetup& s) {
 #pragma unroll
   for (int k = 0; k < 4; ++k) s.X[k] = s.Y[k] = 0;
-  s.n = 0; s.Uc = 1; s.Rc = 1; s.off = 0; s.u0 = 0; s.cnt = 0;
+  s.n = 0; s.Uc = 1; s.Rc = 1; s.off = 0; s.u0 = 0; s.cnt = 0; s.near = true;
   if (i >= nv) return;
   const float halfW = 0.5f * (float)p.W, halfH = 0.5f * (float)p.H;
   const int t = vlist[i];
@@ -1022,6 +1040,7 @@ __device__ __forceinline__ void fp_setup(int i, int nv, const int32_t* __restric
       s.Y[k] = snap(rot ? (tw - px) : py);
       xmin = min(xmin, s.X[k]);
       xmax = max(xmax, s.X[k]);
+      s.near = s.near && max(abs(s.X[k]), abs(s.Y[k])) <= kNearRow;
     }
   }
   s.n = n;
@@ -1032,15 +1051,32 @@ __device__ __forceinline__ void fp_setup(int i, int nv, const int32_t* __restric
   s.cnt = min(s.Uc - 1, max(0, xmax >> 8)) - s.u0 + 1;
 }
 
+// What the raster needs of a set-up entry, 48 bytes: the polygon (a triangle's
+// third vertex twice; 0 vertices: no columns) and `chart`: first profile entry,
+// rows | vertices << 25 | near << 28, columns, columns reached. Rows past 2^20,
+// which no snapped vertex reaches, are cut off.
+struct FpRecord {
+  int4 X, Y, chart;
+};
+__device__ __forceinline__ FpRecord fp_record(const FpSetup& s) {
+  const bool four = s.n > 3;
+  const int rows = min(s.Rc, 1 << 24);
+  return FpRecord{make_int4(s.X[0], s.X[1], s.X[2], four ? s.X[3] : s.X[2]),
+                  make_int4(s.Y[0], s.Y[1], s.Y[2], four ? s.Y[3] : s.Y[2]),
+                  make_int4(s.off, rows | s.n << 25 | (int)s.near << 28, s.Uc, s.cnt)};
+}
+
 // Count: the (triangle, column) items of every group of 64 consecutive
 // visible-list entries (group g = entries 64 g .. 64 g + 63), one wave per
-// group; the blocks past the groups clear the profile.
+// group; the blocks past the groups clear the profile. The entries' records go
+// to `rec` (the large-footprint queue's memory, free until the occupancy),
+// unless there are more than rec_cap of them.
 __global__ __launch_bounds__(kBlock) void k_fp_count(
     const int32_t* __restrict__ vlist, const int32_t* __restrict__ idx,
     const float* __restrict__ pos, const int32_t* __restrict__ cot,
     const fa_chart* __restrict__ charts, const int32_t* __restrict__ fp_off,
     unsigned long long* __restrict__ group_items, int2* __restrict__ prof, unsigned count_blocks,
-    FrameParams p, const FrameState* __restrict__ stp) {
+    int4* __restrict__ rec, int rec_cap, FrameParams p, const FrameState* __restrict__ stp) {
   if (stp->status != FA_OK) return;
   if (blockIdx.x >= count_blocks) {
     const int ncol = stp->fp_columns;
@@ -1056,7 +1092,14 @@ __global__ __launch_bounds__(kBlock) void k_fp_count(
   for (int g = (int)(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave); g < groups;
        g += nw) {
     FpSetup s;
-    fp_setup(g * kWave + lane_id(), nv, vlist, idx, pos, cot, charts, fp_off, p, s);
+    const int i = g * kWave + lane_id();
+    fp_setup(i, nv, vlist, idx, pos, cot, charts, fp_off, p, s);
+    if (i < nv && nv <= rec_cap) {
+      const FpRecord r = fp_record(s);
+      rec[3 * (int64_t)i] = r.X;
+      rec[3 * (int64_t)i + 1] = r.Y;
+      rec[3 * (int64_t)i + 2] = r.chart;
+    }
     const int tot = wave_sum<int>(s.cnt);
     if (lane_id() == 0) group_items[g] = (unsigned long long)tot;
   }
@@ -1087,22 +1130,41 @@ __global__ __launch_bounds__(1024) void k_fp_scan(unsigned long long* __restrict
 // waves (a wave's share is a contiguous range of the groups' items), so the
 // columns of a few large triangles no longer load one wave. A wave finds the
 // group holding its first item by a 64-way search over the group prefix and
-// walks forward; for each group it touches, its lanes set up the group's 64
-// entries again and the wave takes that group's items in its range 64 at a
-// time (owner found by a binary search over the inclusive column counts).
-// Neighbouring triangles share columns: when the columns of a wave's items
-// of a group span fewer than kFpWin profile entries they are reduced in a
-// per-wave LDS window and flushed with one pair of global atomics per
-// touched entry.
-constexpr int kFpWin = 1024;
+// walks forward; of each group it touches, its lanes fetch the 64 records into
+// LDS (first entry and column relative to the items) and the wave takes that
+// group's items in its range 64 at a time. The owner of an item is the last one
+// whose items start at or before it: a mark where each starts and a prefix
+// maximum.
+// An item looks for the sides that cross the left border of its column and
+// takes those crossing the right one from the lane after it, which owns the
+// next column.
+// Neighbouring triangles share columns: the workgroup reduces kFpWin profile
+// entries around those of its first items in LDS and flushes each touched one
+// with one pair of global atomics; entries elsewhere (of other charts, mostly)
+// take global atomics, after a look whether they would change anything (values
+// only ever move one way, so an old one is safe to look at).
+// Bound by the items' vector instructions and by the global atomics. Its
+// workgroups are as many as the chip holds at once, whatever the mesh: few
+// triangles may have many columns. With each item trying every side on both
+// borders in 64-bit arithmetic, the set-up repeated, the owner's values fetched
+// lane by lane and a window per wave and group, 2.2M-triangle frames (131k
+// visible) took 85 us and one of 1500 triangles 28 or more; now 25 and 8, and
+// the records add 4 to the count.
+constexpr int kFpWin = 2048;
+constexpr unsigned kFpGrid = 5 * 256;
 
 __global__ __launch_bounds__(kBlock) void k_fp_raster(
     const int32_t* __restrict__ vlist, const int32_t* __restrict__ idx,
     const float* __restrict__ pos, const int32_t* __restrict__ cot,
     const fa_chart* __restrict__ charts, const int32_t* __restrict__ fp_off,
-    const unsigned long long* __restrict__ group_first, int2* __restrict__ prof, FrameParams p,
+    const unsigned long long* __restrict__ group_first, int2* __restrict__ prof,
+    const int4* __restrict__ rec, int rec_cap, FrameParams p,
     const FrameState* __restrict__ stp) {
-  __shared__ int2 win_all[kBlock / kWave][kFpWin];
+  __shared__ int2 win[kFpWin];
+  __shared__ int span_lo[kBlock / kWave], span_hi[kBlock / kWave];
+  __shared__ int4 all_x[kBlock / kWave][kWave], all_y[kBlock / kWave][kWave];
+  __shared__ int4 all_c[kBlock / kWave][kWave];
+  __shared__ uint32_t all_mark[kBlock / kWave][kWave];
   if (stp->status != FA_OK) return;
   const int nv = stp->visible;
   const int groups = (nv + kWave - 1) / kWave;
@@ -1111,117 +1173,182 @@ __global__ __launch_bounds__(kBlock) void k_fp_raster(
   const int lane = lane_id();
   const unsigned long long nwaves = gridDim.x * (blockDim.x / kWave);
   const unsigned long long wave = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-  const unsigned long long per = (total + nwaves - 1) / nwaves;
+  const unsigned long long per = max((total + nwaves - 1) / nwaves, (unsigned long long)kWave);
   const unsigned long long k0 = min(total, wave * per), k1 = min(total, k0 + per);
-  if (k0 >= k1) return;
-  int2* win = win_all[threadIdx.x / kWave];
-  for (int e = lane; e < kFpWin; e += kWave) win[e] = make_int2(INT_MAX, -1);
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  // last group whose first item <= k0 (group 0 starts at item 0)
-  int lo = 0, hi = groups;
-  while (hi - lo > 1) {
-    const int step = (hi - lo + kWave - 1) / kWave;
-    const int probe = lo + lane * step;
-    const bool le = probe < hi && group_first[probe] <= k0;
-    const int c = __popcll(__ballot(le));
-    lo += (c - 1) * step;
-    hi = min(hi, lo + step);
-  }
-  for (int g = lo; g < groups; ++g) {
-    const unsigned long long gfirst = group_first[g];
-    if (gfirst >= k1) break;
-    FpSetup s;
-    fp_setup(g * kWave + lane, nv, vlist, idx, pos, cot, charts, fp_off, p, s);
-    const int incl = wave_incl_scan<int>(s.cnt);
-    const int gtot = __shfl(incl, kWave - 1, kWave);
-    // this wave's items of the group: [ia, ib) in group-local numbering
-    const int ia = (int)(k0 > gfirst ? k0 - gfirst : 0ull);
-    const int ib = (int)min<unsigned long long>((unsigned long long)gtot, k1 - gfirst);
-    if (ia >= ib) continue;
-    // profile entries this wave's items of the group touch: [elo, ehi] (a
-    // lane's items are [incl - cnt, incl), its columns from u0 on)
-    const int st0 = incl - s.cnt;
+  const int w = threadIdx.x / kWave;
+  int4* lds_x = all_x[w];
+  int4* lds_y = all_y[w];
+  int4* lds_c = all_c[w];
+  uint32_t* mark = all_mark[w];
+  auto settle = [] {  // LDS writes of the wave's lanes before its later reads
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
+  for (int e = threadIdx.x; e < kFpWin; e += kBlock) win[e] = make_int2(INT_MAX, -1);
+  // this wave's items of a group: [ia, ib) in group-local numbering; a lane's
+  // are [st0, st0 + cnt)
+  int ia = 0, ib = 0, cnt = 0, st0 = 0;
+  auto fetch = [&](int g, unsigned long long gfirst, int& elo, int& ehi) {
+    FpRecord r{make_int4(0, 0, 0, 0), make_int4(0, 0, 0, 0), make_int4(0, 0, 0, 0)};
+    const int i = g * kWave + lane;
+    if (nv <= rec_cap) {
+      if (i < nv)
+        r = FpRecord{rec[3 * (int64_t)i], rec[3 * (int64_t)i + 1], rec[3 * (int64_t)i + 2]};
+    } else {
+      FpSetup s;
+      fp_setup(i, nv, vlist, idx, pos, cot, charts, fp_off, p, s);
+      r = fp_record(s);
+    }
+    cnt = r.chart.w;
+    const int u0 = min(r.chart.z - 1, max(0, min(min(r.X.x, r.X.y), min(r.X.z, r.X.w)) >> 8));
+    const int incl = (int)wave_incl_scan_dpp((uint32_t)cnt);
+    const int gtot = __builtin_amdgcn_readlane(incl, kWave - 1);
+    ia = (int)(k0 > gfirst ? k0 - gfirst : 0ull);
+    ib = (int)min<unsigned long long>((unsigned long long)gtot, k1 - gfirst);
+    st0 = incl - cnt;
     const int ja = max(st0, ia), jb = min(incl, ib) - 1;
-    const bool mine = s.cnt > 0 && ja <= jb;
-    const int elo = wave_min<int>(mine ? s.off + s.u0 + (ja - st0) : INT_MAX);
-    const int ehi = wave_max<int>(mine ? s.off + s.u0 + (jb - st0) : INT_MIN);
-    const bool use_win = ehi - elo < kFpWin;
+    const bool mine = cnt > 0 && ja <= jb;
+    elo = mine ? r.chart.x + u0 + (ja - st0) : INT_MAX;
+    ehi = mine ? r.chart.x + u0 + (jb - st0) : INT_MIN;
+    lds_x[lane] = r.X;
+    lds_y[lane] = r.Y;
+    lds_c[lane] = make_int4(r.chart.x + u0 - st0, u0 - st0, r.chart.y, r.chart.z - 1);
+  };
+  // last group whose first item <= k0 (group 0 starts at item 0)
+  int g = 0, elo = INT_MAX, ehi = INT_MIN;
+  if (k0 < k1) {
+    int hi = groups;
+    while (hi - g > 1) {
+      const int step = (hi - g + kWave - 1) / kWave;
+      const int probe = g + lane * step;
+      const bool le = probe < hi && group_first[probe] <= k0;
+      const int c = __popcll(__ballot(le));
+      g += (c - 1) * step;
+      hi = min(hi, g + step);
+    }
+    fetch(g, group_first[g], elo, ehi);
+    elo = wave_min<int>(elo);
+    ehi = wave_max<int>(ehi);
+  }
+  if (lane == 0) {
+    span_lo[w] = elo;
+    span_hi[w] = ehi;
+  }
+  __syncthreads();
+  // the window: from the lowest entry of the waves' first items, or, if they
+  // span more, around those of the first wave
+  int from = span_lo[0], to = span_hi[0];
+#pragma unroll
+  for (int k = 1; k < kBlock / kWave; ++k) {
+    from = min(from, span_lo[k]);
+    to = max(to, span_hi[k]);
+  }
+  if (to - from >= kFpWin) from = (span_lo[0] + span_hi[0]) / 2 - kFpWin / 2;
+  from = max(from - 1, 0);  // (an item may reach into the entry before its own)
+  while (k0 < k1) {
     for (int w0 = ia; w0 < ib; w0 += kWave) {
       const int item = w0 + lane;
-      int o = 0;  // owner: the first lane whose inclusive count exceeds item
+      mark[lane] = 0u;
+      settle();
+      if (cnt > 0 && st0 + cnt > w0 && st0 < w0 + kWave) mark[max(st0 - w0, 0)] = (uint32_t)lane + 1u;
+      settle();
+      const int o = (int)wave_incl_max_dpp(mark[lane]) - 1;  // (item w0 has an owner)
+      const int4 vx = lds_x[o], vy = lds_y[o], vc = lds_c[o];
+      const int32_t PX[4] = {vx.x, vx.y, vx.z, vx.w}, PY[4] = {vy.x, vy.y, vy.z, vy.w};
+      const int u = vc.y + item, entry = vc.x + item;
+      const int rows = vc.z & ((1 << 25) - 1), on = vc.z >> 25 & 7;
+      const bool near = vc.z >> 28 & 1;
+      const bool here = item < ib;
+      const bool open_l = u == 0, open_r = u == vc.w;
+      const int32_t sl = 256 * u, sr = sl + 256;
+      // rows of the sides that cross the column's left border: a triangle has
+      // at most two there, one going right and one going left; of a
+      // near-clipped quadrilateral, which rounding may bend, all four are tried
+      int32_t clo = INT_MAX, chi = INT_MIN;
+      auto cross = [&](int32_t px, int32_t py, int32_t qx, int32_t qy) {
+        const int32_t r = near ? crossing_row_near(px, py, qx, qy, sl)
+                               : crossing_row(px, py, qx, qy, sl);
+        clo = min(clo, r);
+        chi = max(chi, r);
+      };
+      if (here && !open_l && on == 3) {
 #pragma unroll
-      for (int step = 32; step > 0; step >>= 1)
-        if (__shfl(incl, o + step - 1, kWave) <= item) o += step;
-      o = min(o, kWave - 1);
-      const int on = __shfl(s.n, o, kWave);
-      int32_t PX[4], PY[4];
+        for (int h = 0; h < 2; ++h) {
+          int32_t px = 0, py = 0, qx = 0, qy = 0;
+          bool has = false;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        PX[k] = __shfl(s.X[k], o, kWave);
-        PY[k] = __shfl(s.Y[k], o, kWave);
+          for (int k = 0; k < 3; ++k) {
+            const int m = k == 2 ? 0 : k + 1;
+            if (h ? PX[m] < sl && sl < PX[k] : PX[k] < sl && sl < PX[m]) {
+              px = PX[k]; py = PY[k];
+              qx = PX[m]; qy = PY[m];
+              has = true;
+            }
+          }
+          if (has) cross(px, py, qx, qy);
+        }
+      } else if (here && !open_l) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int m = k == 3 ? 0 : k + 1;
+          if (k < on && min(PX[k], PX[m]) < sl && sl < max(PX[k], PX[m]))
+            cross(PX[k], PY[k], PX[m], PY[m]);
+        }
       }
-      const int oUc = __shfl(s.Uc, o, kWave), oRc = __shfl(s.Rc, o, kWave);
-      const int ooff = __shfl(s.off, o, kWave);
-      const int u =
-          __shfl(s.u0, o, kWave) + item - (__shfl(incl, o, kWave) - __shfl(s.cnt, o, kWave));
-      if (item >= ib) continue;
-      const bool open_l = u == 0, open_r = u == oUc - 1;
-      const int64_t sl = 256 * (int64_t)u, sr = sl + 256;
-      int32_t rlo = INT_MAX, rhi = INT_MIN;
+      // the column before takes them too (they cross its right border): it is
+      // the lane before's, but for the first lane
+      const int32_t nlo = __shfl_down(clo, 1, kWave), nhi = __shfl_down(chi, 1, kWave);
+      const int no = __shfl_down(o, 1, kWave);
+      const bool next = lane < kWave - 1 && item + 1 < ib && no == o;
+      if (!here) continue;
+      int32_t rlo = clo, rhi = chi;
+      if (next) {
+        rlo = min(rlo, nlo);
+        rhi = max(rhi, nhi);
+      }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        if (k < on && (open_l || PX[k] >= sl) && (open_r || PX[k] <= sr)) {
+        if ((open_l || PX[k] >= sl) && (open_r || PX[k] <= sr)) {
           rlo = min(rlo, PY[k] >> 8);
           rhi = max(rhi, PY[k] >> 8);
         }
       }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (k >= on) continue;
-        // next vertex with constant indices: k + 1, or vertex 0 after the last
-        const bool wrap = k + 1 >= on;
-        const int64_t Px = PX[k], Py = PY[k];
-        const int64_t Qx = wrap ? PX[0] : PX[k < 3 ? k + 1 : 0];
-        const int64_t Qy = wrap ? PY[0] : PY[k < 3 ? k + 1 : 0];
-        if (Px == Qx) continue;
-        const int64_t lo2 = min(Px, Qx), hi2 = max(Px, Qx);
-        if (!open_l && lo2 < sl && sl < hi2) {
-          const int32_t r = crossing_row(Px, Py, Qx, Qy, sl);
-          rlo = min(rlo, r);
-          rhi = max(rhi, r);
+      auto put = [&](int e, int32_t lo_row, int32_t hi_row) {
+        if (lo_row > hi_row) return;
+        lo_row = min(rows - 1, max(0, lo_row));
+        hi_row = min(rows - 1, max(0, hi_row));
+        const int at = e - from;
+        if (at >= 0 && at < kFpWin) {
+          // (scoped to the workgroup, or the compiler joins them with the
+          // global ones below into flat atomics)
+          __hip_atomic_fetch_min(&win[at].x, lo_row, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_max(&win[at].y, hi_row, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+        } else {
+          const int32_t x = __hip_atomic_load(&prof[e].x, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_WORKGROUP);
+          const int32_t y = __hip_atomic_load(&prof[e].y, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (lo_row < x) atomicMin(&prof[e].x, lo_row);
+          if (hi_row > y) atomicMax(&prof[e].y, hi_row);
         }
-        if (!open_r && lo2 < sr && sr < hi2) {
-          const int32_t r = crossing_row(Px, Py, Qx, Qy, sr);
-          rlo = min(rlo, r);
-          rhi = max(rhi, r);
-        }
-      }
-      if (rlo > rhi) continue;
-      rlo = min(oRc - 1, max(0, rlo));
-      rhi = min(oRc - 1, max(0, rhi));
-      if (use_win) {
-        atomicMin(&win[ooff + u - elo].x, rlo);
-        atomicMax(&win[ooff + u - elo].y, rhi);
-      } else {
-        atomicMin(&prof[ooff + u].x, rlo);
-        atomicMax(&prof[ooff + u].y, rhi);
-      }
+      };
+      put(entry, rlo, rhi);
+      if (lane == 0) put(entry - 1, clo, chi);
     }
-    if (use_win) {
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      for (int e = lane; e <= ehi - elo; e += kWave) {
-        const int2 v = win[e];
-        if (v.y >= 0) {
-          atomicMin(&prof[elo + e].x, v.x);
-          atomicMax(&prof[elo + e].y, v.y);
-          win[e] = make_int2(INT_MAX, -1);
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
+    settle();
+    if (++g >= groups) break;
+    const unsigned long long gfirst = group_first[g];
+    if (gfirst >= k1) break;
+    fetch(g, gfirst, elo, ehi);
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < kFpWin; e += kBlock) {
+    const int2 v = win[e];
+    if (v.y < 0) continue;
+    atomicMin(&prof[from + e].x, v.x);
+    atomicMax(&prof[from + e].y, v.y);
   }
 }
 }  // namespace
@@ -1229,19 +1356,22 @@ __global__ __launch_bounds__(kBlock) void k_fp_raster(
 hipError_t launch_footprint(const int32_t* idx, int64_t T, const FrameParams& p, const Work& w,
                             const int32_t* cot, const fa_chart* charts, Marker& mk,
                             hipStream_t st) {
+  const int rec_cap = (int)std::min<int64_t>(2 * T, kBigCap);  // (three int4 each)
   if (p.fp_cap > 0) {
     // one wave per group of 64 entries, then the blocks that clear the profile
     const unsigned cb = (unsigned)std::max<int64_t>(
         1, std::min<int64_t>((T + kBlock - 1) / kBlock, 2048));
     const unsigned clear = (unsigned)std::min<int64_t>(1024, (p.fp_cap + kBlock - 1) / kBlock);
     k_fp_count<<<cb + clear, kBlock, 0, st>>>(w.vlist, idx, w.pos, cot, charts, w.fp_off,
-                                              w.fp_group, w.fp_prof, cb, p, w.state);
+                                              w.fp_group, w.fp_prof, cb, w.big_fp, rec_cap, p,
+                                              w.state);
   }
   mk(st);
   if (p.fp_cap > 0 && T > 0) {
     k_fp_scan<<<1, 1024, 0, st>>>(w.fp_group, w.state);
-    k_fp_raster<<<visible_grid(T), kBlock, 0, st>>>(w.vlist, idx, w.pos, cot, charts, w.fp_off,
-                                                    w.fp_group, w.fp_prof, p, w.state);
+    k_fp_raster<<<kFpGrid, kBlock, 0, st>>>(w.vlist, idx, w.pos, cot, charts, w.fp_off,
+                                                    w.fp_group, w.fp_prof, w.big_fp, rec_cap, p,
+                                                    w.state);
   }
   mk(st);
   return hipGetLastError();

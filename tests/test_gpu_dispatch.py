@@ -103,6 +103,35 @@ def test_occupancy_sides(n, per, omega):
     compare(check(f), oracle.build_frame(f))
 
 
+# Footprint push: profiles from entries of one triangle to whole groups of 64,
+# of charts from a few columns to more than a window, charts over and under the
+# width that a whole workgroup pushes, gutters of 1 to 5, and lists longer than
+# the records' memory (more than 2^20 entries are set up again).
+@pytest.mark.parametrize("owners,omega,gutter", [
+    (np.arange(1), 256, 1), (np.arange(63), 512, 1), (np.arange(200) // 3, 1024, 1),
+    (np.arange(6) // 3, 4096, 2), (np.arange(3), 8192, 5), (np.arange(40) // 5, 8192, 3),
+    (np.arange(5000) // 2, 4096, 1)])
+def test_footprint_sizes(owners, omega, gutter):
+    f = fans(owners, seed=len(owners), atlas_size=omega, width=3840, height=2160)
+    g = check(f, gutter=gutter, flags=4)
+    compare(g, oracle.build_frame(f, gutter=gutter, footprint=True))
+
+
+def test_footprint_long_list():
+    n = 730
+    y, x = np.mgrid[0:n + 1, 0:n + 1] / n * 2 - 1
+    pos = np.stack([x, y, 0.1 * np.sin(5 * x) * np.cos(4 * y)], -1).reshape(-1, 3)
+    v = (np.arange(n)[:, None] * (n + 1) + np.arange(n)).reshape(-1)
+    tris = np.stack([v, v + 1, v + n + 2, v, v + n + 2, v + n + 1], 1).reshape(-1, 3)
+    assert len(tris) > 1 << 20
+    cam = scenes.make_camera((0.0, 0.0, 2.5), (0.0, 0.0, 0.0), 1920, 1080, 0.05, 100.0,
+                             up=(0, 1, 0))
+    f = scenes.Frame("long list", pos.astype(np.float32), tris.astype(np.int32),
+                     np.ones(len(tris), np.uint8), cam.view_proj, 1920, 1080, 1024, 1.0, 992,
+                     cam.eye, cam.near, 0)
+    compare(check(f, flags=4), oracle.build_frame(f, footprint=True))
+
+
 def _uniform(n, lo, hi, seed=0):
     return np.random.default_rng(seed).uniform(lo, hi, (n, 2))
 
