@@ -530,8 +530,10 @@ __device__ __forceinline__ void k_uf_local_vertex_body(const int32_t* __restrict
   for (int k = 0; k < kPer; ++k) {
     const int i = threadIdx.x + k * NT;
 #pragma unroll
-    for (int e = 0; e < 3; ++e) vk[k][e] = i < cnt ? idx[3 * (int64_t)tk[k] + e] : 0;
+    for (int e = 0; e < 3; ++e) vk[k][e] = 0;
     if (i < cnt) {
+      const int3 v = reinterpret_cast<const int3*>(idx)[tk[k]];
+      vk[k][0] = v.x; vk[k][1] = v.y; vk[k][2] = v.z;
       lv[i] = tk[k];
       lp[i] = i;
     }
@@ -1227,107 +1229,111 @@ __device__ __forceinline__ void k_gather_boxes_body(
     return;
   }
   if (st->status != FA_OK) return;
-  const int64_t base = (int64_t)blockIdx.x * per;
   for (int i = threadIdx.x; i < kSlots; i += blockDim.x) {
     skey[i] = -1;
     sbox[0][i] = sbox[1][i] = 0xFFFFFFFFu;
     sbox[2][i] = sbox[3][i] = 0u;
   }
   __syncthreads();
-  int tv[kGatherItems], cv[kGatherItems], vi[kGatherItems][3];
-  float4 q[kGatherItems][3];
+  for (int64_t blk = blockIdx.x; blk < active; blk += gridDim.x) {
+    int tv[kGatherItems], cv[kGatherItems], vi[kGatherItems][3];
+    float4 q[kGatherItems][3];
 #pragma unroll
-  for (int k = 0; k < kGatherItems; ++k) {
-    const int64_t i = base + (int64_t)k * kGatherBlock + threadIdx.x;
-    tv[k] = i < nv ? vlist[i] : -1;
-  }
-#pragma unroll
-  for (int k = 0; k < kGatherItems; ++k)
-    cv[k] = tv[k] < 0 ? 0 : labelled ? tv[k] : aload(&parent[tv[k]]);
-#pragma unroll
-  for (int k = 0; k < kGatherItems; ++k) {
-    const int t = max(tv[k], 0);
-    cv[k] = tv[k] >= 0 ? cot[cv[k]] : -1;
-#pragma unroll
-    for (int e = 0; e < 3; ++e) vi[k][e] = tv[k] >= 0 ? idx[3 * (int64_t)t + e] : 0;
-  }
-#pragma unroll
-  for (int k = 0; k < kGatherItems; ++k)
-#pragma unroll
-    for (int e = 0; e < 3; ++e) q[k][e] = clip_of(pos, vi[k][e], p);
-  // items are taken from slot 0 and shifted down after each one: constant
-  // indices keep the arrays in registers (the clipping body is too large to
-  // unroll, and a runtime index would move them to scratch memory)
-  for (int k = 0; k < kGatherItems; ++k) {
-    const bool valid = tv[0] >= 0;
-    const int c = cv[0];
-    bool has = false;
-    float4 box = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (valid) {
-      if (labelled) {
-        // (chart_of_tri and chart_of_vert are written)
-      } else if (p.flags & FA_FLAG_EDGE_ONLY_CHARTS) {
-        cot[tv[0]] = c;
-        // a vertex may touch several edge-connected charts: keep the smallest
-        // (chart_of_vert starts at -1, the largest unsigned value)
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-          atomicMin(reinterpret_cast<uint32_t*>(&cov[vi[0][e]]), (uint32_t)c);
-      } else {
-        cot[tv[0]] = c;
-        cov[vi[0][0]] = c;
-        cov[vi[0][1]] = c;
-        cov[vi[0][2]] = c;
-      }
-      has = triangle_ndc_box(q[0][0], q[0][1], q[0][2], !(p.flags & FA_FLAG_NO_SIDE_CLIP), box);
+    for (int k = 0; k < kGatherItems; ++k) {
+      const int64_t i = blk * per + (int64_t)k * kGatherBlock + threadIdx.x;
+      tv[k] = i < nv ? vlist[i] : -1;
     }
 #pragma unroll
-    for (int m = 0; m + 1 < kGatherItems; ++m) {
-      tv[m] = tv[m + 1];
-      cv[m] = cv[m + 1];
+    for (int k = 0; k < kGatherItems; ++k)
+      cv[k] = tv[k] < 0 ? 0 : labelled ? tv[k] : aload(&parent[tv[k]]);
 #pragma unroll
-      for (int e = 0; e < 3; ++e) {
-        vi[m][e] = vi[m + 1][e];
-        q[m][e] = q[m + 1][e];
+    for (int k = 0; k < kGatherItems; ++k) {
+      const int t = max(tv[k], 0);
+      cv[k] = tv[k] >= 0 ? cot[cv[k]] : -1;
+      vi[k][0] = vi[k][1] = vi[k][2] = 0;
+      if (tv[k] >= 0) {
+        const int3 v = reinterpret_cast<const int3*>(idx)[t];
+        vi[k][0] = v.x; vi[k][1] = v.y; vi[k][2] = v.z;
       }
     }
-    uint32_t e0 = ord_of(box.x), e1 = ord_of(box.y), e2 = ord_of(box.z), e3 = ord_of(box.w);
-    bool put = has;  // this lane enters its box (its own or its group's) into the table
-    unsigned long long todo = __ballot(has);
-    while (todo) {
-      const int leader = __ffsll((long long)todo) - 1;
-      const int cl = __builtin_amdgcn_readlane(c, leader);
-      const bool mine = has && c == cl;
-      const unsigned long long grp = __ballot(mine);
-      if (__popcll(grp) >= kGatherGroup) {
-        const uint32_t a0 = wave_min_dpp(mine ? e0 : 0xFFFFFFFFu);
-        const uint32_t a1 = wave_min_dpp(mine ? e1 : 0xFFFFFFFFu);
-        const uint32_t a2 = ~wave_min_dpp(mine ? ~e2 : 0xFFFFFFFFu);
-        const uint32_t a3 = ~wave_min_dpp(mine ? ~e3 : 0xFFFFFFFFu);
-        if (mine) {
-          e0 = a0; e1 = a1; e2 = a2; e3 = a3;
-          put = lane_id() == leader;
+#pragma unroll
+    for (int k = 0; k < kGatherItems; ++k)
+#pragma unroll
+      for (int e = 0; e < 3; ++e) q[k][e] = clip_of(pos, vi[k][e], p);
+    // items are taken from slot 0 and shifted down after each one: constant
+    // indices keep the arrays in registers (the clipping body is too large to
+    // unroll, and a runtime index would move them to scratch memory)
+    for (int k = 0; k < kGatherItems; ++k) {
+      const bool valid = tv[0] >= 0;
+      const int c = cv[0];
+      bool has = false;
+      float4 box = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (valid) {
+        if (labelled) {
+          // (chart_of_tri and chart_of_vert are written)
+        } else if (p.flags & FA_FLAG_EDGE_ONLY_CHARTS) {
+          cot[tv[0]] = c;
+          // a vertex may touch several edge-connected charts: keep the smallest
+          // (chart_of_vert starts at -1, the largest unsigned value)
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            atomicMin(reinterpret_cast<uint32_t*>(&cov[vi[0][e]]), (uint32_t)c);
+        } else {
+          cot[tv[0]] = c;
+          cov[vi[0][0]] = c;
+          cov[vi[0][1]] = c;
+          cov[vi[0][2]] = c;
+        }
+        has = triangle_ndc_box(q[0][0], q[0][1], q[0][2], !(p.flags & FA_FLAG_NO_SIDE_CLIP), box);
+      }
+#pragma unroll
+      for (int m = 0; m + 1 < kGatherItems; ++m) {
+        tv[m] = tv[m + 1];
+        cv[m] = cv[m + 1];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          vi[m][e] = vi[m + 1][e];
+          q[m][e] = q[m + 1][e];
         }
       }
-      todo &= ~grp;
-    }
-    if (put) {
-      int h = c & (kSlots - 1), slot = -1;
-      for (int probe = 0; probe < kSlotProbes; ++probe) {
-        const int prev = atomicCAS(&skey[h], -1, c);
-        if (prev == -1 || prev == c) { slot = h; break; }
-        h = (h + 1) & (kSlots - 1);
+      uint32_t e0 = ord_of(box.x), e1 = ord_of(box.y), e2 = ord_of(box.z), e3 = ord_of(box.w);
+      bool put = has;  // this lane enters its box (its own or its group's) into the table
+      unsigned long long todo = __ballot(has);
+      while (todo) {
+        const int leader = __ffsll((long long)todo) - 1;
+        const int cl = __builtin_amdgcn_readlane(c, leader);
+        const bool mine = has && c == cl;
+        const unsigned long long grp = __ballot(mine);
+        if (__popcll(grp) >= kGatherGroup) {
+          const uint32_t a0 = wave_min_dpp(mine ? e0 : 0xFFFFFFFFu);
+          const uint32_t a1 = wave_min_dpp(mine ? e1 : 0xFFFFFFFFu);
+          const uint32_t a2 = ~wave_min_dpp(mine ? ~e2 : 0xFFFFFFFFu);
+          const uint32_t a3 = ~wave_min_dpp(mine ? ~e3 : 0xFFFFFFFFu);
+          if (mine) {
+            e0 = a0; e1 = a1; e2 = a2; e3 = a3;
+            put = lane_id() == leader;
+          }
+        }
+        todo &= ~grp;
       }
-      if (slot >= 0) {
-        atomicMin(&sbox[0][slot], e0);
-        atomicMin(&sbox[1][slot], e1);
-        atomicMax(&sbox[2][slot], e2);
-        atomicMax(&sbox[3][slot], e3);
-      } else {
-        atomicMin(&accum[4 * c + 0], e0);
-        atomicMin(&accum[4 * c + 1], e1);
-        atomicMax(&accum[4 * c + 2], e2);
-        atomicMax(&accum[4 * c + 3], e3);
+      if (put) {
+        int h = c & (kSlots - 1), slot = -1;
+        for (int probe = 0; probe < kSlotProbes; ++probe) {
+          const int prev = atomicCAS(&skey[h], -1, c);
+          if (prev == -1 || prev == c) { slot = h; break; }
+          h = (h + 1) & (kSlots - 1);
+        }
+        if (slot >= 0) {
+          atomicMin(&sbox[0][slot], e0);
+          atomicMin(&sbox[1][slot], e1);
+          atomicMax(&sbox[2][slot], e2);
+          atomicMax(&sbox[3][slot], e3);
+        } else {
+          atomicMin(&accum[4 * c + 0], e0);
+          atomicMin(&accum[4 * c + 1], e1);
+          atomicMax(&accum[4 * c + 2], e2);
+          atomicMax(&accum[4 * c + 3], e3);
+        }
       }
     }
   }
@@ -1405,6 +1411,11 @@ __global__ __launch_bounds__(kFrontThreads) void k_front_b(const BatchView* __re
 }
 
 }  // namespace
+
+unsigned view_groups(int64_t T, int64_t items, int threads, int n) {
+  const int64_t most = std::max<int64_t>(kViewThreads / ((int64_t)threads * n), 16);
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>((T + items - 1) / items, most));
+}
 
 unsigned visible_grid(int64_t T) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>((T + kBlock - 1) / kBlock, 2048));
@@ -1572,12 +1583,12 @@ hipError_t launch_charts_batched(const BatchView* dev, int n, const float* pos,
     k_vis_compact_b<<<dim3(tt, n), kBlock, 0, st>>>(dev, T);
     k_uf_local_vertex_b<<<dim3(std::max(1u, grid_for(T, 2048)) + kFillGroups, n), 1024, 0, st>>>(
         dev, idx);
-    k_uf_vertex_hook_b<<<dim3(std::max(1u, visible_grid(T) * kBlock / kHookThreads), n),
-                         kHookThreads, 0, st>>>(dev, idx);
+    k_uf_vertex_hook_b<<<dim3(view_groups(T, kHookThreads, kHookThreads, n), n), kHookThreads, 0,
+                         st>>>(dev, idx);
     k_uf_flatten_count_b<<<dim3(vt, n), kBlock, 0, st>>>(dev);
     k_assign_roots_b<<<dim3(vt, n), kBlock, 0, st>>>(dev);
-    k_gather_boxes_b<<<dim3(grid_for(T, kGatherBlock * kGatherItems), n), kGatherBlock, 0, st>>>(
-        dev, idx, false);
+    k_gather_boxes_b<<<dim3(view_groups(T, kGatherBlock * kGatherItems, kGatherBlock, n), n),
+                       kGatherBlock, 0, st>>>(dev, idx, false);
   }
   return hipGetLastError();
 }

@@ -1388,13 +1388,16 @@ hipError_t launch_occupancy_batched(const BatchView* dev, int n, const int32_t* 
                                     hipStream_t st) {
   if (n <= 0) return hipSuccess;
   const uint32_t cap = (uint32_t)std::min<int64_t>(2 * std::max<int64_t>(T, 1), kBigCap);
-  const unsigned occ_blocks = T > 0 ? visible_grid(T) : 0;
+  const unsigned occ_blocks = T > 0 ? view_groups(T, kOccSmallBlock, kOccSmallBlock, n) : 0;
   const unsigned uv_blocks = (unsigned)((V + kOccSmallBlock * kUvPerBatch - 1) /
                                          (kOccSmallBlock * kUvPerBatch));
   if (occ_blocks + uv_blocks > 0)
     k_occ_small_b<<<dim3(occ_blocks + uv_blocks, n), kOccSmallBlock, 0, st>>>(
         dev, idx, cap, small_texels, lane_texels, occ_blocks, V);
-  if (T > 0) k_occ_big_b<<<dim3(kOccBigGrid, n), kBlock, 0, st>>>(dev, idx, cap);
+  if (T > 0)
+    // (half as many: each wave starts with a search)
+    k_occ_big_b<<<dim3(std::min<unsigned>(kOccBigGrid, kViewThreads / (2 * kBlock * n)), n),
+                  kBlock, 0, st>>>(dev, idx, cap);
   k_occ_count_meta_b<<<dim3(count_grid(max_omega), n), kCountBlock, 0, st>>>(dev);
   return hipGetLastError();
 }

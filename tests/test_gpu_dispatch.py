@@ -350,3 +350,37 @@ def test_front_over_capacity():
     m = out.to_numpy()["meta"]
     ctx.close()
     assert m["status"] == fa.FA_ERR_CAPACITY and m["num_charts"] == 40
+
+
+# In a batch the kernels over the visible list start a limited number of
+# workgroups per view and take several turns: 16 views with everything visible
+# against the same frames alone.
+def test_batch_turns():
+    fa = _fa()
+    n = 400
+    y, x = np.mgrid[0:n + 1, 0:n + 1] / n * 2 - 1
+    pos = np.stack([x, y, 0.2 * np.sin(9 * x) * np.cos(7 * y)], -1).reshape(-1, 3)
+    v = (np.arange(n)[:, None] * (n + 1) + np.arange(n)).reshape(-1)
+    tris = np.stack([v, v + 1, v + n + 2, v, v + n + 2, v + n + 1], 1).reshape(-1, 3)
+    T, V = len(tris), len(pos)
+    mesh = fa.Mesh(pos.astype(np.float32), tris.astype(np.int32), 993)
+    cams = [scenes.make_camera((0.3 * k - 2, 0.2 * k - 1, 2.0 + 0.1 * k), (0.0, 0.0, 0.0), 640, 360,
+                               0.05, 100.0, up=(0, 1, 0)) for k in range(16)]
+    rng = np.random.default_rng(4)
+    vis = [torch.as_tensor((rng.uniform(size=T) < (1.0 if k % 2 else 0.1 * k)).astype(np.uint8)
+                           ).cuda() for k in range(16)]
+    ctx = fa.Context(T, V, max_charts=65536, max_atlas=1024, max_views=16, tuning_table=None)
+    print("[gpu] batch of 16 views", flush=True)
+    outs = [ctx.outputs(mesh, 1024) for _ in cams]
+    ctx.build_atlas_batch(mesh, [(a, c.view_proj, 640, 360, 1024, 1.0) for a, c in zip(vis, cams)],
+                          outs)
+    torch.cuda.synchronize()
+    for a, c, o in zip(vis, cams, outs):
+        alone = ctx.build_atlas(mesh, a, c.view_proj, 640, 360, 1024, 1.0)
+        torch.cuda.synchronize()
+        g, h = o.to_numpy(), alone.to_numpy()
+        assert g["meta"] == h["meta"]
+        for k in ("chart_of_tri", "chart_of_vert", "occupancy", "candidates", "charts"):
+            assert np.array_equal(g[k], h[k]), k
+        assert np.array_equal(g["uv"].view(np.uint32), h["uv"].view(np.uint32))
+    ctx.close()
