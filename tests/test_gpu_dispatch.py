@@ -352,6 +352,41 @@ def test_front_over_capacity():
     assert m["status"] == fa.FA_ERR_CAPACITY and m["num_charts"] == 40
 
 
+# Edge-connected charts join tiles of consecutive visible triangles in LDS and
+# look for a neighbour where it is if nothing in between is hidden: grids whose
+# visible lists end around a tile, with none, a few and most triangles hidden.
+@pytest.mark.parametrize("tile", [2048, 4096, 8192])
+@pytest.mark.parametrize("count", [1, 2047, 2048, 2049, 8191, 8193, 20000])
+@pytest.mark.parametrize("hidden", [0.0, 0.02, 0.8])
+def test_edge_tiles(tile, count, hidden):
+    fa = _fa()
+    n = max(2, int(np.ceil(np.sqrt(count / (1.0 - hidden) / 2))) + 2)
+    y, x = np.mgrid[0:n + 1, 0:n + 1] / n * 2 - 1
+    pos = np.stack([x, y, 0.2 * np.sin(9 * x) * np.cos(7 * y)], -1).reshape(-1, 3)
+    v = (np.arange(n)[:, None] * (n + 1) + np.arange(n)).reshape(-1)
+    tris = np.stack([v, v + 1, v + n + 2, v, v + n + 2, v + n + 1], 1).reshape(-1, 3)
+    T = len(tris)
+    rng = np.random.default_rng(count)
+    keep = np.flatnonzero(rng.uniform(size=T) >= hidden)[:count]
+    vis = np.zeros(T, np.uint8)
+    vis[keep] = 1
+    cam = scenes.make_camera((0.0, 0.0, 2.5), (0.0, 0.0, 0.0), 1280, 720, 0.05, 100.0, up=(0, 1, 0))
+    f = scenes.Frame(f"edge tiles {count}", pos.astype(np.float32), tris.astype(np.int32), vis,
+                     cam.view_proj, 1280, 720, 2048, 1.0, 994, cam.eye, cam.near, 0)
+    print(f"[gpu] {f.name} hidden={hidden} tile={tile}", flush=True)
+    ctx = fa.Context(T, len(pos), max_charts=65536, max_atlas=2048, flags=2, tuning_table=None)
+    ctx.set_tuning(fa.FA_TUNE_UF_TILE, tile)
+    out = ctx.build_atlas(fa.Mesh(f.positions, f.indices, 994), torch.as_tensor(vis).cuda(),
+                          f.view_proj, 1280, 720, 2048, 1.0)
+    torch.cuda.synchronize()
+    g = out.to_numpy()
+    ctx.close()
+    r = oracle.build_frame(f, edge_only=True)
+    assert g["meta"]["status"] == r["status"] and g["meta"]["num_charts"] == r["num_charts"]
+    assert np.array_equal(g["chart_of_tri"], r["chart_of_tri"])
+    assert np.array_equal(g["charts"]["root_tri"], r["roots"])
+
+
 # In a batch the kernels over the visible list start a limited number of
 # workgroups per view and take several turns: 16 views with everything visible
 # against the same frames alone.
