@@ -231,7 +231,7 @@ __global__ void k_edge_runs(const unsigned long long* __restrict__ keys,
 // read, the indices of a bucket gathered (from the L2, mostly) and 4 bytes a
 // half-edge written. Six radix passes of 12-byte keys and values took 715 us
 // for 2.2M triangles, their 160 MB of buffers another 400 us to allocate and
-// free (1188 us in all for a scene that comes in); this way 110 and none (198 us).
+// free (1188 us in all for a scene that comes in); this way 92 and none (190 us).
 // A bucket above kAdjCap half-edges (a vertex with thousands of triangles, or
 // few of many vertices in use) sends the mesh to the sort.
 constexpr int kAdjTile = 2048;
@@ -285,14 +285,14 @@ __global__ __launch_bounds__(kAdjThreads) void k_adj_buckets(
   int bk[kPer][3];
   uint32_t at[kPer][3];
   bool bad = false;
+  int3 x[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k)
+    x[k] = reinterpret_cast<const int3*>(idx)[min(t0 + threadIdx.x + k * kAdjThreads, T - 1)];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     const int64_t t = t0 + threadIdx.x + k * kAdjThreads;
-    int v[3] = {0, 0, 0};
-    if (t < T) {
-#pragma unroll
-      for (int e = 0; e < 3; ++e) v[e] = idx[3 * t + e];
-    }
+    const int v[3] = {x[k].x, x[k].y, x[k].z};
 #pragma unroll
     for (int e = 0; e < 3; ++e) {
       const int a = v[e], c = v[e == 2 ? 0 : e + 1];
@@ -354,11 +354,16 @@ __global__ __launch_bounds__(1024) void k_adj_scan(uint32_t* __restrict__ next, 
   }
 }
 
-// The half-edges of one bucket matched by edge.
-__global__ __launch_bounds__(kAdjThreads) void k_adj_match(const int32_t* __restrict__ idx,
-                                                           const uint32_t* __restrict__ first,
-                                                           const uint32_t* __restrict__ half,
-                                                           int32_t* __restrict__ nbr) {
+// The half-edges of one bucket matched by edge, four a thread: the gathers of
+// their triangles' indices go out together, and the LDS holds two workgroups'
+// 32 waves (2.2M triangles: 62 us with eight a thread one after another, now
+// 45).
+constexpr int kMatchThreads = 1024;
+__global__ __launch_bounds__(kMatchThreads) void k_adj_match(const int32_t* __restrict__ idx,
+                                                             const uint32_t* __restrict__ first,
+                                                             const uint32_t* __restrict__ half,
+                                                             int32_t* __restrict__ nbr) {
+  constexpr int kPer = kAdjCap / kMatchThreads;
   __shared__ uint32_t head[kAdjSlots];
   __shared__ uint2 key[kAdjCap];
   __shared__ uint32_t hs[kAdjCap];
@@ -367,34 +372,52 @@ __global__ __launch_bounds__(kAdjThreads) void k_adj_match(const int32_t* __rest
   static_assert(kAdjCap <= (int)kEnd, "chain links fit 16 bits");
   const uint32_t b0 = first[blockIdx.x];
   const int n = min((int)(first[blockIdx.x + 1] - b0), kAdjCap);
-  for (int s = threadIdx.x; s < kAdjSlots; s += kAdjThreads) head[s] = kEnd;
+  uint32_t h[kPer];
+  int3 x[kPer];
+  uint2 mine[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = threadIdx.x + k * kMatchThreads;
+    h[k] = i < n ? half[b0 + i] : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = threadIdx.x + k * kMatchThreads;
+    x[k] = make_int3(0, 0, 0);
+    if (i < n) x[k] = reinterpret_cast<const int3*>(idx)[h[k] / 3u];
+  }
+  for (int s = threadIdx.x; s < kAdjSlots; s += kMatchThreads) head[s] = kEnd;
   __syncthreads();
-  for (int i = threadIdx.x; i < n; i += kAdjThreads) {
-    const uint32_t h = half[b0 + i];
-    const uint32_t t = h / 3u, e = h - 3u * t;
-    const uint32_t a = (uint32_t)idx[3 * (int64_t)t + e];
-    const uint32_t c = (uint32_t)idx[3 * (int64_t)t + (e == 2u ? 0u : e + 1u)];
-    const uint2 k = make_uint2(min(a, c), max(a, c));
-    key[i] = k;
-    hs[i] = h;
-    nxt[i] = (uint16_t)atomicExch(&head[adj_hash(k.x, k.y)], (uint32_t)i);
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = threadIdx.x + k * kMatchThreads;
+    const uint32_t e = h[k] % 3u;
+    const uint32_t a = (uint32_t)(e == 0u ? x[k].x : e == 1u ? x[k].y : x[k].z);
+    const uint32_t c = (uint32_t)(e == 0u ? x[k].y : e == 1u ? x[k].z : x[k].x);
+    mine[k] = make_uint2(min(a, c), max(a, c));
+    if (i < n) {
+      key[i] = mine[k];
+      hs[i] = h[k];
+      nxt[i] = (uint16_t)atomicExch(&head[adj_hash(mine[k].x, mine[k].y)], (uint32_t)i);
+    }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < n; i += kAdjThreads) {
-    const uint2 k = key[i];
-    const uint32_t h = hs[i];
-    // the smallest half-edge of this edge above h, and the smallest of all
-    // others
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = threadIdx.x + k * kMatchThreads;
+    if (i >= n) break;
+    // the smallest half-edge of this edge above this one, and the smallest of
+    // all others
     uint32_t above = 0xFFFFFFFFu, least = 0xFFFFFFFFu;
-    for (uint32_t j = head[adj_hash(k.x, k.y)]; j != kEnd; j = nxt[j]) {
+    for (uint32_t j = head[adj_hash(mine[k].x, mine[k].y)]; j != kEnd; j = nxt[j]) {
       const uint2 kj = key[j];
       const uint32_t hj = hs[j];
-      if (kj.x != k.x || kj.y != k.y || hj == h) continue;
+      if (kj.x != mine[k].x || kj.y != mine[k].y || hj == h[k]) continue;
       least = min(least, hj);
-      if (hj > h) above = min(above, hj);
+      if (hj > h[k]) above = min(above, hj);
     }
     const uint32_t to = above != 0xFFFFFFFFu ? above : least;
-    nbr[h] = to == 0xFFFFFFFFu ? -1 : (int32_t)(to / 3u);
+    nbr[h[k]] = to == 0xFFFFFFFFu ? -1 : (int32_t)(to / 3u);
   }
 }
 
@@ -942,7 +965,7 @@ hipError_t launch_adjacency_match(const int32_t* idx, int64_t T, int64_t V, cons
   k_adj_buckets<true><<<(unsigned)((T + kAdjTile - 1) / kAdjTile), kAdjThreads,
                         4 * (size_t)pl.buckets, st>>>(idx, T, V, pl.shift, pl.buckets, next,
                                                       nullptr, half, nbr);
-  k_adj_match<<<(unsigned)pl.buckets, kAdjThreads, 0, st>>>(idx, next + pl.buckets, half, nbr);
+  k_adj_match<<<(unsigned)pl.buckets, kMatchThreads, 0, st>>>(idx, next + pl.buckets, half, nbr);
   return hipGetLastError();
 }
 
