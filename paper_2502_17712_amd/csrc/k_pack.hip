@@ -1371,17 +1371,28 @@ __device__ __forceinline__ void k_select_place_body(
   if (blockIdx.x > 0 && (int64_t)blockIdx.x * kBlock >= C) return;
   if (tid < kMaxStrips) strips[tid] = 0u;
   if (tid < kWave) {
-    int j = 0, L = 1, H = 0, rows = 0;
+    int j = 0, L = 1, H0 = 0, rows0 = 0;
     if (tid < p.J) {
       const int32_t* t = cand_tab + tid * kCandStride;
-      if (t[0]) { j = tid + 1; L = t[2]; H = t[3]; rows = t[4]; }
+      if (t[0]) { j = tid + 1; L = t[2]; H0 = t[3]; rows0 = t[4]; }
     }
+    // over the rows of 16 lanes by DPP (pairs, quads, half rows, rows), then
+    // over the rows
+    auto better = [&](int oj, int oL) {
+      if (sel_better(oj, oL, j, L)) { j = oj; L = oL; }
+    };
+    better(dpp_keep<0xB1>(j), dpp_keep<0xB1>(L));
+    better(dpp_keep<0x4E>(j), dpp_keep<0x4E>(L));
+    better(dpp_keep<0x141>(j), dpp_keep<0x141>(L));
+    better(dpp_keep<0x140>(j), dpp_keep<0x140>(L));
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const int oj = __shfl_xor(j, o, kWave), oL = __shfl_xor(L, o, kWave);
-      const int oH = __shfl_xor(H, o, kWave), orows = __shfl_xor(rows, o, kWave);
-      if (sel_better(oj, oL, j, L)) { j = oj; L = oL; H = oH; rows = orows; }
-    }
+    for (int r = 0; r < kWave; r += 16)
+      better(__builtin_amdgcn_readlane(j, r), __builtin_amdgcn_readlane(L, r));
+    j = __builtin_amdgcn_readfirstlane(j);
+    L = __builtin_amdgcn_readfirstlane(L);
+    // (the winner's record is in lane j - 1)
+    const int H = __builtin_amdgcn_readlane(H0, max(j - 1, 0));
+    const int rows = __builtin_amdgcn_readlane(rows0, max(j - 1, 0));
     if (tid == 0) {
       sj = j;
       sL = L;

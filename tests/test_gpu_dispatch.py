@@ -158,6 +158,9 @@ PUSH_CASES = {
     "overflow on both sides of 1024": (_uniform(60, 100, 1400), 4096, {}),
     "rows longer than a chunk": (_uniform(30000, 0.2, 6), 8192, dict(g=0, mmin=1)),
     "rows of a third of a chunk": (_uniform(20000, 0.2, 6), 4096, dict(g=0, mmin=2)),
+    "255 boxes": (_uniform(255, 5, 30).round(), 1024, {}),
+    "256 boxes": (_uniform(256, 5, 30).round(), 1024, {}),
+    "257 boxes": (_uniform(257, 5, 30).round(), 1024, {}),
     "2047 boxes": (_uniform(2047, 1, 30), 2048, {}),
     "2048 boxes": (_uniform(2048, 1, 30), 2048, {}),
     "2049 boxes": (_uniform(2049, 1, 30), 2048, {}),
