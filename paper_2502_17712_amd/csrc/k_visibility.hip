@@ -181,22 +181,24 @@ __global__ __launch_bounds__(kCullBlock) void k_vis_cull(
 // 47.2, single ones 46.5; 8 or 4 workgroups per CU 47, 3 52).
 constexpr int kVisBatch = kWave;
 constexpr int kVisRun = 4;
+// Footprints of more samples than this are walked one after another, without
+// looking for the owner of each sample, and short lists go one entry a
+// workgroup (two triangles over all of 480 x 270 samples: 850 -> 121 us, forty
+// over half of it 1550 -> 506; by one wave each they took 1040 and 17077).
+constexpr uint32_t kVisMany = 1024;
 constexpr int kVisGrid = 6 * 256;  // most workgroups: what the chip holds at once
 
-// depth of sample (px, py) if footprint `o` covers it
-__device__ __forceinline__ bool sample(const double (*X)[kVisBatch], const double (*Y)[kVisBatch],
-                                       const double (*Z)[kVisBatch], int o, int px, int py,
-                                       double& z) {
+// edge functions of a footprint at the centre of sample (px, py); false: not
+// covered
+__device__ __forceinline__ bool covered(double X0, double X1, double X2, double Y0, double Y1,
+                                        double Y2, int px, int py, double (&e)[3], double& area) {
   const double cx = (double)px + 0.5, cy = (double)py + 0.5;
-  const double e0 = (X[2][o] - X[1][o]) * (cy - Y[1][o]) - (Y[2][o] - Y[1][o]) * (cx - X[1][o]);
-  const double e1 = (X[0][o] - X[2][o]) * (cy - Y[2][o]) - (Y[0][o] - Y[2][o]) * (cx - X[2][o]);
-  const double e2 = (X[1][o] - X[0][o]) * (cy - Y[0][o]) - (Y[1][o] - Y[0][o]) * (cx - X[0][o]);
-  const double area = (e0 + e1) + e2;
-  const bool in = area != 0.0 &&
-                  ((e0 >= 0.0 && e1 >= 0.0 && e2 >= 0.0) || (e0 <= 0.0 && e1 <= 0.0 && e2 <= 0.0));
-  if (!in) return false;
-  z = ((e0 * Z[0][o] + e1 * Z[1][o]) + e2 * Z[2][o]) / area;
-  return true;
+  e[0] = (X2 - X1) * (cy - Y1) - (Y2 - Y1) * (cx - X1);
+  e[1] = (X0 - X2) * (cy - Y2) - (Y0 - Y2) * (cx - X2);
+  e[2] = (X1 - X0) * (cy - Y0) - (Y1 - Y0) * (cx - X0);
+  area = (e[0] + e[1]) + e[2];
+  return area != 0.0 && ((e[0] >= 0.0 && e[1] >= 0.0 && e[2] >= 0.0) ||
+                         (e[0] <= 0.0 && e[1] <= 0.0 && e[2] <= 0.0));
 }
 
 template <bool MARK>
@@ -214,6 +216,8 @@ __global__ __launch_bounds__(kBlock, 6) void k_vis_depth(const float* __restrict
   __shared__ int ix0[kVisBatch], iy0[kVisBatch], nx[kVisBatch];
   __shared__ unsigned long long end[kVisBatch];  // samples of the batch up to and with each
   __shared__ uint32_t seen[kVisBatch];           // 1: covers a sample, 3: ... and passes at one
+  __shared__ uint32_t many[kVisBatch];           // samples of a footprint that is walked alone
+  __shared__ unsigned long long alone;           // ... and which those are
   const int tid = threadIdx.x, lane = lane_id();
   uint32_t n_occ;
   {
@@ -225,13 +229,15 @@ __global__ __launch_bounds__(kBlock, 6) void k_vis_depth(const float* __restrict
     __syncthreads();
   }
   // one batch a workgroup, smaller ones if that makes more workgroups
-  const uint32_t batches = max((n_occ + kVisBatch - 1) / kVisBatch,
-                               min(gridDim.x, (n_occ + kVisRun - 1) / kVisRun));
+  const uint32_t run = n_occ > kVisRun * gridDim.x ? kVisRun : 1;
+  const uint32_t batches =
+      max((n_occ + kVisBatch - 1) / kVisBatch, min(gridDim.x, (n_occ + run - 1) / run));
   for (uint32_t b = blockIdx.x; b < batches; b += gridDim.x) {
     int32_t t = -1;
     if (tid < kVisBatch) {  // (the first wave)
       unsigned long long n = 0;
-      const uint32_t i = ((lane / kVisRun) * batches + b) * kVisRun + lane % kVisRun;
+      const uint32_t i = run == 1 ? lane * batches + b
+                                  : ((lane / kVisRun) * batches + b) * kVisRun + lane % kVisRun;
       if (i < n_occ) {
         int lo = 0, hi = nseg;  // last segment that starts at or before i
         while (hi - lo > 1) {
@@ -261,8 +267,11 @@ __global__ __launch_bounds__(kBlock, 6) void k_vis_depth(const float* __restrict
         nx[lane] = w;
         n = (unsigned long long)w * max(s.iy1 - s.iy0 + 1, 0);
       }
-      end[lane] = wave_incl_scan<unsigned long long>(n);
+      const unsigned long long large = __ballot(n > kVisMany);
+      many[lane] = (uint32_t)n;
+      end[lane] = wave_incl_scan<unsigned long long>(n > kVisMany ? 0ull : n);
       if (MARK) seen[lane] = 0u;
+      if (lane == 0) alone = large;
     }
     __syncthreads();
     const unsigned long long all = end[kVisBatch - 1];
@@ -275,13 +284,37 @@ __global__ __launch_bounds__(kBlock, 6) void k_vis_depth(const float* __restrict
       const uint32_t k = (uint32_t)(s - (o ? end[o - 1] : 0ull));
       const uint32_t row = k / (uint32_t)nx[o];
       const int px = ix0[o] + (int)(k - row * (uint32_t)nx[o]), py = iy0[o] + (int)row;
-      double z;
-      if (!sample(X, Y, Z, o, px, py, z)) continue;
+      double e[3], area;
+      if (!covered(X[0][o], X[1][o], X[2][o], Y[0][o], Y[1][o], Y[2][o], px, py, e, area))
+        continue;
+      const double z = ((e[0] * Z[0][o] + e[1] * Z[1][o]) + e[2] * Z[2][o]) / area;
       const int64_t pix = (int64_t)py * q.Wc + px;
       if (MARK)
         atomicOr(&seen[o], z <= dval(dload(&depth[pix])) + 1e-6 ? 3u : 1u);
       else
         atomicMin(&depth[pix], dkey(z));
+    }
+    for (unsigned long long left = alone; left; left &= left - 1) {
+      const int o = __ffsll((long long)left) - 1;
+      const double X0 = X[0][o], X1 = X[1][o], X2 = X[2][o];
+      const double Y0 = Y[0][o], Y1 = Y[1][o], Y2 = Y[2][o];
+      const double Z0 = Z[0][o], Z1 = Z[1][o], Z2 = Z[2][o];
+      const uint32_t n = many[o], w = (uint32_t)nx[o];
+      const int ox = ix0[o], oy = iy0[o];
+      for (uint32_t k = tid; k < n; k += kBlock) {
+        const uint32_t row = k / w;
+        const int px = ox + (int)(k - row * w), py = oy + (int)row;
+        double e[3], area;
+        if (covered(X0, X1, X2, Y0, Y1, Y2, px, py, e, area)) {
+          const double z = ((e[0] * Z0 + e[1] * Z1) + e[2] * Z2) / area;
+          const int64_t pix = (int64_t)py * q.Wc + px;
+          if (MARK)
+            atomicOr(&seen[o], z <= dval(dload(&depth[pix])) + 1e-6 ? 3u : 1u);
+          else
+            atomicMin(&depth[pix], dkey(z));
+        }
+        if (MARK && seen[o] == 3u) break;
+      }
     }
     __syncthreads();
     if (MARK && t >= 0) vis[t] = seen[lane] != 1u ? 1 : 0;
@@ -412,7 +445,7 @@ hipError_t launch_visibility(const float* pos, const int32_t* idx, int64_t T, co
   k_vis_cull<<<g, kCullBlock, 0, st>>>(pos, idx, T, nseg, q, vis, occl, counts, depth, nd);
   if (q.coarse > 0) {
     const unsigned og =
-        (unsigned)std::min<int64_t>((T + kVisRun - 1) / kVisRun, kVisGrid);
+        (unsigned)std::min<int64_t>(T, kVisGrid);
     k_vis_depth<false><<<og, kBlock, 0, st>>>(pos, idx, T, nseg, q, occl, counts, depth, vis);
     k_vis_depth<true><<<og, kBlock, 0, st>>>(pos, idx, T, nseg, q, occl, counts, depth, vis);
   }
