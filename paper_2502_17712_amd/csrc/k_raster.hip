@@ -1174,6 +1174,7 @@ __global__ __launch_bounds__(kBlock) void k_fp_raster(
   const unsigned long long nwaves = gridDim.x * (blockDim.x / kWave);
   const unsigned long long wave = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
   const unsigned long long per = max((total + nwaves - 1) / nwaves, (unsigned long long)kWave);
+  if (blockIdx.x * (unsigned long long)(blockDim.x / kWave) * per >= total) return;  // (no items)
   const unsigned long long k0 = min(total, wave * per), k1 = min(total, k0 + per);
   const int w = threadIdx.x / kWave;
   int4* lds_x = all_x[w];
@@ -1243,7 +1244,7 @@ __global__ __launch_bounds__(kBlock) void k_fp_raster(
     from = min(from, span_lo[k]);
     to = max(to, span_hi[k]);
   }
-  if (to - from >= kFpWin) from = (span_lo[0] + span_hi[0]) / 2 - kFpWin / 2;
+  if (to - from >= kFpWin) from = span_lo[0] + (span_hi[0] - span_lo[0]) / 2 - kFpWin / 2;
   from = max(from - 1, 0);  // (an item may reach into the entry before its own)
   while (k0 < k1) {
     for (int w0 = ia; w0 < ib; w0 += kWave) {
