@@ -103,6 +103,27 @@ def test_occupancy_sides(n, per, omega):
     compare(check(f), oracle.build_frame(f))
 
 
+# Footprints drawn by the whole wave, 64 texels at a time, likewise: all of them
+# up to 4096 texels, within 512 texels of their first vertex or beyond.
+@pytest.mark.parametrize("n,per", [(1, 1), (4, 5), (9, 4), (36, 2), (400, 5), (3000, 1)])
+@pytest.mark.parametrize("omega", [256, 2048, 8192])
+def test_occupancy_expanded(n, per, omega):
+    fa = _fa()
+    f = fans(np.arange(n * per) // per, seed=n + per, atlas_size=omega, width=3840, height=2160)
+    print(f"[gpu] expanded {f.name} omega={omega}", flush=True)
+    ctx = fa.Context(f.num_triangles, f.num_vertices, max_charts=65536, max_atlas=8192,
+                     tuning_table=None)
+    ctx.set_tuning(fa.FA_TUNE_OCC_LANE_TEXELS, 0)
+    ctx.set_tuning(fa.FA_TUNE_OCC_SMALL_TEXELS, 4096)
+    out = ctx.build_atlas(fa.Mesh(f.positions, f.indices, f.scene_key),
+                          torch.as_tensor(f.visible).cuda(), f.view_proj, f.width, f.height, omega,
+                          f.rate)
+    torch.cuda.synchronize()
+    g = out.to_numpy()
+    ctx.close()
+    compare(g, oracle.build_frame(f))
+
+
 # Footprint push: profiles from entries of one triangle to whole groups of 64,
 # of charts from a few columns to more than a window, charts over and under the
 # width that a whole workgroup pushes, gutters of 1 to 5, and lists longer than
