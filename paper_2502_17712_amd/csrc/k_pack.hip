@@ -1356,23 +1356,22 @@ __device__ __forceinline__ void k_select_place_body(
     const unsigned long long* __restrict__ big_counter = nullptr) {
   __shared__ int sj, sL;
   __shared__ uint32_t strips[kMaxStrips];
-  const bool ok = st->status == FA_OK;
   const int C = st->num_charts;
   const int tid = threadIdx.x;
-  if (blockIdx.x == 0 && tid < p.J && cand_out) {
-    const int32_t* t = cand_tab + tid * kCandStride;
-    int32_t* o = cand_out + 4 * tid;
-    o[0] = ok ? t[0] : 0; o[1] = ok ? t[1] : 0; o[2] = ok ? t[2] : 0; o[3] = ok ? t[3] : 0;
-  }
-  if (!ok) {
-    if (meta && blockIdx.x == 0 && tid == 0) write_meta(p, st, big_counter, false, 0ull, meta);
-    return;
-  }
   if (blockIdx.x > 0 && (int64_t)blockIdx.x * kBlock >= C) return;
   if (tid < kMaxStrips) strips[tid] = 0u;
   if (tid < kWave) {
+    // the first wave alone reads the status, which workgroup 0 may set below
+    // while others start: were every wave to read it, some of a workgroup's
+    // might leave and the rest place boxes by a winner that nobody wrote
+    const bool ok = st->status == FA_OK;
+    if (blockIdx.x == 0 && tid < p.J && cand_out) {
+      const int32_t* t = cand_tab + tid * kCandStride;
+      int32_t* o = cand_out + 4 * tid;
+      o[0] = ok ? t[0] : 0; o[1] = ok ? t[1] : 0; o[2] = ok ? t[2] : 0; o[3] = ok ? t[3] : 0;
+    }
     int j = 0, L = 1, H0 = 0, rows0 = 0;
-    if (tid < p.J) {
+    if (ok && tid < p.J) {
       const int32_t* t = cand_tab + tid * kCandStride;
       if (t[0]) { j = tid + 1; L = t[2]; H0 = t[3]; rows0 = t[4]; }
     }
@@ -1397,15 +1396,17 @@ __device__ __forceinline__ void k_select_place_body(
       sj = j;
       sL = L;
       if (blockIdx.x == 0) {
-        st->jstar = j;
-        if (!j) {
-          st->status = FA_ERR_NOFIT;
-        } else {
-          st->layout_w = L;
-          st->layout_h = H;
-          st->rows = rows;
-          st->s_star = (float)j / (float)p.J;
-          st->q_star = (float)p.omega / (float)L;
+        if (ok) {
+          st->jstar = j;
+          if (!j) {
+            st->status = FA_ERR_NOFIT;
+          } else {
+            st->layout_w = L;
+            st->layout_h = H;
+            st->rows = rows;
+            st->s_star = (float)j / (float)p.J;
+            st->q_star = (float)p.omega / (float)L;
+          }
         }
         if (meta) write_meta(p, st, big_counter, false, 0ull, meta);
       }

@@ -1,0 +1,65 @@
+"""Frames, batches and scenes at the limits of the library's dispatch: frames
+that end without a packing or over a capacity, indices that no scene has
+checked, batches whose views need several turns of their workgroups."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from synth import scenes
+from test_gpu_dispatch import fans
+from test_gpu_parity import _fa, compare
+
+pytestmark = pytest.mark.gpu
+
+
+def _poison(o):
+    for t in (o.chart_of_tri, o.chart_of_vert, o.occupancy, o.candidates, o.charts, o.meta):
+        t.fill_(-7)
+    o.uv.fill_(-7.0)
+
+
+# A frame that fits at no scale places nothing, however many workgroups the
+# placement has (256 charts each): the placement words of the chart records keep
+# what they held, the map is empty and no vertex is mapped. One frame, views of
+# a batch on streams and in one launch, and boxes alone.
+@pytest.mark.parametrize("n", [256, 257, 3000, 20000])
+def test_no_fit_places_nothing(n):
+    fa = _fa()
+    f = fans(np.arange(n), seed=n, atlas_size=16)
+    want = oracle.build_frame(f)
+    assert want["status"] == oracle.STATUS_NOFIT
+    ctx = fa.Context(f.num_triangles, f.num_vertices, max_charts=32768, max_atlas=64, max_views=3,
+                     tuning_table=None)
+    mesh = fa.Mesh(f.positions, f.indices, 3)
+    vis = torch.as_tensor(f.visible).cuda()
+    for way in ("frame", "streams", "one launch"):
+        print(f"[gpu] no fit, {n} charts, {way}", flush=True)
+        outs = [ctx.outputs(mesh, 16) for _ in range(1 if way == "frame" else 3)]
+        for o in outs:
+            _poison(o)
+        if way == "frame":
+            ctx.build_atlas(mesh, vis, f.view_proj, f.width, f.height, 16, 1.0, out=outs[0])
+        else:
+            ctx.set_tuning(fa.FA_TUNE_BATCH_LAUNCH, int(way == "one launch"))
+            ctx.build_atlas_batch(mesh, [(vis, f.view_proj, f.width, f.height, 16, 1.0)] * 3, outs)
+        torch.cuda.synchronize()
+        for o in outs:
+            g = o.to_numpy()
+            compare(g, want)
+            assert g["meta"]["occupied_texels"] == 0 and g["meta"]["layout_width"] == 0
+            for k in ("x", "y", "w", "h"):
+                assert (g["charts"][k] == -7).all(), k
+            assert (g["occupancy"] == -1).all() and np.isnan(g["uv"]).all()
+    print(f"[gpu] no fit, {n} boxes", flush=True)
+    sizes = torch.as_tensor(np.ascontiguousarray(want["target"], np.float32)).cuda()
+    meta = torch.zeros(16, dtype=torch.int32, device="cuda")
+    cand = torch.zeros((64, 4), dtype=torch.int32, device="cuda")
+    placed = torch.full((n, 5), -7, dtype=torch.int32, device="cuda")
+    assert fa.fa_pack_boxes(ctx.h, sizes.data_ptr(), n, 16, placed.data_ptr(), meta.data_ptr(),
+                            cand.data_ptr(), torch.cuda.current_stream().cuda_stream) == fa.FA_OK
+    torch.cuda.synchronize()
+    assert fa.parse_meta(meta)["status"] == fa.FA_ERR_NOFIT
+    assert (placed == -7).all().item()
+    assert np.array_equal(cand.cpu().numpy()[:, :3], want["cand"][:, :3])
+    ctx.close()
