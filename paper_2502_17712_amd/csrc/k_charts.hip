@@ -815,14 +815,14 @@ __global__ void k_uf_flatten_count(const int32_t* __restrict__ vlist, int32_t* p
 // triangle. Each workgroup sums the root counts of the tiles before its own;
 // the last one records the chart count (above max_charts: FA_ERR_CAPACITY;
 // no chart index at or past max_charts is written, and every later stage
-// stops on the status).
+// stops on the status). The status is not read here: the last workgroup may set
+// it while others start, and a frame that ended before has an empty list.
 __device__ __forceinline__ void k_assign_roots_body(const int32_t* __restrict__ vlist,
                                const int32_t* __restrict__ parent,
                                const uint32_t* __restrict__ tile_count, int32_t* __restrict__ cot,
                                fa_chart* __restrict__ charts, uint32_t* __restrict__ accum,
                                int32_t max_charts, FrameState* __restrict__ st) {
   __shared__ uint32_t sh[kBlock / kWave];
-  if (st->status != FA_OK) return;
   const int nv = st->visible;
   if ((int64_t)blockIdx.x * kTriTile >= nv) return;
   const uint32_t off = tiles_before(tile_count, blockIdx.x, sh);

@@ -63,3 +63,34 @@ def test_no_fit_places_nothing(n):
     assert (placed == -7).all().item()
     assert np.array_equal(cand.cpu().numpy()[:, :3], want["cand"][:, :3])
     ctx.close()
+
+
+# A frame of more charts than the context holds ends with FA_ERR_CAPACITY and the
+# whole count; the roots of the charts below the capacity are labelled, whichever
+# workgroups (1024 visible triangles each) start after the last one reports it.
+@pytest.mark.parametrize("n,cap,static", [
+    (8192, 1, False), (8193, 8192, False), (60000, 700, False), (60000, 59999, False),
+    (8192, 4096, True), (20000, 4096, True)])
+def test_over_capacity_labels(n, cap, static):
+    fa = _fa()
+    f = fans(np.arange(n), seed=n, atlas_size=64)
+    print(f"[gpu] {n} charts, capacity {cap}, static={static}", flush=True)
+    mesh = fa.Mesh(f.positions, f.indices, 4)
+    vis = torch.as_tensor(f.visible).cuda()
+    out = fa.AtlasOutputs(n, f.num_vertices, cap, 64, 64)
+    _poison(out)
+    ctx = None
+    if static:
+        fa.build_atlas_static(mesh, vis, f.view_proj, f.width, f.height, 64, 1.0, out=out)
+    else:
+        ctx = fa.Context(n, f.num_vertices, max_charts=cap, max_atlas=64, tuning_table=None)
+        ctx.build_atlas(mesh, vis, f.view_proj, f.width, f.height, 64, 1.0, out=out)
+    torch.cuda.synchronize()
+    m = fa.parse_meta(out.meta)
+    assert m["status"] == fa.FA_ERR_CAPACITY and m["num_charts"] == n
+    label = np.where(np.arange(n) < cap, np.arange(n), -1)  # (every triangle is a root)
+    assert np.array_equal(out.chart_of_tri.cpu().numpy(), label)
+    assert np.array_equal(fa.parse_charts(out.charts, cap)["root_tri"], np.arange(cap))
+    assert (out.occupancy == -1).all().item() and torch.isnan(out.uv).all().item()
+    if ctx is not None:
+        ctx.close()
