@@ -94,3 +94,49 @@ def test_over_capacity_labels(n, cap, static):
     assert (out.occupancy == -1).all().item() and torch.isnan(out.uv).all().item()
     if ctx is not None:
         ctx.close()
+
+
+# A batch in one launch per stage limits the workgroups of its views: with 16
+# views a turn holds 131072 list entries of the vertex hook and of the raster and
+# 262144 of the box gather, whose table of charts then serves all its turns. Odd
+# views show 320000 triangles, even ones fewer; one chart (a sheet) and 10000
+# (the sheet cut into squares of 4 x 4 cells).
+@pytest.mark.parametrize("square", [400, 4])
+def test_one_launch_batch_takes_turns(square):
+    fa = _fa()
+    n, k = 400, 400 // square
+    cell = np.arange(square + 1) / square
+    at = (np.stack(np.meshgrid(np.arange(k), np.arange(k), indexing="ij"), -1).reshape(-1, 1, 1, 2)
+          + 0.98 * np.stack(np.meshgrid(cell, cell, indexing="ij"), -1)) / k * 2 - 1
+    y, x = at[..., 0], at[..., 1]
+    pos = np.stack([x, y, 0.2 * np.sin(9 * x) * np.cos(7 * y)], -1).reshape(-1, 3)
+    s1 = square + 1
+    v = (np.arange(square)[:, None] * s1 + np.arange(square)).reshape(-1)
+    quad = np.stack([v, v + 1, v + s1 + 1, v, v + s1 + 1, v + s1], 1).reshape(-1, 3)
+    tris = (np.arange(k * k)[:, None, None] * s1 * s1 + quad).reshape(-1, 3)
+    assert len(tris) == 2 * n * n
+    pos, tris = pos.astype(np.float32), tris.astype(np.int32)
+    rng = np.random.default_rng(square)
+    views = []
+    for i in range(16):
+        cam = scenes.make_camera((0.1 * i - 0.8, 0.7 - 0.1 * i, 2.0 + 0.1 * i), (0.0, 0.0, 0.0), 640,
+                                 360, 0.05, 100.0, up=(0, 1, 0))
+        vis = (rng.uniform(size=len(tris)) < (1.0 if i % 2 else 0.06 * i)).astype(np.uint8)
+        views.append(scenes.Frame(f"turns/{square}/{i}", pos, tris, vis, cam.view_proj, 640, 360,
+                                  1024, 1.0 + 0.1 * i, 995, cam.eye, cam.near, 0))
+    ctx = fa.Context(len(tris), len(pos), max_charts=65536, max_atlas=1024, max_views=16,
+                     tuning_table=None)
+    ctx.set_tuning(fa.FA_TUNE_BATCH_LAUNCH, 1)
+    assert ctx.get_tuning(fa.FA_TUNE_BATCH_LAUNCH) == 1
+    mesh = fa.Mesh(pos, tris, 995)
+    outs = [ctx.outputs(mesh, 1024) for _ in views]
+    for o in outs:
+        _poison(o)
+    shown = [torch.as_tensor(f.visible).cuda() for f in views]
+    print(f"[gpu] 16 views in one launch, squares of {square}", flush=True)
+    ctx.build_atlas_batch(mesh, [(a, f.view_proj, 640, 360, 1024, f.rate)
+                                 for a, f in zip(shown, views)], outs)
+    torch.cuda.synchronize()
+    for o, f in zip(outs, views):
+        compare(o.to_numpy(), oracle.build_frame(f))
+    ctx.close()
