@@ -140,3 +140,35 @@ def test_one_launch_batch_takes_turns(square):
     for o, f in zip(outs, views):
         compare(o.to_numpy(), oracle.build_frame(f))
     ctx.close()
+
+
+# Small meshes have their charts built by one workgroup a view in a batch too: two
+# triangles a thread up to 2048 of them and eight above; views of uneven atlas
+# sizes that show nothing, some and all of the mesh.
+@pytest.mark.parametrize("n", [1, 64, 1025, 2048, 2049, 8192])
+def test_small_mesh_batch(n):
+    fa = _fa()
+    rng = np.random.default_rng(n)
+    owners = np.unique(np.sort(rng.integers(0, max(1, n // 3), n)), return_inverse=True)[1]
+    base = fans(owners, seed=n)
+    views = []
+    for i, omega in enumerate((64, 2048, 256, 1024, 512)):
+        vis = (rng.uniform(size=n) < (0.0, 1.0, 0.5, 0.9, 0.1)[i]).astype(np.uint8)
+        views.append(scenes.Frame(f"{base.name}/{i}", base.positions, base.indices, vis,
+                                  base.view_proj, base.width, base.height, omega, 0.7, 996,
+                                  base.eye, base.near, 0))
+    ctx = fa.Context(n, base.num_vertices, max_charts=4096, max_atlas=2048, max_views=3,
+                     tuning_table=None)
+    ctx.set_tuning(fa.FA_TUNE_BATCH_LAUNCH, 1)
+    mesh = fa.Mesh(base.positions, base.indices, 996)
+    outs = [ctx.outputs(mesh, f.atlas_size) for f in views]
+    for o in outs:
+        _poison(o)
+    shown = [torch.as_tensor(f.visible).cuda() for f in views]
+    print(f"[gpu] 5 views of {n} triangles on 3 slots", flush=True)
+    ctx.build_atlas_batch(mesh, [(a, f.view_proj, f.width, f.height, f.atlas_size, f.rate)
+                                 for a, f in zip(shown, views)], outs)
+    torch.cuda.synchronize()
+    for o, f in zip(outs, views):
+        compare(o.to_numpy(), oracle.build_frame(f))
+    ctx.close()
