@@ -172,3 +172,41 @@ def test_small_mesh_batch(n):
     for o, f in zip(outs, views):
         compare(o.to_numpy(), oracle.build_frame(f))
     ctx.close()
+
+
+# The allocation-free entry point checks the indices itself. Meshes above 8192
+# triangles or 16384 vertices do it by tiles of 1024 triangles, four a workgroup,
+# and the compaction of the last tile ends the frame: bad indices at each of a
+# workgroup's tiles, in the first, inner and last (full or partial) tile, of
+# hidden triangles, and of all triangles at once; then a good frame.
+@pytest.mark.parametrize("T,spare", [(8193, 0), (21504, 0), (20001, 1000), (5000, 12000)])
+def test_static_index_check_in_tiles(T, spare):
+    fa = _fa()
+    f = fans(np.arange(T) // 8, seed=T, atlas_size=512)
+    f.positions = np.concatenate([f.positions, np.zeros((spare, 3), np.float32)])
+    V = f.num_vertices
+    assert V <= fa.STATIC_MAX_VERTICES and (T > 8192 or V > 16384)
+    want = oracle.build_frame(f)
+    mesh = fa.Mesh(f.positions, f.indices, 5)
+    out = fa.AtlasOutputs(T, V, fa.STATIC_MAX_CHARTS, 512, 64)
+    hidden = f.visible.copy()
+    hidden[::3] = 0
+    where = [0, 1023, 1024, 2049, 3072 + 3, 4096, T // 2, T - 1, slice(None),
+             slice((T - 1) // 1024 * 1024, T)]
+    for k, at in enumerate(where):
+        idx = f.indices.copy()
+        idx[at, k % 3] = (V, -1, 2**31 - 1, -2**31)[k % 4]
+        vis = torch.as_tensor(hidden if k % 2 else f.visible).cuda()
+        print(f"[gpu] static: T={T} V={V}, bad index at {at}", flush=True)
+        _poison(out)
+        fa.build_atlas_static(fa.Mesh(f.positions, idx, 6), vis, f.view_proj, f.width, f.height,
+                              512, f.rate, out=out)
+        torch.cuda.synchronize()
+        m = fa.parse_meta(out.meta)
+        assert m["status"] == fa.FA_ERR_INVALID_ARG, at
+        assert m["visible_triangles"] == 0 and m["num_charts"] == 0 and m["chosen_j"] == 0, at
+    _poison(out)
+    fa.build_atlas_static(mesh, torch.as_tensor(f.visible).cuda(), f.view_proj, f.width, f.height,
+                          512, f.rate, out=out)
+    torch.cuda.synchronize()
+    compare(out.to_numpy(), want)
