@@ -210,3 +210,27 @@ def test_static_index_check_in_tiles(T, spare):
                           512, f.rate, out=out)
     torch.cuda.synchronize()
     compare(out.to_numpy(), want)
+
+
+# Meshes of more buckets than the adjacency's vertex ranges have, and those whose
+# half-edges do not fit the context's scratch, are sorted, and their indices
+# checked by a kernel of its own: good ones against the oracle, bad ones (at the
+# ends and inside) refused.
+@pytest.mark.parametrize("T,V", [(2_810_000, 8200), (5_600_000, 8000)])
+def test_adjacency_of_large_meshes(T, V):
+    fa = _fa()
+    idx = np.random.default_rng(T).integers(0, V, (T, 3), dtype=np.int32)
+    ctx = fa.Context(T, V, max_charts=16, max_atlas=16)
+    pos = np.zeros((V, 3), np.float32)
+    print(f"[gpu] sorted adjacency T={T} V={V}", flush=True)
+    nbr = ctx.adjacency(fa.Mesh(pos, idx, 5))
+    torch.cuda.synchronize()
+    assert np.array_equal(nbr.cpu().numpy(), oracle.adjacency(idx))
+    for at, value in (((0, 0), V), ((T - 1, 2), -1), ((T // 2, 1), 2**31 - 1)):
+        bad = idx.copy()
+        bad[at] = value
+        print(f"[gpu] sorted adjacency T={T}, index {value} at {at}", flush=True)
+        with pytest.raises(fa.FastAtlasError) as e:
+            ctx.adjacency(fa.Mesh(pos, bad, 6))
+        assert e.value.code == fa.FA_ERR_INVALID_ARG
+    ctx.close()
