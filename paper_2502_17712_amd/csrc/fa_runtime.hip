@@ -37,6 +37,7 @@ enum { kStages = 21 };
 
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
+constexpr size_t kCheckBytes = 8;    // fa_ctx::check_flag
 constexpr int kMaxBatchViews = 256;  // views per batched call (more: per-view launches)
 
 bool is_pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
@@ -222,12 +223,12 @@ int fa_create(const fa_config* cfg_in, fa_ctx** out_ctx) {
     ctx->slot_streams.push_back(s);
     ctx->slot_join.push_back(e);
   }
-  ctx->held_bytes += 4 + sizeof(BatchView) * kMaxBatchViews;
+  ctx->held_bytes += kCheckBytes + sizeof(BatchView) * kMaxBatchViews;
   if (cfg.hbm_budget_bytes > 0 && (int64_t)ctx->held_bytes > cfg.hbm_budget_bytes) {
     fa_destroy(ctx);
     return FA_ERR_OUT_OF_MEMORY;
   }
-  if (hipMalloc(&ctx->check_flag, 8) != hipSuccess ||
+  if (hipMalloc(&ctx->check_flag, kCheckBytes) != hipSuccess ||
       hipMalloc(&ctx->bv_dev, sizeof(BatchView) * kMaxBatchViews) != hipSuccess ||
       hipHostMalloc((void**)&ctx->bv_host, sizeof(BatchView) * kMaxBatchViews,
                     hipHostMallocDefault) != hipSuccess ||
@@ -347,11 +348,13 @@ static int get_scene(fa_ctx* ctx, const fa_mesh* mesh, hipStream_t st, Scene** o
           hipSuccess)
         return FA_ERR_DEVICE;
     } else {
-      if (hipMemcpyAsync(ctx->check_flag, info, 8, hipMemcpyHostToDevice, st) != hipSuccess)
+      if (hipMemcpyAsync(ctx->check_flag, info, kCheckBytes, hipMemcpyHostToDevice, st) !=
+          hipSuccess)
         return FA_ERR_DEVICE;
       k_check_indices<<<1024, kBlock, 0, st>>>(mesh->indices, 3 * T, V, ctx->check_flag);
     }
-    if (hipMemcpyAsync(info, ctx->check_flag, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+    if (hipMemcpyAsync(info, ctx->check_flag, kCheckBytes, hipMemcpyDeviceToHost, st) !=
+            hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
       return FA_ERR_DEVICE;
     if (info[0]) return FA_ERR_INVALID_ARG;

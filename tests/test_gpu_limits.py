@@ -234,3 +234,14 @@ def test_adjacency_of_large_meshes(T, V):
             ctx.adjacency(fa.Mesh(pos, bad, 6))
         assert e.value.code == fa.FA_ERR_INVALID_ARG
     ctx.close()
+
+
+def test_device_bytes_count_the_check_words():
+    # what a context holds: scratch parts and view descriptors, all multiples of
+    # 256 bytes, and the two words of the index check
+    fa = _fa()
+    for T, V, views in ((1, 1, 1), (1000, 777, 3), (70001, 30001, 2)):
+        ctx = fa.Context(T, V, max_charts=100, max_atlas=64, max_views=views)
+        print(f"[gpu] device bytes T={T} V={V} views={views}", flush=True)
+        assert ctx.device_bytes() % 256 == 8
+        ctx.close()
