@@ -394,9 +394,10 @@ __global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
 // columns; by rows, at about 1 us a row, they take 179 and 34 us.
 // By columns: candidates with a wide overflow m (a few boxes nearly as wide as
 // the atlas), where the edges are most of the frontline, rows so long that two
-// of them do not fit a chunk, and frames of up to kFewBoxes charts, whose few
+// of them do not fit a chunk, frames of up to kFewBoxes charts, whose few
 // columns walks take less than finding what lies under each box (one chart:
-// 7.6 us by columns, 8.5 by rows).
+// 7.6 us by columns, 8.5 by rows), and candidates whose boxes are narrow or lie
+// many to an edge (columns_cheaper).
 constexpr int kFoldItems = 4;   // consecutive boxes per thread in the fold
 constexpr int kNarrow = 8;      // by columns: boxes up to this wide are pushed by one lane
 constexpr int kMidList = 2048, kWideList = 256;  // by columns: entries of the box lists
@@ -442,6 +443,35 @@ struct PushArgs {
   int32_t* Y;              // positions out
   int C, omega, lg, m, kcap;
 };
+
+// Whether the push by columns takes less, from what both depend on, in ns: by
+// rows a row, a box and a box over edge columns (about m C / omega of them a row
+// and side; they are pushed by 16 lanes each and, above kTabBoxes a row, looked
+// up one by one); by columns a column, a row and a box of at most kNarrow, at
+// most 64 and more columns. Fitted to 810 sets of 9 to 60000 boxes in one
+// candidate each, alike and with a share of boxes 3 to 30 times as large, at
+// atlases of 512 to 8192 and every block size (1.03 and 500: rows where the two
+// are level); within 4 us or 15% of the faster way for all but 11 of them. Boxes
+// of 4 to 6 columns with a few of 130 took 538, 450 and 206 us by rows (261, 269
+// and 145 by columns), most sets of wider boxes 1.3 to 2 times as long by columns
+// as by rows; 64 candidates of 60000 such boxes 475 us by rows, 311 so.
+template <int NT>
+__device__ __forceinline__ bool columns_cheaper(const PushArgs& q, float rows, float narrow,
+                                                float wide) {
+  constexpr int k = NT == 1024 ? 0 : NT == 512 ? 1 : 2;
+  constexpr float kStart[3] = {2540.f, 2100.f, 2150.f}, kRow[3] = {972.f, 850.f, 766.f};
+  constexpr float kBox[3] = {2.0f, 2.95f, 5.8f}, kBoxColumn[3] = {2.4e-4f, 2.6e-4f, 3.5e-4f};
+  constexpr float kEdge[3] = {100.f, 114.f, 127.f};
+  constexpr float kColumn[3] = {0.35f, 0.43f, 0.70f}, kColumnRow[3] = {1341.f, 1250.f, 1106.f};
+  constexpr float kUpTo8[3] = {2.24f, 2.7f, 4.6f}, kUpTo64[3] = {8.6f, 13.2f, 27.f};
+  constexpr float kAbove64[3] = {30.f, 53.f, 101.f};
+  const float boxes = (float)q.C, omega = (float)q.omega;
+  const float by_rows = kStart[k] + kRow[k] * rows + (kBox[k] + kBoxColumn[k] * omega) * boxes +
+                        kEdge[k] * (float)q.m * boxes / omega;
+  const float by_columns = kColumn[k] * omega + kColumnRow[k] * rows + kUpTo8[k] * narrow +
+                           kUpTo64[k] * (boxes - narrow - wide) + kAbove64[k] * wide;
+  return 1.03f * by_columns + 500.f < by_rows;
+}
 
 // The next chunk [c0, c0 + cn) from the fold in global memory.
 template <int NT>
@@ -1051,6 +1081,7 @@ __device__ __forceinline__ void k_pack_box_body(const float2* __restrict__ wh,
   constexpr int NW = NT / kWave;
   __shared__ uint32_t shs[2][NW];
   __shared__ int32_t shm[NW], shb[NW];
+  __shared__ uint2 shn[NW];
   __shared__ int32_t Hsh[3];
   __shared__ long long last_x;
   __shared__ long long sh64[NW];
@@ -1075,6 +1106,7 @@ __device__ __forceinline__ void k_pack_box_body(const float2* __restrict__ wh,
   const int pad = 2 * p.gutter;
   long long run = 0;
   int mloc = INT_MIN, bad = 0;
+  uint32_t narrow = 0, wide = 0;  // boxes of at most kNarrow and of more than 64 columns
   if (tid == 0) last_x = 0;
   if (C <= kFewBoxes) columns_clear<NT>(omega, S + 3 * kcap + 4, Hsh, LC);
   int pass = 0;
@@ -1110,6 +1142,8 @@ __device__ __forceinline__ void k_pack_box_body(const float2* __restrict__ wh,
         ABg[i] = abs_[u];
         if (i == C - 1) last_x = Xi;
         mloc = max(mloc, (int)(Xi & (long long)(omega - 1)) + a[u] - omega);
+        narrow += a[u] <= kNarrow;
+        wide += a[u] > kWave;
         Xi += a[u];
       }
     }
@@ -1122,18 +1156,23 @@ __device__ __forceinline__ void k_pack_box_body(const float2* __restrict__ wh,
   }
   {
     const int wm = wave_max_dpp(mloc), wb = wave_max_dpp(bad);
-    if (lane == 0) {
+    const uint32_t wn = wave_incl_scan_dpp(narrow), ww = wave_incl_scan_dpp(wide);
+    if (lane == kWave - 1) {
       shm[w] = wm;
       shb[w] = wb;
+      shn[w] = make_uint2(wn, ww);
     }
   }
   __syncthreads();
   int m = 0;
   bad = 0;
+  narrow = wide = 0;
 #pragma unroll
   for (int k = 0; k < NW; ++k) {
     m = max(m, shm[k]);
     bad = max(bad, shb[k]);
+    narrow += shn[k].x;
+    wide += shn[k].y;
   }
   if (bad) {
     // a box side above 2 omega rejects the candidate; its overflow m and row
@@ -1179,8 +1218,10 @@ __device__ __forceinline__ void k_pack_box_body(const float2* __restrict__ wh,
   const PushArgs q{Xg, ABg, Y, C, omega, lg, m, kcap};
   // two rows have to fit a chunk (a row holds boxes at least min_box + 2
   // gutter wide that start in omega columns)
-  if (C > kFewBoxes && m <= kEdgeMax &&
-      2 * (omega / (p.min_box + pad) + 2) <= row_kcap(omega)) {
+  const bool by_rows = C > kFewBoxes && m <= kEdgeMax &&
+                       2 * (omega / (p.min_box + pad) + 2) <= row_kcap(omega) &&
+                       !columns_cheaper<NT>(q, (float)rows, (float)narrow, (float)wide);
+  if (__builtin_amdgcn_readfirstlane(by_rows)) {
     push_rows<NT>(q, S, pass, shs, Hsh);
   } else {
     push_columns<NT>(q, S, pass, shs, Hsh, LC);

@@ -245,3 +245,48 @@ def test_device_bytes_count_the_check_words():
         print(f"[gpu] device bytes T={T} V={V} views={views}", flush=True)
         assert ctx.device_bytes() % 256 == 8
         ctx.close()
+
+
+# The box push goes by rows or by columns, whichever is estimated to take less
+# from the rows, the boxes' widths and how many lie over edge columns: sets on
+# either side and around the line, of one chunk and of several, with more boxes
+# over edge columns than a row's table holds.
+def _mixed(n, mean, aspect, share, factor, seed):
+    rng = np.random.default_rng(seed)
+    z = rng.lognormal(0, 0.3, (n, 2)) * np.array([aspect ** 0.5, aspect ** -0.5])
+    k = max(1, int(n * share))
+    z[:k] = rng.lognormal(0, 0.3, (k, 2)) * factor
+    return (rng.permutation(z) * mean / np.sqrt((z[:, 0] * z[:, 1]).mean())).astype(np.float32)
+
+
+PUSH_WAYS = {
+    "rows, many over edges": (_mixed(4000, 40, 1.0, 0.01, 10, 1), 4096),
+    "rows, several chunks, many over edges": (_mixed(20000, 20, 0.25, 0.01, 10, 2), 4096),
+    "columns, narrow boxes": (_mixed(20000, 13, 0.06, 0.01, 1, 3), 4096),
+    "columns, narrow with wide": (_mixed(16000, 5, 1.0, 0.01, 30, 4), 1024),
+    "columns, several chunks, with wide": (_mixed(16000, 20, 0.25, 0.01, 30, 5), 4096),
+    "few boxes": (_mixed(20, 100, 1.0, 0.1, 3, 6), 1024),
+    "around the line": (_mixed(1000, 20, 1.0, 0.01, 10, 7), 1024),
+}
+
+
+@pytest.mark.parametrize("name", list(PUSH_WAYS))
+@pytest.mark.parametrize("block", [256, 512, 1024])
+def test_push_ways(name, block):
+    from test_gpu_parity import _oracle_pack
+    fa = _fa()
+    sizes, omega = PUSH_WAYS[name]
+    print(f"[gpu] push {name} n={len(sizes)} omega={omega} block={block}", flush=True)
+    ctx = fa.Context(1, 1, max_charts=32768, max_atlas=4096, num_scales=16, tuning_table=None)
+    ctx.set_tuning(fa.FA_TUNE_PACK_BLOCK, block)
+    placed, meta, cand = ctx.pack_boxes(torch.as_tensor(sizes).cuda(), omega)
+    torch.cuda.synchronize()
+    m, c = fa.parse_meta(meta), cand.cpu().numpy()
+    placed = placed.cpu().numpy()
+    ctx.close()
+    js, table, want = _oracle_pack(sizes, omega, 16, 1, 2)
+    assert js > 0 and m["chosen_j"] == js and np.array_equal(placed, want)
+    assert np.array_equal(c[:, :3], table[:, :3])
+    fit = table[:, 0] == 1
+    assert np.array_equal(c[fit, 3], table[fit, 3])
+    assert ((c[~fit, 3] == -1) | (c[~fit, 3] > c[~fit, 2])).all()
