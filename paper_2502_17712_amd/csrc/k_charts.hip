@@ -347,16 +347,24 @@ __device__ __forceinline__ void pairs_clear(unsigned long long* pairs) {
   for (int h = threadIdx.x; h < kPairSlots; h += blockDim.x) pairs[h] = ~0ull;
   __syncthreads();
 }
-__device__ __forceinline__ bool pair_fresh(unsigned long long* pairs, int a, int b) {
+__device__ __forceinline__ void join_once(unsigned long long* pairs, int32_t* parent, int a,
+                                          int b) {
   const unsigned long long key = ((unsigned long long)(uint32_t)a << 32) | (uint32_t)b;
   uint32_t h = (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> 40) & (kPairSlots - 1);
+  bool fresh = true;
+  // (as a loop: unrolled, the vertex hook of one million triangles took 61 us
+  // in place of 56, and without the tiles' joins before it 375 in place of 315)
+#pragma unroll 1
   for (int probe = 0; probe < 16; ++probe) {
     const unsigned long long old = atomicCAS(&pairs[h], ~0ull, key);
-    if (old == ~0ull) return true;
-    if (old == key) return false;
+    if (old == ~0ull) break;
+    if (old == key) {
+      fresh = false;
+      break;
+    }
     h = (h + 1) & (kPairSlots - 1);
   }
-  return true;  // a full table only costs extra joins
+  if (fresh) uf_join(parent, a, b);  // a full table only costs extra joins
 }
 
 // Hook across every shared edge once (u < v) (Alg. 1, second loop).
@@ -430,7 +438,7 @@ __global__ __launch_bounds__(kHookThreads) void k_uf_cross(
         if (lane == leader) keep = true;
         todo &= ~__ballot(want && a == la && b == lb);
       }
-      if (keep && pair_fresh(pairs, a, b)) uf_join(parent, a, b);
+      if (keep) join_once(pairs, parent, a, b);
     }
   }
 }
@@ -747,7 +755,7 @@ __device__ __forceinline__ void k_uf_vertex_hook_body(const int32_t* __restrict_
         if (lane == leader) keep = true;
         todo &= ~__ballot(want && a == la && b == lb);
       }
-      if (keep && pair_fresh(pairs, a, b)) uf_join(parent, a, b);
+      if (keep) join_once(pairs, parent, a, b);
     }
   }
 }
