@@ -133,6 +133,23 @@ __device__ __forceinline__ uint32_t visible4(const uint8_t* __restrict__ vis, in
   return m;
 }
 
+// The neighbours of the triangles [t, t + 4) below T (t a multiple of four; nbr
+// comes from an allocation of its own, so four triangles' are three aligned
+// words); -1 past the end.
+__device__ __forceinline__ void neighbours4(const int32_t* __restrict__ nbr, int64_t t, int64_t T,
+                                            int (&n)[12]) {
+  if (t + 4 <= T) {
+    const int4* w = reinterpret_cast<const int4*>(nbr + 3 * t);
+    const int4 a = w[0], b = w[1], c = w[2];
+    n[0] = a.x; n[1] = a.y; n[2] = a.z; n[3] = a.w;
+    n[4] = b.x; n[5] = b.y; n[6] = b.z; n[7] = b.w;
+    n[8] = c.x; n[9] = c.y; n[10] = c.z; n[11] = c.w;
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 12; ++e) n[e] = t + e / 3 < T ? nbr[3 * t + e] : -1;
+}
+
 // Prologue of a frame: frame state, per-vertex scratch (vertex minima and
 // chart_of_vert = -1; clip positions are computed where they are read),
 // chart_of_tri = -1, the union-find start of every visible triangle and the
@@ -143,15 +160,18 @@ __device__ __forceinline__ uint32_t visible4(const uint8_t* __restrict__ vis, in
 // the stores: 16 bytes a lane each, and few enough workgroups that starting
 // them does not count (with one tile or 1024 vertices a workgroup in single
 // words 2.2M triangles took 8.1 us, now 6.5, and the compaction 7.4, now 5.3;
-// 16 views 102 and 45, now 84 and 20). uf_init 2: a visible triangle
+// 16 views 102 and 45, now 84 and 20). UF_INIT 2: a visible triangle
 // starts linked to the smallest of itself and its visible edge neighbours
 // (Alg. 1, first loop); 1: as its own root (same labels); 0: not written (a
-// later pass writes it).
+// later pass writes it). The neighbours are a chain of two loads a triangle, so
+// they want waves: a tile a workgroup then (2.2M triangles: a tile a wave 26 us,
+// so 11.0; one word at a time, a tile a workgroup, 12.6).
+template <int UF_INIT>
 __device__ __forceinline__ void k_prologue_body(int64_t V, int32_t* __restrict__ vmin,
                            int32_t* __restrict__ cov, const uint8_t* __restrict__ vis,
                            const int32_t* __restrict__ nbr, int64_t T,
                            int32_t* __restrict__ parent, int32_t* __restrict__ cot,
-                           uint32_t* __restrict__ tile_vis, int uf_init,
+                           uint32_t* __restrict__ tile_vis,
                            unsigned vblocks, FrameState* st,
                            unsigned long long* __restrict__ big_counter,
                            const int32_t* __restrict__ check_idx = nullptr) {
@@ -173,21 +193,25 @@ __device__ __forceinline__ void k_prologue_body(int64_t V, int32_t* __restrict__
     }
     return;
   }
-  const int64_t tile =
-      (int64_t)(blockIdx.x - vblocks) * kTilesPer + threadIdx.x / kWave;
+  // (with neighbours to look up, a step of the tile by each wave)
+  constexpr int kSteps = UF_INIT == 2 ? 1 : kTileSteps;
+  static_assert(kTileSteps == kTilesPer, "a wave takes a tile or a step of one");
+  const int w = threadIdx.x / kWave;
+  const int64_t tile = UF_INIT == 2 ? (int64_t)(blockIdx.x - vblocks)
+                                    : (int64_t)(blockIdx.x - vblocks) * kTilesPer + w;
   if (tile * kTriTile >= T) return;
-  const int64_t t0 = tile * kTriTile + 4 * lane_id();
+  const int64_t t0 = tile * kTriTile + 4 * lane_id() + (UF_INIT == 2 ? w * 4 * kWave : 0);
   const bool wide_vis = ((uintptr_t)vis & 3u) == 0, wide_cot = aligned16(cot);
-  uint32_t m[kTileSteps];
+  uint32_t m[kSteps];
 #pragma unroll
-  for (int k = 0; k < kTileSteps; ++k) m[k] = visible4(vis, t0 + k * 4 * kWave, T, wide_vis);
+  for (int k = 0; k < kSteps; ++k) m[k] = visible4(vis, t0 + k * 4 * kWave, T, wide_vis);
   uint32_t nv = 0;
 #pragma unroll
-  for (int k = 0; k < kTileSteps; ++k) {
+  for (int k = 0; k < kSteps; ++k) {
     const int64_t t = t0 + k * 4 * kWave;
     fill4(cot, t, T, -1, wide_cot);
     nv += (uint32_t)__popc(m[k]);
-    if (check_idx) {
+    if (UF_INIT != 2 && check_idx) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (t + j >= T) break;
@@ -196,35 +220,46 @@ __device__ __forceinline__ void k_prologue_body(int64_t V, int32_t* __restrict__
           nv += 2 * kTriTile;  // (a tile counts at most kTriTile visible)
       }
     }
-    if (!uf_init) continue;
+    if (UF_INIT == 0) continue;
+    int q[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (!(m[k] >> j & 1u)) continue;
-      int q = (int)(t + j);
-      if (uf_init == 2) {
+    for (int j = 0; j < 4; ++j) q[j] = (int)(t + j);
+    if (UF_INIT == 2 && m[k]) {
+      // four triangles' neighbours, then the bytes of all of them, in flight together
+      int n[12];
+      neighbours4(nbr, t, T, n);
+      uint32_t seen = 0;
 #pragma unroll
-        for (int e = 0; e < 3; ++e) {
-          const int n = nbr[3 * (t + j) + e];
-          if (n >= 0 && vis[n]) q = min(q, n);
-        }
-      }
-      astore(&parent[t + j], q);
+      for (int e = 0; e < 12; ++e)
+        seen |= (m[k] >> (e / 3) & 1u) && n[e] >= 0 && vis[n[e]] ? 1u << e : 0u;
+#pragma unroll
+      for (int e = 0; e < 12; ++e) q[e / 3] = seen >> e & 1u ? min(q[e / 3], n[e]) : q[e / 3];
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (m[k] >> j & 1u) astore(&parent[t + j], q[j]);
+  }
+  if (UF_INIT == 2) {
+    __shared__ uint32_t sh[kBlock / kWave];
+    nv = block_sum<uint32_t>(nv, sh);
+    if (threadIdx.x == 0) tile_vis[tile] = nv;
+    return;
   }
   nv = wave_sum<uint32_t>(nv);
   if (check_idx) nv = nv % (2 * kTriTile) + (nv >= 2 * kTriTile ? kBadTile : 0u);
   if (lane_id() == 0) tile_vis[tile] = nv;
 }
+template <int UF_INIT>
 __global__ void k_prologue(int64_t V, int32_t* __restrict__ vmin,
                            int32_t* __restrict__ cov, const uint8_t* __restrict__ vis,
                            const int32_t* __restrict__ nbr, int64_t T,
                            int32_t* __restrict__ parent, int32_t* __restrict__ cot,
-                           uint32_t* __restrict__ tile_vis, int uf_init,
+                           uint32_t* __restrict__ tile_vis,
                            unsigned vblocks, FrameState* st,
                            unsigned long long* __restrict__ big_counter,
                            const int32_t* __restrict__ check_idx) {
-  k_prologue_body(V, vmin, cov, vis, nbr, T, parent, cot, tile_vis, uf_init, vblocks, st,
-                  big_counter, check_idx);
+  k_prologue_body<UF_INIT>(V, vmin, cov, vis, nbr, T, parent, cot, tile_vis, vblocks, st,
+                           big_counter, check_idx);
 }
 
 // Sum of cnt[0 .. n) by one workgroup (the exclusive prefix of tile n);
@@ -1413,8 +1448,8 @@ inline unsigned grid_for(int64_t n, int block) { return (unsigned)((n + block - 
 __global__ void k_prologue_b(const BatchView* __restrict__ bv, int64_t V, const int32_t* __restrict__ nbr, int64_t T,
                              unsigned vblocks) {
   const BatchView& v = bv[blockIdx.y];
-  k_prologue_body(V, in_global(v.w.vmin), in_global(v.cov), in_global(v.visible), nbr, T, in_global(v.w.parent), in_global(v.cot),
-                  in_global(v.w.tile_vis), 0, vblocks, in_global(v.w.state), in_global(v.w.big_counter));
+  k_prologue_body<0>(V, in_global(v.w.vmin), in_global(v.cov), in_global(v.visible), nbr, T, in_global(v.w.parent), in_global(v.cot),
+                  in_global(v.w.tile_vis), vblocks, in_global(v.w.state), in_global(v.w.big_counter));
 }
 __global__ __launch_bounds__(1024) void k_tile_scan_b(const BatchView* __restrict__ bv,
                                                       unsigned tiles) {
@@ -1479,9 +1514,15 @@ hipError_t launch_prologue(int64_t V, const uint8_t* vis, const int32_t* nbr,
                            hipStream_t st) {
   const unsigned vb = std::max(1u, grid_for(V, kBlock * kProVerts));
   const unsigned tt = grid_for(T, kTriTile * kTilesPer);
-  k_prologue<<<vb + tt, kBlock, 0, st>>>(V, w.vmin, cov, vis, nbr, T, w.parent,
-                                         cot, w.tile_vis, uf_init, vb, w.state,
-                                         w.big_counter, check_idx);
+  // (neighbours are known of checked meshes only)
+  if (uf_init == 2 && check_idx) return hipErrorInvalidValue;
+  auto prologue = [&](auto kernel, unsigned tile_groups) {
+    kernel<<<vb + tile_groups, kBlock, 0, st>>>(V, w.vmin, cov, vis, nbr, T, w.parent, cot, w.tile_vis, vb,
+                                       w.state, w.big_counter, check_idx);
+  };
+  if (uf_init == 2) prologue(k_prologue<2>, grid_for(T, kTriTile));
+  else if (uf_init == 1) prologue(k_prologue<1>, tt);
+  else prologue(k_prologue<0>, tt);
   mk(st);
   mk(st);  // (the visible-count scan is part of the compaction)
   if (T > 0)

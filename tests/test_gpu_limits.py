@@ -290,3 +290,39 @@ def test_push_ways(name, block):
     fit = table[:, 0] == 1
     assert np.array_equal(c[fit, 3], table[fit, 3])
     assert ((c[~fit, 3] == -1) | (c[~fit, 3] > c[~fit, 2])).all()
+
+
+# Union-find modes 0 and 1 start every visible triangle at its smallest visible
+# neighbour, four triangles a lane and a tile of 1024 a workgroup: sizes around
+# those, neighbours hidden or not, visible buffers of any alignment, and triangles
+# that name an edge twice.
+@pytest.mark.parametrize("T", [8193, 9215, 12291, 16384, 20002])
+@pytest.mark.parametrize("hooks", [0, 1])
+def test_linked_start(T, hooks):
+    fa = _fa()
+    n = int(np.ceil(np.sqrt(T / 2)))
+    y, x = np.mgrid[0:n + 1, 0:n + 1] / n * 2 - 1
+    pos = np.stack([x, y, 0.2 * np.sin(9 * x) * np.cos(7 * y)], -1).reshape(-1, 3)
+    v = (np.arange(n)[:, None] * (n + 1) + np.arange(n)).reshape(-1)
+    tris = np.stack([v, v + 1, v + n + 2, v, v + n + 2, v + n + 1], 1).reshape(-1, 3)[:T]
+    rng = np.random.default_rng(T + hooks)
+    tris = tris[rng.permutation(T)] if T % 2 else tris
+    tris[T // 3] = tris[T // 3][[0, 1, 0]]
+    cam = scenes.make_camera((0.0, 0.0, 2.5), (0.0, 0.0, 0.0), 1280, 720, 0.05, 100.0, up=(0, 1, 0))
+    ctx = fa.Context(T, len(pos), max_charts=16384, max_atlas=1024, tuning_table=None)
+    ctx.set_tuning(fa.FA_TUNE_UF_EDGE_HOOKS, hooks)
+    assert ctx.get_tuning(fa.FA_TUNE_UF_LINK_INIT) == 1
+    mesh = fa.Mesh(pos, tris, 997)
+    for shift, share in ((0, 1.0), (1, 0.6), (2, 0.3), (3, 0.02)):
+        vis = (rng.uniform(size=T) < share).astype(np.uint8)
+        f = scenes.Frame(f"linked {T}", pos.astype(np.float32), tris.astype(np.int32), vis,
+                         cam.view_proj, 1280, 720, 1024, 1.0, 997, cam.eye, cam.near, 0)
+        print(f"[gpu] linked start T={T} hooks={hooks} shift={shift}", flush=True)
+        shown = torch.zeros(T + 4, dtype=torch.uint8, device="cuda")[shift:shift + T]
+        shown.copy_(torch.as_tensor(vis))
+        out = ctx.outputs(mesh, 1024)
+        _poison(out)
+        ctx.build_atlas(mesh, shown, f.view_proj, 1280, 720, 1024, 1.0, out=out)
+        torch.cuda.synchronize()
+        compare(out.to_numpy(), oracle.build_frame(f))
+    ctx.close()
