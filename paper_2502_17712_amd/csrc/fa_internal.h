@@ -502,9 +502,9 @@ struct BatchView {
 // The views (device array dev[0..n)) use hook mode 5, the box push, and all
 // have occupancy and UVs; host[0..n) is the same array on the host (for the
 // launch shapes). Every view's results equal fa_build_atlas's for it.
-hipError_t launch_charts_batched(const BatchView* dev, int n, const float* pos,
-                                 const int32_t* idx, const int32_t* nbr, int64_t T, int64_t V,
-                                 int max_omega, hipStream_t st);
+hipError_t launch_charts_batched(const BatchView* dev, int n, const int32_t* idx,
+                                 const int32_t* nbr, int64_t T, int64_t V, int max_omega,
+                                 hipStream_t st);
 hipError_t launch_order_batched(const BatchView* dev, int n, hipStream_t st);
 hipError_t launch_pack_batched(const BatchView* dev, int n, int J, int64_t max_charts, int block,
                                hipStream_t st);
@@ -543,7 +543,6 @@ struct AdjTmp {
   int32_t* vals_b;
   uint32_t* hist;
   uint32_t* part;  // per-chunk sums of the histogram scan
-  uint32_t* n_dev;
 };
 size_t adjacency_hist_words(int64_t T);
 size_t adjacency_part_words(int64_t T);

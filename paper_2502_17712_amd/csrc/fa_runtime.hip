@@ -736,7 +736,7 @@ static int enqueue_batched(fa_ctx* ctx, const fa_mesh* mesh, Scene* sc, int32_t 
     const BatchView* d = ctx->bv_dev + r0;
     int omega = 0;
     for (int i = r0; i < r0 + m; ++i) omega = std::max(omega, views[i].atlas_size);
-    ok(launch_charts_batched(d, m, mesh->positions, mesh->indices, sc->nbr, T, V, omega, st));
+    ok(launch_charts_batched(d, m, mesh->indices, sc->nbr, T, V, omega, st));
     ok(launch_order_batched(d, m, st));
     ok(launch_pack_batched(d, m, ctx->cfg.num_scales, ctx->cfg.max_charts, kn.pack_block, st));
     ok(launch_occupancy_batched(d, m, mesh->indices, T, V, omega, kn.small_texels, kn.lane_texels,

@@ -524,8 +524,7 @@ __device__ __forceinline__ void lds_join(int* lp, int a, int b) {
 // the vertex hook then joins every set that touches a common vertex (which
 // covers the edges between tiles too).
 template <int TILE, int NT>
-__global__ __launch_bounds__(NT) void k_uf_local(const uint8_t* __restrict__ vis,
-                                                 const int32_t* __restrict__ nbr,
+__global__ __launch_bounds__(NT) void k_uf_local(const int32_t* __restrict__ nbr,
                                                  const int32_t* __restrict__ vlist,
                                                  int32_t* __restrict__ parent,
                                                  const int32_t* __restrict__ idx,
@@ -566,7 +565,8 @@ __global__ __launch_bounds__(NT) void k_uf_local(const uint8_t* __restrict__ vis
       const int n = nk[k][e];
       if (n <= t || n > last) continue;
       // n, if visible, is one of the n - t entries after i: at the last of them
-      // where everything in between is visible
+      // where everything in between is visible. A hidden neighbour is one that
+      // is not found here; nothing else keeps it out.
       int lo = i + 1, hi = min(cnt - 1, i + (n - t));
       if (lv[hi] != n) {
         while (lo < hi) {
@@ -1580,13 +1580,13 @@ hipError_t launch_charts(const uint8_t* vis, const int32_t* idx, const int32_t* 
       const int tile = p.uf_tile;
       if (tile == 8192)
         k_uf_local<8192, 1024><<<std::max(1u, grid_for(T, 8192)), 1024, 0, st>>>(
-            vis, nbr, w.vlist, w.parent, nullptr, w.vmin, w.state);
+            nbr, w.vlist, w.parent, nullptr, w.vmin, w.state);
       else if (tile == 4096)
         k_uf_local<4096, 1024><<<std::max(1u, grid_for(T, 4096)), 1024, 0, st>>>(
-            vis, nbr, w.vlist, w.parent, nullptr, w.vmin, w.state);
+            nbr, w.vlist, w.parent, nullptr, w.vmin, w.state);
       else
         k_uf_local<2048, 1024><<<std::max(1u, grid_for(T, 2048)), 1024, 0, st>>>(
-            vis, nbr, w.vlist, w.parent, nullptr, w.vmin, w.state);
+            nbr, w.vlist, w.parent, nullptr, w.vmin, w.state);
       k_uf_cross<<<std::max(1u, g * kBlock / kHookThreads), kHookThreads, 0, st>>>(
           vis, nbr, w.vlist, w.parent, tile, w.state);
     }
@@ -1610,13 +1610,13 @@ hipError_t launch_charts(const uint8_t* vis, const int32_t* idx, const int32_t* 
       const int32_t* vidx = p.edge_hooks == 4 ? idx : nullptr;
       if (tile == 8192)
         k_uf_local<8192, 1024><<<std::max(1u, grid_for(T, 8192)), 1024, 0, st>>>(
-            vis, nbr, w.vlist, w.parent, vidx, w.vmin, w.state);
+            nbr, w.vlist, w.parent, vidx, w.vmin, w.state);
       else if (tile == 4096)
         k_uf_local<4096, 1024><<<std::max(1u, grid_for(T, 4096)), 1024, 0, st>>>(
-            vis, nbr, w.vlist, w.parent, vidx, w.vmin, w.state);
+            nbr, w.vlist, w.parent, vidx, w.vmin, w.state);
       else
         k_uf_local<2048, 1024><<<std::max(1u, grid_for(T, 2048)), 1024, 0, st>>>(
-            vis, nbr, w.vlist, w.parent, vidx, w.vmin, w.state);
+            nbr, w.vlist, w.parent, vidx, w.vmin, w.state);
       if (p.edge_hooks == 2)
         k_uf_cross<<<std::max(1u, g * kBlock / kHookThreads), kHookThreads, 0, st>>>(
             vis, nbr, w.vlist, w.parent, tile, w.state);
@@ -1655,9 +1655,9 @@ hipError_t launch_charts(const uint8_t* vis, const int32_t* idx, const int32_t* 
   return hipGetLastError();
 }
 
-hipError_t launch_charts_batched(const BatchView* dev, int n, const float* pos,
-                                 const int32_t* idx, const int32_t* nbr, int64_t T, int64_t V,
-                                 int max_omega, hipStream_t st) {
+hipError_t launch_charts_batched(const BatchView* dev, int n, const int32_t* idx,
+                                 const int32_t* nbr, int64_t T, int64_t V, int max_omega,
+                                 hipStream_t st) {
   if (n <= 0) return hipSuccess;
   if (T > 0 && T <= kFrontTris && V <= kFrontVerts) {  // (batched views have vertex charts)
     const dim3 grid(1u + fill_groups((int64_t)max_omega * max_omega / 4), n);

@@ -348,7 +348,7 @@ __device__ __forceinline__ void add(Edges32& e, const Edges32& d) {
   e.e0 += d.e0; e.e1 += d.e1; e.e2 += d.e2;
 }
 
-__global__ void k_occ_fill(int4* __restrict__ occ, int64_t n4, const FrameState* __restrict__ st) {
+__global__ void k_occ_fill(int4* __restrict__ occ, int64_t n4) {
   const int4 neg = make_int4(-1, -1, -1, -1);
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4;
        i += (int64_t)gridDim.x * blockDim.x)
@@ -574,9 +574,7 @@ __global__ __launch_bounds__(kOccSmallBlock) void k_occ_small(
 // and the set-up take 7 and the footprints' broadcasts 4). Wider searches (256
 // probes a round) read more lines and are 1 us slower.
 __device__ __forceinline__ void k_occ_big_body(
-    const int32_t* __restrict__ idx, FrameParams p, const float* __restrict__ pos,
-    const int32_t* __restrict__ cot, const fa_chart* __restrict__ charts,
-    const int4* __restrict__ chart_tex, int32_t* __restrict__ occ,
+    FrameParams p, int32_t* __restrict__ occ,
     const ulonglong2* __restrict__ big, const int4* __restrict__ big_fp, uint32_t big_cap,
     const unsigned long long* __restrict__ big_counter, const FrameState* __restrict__ stp) {
   const FrameState st = *stp;
@@ -751,12 +749,10 @@ __device__ __forceinline__ void k_occ_big_body(
   }
 }
 __global__ __launch_bounds__(kBlock) void k_occ_big(
-    const int32_t* __restrict__ idx, FrameParams p, const float* __restrict__ pos,
-    const int32_t* __restrict__ cot, const fa_chart* __restrict__ charts,
-    const int4* __restrict__ chart_tex, int32_t* __restrict__ occ,
+    FrameParams p, int32_t* __restrict__ occ,
     const ulonglong2* __restrict__ big, const int4* __restrict__ big_fp, uint32_t big_cap,
     const unsigned long long* __restrict__ big_counter, const FrameState* __restrict__ stp) {
-  k_occ_big_body(idx, p, pos, cot, charts, chart_tex, occ, big, big_fp, big_cap, big_counter, stp);
+  k_occ_big_body(p, occ, big, big_fp, big_cap, big_counter, stp);
 }
 
 __global__ void k_meta(FrameParams p, FrameState* stp,
@@ -843,10 +839,9 @@ __global__ __launch_bounds__(kOccSmallBlock) void k_occ_small_b(
                    occ_blocks, V, in_global(v.cov), reinterpret_cast<float2*>(in_global(v.uv)));
 }
 __global__ __launch_bounds__(kBlock) void k_occ_big_b(const BatchView* __restrict__ bv,
-                                                      const int32_t* __restrict__ idx,
                                                       uint32_t big_cap) {
   const BatchView& v = bv[blockIdx.y];
-  k_occ_big_body(idx, v.p, in_global(v.w.pos), in_global(v.cot), in_global(v.charts), in_global(v.w.chart_tex), in_global(v.occ), in_global(v.w.big), in_global(v.w.big_fp),
+  k_occ_big_body(v.p, in_global(v.occ), in_global(v.w.big), in_global(v.w.big_fp),
                  big_cap, in_global(v.w.big_counter), in_global(v.w.state));
 }
 __global__ __launch_bounds__(kCountBlock) void k_occ_count_meta_b(
@@ -893,7 +888,7 @@ hipError_t launch_occupancy(const int32_t* idx, int64_t T, const FrameParams& p,
   const int64_t n4 = (int64_t)p.omega * p.omega / 4;
   if (x.fill) {
     const unsigned fill_grid = (unsigned)std::min<int64_t>((n4 + kBlock - 1) / kBlock, 4096);
-    k_occ_fill<<<fill_grid, kBlock, 0, st>>>(reinterpret_cast<int4*>(occ), n4, w.state);
+    k_occ_fill<<<fill_grid, kBlock, 0, st>>>(reinterpret_cast<int4*>(occ), n4);
   }
   mk(st);
   const uint32_t cap = (uint32_t)std::min<int64_t>(2 * std::max<int64_t>(T, 1), kBigCap);
@@ -908,8 +903,8 @@ hipError_t launch_occupancy(const int32_t* idx, int64_t T, const FrameParams& p,
         reinterpret_cast<float2*>(x.uv));
   mk(st);
   if (T > 0)
-    k_occ_big<<<kOccBigGrid, kBlock, 0, st>>>(idx, p, w.pos, cot, charts, w.chart_tex, occ,
-                                              w.big, w.big_fp, cap, w.big_counter, w.state);
+    k_occ_big<<<kOccBigGrid, kBlock, 0, st>>>(p, occ, w.big, w.big_fp, cap, w.big_counter,
+                                              w.state);
   mk(st);
   if (x.meta)  // a scaled copy (no frame record) needs no count
     k_occ_count_meta<<<count_grid(p.omega), kCountBlock, 0, st>>>(p, reinterpret_cast<const int4*>(occ),
@@ -1414,7 +1409,7 @@ hipError_t launch_occupancy_batched(const BatchView* dev, int n, const int32_t* 
   if (T > 0)
     // (half as many: each wave starts with a search)
     k_occ_big_b<<<dim3(std::min<unsigned>(kOccBigGrid, kViewThreads / (2 * kBlock * n)), n),
-                  kBlock, 0, st>>>(dev, idx, cap);
+                  kBlock, 0, st>>>(dev, cap);
   k_occ_count_meta_b<<<dim3(count_grid(max_omega), n), kCountBlock, 0, st>>>(dev);
   return hipGetLastError();
 }

@@ -19,9 +19,8 @@ namespace fa {
 namespace {
 
 template <typename K>
-__global__ void k_radix_hist(const K* __restrict__ keys, const int32_t* __restrict__ n_dev,
-                             int64_t n_host, int shift, uint32_t* __restrict__ hist) {
-  const int64_t n = n_dev ? min((int64_t)*n_dev, n_host) : n_host;
+__global__ void k_radix_hist(const K* __restrict__ keys, int64_t n, int shift,
+                             uint32_t* __restrict__ hist) {
   const int64_t ntiles = (n + kSortTile - 1) / kSortTile;
   const int64_t b = blockIdx.x;
   if (b >= ntiles) return;
@@ -43,17 +42,15 @@ __global__ void k_radix_hist(const K* __restrict__ keys, const int32_t* __restri
 constexpr int kScanThreads = 1024;
 constexpr int kScanChunk = 4 * kScanThreads;
 
-__device__ __forceinline__ int64_t hist_words(const int32_t* n_dev, int64_t n_host) {
-  const int64_t n = n_dev ? min((int64_t)*n_dev, n_host) : n_host;
+__device__ __forceinline__ int64_t hist_words(int64_t n) {
   return (n + kSortTile - 1) / kSortTile * kRadix;
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* __restrict__ hist,
-                                                              const int32_t* __restrict__ n_dev,
-                                                              int64_t n_host,
+                                                              int64_t n,
                                                               uint32_t* __restrict__ part) {
   __shared__ uint32_t sh[kScanThreads / kWave];
-  const int64_t total = hist_words(n_dev, n_host);
+  const int64_t total = hist_words(n);
   const int64_t i0 = (int64_t)blockIdx.x * kScanChunk + 4 * (int64_t)threadIdx.x;
   if ((int64_t)blockIdx.x * kScanChunk >= total) return;
   uint32_t v = 0;
@@ -64,10 +61,9 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* __
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_parts(uint32_t* __restrict__ part,
-                                                             const int32_t* __restrict__ n_dev,
-                                                             int64_t n_host) {
+                                                             int64_t n) {
   __shared__ uint32_t sh[kScanThreads / kWave];
-  const int64_t nb = (hist_words(n_dev, n_host) + kScanChunk - 1) / kScanChunk;
+  const int64_t nb = (hist_words(n) + kScanChunk - 1) / kScanChunk;
   uint32_t run = 0;
   for (int64_t c0 = 0; c0 < nb; c0 += kScanThreads) {
     const int64_t i = c0 + threadIdx.x;
@@ -80,11 +76,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_parts(uint32_t* __restric
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_apply(uint32_t* __restrict__ hist,
-                                                             const int32_t* __restrict__ n_dev,
-                                                             int64_t n_host,
+                                                             int64_t n,
                                                              const uint32_t* __restrict__ part) {
   __shared__ uint32_t sh[kScanThreads / kWave];
-  const int64_t total = hist_words(n_dev, n_host);
+  const int64_t total = hist_words(n);
   if ((int64_t)blockIdx.x * kScanChunk >= total) return;
   const int64_t i0 = (int64_t)blockIdx.x * kScanChunk + 4 * (int64_t)threadIdx.x;
   uint32_t v[4];
@@ -104,9 +99,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(uint32_t* __restric
 template <typename K>
 __global__ __launch_bounds__(kRadix) void k_radix_scatter(
     const K* __restrict__ kin, const int32_t* __restrict__ vin, K* __restrict__ kout,
-    int32_t* __restrict__ vout, const int32_t* __restrict__ n_dev, int64_t n_host, int shift,
-    const uint32_t* __restrict__ hist) {
-  const int64_t n = n_dev ? min((int64_t)*n_dev, n_host) : n_host;
+    int32_t* __restrict__ vout, int64_t n, int shift, const uint32_t* __restrict__ hist) {
   const int64_t ntiles = (n + kSortTile - 1) / kSortTile;
   const int64_t b = blockIdx.x;
   if (b >= ntiles) return;
@@ -156,9 +149,8 @@ __global__ __launch_bounds__(kRadix) void k_radix_scatter(
 
 template <typename K>
 hipError_t radix_sort(K* keys_a, int32_t* vals_a, K* keys_b, int32_t* vals_b, uint32_t* hist,
-                      uint32_t* part, const int32_t* n_dev, int64_t n_cap, int bits,
-                      hipStream_t st, bool* in_b) {
-  const unsigned tiles = (unsigned)((n_cap + kSortTile - 1) / kSortTile);
+                      uint32_t* part, int64_t n, int bits, hipStream_t st, bool* in_b) {
+  const unsigned tiles = (unsigned)((n + kSortTile - 1) / kSortTile);
   const unsigned chunks =
       std::max(1u, (unsigned)(((int64_t)tiles * kRadix + kScanChunk - 1) / kScanChunk));
   bool flip = false;
@@ -167,12 +159,12 @@ hipError_t radix_sort(K* keys_a, int32_t* vals_a, K* keys_b, int32_t* vals_b, ui
     const int32_t* vi = flip ? vals_b : vals_a;
     K* ko = flip ? keys_a : keys_b;
     int32_t* vo = flip ? vals_a : vals_b;
-    if (tiles) k_radix_hist<K><<<tiles, kRadix, 0, st>>>(ki, n_dev, n_cap, shift, hist);
-    k_scan_reduce<<<chunks, kScanThreads, 0, st>>>(hist, n_dev, n_cap, part);
-    k_scan_parts<<<1, kScanThreads, 0, st>>>(part, n_dev, n_cap);
-    k_scan_apply<<<chunks, kScanThreads, 0, st>>>(hist, n_dev, n_cap, part);
+    if (tiles) k_radix_hist<K><<<tiles, kRadix, 0, st>>>(ki, n, shift, hist);
+    k_scan_reduce<<<chunks, kScanThreads, 0, st>>>(hist, n, part);
+    k_scan_parts<<<1, kScanThreads, 0, st>>>(part, n);
+    k_scan_apply<<<chunks, kScanThreads, 0, st>>>(hist, n, part);
     if (tiles)
-      k_radix_scatter<K><<<tiles, kRadix, 0, st>>>(ki, vi, ko, vo, n_dev, n_cap, shift, hist);
+      k_radix_scatter<K><<<tiles, kRadix, 0, st>>>(ki, vi, ko, vo, n, shift, hist);
     flip = !flip;
   }
   *in_b = flip;
@@ -1003,7 +995,7 @@ hipError_t launch_adjacency(const int32_t* idx, int64_t T, int64_t V, const AdjT
                                                                        tmp.keys_a, tmp.vals_a);
   bool in_b = false;
   hipError_t e = radix_sort<unsigned long long>(tmp.keys_a, tmp.vals_a, tmp.keys_b, tmp.vals_b,
-                                                tmp.hist, tmp.part, nullptr, n, bits, st, &in_b);
+                                                tmp.hist, tmp.part, n, bits, st, &in_b);
   if (e != hipSuccess) return e;
   k_edge_runs<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(
       in_b ? tmp.keys_b : tmp.keys_a, in_b ? tmp.vals_b : tmp.vals_a, n, deg, nbr);
