@@ -109,10 +109,11 @@ typedef struct fa_config {
                               exceeds it. Before a new scene's adjacency
                               (12 B per triangle, plus its sort buffers while
                               it is built) or a larger visibility buffer
-                              would exceed it, the least recently used
-                              resident scenes are evicted (after waiting for
-                              the device); if it still does not fit, the call
-                              returns FA_ERR_OUT_OF_MEMORY                   */
+                              would exceed it (the sort buffers are counted
+                              whether or not this mesh needs them), the least
+                              recently used resident scenes are evicted (after
+                              waiting for the device); if it still does not
+                              fit, the call returns FA_ERR_OUT_OF_MEMORY     */
 } fa_config;
 
 typedef struct fa_mesh {
@@ -305,11 +306,11 @@ int fa_pack_boxes(fa_ctx* ctx, const float* sizes, int32_t n, int32_t atlas_size
  * (J = 64, gutter 1, min_box 2, no flags, default knobs) and no context:
  * every scratch buffer lives in one static device array of
  * FA_STATIC_SCRATCH_MIB MiB that each device holds for the life of the
- * process (nothing of a scene stays resident). The call allocates nothing and never synchronizes; it runs on the
- * current device and enqueues on `stream`. Limits: T <= FA_STATIC_MAX_TRIANGLES,
- * V <= FA_STATIC_MAX_VERTICES (FA_ERR_CAPACITY above them), at most
- * FA_STATIC_MAX_CHARTS charts (FA_ERR_CAPACITY in meta->status),
- * atlas_size a power of two 16..8192. Out-of-range indices are found on the
+ * process (nothing of a scene stays resident). The call allocates nothing and
+ * never synchronizes; it runs on the current device and enqueues on `stream`.
+ * Limits: T <= FA_STATIC_MAX_TRIANGLES, V <= FA_STATIC_MAX_VERTICES
+ * (FA_ERR_CAPACITY above them), at most FA_STATIC_MAX_CHARTS charts
+ * (FA_ERR_CAPACITY in meta->status), atlas_size a power of two 16..8192. Out-of-range indices are found on the
  * device: meta->status = FA_ERR_INVALID_ARG and no other output is valid.
  * Arguments, outputs and the other errors are as for fa_build_atlas
  * (candidates, when given, has 64 rows). Every call on a device shares that
@@ -354,8 +355,13 @@ int fa_build_atlas_static(const fa_mesh* mesh, const uint8_t* visible, const fa_
  *                             0: vertices only
  *                             (every shared edge is a shared vertex: the
  *                             charts are the same for all six)
- *   FA_TUNE_UF_TILE           visible-list entries per LDS union-find tile
- *                             (modes 2, 3, 4): 2048, 4096 (default), 8192
+ *   FA_TUNE_UF_TILE           visible-list entries per LDS union-find tile:
+ *                             2048, 4096 (default), 8192 (modes 2, 3, 4; with
+ *                             FA_FLAG_EDGE_ONLY_CHARTS every mode but 1)
+ *                             The three union-find knobs do nothing for meshes
+ *                             of up to 8192 triangles and 16384 vertices
+ *                             without FA_FLAG_EDGE_ONLY_CHARTS, whose charts
+ *                             one workgroup builds
  *   FA_TUNE_BATCH_GRAPH       1: fa_build_atlas_batch captures its views into
  *                             a hipGraph once per distinct set of view
  *                             descriptors and replays it (one launch); 0: off

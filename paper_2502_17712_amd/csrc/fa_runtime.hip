@@ -368,7 +368,8 @@ static int get_scene(fa_ctx* ctx, const fa_mesh* mesh, hipStream_t st, Scene** o
                                        align_up(4 * adjacency_hist_words(T)) +
                                        align_up(4 * adjacency_part_words(T)) + 256
                                  : 0;
-  // the adjacency and, while it is built, its sort buffers must fit the budget
+  // the adjacency and, while it is built, its sort buffers must fit the budget:
+  // a scene is admitted by its size alone, also where the buckets need no buffers
   if (!make_room(ctx, scene_bytes(T) + tmp_bytes, mesh->scene_key, st))
     return FA_ERR_OUT_OF_MEMORY;
   if (hipMalloc(&sc.nbr, scene_bytes(T)) != hipSuccess) return FA_ERR_OUT_OF_MEMORY;

@@ -915,9 +915,10 @@ __global__ void k_assign_roots(const int32_t* __restrict__ vlist,
 // vertices' first triangles and the parents of the triangles in LDS, indexed
 // directly. Six launches of little work each cost about 4 us of launch and
 // drain. This one is bound by LDS latency, the walks of the joins above all.
-// A whole frame with the six launches and with this one: 70 and 54 us at 2048
-// triangles, 76 and 69 at 8192, 81 and 92 at 15842 (grids in row order), so the
-// line lies at 8192 (other meshes there: 82 and 70, 80 and 77).
+// A whole frame with the six launches and with this one: 66 and 47 us at 2048
+// triangles, 68 and 58 at 4096, 73 and 69 at 8192 (grids in row order; objects
+// 66 and 54 at 2048, 75 and 76 at 8000) and 81 and 92 at 15842, so the line lies
+// at 8192.
 // Workgroups past the first fill the occupancy map.
 constexpr int kFrontTris = 8192;
 constexpr int kFrontVerts = 16384;

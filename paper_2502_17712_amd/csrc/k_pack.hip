@@ -401,8 +401,13 @@ __global__ __launch_bounds__(NT) void k_pack(const float2* __restrict__ wh,
 constexpr int kFoldItems = 4;   // consecutive boxes per thread in the fold
 constexpr int kNarrow = 8;      // by columns: boxes up to this wide are pushed by one lane
 constexpr int kMidList = 2048, kWideList = 256;  // by columns: entries of the box lists
+// (9 to 16 boxes take 0.5 to 1 us less by columns too, which columns_cheaper finds)
 constexpr int kFewBoxes = 8;
-constexpr int kEdgeMax = 1024;  // by rows: most edge columns on either side
+// By rows: most edge columns on either side. With half as many, 1000 boxes with
+// an overflow of 642 columns take 73 us in place of 50, 4000 with one of 532 125
+// in place of 98; with twice as many nothing is faster and 200 boxes with one of
+// 1142 take 39 in place of 35.
+constexpr int kEdgeMax = 1024;
 constexpr int kUnderLane = 8;   // by rows: boxes under a box that one lane looks at
 // By rows: the mark of a box that 16 lanes push together, in its a | b << 16
 // (a and b are below 2^15), which the push leaves as it is.
@@ -410,8 +415,11 @@ constexpr uint32_t kShared16 = 1u << 31;
 
 constexpr int kCellBits = 12;   // by rows: 2^12 cells index a chunk's fold positions
 constexpr int kCells = 1 << kCellBits;
-constexpr int kTabRows = 128;   // by rows: rows of a chunk with a table of their shared boxes
-constexpr int kTabBoxes = 8;    // ... of this many
+// By rows: rows of a chunk with a table of their shared boxes, and boxes in it
+// (32 rows: 16000 boxes in 110 rows 176 -> 186 us; 4 boxes: 60000 boxes in 156
+// rows 373 -> 413; 16 boxes do not fit the LDS at 4096 columns).
+constexpr int kTabRows = 128;
+constexpr int kTabBoxes = 8;
 
 // Boxes per chunk by columns (by rows: the multiples of it end a segment too,
 // so that both stop at the same box) and by rows, and the dynamic LDS of a

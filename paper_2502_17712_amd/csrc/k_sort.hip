@@ -225,7 +225,13 @@ __global__ void k_edge_runs(const unsigned long long* __restrict__ keys,
 // for 2.2M triangles, their 160 MB of buffers another 400 us to allocate and
 // free (1188 us in all for a scene that comes in); this way 92 and none (190 us).
 // A bucket above kAdjCap half-edges (a vertex with thousands of triangles, or
-// few of many vertices in use) sends the mesh to the sort.
+// few of many vertices in use) sends the mesh to the sort, which pays for the
+// count too (60000 triangles around a vertex 231 -> 236 us, 2M with such a vertex
+// 1235 -> 1270), and so do meshes of more than kAdjMaxBuckets ranges: from 2.8M
+// to 5.6M triangles on, by their share of vertices (3M in a strip 209 us, 6M
+// 3.1 ms as before). An edge of very many triangles is a long chain (1300 at one
+// edge 297 -> 480 us for the load; sorting such a bucket in LDS gave 150, but took
+// the match of an ordinary mesh from 47 to 50 us).
 constexpr int kAdjTile = 2048;
 constexpr int kAdjThreads = 512;
 constexpr int kAdjCap = 4096;
@@ -478,8 +484,10 @@ __device__ __forceinline__ bool box_size(const float* __restrict__ sizes, int c,
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderLds = 2048;  // most charts one workgroup orders, in LDS
 // ... and by counting, without the passes and their barriers: 1 chart 5.5 -> 3.7
-// us, 144 charts 5.8 -> 4.2, 234 charts 6.1 -> 5.4 (comparing everything with
-// everything, it would lose from about 400 on)
+// us, 144 charts 5.8 -> 4.2, 234 charts 6.1 -> 5.4. Everything is compared with
+// everything: level with the passes at 300 to 350 charts (packings of one
+// candidate, counted and sorted: 100 boxes 22.4 and 23.6 us, 200 24.9 and 25.6,
+// 256 27.3 and 27.7, 300 28.2 and 28.4, 400 30.7 and 30.0, 512 33.8 and 32.0)
 constexpr int kCountBits = 8;
 constexpr int kOrderCount = 1 << kCountBits;
 static_assert(kKeyCap < 1 << (32 - kCountBits), "key and chart fit a word");

@@ -46,14 +46,13 @@ __device__ __forceinline__ unsigned long long dload(const unsigned long long* p)
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Screen footprint of an occluder: vertices in coarse pixels (x right, y down)
-// with their NDC z, and the range of sample centres inside its bounding box.
+// Screen footprint of an occluder, from its clip-space vertices: vertices in
+// coarse pixels (x right, y down) with their NDC z, and the range of sample
+// centres inside its bounding box (all that the cull asks for).
 struct Shot {
   double X[3], Y[3], Z[3];
   int ix0, ix1, iy0, iy1;
 };
-
-// (from the clip-space vertices: the cull asks for the range alone)
 
 __device__ __forceinline__ void shot_of(const VisParams& q, const double4 (&c)[3], Shot& s) {
 #pragma unroll
@@ -178,13 +177,20 @@ __global__ __launch_bounds__(kCullBlock) void k_vis_cull(
 // is then even and the passes wait for loads. The two passes on that scene,
 // with the cull and the reuse flags: 133 us with a lane or a wave per occluder,
 // 71 with consecutive batches of 64, 61 of 16, 45.2 in runs of 4 (runs of 8
-// 47.2, single ones 46.5; 8 or 4 workgroups per CU 47, 3 52).
+// 47.2, single ones 46.5; 8 or 4 workgroups per CU 47, 3 52). Where samples are
+// even all over the list, batches of 64 keep the lines of the depth buffer
+// together: a heightfield of one million triangles at half resolution 52.7 us
+// with them, 58.4 with runs of 4, but 119 and 70 on the scene above.
 constexpr int kVisBatch = kWave;
 constexpr int kVisRun = 4;
 // Footprints of more samples than this are walked one after another, without
 // looking for the owner of each sample, and short lists go one entry a
 // workgroup (two triangles over all of 480 x 270 samples: 850 -> 121 us, forty
 // over half of it 1550 -> 506; by one wave each they took 1040 and 17077).
+// With 1024, 4096 and 16384: a 2.2M-triangle scene sampled at full resolution
+// 180, 189 and 194 us, at half of it 69, 76 and 76; 1000 triangles of 50000
+// samples 685 with each; only a list of 100000 triangles with 6000 samples each
+// prefers to share them (7.06, 7.06 and 5.82 ms).
 constexpr uint32_t kVisMany = 1024;
 constexpr int kVisGrid = 6 * 256;  // most workgroups: what the chip holds at once
 

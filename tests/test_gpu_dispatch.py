@@ -87,11 +87,6 @@ def test_occupied_texels(omega, n):
     compare(g, oracle.build_frame(f))
 
 
-# The box push goes by rows (each box rests on the few boxes of the row before)
-# or by columns (a whole frontline): by columns up to 8 boxes, with overflows
-# above 1024 columns and where two rows may not fit a chunk. Other edges: chunks
-# of 8128 boxes (and stop checks at multiples of another number), boxes over
-# more than 8 and 16 others, more than 8 boxes of a row over edge columns.
 # Triangles whose vertices are within 512 texels of the first one are tested in
 # 32 bits, larger ones in 64: fans of a few triangles whose sides go from
 # beyond 2000 texels to below 60, some of them on both sides of 512.
@@ -153,6 +148,11 @@ def test_footprint_long_list():
     compare(check(f, flags=4), oracle.build_frame(f, footprint=True))
 
 
+# The box push goes by rows (each box rests on the few boxes of the row before)
+# or by columns (a whole frontline): by columns up to 8 boxes, with overflows
+# above 1024 columns and where two rows may not fit a chunk. Other edges: chunks
+# of 8128 boxes (and stop checks at multiples of another number), boxes over
+# more than 8 and 16 others, more than 8 boxes of a row over edge columns.
 def _uniform(n, lo, hi, seed=0):
     return np.random.default_rng(seed).uniform(lo, hi, (n, 2))
 
@@ -411,9 +411,9 @@ def test_edge_tiles(tile, count, hidden):
     assert np.array_equal(g["charts"]["root_tri"], r["roots"])
 
 
-# In a batch the kernels over the visible list start a limited number of
-# workgroups per view and take several turns: 16 views with everything visible
-# against the same frames alone.
+# A batch of 16 views on their slots' streams, half of them with everything
+# visible, against the same frames alone. (One launch for all views, whose kernels
+# then take several turns, is tested against the oracle with the other limits.)
 def test_batch_turns():
     fa = _fa()
     n = 400
