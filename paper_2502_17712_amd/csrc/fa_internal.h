@@ -79,6 +79,7 @@ struct FrameParams {
   int32_t uf_tile;     // visible-list entries per LDS union-find tile (2048, 4096, 8192)
   int32_t fp_cap;      // footprint push: capacity of the profile columns (0: box push)
   int64_t pool_stride; // footprint push: pooled profile entries per candidate
+  int32_t edge_fans;   // the mesh has edges of more than two half-edges (edge-connected charts)
 };
 
 // Clip position of vertex v: clip = M (x, y, z, 1)^T, each row summed left to
@@ -548,5 +549,22 @@ size_t adjacency_hist_words(int64_t T);
 size_t adjacency_part_words(int64_t T);
 hipError_t launch_adjacency(const int32_t* idx, int64_t T, int64_t V, const AdjTmp& tmp,
                             int32_t* nbr, hipStream_t st);
+// *fans (0 before) is set where an edge has more than two half-edges
+hipError_t launch_find_fans(const int32_t* idx, const int32_t* nbr, int64_t T, uint32_t* fans,
+                            hipStream_t st);
+// Edge e of triangle t, as the last of n's edges that joins the same two vertices;
+// -1: none does.
+__device__ __forceinline__ int same_edge(const int32_t* __restrict__ idx, int64_t t, int e,
+                                         int64_t n) {
+  const int a = idx[3 * t + e], b = idx[3 * t + (e == 2 ? 0 : e + 1)];
+  const int v[3] = {idx[3 * n], idx[3 * n + 1], idx[3 * n + 2]};
+  int at = -1;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int c = v[k], d = v[k == 2 ? 0 : k + 1];
+    if ((c == a && d == b) || (c == b && d == a)) at = k;
+  }
+  return at;
+}
 
 }  // namespace fa

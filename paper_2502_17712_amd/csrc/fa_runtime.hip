@@ -28,6 +28,7 @@ struct TuneEntry {
 struct Scene {
   int32_t* nbr = nullptr;
   int64_t T = 0, V = 0;
+  bool fans = false;      // edges of more than two half-edges (looked for with edge-connected charts)
   uint64_t last_use = 0;  // use counter of the context when last used (LRU eviction)
 };
 
@@ -403,6 +404,19 @@ static int get_scene(fa_ctx* ctx, const fa_mesh* mesh, hipStream_t st, Scene** o
       return FA_ERR_DEVICE;
     }
   }
+  if (T > 0 && (ctx->cfg.flags & FA_FLAG_EDGE_ONLY_CHARTS)) {
+    uint32_t fans[2] = {0u, 0u};
+    if (hipMemcpyAsync(ctx->check_flag, fans, kCheckBytes, hipMemcpyHostToDevice, st) !=
+            hipSuccess ||
+        launch_find_fans(mesh->indices, sc.nbr, T, ctx->check_flag, st) != hipSuccess ||
+        hipMemcpyAsync(fans, ctx->check_flag, kCheckBytes, hipMemcpyDeviceToHost, st) !=
+            hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess) {
+      (void)hipFree(sc.nbr);
+      return FA_ERR_DEVICE;
+    }
+    sc.fans = fans[0] != 0u;
+  }
   ctx->held_bytes += scene_bytes(T);
   auto res = ctx->scenes.emplace(mesh->scene_key, sc);
   *out = &res.first->second;
@@ -640,6 +654,7 @@ static int run_frame(fa_ctx* ctx, const Work& w, const fa_mesh* mesh, Scene* sc,
   Marker mk;
   if (ctx->timing) { mk.ev = ctx->ev; mk.cap = kStages + 1; }
   FrameParams p = p_in;
+  p.edge_fans = sc->fans ? 1 : 0;
   const Knobs kn = frame_knobs(ctx, mesh->num_triangles, &p);
   const int rc = run_frame_core(kn, w, mesh, sc->nbr, visible, p, out, false, mk, st);
   ctx->ev_marks = mk.n;

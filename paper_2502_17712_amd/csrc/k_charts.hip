@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstddef>
+#include <type_traits>
 
 #include "fa_internal.h"
 
@@ -402,19 +403,38 @@ __device__ __forceinline__ void join_once(unsigned long long* pairs, int32_t* pa
   if (fresh) uf_join(parent, a, b);  // a full table only costs extra joins
 }
 
+// Edges of more than two triangles (FANS): nbr goes from one to the next and
+// from the last to the first, so a hidden triangle is passed over to the next
+// visible one, or -1 where there is none but t. Each edge's visible triangles
+// are then joined in a row. n: the neighbour of t across its edge e.
+__device__ __forceinline__ int next_visible(const int32_t* __restrict__ idx,
+                                            const int32_t* __restrict__ nbr,
+                                            const uint8_t* __restrict__ vis, int t, int e, int n,
+                                            int64_t T) {
+  // (an edge is walked once around at most)
+  for (int64_t step = 0; step < T && n >= 0 && n != t && !vis[n]; ++step) {
+    const int k = same_edge(idx, t, e, n);
+    n = k < 0 ? -1 : nbr[3 * (int64_t)n + k];
+  }
+  return n == t ? -1 : n;
+}
+
 // Hook across every shared edge once (u < v) (Alg. 1, second loop).
 // With tile > 0 only edges leaving the entry's tile of `tile` consecutive
 // list entries are hooked (the others were joined inside the tile).
+template <bool FANS>
 __global__ void k_uf_hook(const uint8_t* __restrict__ vis, const int32_t* __restrict__ nbr,
                           const int32_t* __restrict__ vlist, int32_t* parent, int tile,
-                          const FrameState* __restrict__ st) {
+                          const FrameState* __restrict__ st, const int32_t* __restrict__ mesh_idx,
+                          int64_t T) {
   const int nv = st->visible;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += gridDim.x * blockDim.x) {
     const int t = vlist[i];
     const int last = tile > 0 ? vlist[min(nv, (i / tile + 1) * tile) - 1] : -1;
 #pragma unroll
     for (int e = 0; e < 3; ++e) {
-      const int n = nbr[3 * (int64_t)t + e];
+      int n = nbr[3 * (int64_t)t + e];
+      if (FANS) n = next_visible(mesh_idx, nbr, vis, t, e, n, T);
       if (n > t && n > last && vis[n]) uf_join(parent, t, n);
     }
   }
@@ -427,10 +447,11 @@ __global__ void k_uf_hook(const uint8_t* __restrict__ vis, const int32_t* __rest
 // hooked by every lane contending for the same root. Bound by the chain of
 // loads and the walks of the joins; the loads of a triangle's three edges go
 // out together.
+template <bool FANS>
 __global__ __launch_bounds__(kHookThreads) void k_uf_cross(
     const uint8_t* __restrict__ vis, const int32_t* __restrict__ nbr,
     const int32_t* __restrict__ vlist, int32_t* parent, int tile,
-    const FrameState* __restrict__ st) {
+    const FrameState* __restrict__ st, const int32_t* __restrict__ mesh_idx, int64_t T) {
   __shared__ unsigned long long pairs[kPairSlots];
   pairs_clear(pairs);
   const int nv = st->visible;
@@ -444,6 +465,10 @@ __global__ __launch_bounds__(kHookThreads) void k_uf_cross(
     if (valid) {
       const int3 x = reinterpret_cast<const int3*>(nbr)[t];
       n[0] = x.x; n[1] = x.y; n[2] = x.z;
+      if (FANS) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) n[e] = next_visible(mesh_idx, nbr, vis, t, e, n[e], T);
+      }
     }
     // the three edges' loads together (a hidden neighbour's parent is read in
     // vain)
@@ -523,13 +548,15 @@ __device__ __forceinline__ void lds_join(int* lp, int a, int b) {
 // triangle of a set that touches the vertex, so the local root serves, and
 // the vertex hook then joins every set that touches a common vertex (which
 // covers the edges between tiles too).
-template <int TILE, int NT>
+template <int TILE, int NT, bool FANS>
 __global__ __launch_bounds__(NT) void k_uf_local(const int32_t* __restrict__ nbr,
                                                  const int32_t* __restrict__ vlist,
                                                  int32_t* __restrict__ parent,
                                                  const int32_t* __restrict__ idx,
                                                  int32_t* __restrict__ vmin,
-                                                 const FrameState* __restrict__ st) {
+                                                 const FrameState* __restrict__ st,
+                                                 const uint8_t* __restrict__ vis,
+                                                 const int32_t* __restrict__ mesh_idx, int64_t T) {
   constexpr int kPer = TILE / NT;  // entries per thread: i = threadIdx.x + k NT
   __shared__ int lv[TILE];
   __shared__ int lp[TILE];
@@ -551,6 +578,11 @@ __global__ __launch_bounds__(NT) void k_uf_local(const int32_t* __restrict__ nbr
     if (i < cnt) {
       const int3 x = reinterpret_cast<const int3*>(nbr)[tk[k]];
       nk[k][0] = x.x; nk[k][1] = x.y; nk[k][2] = x.z;
+      if (FANS) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          nk[k][e] = next_visible(mesh_idx, nbr, vis, tk[k], e, nk[k][e], T);
+      }
       lv[i] = tk[k];
       lp[i] = i;
     }
@@ -1575,29 +1607,34 @@ hipError_t launch_charts(const uint8_t* vis, const int32_t* idx, const int32_t* 
   bool fill_done = false;
   if (T > 0 && (p.flags & FA_FLAG_EDGE_ONLY_CHARTS)) {
     // edge-connected charts: shared edges only, no vertex passes
-    if (p.edge_hooks == 1) {
-      k_uf_hook<<<g, kBlock, 0, st>>>(vis, nbr, w.vlist, w.parent, 0, w.state);
-    } else {
-      const int tile = p.uf_tile;
+    const int tile = p.uf_tile;
+    auto join = [&](auto fans) {
+      constexpr bool F = decltype(fans)::value;
+      if (p.edge_hooks == 1) {
+        k_uf_hook<F><<<g, kBlock, 0, st>>>(vis, nbr, w.vlist, w.parent, 0, w.state, idx, T);
+        return;
+      }
       if (tile == 8192)
-        k_uf_local<8192, 1024><<<std::max(1u, grid_for(T, 8192)), 1024, 0, st>>>(
-            nbr, w.vlist, w.parent, nullptr, w.vmin, w.state);
+        k_uf_local<8192, 1024, F><<<std::max(1u, grid_for(T, 8192)), 1024, 0, st>>>(
+            nbr, w.vlist, w.parent, nullptr, w.vmin, w.state, vis, idx, T);
       else if (tile == 4096)
-        k_uf_local<4096, 1024><<<std::max(1u, grid_for(T, 4096)), 1024, 0, st>>>(
-            nbr, w.vlist, w.parent, nullptr, w.vmin, w.state);
+        k_uf_local<4096, 1024, F><<<std::max(1u, grid_for(T, 4096)), 1024, 0, st>>>(
+            nbr, w.vlist, w.parent, nullptr, w.vmin, w.state, vis, idx, T);
       else
-        k_uf_local<2048, 1024><<<std::max(1u, grid_for(T, 2048)), 1024, 0, st>>>(
-            nbr, w.vlist, w.parent, nullptr, w.vmin, w.state);
-      k_uf_cross<<<std::max(1u, g * kBlock / kHookThreads), kHookThreads, 0, st>>>(
-          vis, nbr, w.vlist, w.parent, tile, w.state);
-    }
+        k_uf_local<2048, 1024, F><<<std::max(1u, grid_for(T, 2048)), 1024, 0, st>>>(
+            nbr, w.vlist, w.parent, nullptr, w.vmin, w.state, vis, idx, T);
+      k_uf_cross<F><<<std::max(1u, g * kBlock / kHookThreads), kHookThreads, 0, st>>>(
+          vis, nbr, w.vlist, w.parent, tile, w.state, idx, T);
+    };
+    if (p.edge_fans) join(std::true_type{});
+    else join(std::false_type{});
     mk(st);
     mk(st);
     mk(st);
     k_uf_flatten_count<<<vt, kBlock, 0, st>>>(w.vlist, w.parent, w.tile_count, w.state);
   } else if (T > 0) {
     if (p.edge_hooks == 1) {
-      k_uf_hook<<<g, kBlock, 0, st>>>(vis, nbr, w.vlist, w.parent, 0, w.state);
+      k_uf_hook<false><<<g, kBlock, 0, st>>>(vis, nbr, w.vlist, w.parent, 0, w.state, idx, T);
     } else if (p.edge_hooks == 5) {
       // tiles of 2048 entries and a 4096-slot table (at most ~3/4 full); at
       // least kFillGroups workgroups past the largest visible list fill the
@@ -1610,17 +1647,17 @@ hipError_t launch_charts(const uint8_t* vis, const int32_t* idx, const int32_t* 
       const int tile = p.uf_tile;
       const int32_t* vidx = p.edge_hooks == 4 ? idx : nullptr;
       if (tile == 8192)
-        k_uf_local<8192, 1024><<<std::max(1u, grid_for(T, 8192)), 1024, 0, st>>>(
-            nbr, w.vlist, w.parent, vidx, w.vmin, w.state);
+        k_uf_local<8192, 1024, false><<<std::max(1u, grid_for(T, 8192)), 1024, 0, st>>>(
+            nbr, w.vlist, w.parent, vidx, w.vmin, w.state, vis, idx, T);
       else if (tile == 4096)
-        k_uf_local<4096, 1024><<<std::max(1u, grid_for(T, 4096)), 1024, 0, st>>>(
-            nbr, w.vlist, w.parent, vidx, w.vmin, w.state);
+        k_uf_local<4096, 1024, false><<<std::max(1u, grid_for(T, 4096)), 1024, 0, st>>>(
+            nbr, w.vlist, w.parent, vidx, w.vmin, w.state, vis, idx, T);
       else
-        k_uf_local<2048, 1024><<<std::max(1u, grid_for(T, 2048)), 1024, 0, st>>>(
-            nbr, w.vlist, w.parent, vidx, w.vmin, w.state);
+        k_uf_local<2048, 1024, false><<<std::max(1u, grid_for(T, 2048)), 1024, 0, st>>>(
+            nbr, w.vlist, w.parent, vidx, w.vmin, w.state, vis, idx, T);
       if (p.edge_hooks == 2)
-        k_uf_cross<<<std::max(1u, g * kBlock / kHookThreads), kHookThreads, 0, st>>>(
-            vis, nbr, w.vlist, w.parent, tile, w.state);
+        k_uf_cross<false><<<std::max(1u, g * kBlock / kHookThreads), kHookThreads, 0, st>>>(
+            vis, nbr, w.vlist, w.parent, tile, w.state, idx, T);
     }
     mk(st);
     if (p.edge_hooks < 4)  // modes 4, 5: the tile kernel lowered the vertex minima

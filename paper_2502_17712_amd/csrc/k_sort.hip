@@ -945,6 +945,23 @@ __global__ __launch_bounds__(kOrderThreads) void k_sizes_order_b(const BatchView
                      in_global(v.w.sorted_wh), nullptr, nullptr, in_global(v.w.state), in_global(v.w.hist), in_global(v.w.partial));
 }
 
+// A half-edge whose neighbour's neighbour across the same edge is another
+// triangle has more than two of them there.
+__global__ void k_find_fans(const int32_t* __restrict__ idx, const int32_t* __restrict__ nbr,
+                            int64_t T, uint32_t* __restrict__ fans) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= T) return;
+  bool found = false;
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    const int n = nbr[3 * t + e];
+    if (n < 0) continue;
+    const int k = same_edge(idx, t, e, n);
+    found = found || (k >= 0 && nbr[3 * (int64_t)n + k] != (int)t);
+  }
+  if (found) atomicOr(fans, 1u);
+}
+
 }  // namespace
 
 size_t adjacency_hist_words(int64_t T) {
@@ -1007,6 +1024,13 @@ hipError_t launch_adjacency(const int32_t* idx, int64_t T, int64_t V, const AdjT
   if (e != hipSuccess) return e;
   k_edge_runs<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(
       in_b ? tmp.keys_b : tmp.keys_a, in_b ? tmp.vals_b : tmp.vals_a, n, deg, nbr);
+  return hipGetLastError();
+}
+
+hipError_t launch_find_fans(const int32_t* idx, const int32_t* nbr, int64_t T, uint32_t* fans,
+                            hipStream_t st) {
+  if (T > 0)
+    k_find_fans<<<(unsigned)((T + kBlock - 1) / kBlock), kBlock, 0, st>>>(idx, nbr, T, fans);
   return hipGetLastError();
 }
 

@@ -326,3 +326,48 @@ def test_linked_start(T, hooks):
         torch.cuda.synchronize()
         compare(out.to_numpy(), oracle.build_frame(f))
     ctx.close()
+
+
+# Edge-connected charts over edges of more than two triangles: the visible ones of
+# an edge are joined whichever of the others between them are hidden, in the global
+# hook and in tiles; triangles that name an edge twice, and edges across tiles.
+@pytest.mark.parametrize("kind", ["pages", "books", "soup"])
+@pytest.mark.parametrize("hooks,tile", [(1, 2048), (5, 2048), (5, 4096), (5, 8192)])
+def test_edge_charts_over_many_at_an_edge(kind, hooks, tile):
+    fa = _fa()
+    rng = np.random.default_rng(tile + hooks)
+    if kind == "pages":    # all of them at one edge
+        tris = np.stack([np.zeros(300, int), np.ones(300, int), 2 + np.arange(300)], 1)
+    elif kind == "books":  # edges of 3 to 5 triangles, which lie all over the list
+        k, n = 2500, rng.integers(3, 6, 2500)
+        spine = np.repeat(np.arange(k), n)
+        tris = np.stack([2 * spine, 2 * spine + 1, 2 * k + np.arange(len(spine))], 1)
+        tris = tris[rng.permutation(len(tris))]
+    else:
+        tris = rng.integers(0, 400, (6000, 3))
+    flip = rng.uniform(size=len(tris)) < 0.5
+    tris[flip] = tris[flip][:, [1, 0, 2]]
+    tris[7] = tris[7][[0, 1, 0]]
+    V = int(tris.max()) + 1
+    pos = rng.uniform(-1, 1, (V, 3)).astype(np.float32)
+    cam = scenes.make_camera((0.0, 0.0, 3.0), (0.0, 0.0, 0.0), 640, 360, 0.05, 100.0, up=(0, 1, 0))
+    ctx = fa.Context(len(tris), V, max_charts=16384, max_atlas=1024, flags=2, tuning_table=None)
+    ctx.set_tuning(fa.FA_TUNE_UF_EDGE_HOOKS, hooks)
+    ctx.set_tuning(fa.FA_TUNE_UF_TILE, tile)
+    mesh = fa.Mesh(pos, tris, 998)
+    for share in (0.05, 0.5, 0.9, 1.0):
+        vis = (rng.uniform(size=len(tris)) < share).astype(np.uint8)
+        f = scenes.Frame(f"{kind} {share}", pos, tris.astype(np.int32), vis, cam.view_proj, 640, 360,
+                         1024, 0.25, 998, cam.eye, cam.near, 0)
+        print(f"[gpu] edge charts, {kind}, hooks={hooks} tile={tile} shown {share}", flush=True)
+        out = ctx.outputs(mesh, 1024)
+        _poison(out)
+        ctx.build_atlas(mesh, torch.as_tensor(vis).cuda(), f.view_proj, 640, 360, 1024, 0.25,
+                        out=out)
+        torch.cuda.synchronize()
+        g, r = out.to_numpy(), oracle.build_frame(f, edge_only=True)
+        assert g["meta"]["status"] == r["status"] and g["meta"]["num_charts"] == r["num_charts"]
+        assert np.array_equal(g["chart_of_tri"], r["chart_of_tri"])
+        assert np.array_equal(g["chart_of_vert"], r["chart_of_vert"])
+        assert np.array_equal(g["charts"]["root_tri"], r["roots"])
+    ctx.close()
