@@ -228,8 +228,8 @@ __global__ void k_edge_runs(const unsigned long long* __restrict__ keys,
 // few of many vertices in use) sends the mesh to the sort, which pays for the
 // count too (60000 triangles around a vertex 231 -> 236 us, 2M with such a vertex
 // 1235 -> 1270), and so do meshes of more than kAdjMaxBuckets ranges: from 2.8M
-// to 5.6M triangles on, by their share of vertices (3M in a strip 209 us, 6M
-// 3.1 ms as before). An edge of very many triangles is a long chain (1300 at one
+// to 5.6M triangles on, by their share of vertices (strips: 3M triangles 1490 us
+// by the sort and 209 so, 6M 3.1 ms either way). An edge of very many triangles is a long chain (1300 at one
 // edge 297 -> 480 us for the load; sorting such a bucket in LDS gave 150, but took
 // the match of an ordinary mesh from 47 to 50 us).
 constexpr int kAdjTile = 2048;
