@@ -46,7 +46,7 @@ def kernel_bytes(name, T, V, Tv, Vv, C, J, omega, occupied):
     per = {
         "prologue": V * (4 + 4) + T * (1 + 4),
         "vis_compact": T * 1 + Tv * 4,
-        "uf_hook": Tv * (4 + 12 + 3 + 4),
+        "uf_hook": Tv * (4 + 12 + 4),
         "uf_vertex_min": Tv * (4 + 4 + 12 + 12),
         "uf_vertex_hook": Tv * (4 + 12 + 12 + 4),
         "uf_flatten": Tv * (4 + 4 + 4),
